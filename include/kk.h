@@ -136,8 +136,9 @@ kk_status kk_create_triangular_ex(kk_sim **out, uint32_t L, uint32_t H, uint32_t
                                   double omega_kT, uint64_t seed, void *hip_stream);
 
 /* Whole-sweep tiles of a triangular handle.  Class schedule: with cols > 0
- * every sweep is one launch whose workgroups each own a cols x rows tile and
- * run all 16 classes on an LDS window of the ring around it (33 more sites on
+ * every sweep is one launch whose workgroups each own a cols x rows tile (a
+ * tile too large for one workgroup's bit planes: an equal part of it) and run
+ * all 16 classes on an LDS window of the ring around it (33 more sites on
  * every side, recomputed by each tile), writing the tile to the other lattice
  * buffer; cols == 0 selects one launch per class, in place.  Literal MPKK:
  * with cols > 0 every step of 7 iterations is one launch on windows with 21

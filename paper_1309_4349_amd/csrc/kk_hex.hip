@@ -1,0 +1,546 @@
+// kk_hex.hip -- whole-sweep kernels of the triangular lattice on bit planes
+// (Materials and Methods, "Monte Carlo model with Kawasaki based kinetics",
+// Fig. 2; "Massive Parallel Kawasaki Kinetics", Fig. 4).  Gfx950 (CDNA4, wave64).
+//
+// A workgroup holds a window of the ring in LDS (rows of consecutive ring
+// sites, cell (r, c) = site base + r*L + c), one bit per site, the columns of
+// a row dealt into G classes c mod G: word (r, q) holds the cells c = G*j + q,
+// bit j.  All centres of one class of a row are then one word, decided
+// together with bitwise logic, and the neighbours of the whole word are words
+// of the rows r-2 .. r+2 and classes q-2 .. q+2 mod G, turned by one bit where
+// the class wraps.  G = 16 for the class schedule (class = ring index mod 16:
+// one column class per row and phase), G = 14 for the literal MPKK (centres
+// every 7 sites: two column classes per row and iteration, the even and the
+// odd domains, which share their Philox blocks).
+//
+// Random numbers: each attempt needs its direction d in 0..5 and the
+// comparisons of its uniform U with three thresholds.  The two sites a and b
+// of an exchange have two common neighbours, each unlike exactly one of the
+// two, so the count n of unlike neighbours lies in 2..8 and only n = 2, 3, 4
+// (omega > 0) or 6, 7, 8 (omega < 0) can be rejected.  So an attempt's random
+// state is six bits -- sign and axis of d, U < T for three thresholds -- drawn
+// for the whole sweep before the first phase: each lane draws one Philox block
+// for two sites of its row and shifts the twelve outcomes into twelve words
+// (compare and add-with-carry), and the blocks are computed once instead of
+// once per site.
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+#include "kk_common.hpp"
+#include "kk_kernels.hpp"
+#include "kk_tri.hpp"
+
+namespace kk {
+namespace {
+
+constexpr uint32_t kTagTri = 6u, kTagTriOrder = 7u;
+
+// Three-input bitwise functions by truth table, a = 0xF0, b = 0xCC, c = 0xAA.
+constexpr unsigned kA = 0xF0u, kB = 0xCCu, kC = 0xAAu;
+template <unsigned TT>
+__device__ __forceinline__ uint32_t lut3(uint32_t a, uint32_t b, uint32_t c) {
+  return __builtin_amdgcn_bitop3_b32(a, b, c, TT & 0xFFu);
+}
+__device__ __forceinline__ uint32_t mux(uint32_t s, uint32_t one, uint32_t zero) {
+  return lut3<(kA & kB) | (~kA & kC)>(s, one, zero);
+}
+__device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c) { return lut3<kA ^ kB ^ kC>(a, b, c); }
+__device__ __forceinline__ uint32_t rotr(uint32_t x, uint32_t n) { return __builtin_amdgcn_alignbit(x, x, n); }
+
+// plane = 2 * plane + (u < thr), plane = 2 * plane + (u >= thr): the compare's
+// carry goes straight into an add-with-carry.
+__device__ __forceinline__ void push_lt(uint32_t& plane, uint32_t u, uint32_t thr) {
+  asm("v_cmp_gt_u32_e32 vcc, %2, %1\n\tv_addc_co_u32_e32 %0, vcc, %0, %0, vcc" : "+v"(plane) : "v"(u), "s"(thr) : "vcc");
+}
+__device__ __forceinline__ void push_ge(uint32_t& plane, uint32_t u, uint32_t thr) {
+  asm("v_cmp_le_u32_e32 vcc, %2, %1\n\tv_addc_co_u32_e32 %0, vcc, %0, %0, vcc" : "+v"(plane) : "v"(u), "s"(thr) : "vcc");
+}
+
+// The random state of one word of centres, bit by bit: sign and axis (0: +-1,
+// 1: +-L, 2: +-(L-1); ax1 = axis >= 1, ax2 = axis == 2) of the direction, and
+// U < T for the three thresholds.
+struct Draw {
+  uint32_t sgn, ax1, ax2, a0, a1, a2;
+};
+
+// Philox4x32-10 of counter (b, j, t_lo, t_hi) where only b differs between the
+// lanes: the products of t_lo and of the first round's uniform word, and all
+// that follows from them, stay in scalar registers, which leaves 18 multiplies
+// per block.
+struct Head {
+  uint32_t u0c, u1, u2x, u3;  // round 1: hi(t_lo M1) ^ j ^ k0 multiplied out, lo(t_lo M1)
+  uint32_t th1, k0, k1;
+};
+__device__ __forceinline__ Head philox_head(uint32_t j, uint32_t tl, uint32_t th, uint32_t k0, uint32_t k1) {
+  const uint64_t p1 = (uint64_t)tl * 0xCD9E8D57u;
+  const uint64_t p0 = (uint64_t)((uint32_t)(p1 >> 32) ^ j ^ k0) * 0xD2511F53u;
+  Head h;
+  h.u0c = (uint32_t)p1 ^ (k0 + 0x9E3779B9u);              // round 2's c1 ^ k0
+  h.u2x = (uint32_t)(p0 >> 32) ^ (k1 + 0xBB67AE85u);      // round 2's hi(p0) ^ k1
+  h.u3 = (uint32_t)p0;                                    // round 2's new c3
+  h.u1 = 0u;
+  h.th1 = th ^ k1;                                        // round 1's c3 ^ k1
+  h.k0 = k0;
+  h.k1 = k1;
+  return h;
+}
+__device__ __forceinline__ Philox4 philox_tail(const Head& h, uint32_t b) {
+  const uint64_t q0 = (uint64_t)b * 0xD2511F53u;
+  uint32_t c2 = (uint32_t)(q0 >> 32) ^ h.th1, c3 = (uint32_t)q0;
+  const uint64_t q1 = (uint64_t)c2 * 0xCD9E8D57u;
+  uint32_t c0 = (uint32_t)(q1 >> 32) ^ h.u0c, c1 = (uint32_t)q1;
+  c2 = h.u2x ^ c3;
+  c3 = h.u3;
+  uint32_t k0 = h.k0 + 2u * 0x9E3779B9u, k1 = h.k1 + 2u * 0xBB67AE85u;
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    const uint64_t p0 = (uint64_t)c0 * 0xD2511F53u;
+    const uint64_t p1 = (uint64_t)c2 * 0xCD9E8D57u;
+    const uint32_t n0 = xor3((uint32_t)(p1 >> 32), c1, k0), n2 = xor3((uint32_t)(p0 >> 32), c3, k1);
+    c1 = (uint32_t)p1;
+    c3 = (uint32_t)p0;
+    c0 = n0;
+    c2 = n2;
+    k0 += 0x9E3779B9u;
+    k1 += 0xBB67AE85u;
+  }
+  return Philox4{c0, c1, c2, c3};
+}
+
+// One attempt's outcomes shifted into its draw: direction word w, uniform u.
+// d = (w * 6) >> 32: d >= 2 and d >= 4 are comparisons of w with 2^33/6 and
+// 2^34/6 (rounded up), and d mod 2 is the top bit of 3w mod 2^32.
+__device__ __forceinline__ void push_attempt(Draw& q, uint32_t w, uint32_t u, const HexAccept& acc) {
+  q.sgn = __builtin_amdgcn_alignbit(q.sgn, (w << 1) + w, 31);
+  push_ge(q.ax1, w, 0x55555556u);
+  push_ge(q.ax2, w, 0xAAAAAAABu);
+  push_lt(q.a0, u, acc.thr[0]);
+  push_lt(q.a1, u, acc.thr[1]);
+  push_lt(q.a2, u, acc.thr[2]);
+}
+
+// The window words a decision reads, aligned to the centre's bits; the centre
+// is a, its neighbours e (+1), w (-1), s (+L), n (-L), sw (+(L-1)), ne
+// (-(L-1)), and the twelve cells two steps away.
+struct Around {
+  uint32_t a, e, w, s, n, sw, ne;
+  uint32_t e2, w2, s2, n2, sw2, ne2;  // two steps straight on
+  uint32_t se, nw;                    // (+1, +1), (-1, -1)
+  uint32_t nee, sww;                  // (-1, +2), (+1, -2)
+  uint32_t ssw, nne;                  // (+2, -1), (-2, +1)
+};
+
+// Where a lane finds the words around its own: A[d + 2] the word of class
+// q + d mod G two rows above (so that every row offset is a positive
+// immediate), rot[d + 2] the turn that aligns that class's words to the
+// centres (1 where the class passed G - 1, 31 where it passed 0).
+struct Place {
+  int A[5];
+  uint32_t rot[5];
+};
+template <int G, int ROW>
+__device__ __forceinline__ Place class_place(int r, int q) {
+  Place p;
+#pragma unroll
+  for (int d = -2; d <= 2; ++d) {
+    const int k = q + d;
+    const bool lo = k < 0, hi = k >= G;
+    p.A[d + 2] = (r - 2) * ROW + (lo ? k + G : (hi ? k - G : k));
+    p.rot[d + 2] = lo ? 31u : (hi ? 1u : 0u);
+  }
+  return p;
+}
+
+template <int ROW>
+__device__ __forceinline__ Around read_around(const uint32_t* S, const Place& p) {
+  const int* A = p.A;
+  Around v;
+  v.n2 = S[A[2]];
+  v.n = S[A[2] + ROW];
+  v.a = S[A[2] + 2 * ROW];
+  v.s = S[A[2] + 3 * ROW];
+  v.s2 = S[A[2] + 4 * ROW];
+  v.nne = rotr(S[A[3]], p.rot[3]);
+  v.ne = rotr(S[A[3] + ROW], p.rot[3]);
+  v.e = rotr(S[A[3] + 2 * ROW], p.rot[3]);
+  v.se = rotr(S[A[3] + 3 * ROW], p.rot[3]);
+  v.nw = rotr(S[A[1] + ROW], p.rot[1]);
+  v.w = rotr(S[A[1] + 2 * ROW], p.rot[1]);
+  v.sw = rotr(S[A[1] + 3 * ROW], p.rot[1]);
+  v.ssw = rotr(S[A[1] + 4 * ROW], p.rot[1]);
+  v.ne2 = rotr(S[A[4]], p.rot[4]);
+  v.nee = rotr(S[A[4] + ROW], p.rot[4]);
+  v.e2 = rotr(S[A[4] + 2 * ROW], p.rot[4]);
+  v.w2 = rotr(S[A[0] + 2 * ROW], p.rot[0]);
+  v.sww = rotr(S[A[0] + 3 * ROW], p.rot[0]);
+  v.sw2 = rotr(S[A[0] + 4 * ROW], p.rot[0]);
+  return v;
+}
+
+// The accepted centres of a word.  For direction k of the six in cyclic order
+// (e, s, sw, w, n, ne) the centre's own neighbours are the three opposite the
+// partner and the partner's own are the three beyond it; the two common ones
+// add 2 to n whatever they hold.  First the sign picks between each cell and
+// its mirror image through the centre, then the axis picks among three.  m = n
+// - 1 = 1 (the partner) + unlike own neighbours, in 1..7, is summed relative
+// to the centre by a bit-sliced 7 -> 3 counter; slot (m & 3) - 1 holds U < T.
+__device__ __forceinline__ uint32_t decide(const Around& v, const Draw& q, uint32_t negmask, uint32_t cmask) {
+  const uint32_t s = q.sgn;
+  const uint32_t pe = mux(s, v.w, v.e), ps = mux(s, v.n, v.s), psw = mux(s, v.ne, v.sw);
+  const uint32_t me = mux(s, v.e, v.w), ms = mux(s, v.s, v.n), msw = mux(s, v.sw, v.ne);
+  const uint32_t q1 = mux(s, v.w2, v.e2), q2 = mux(s, v.n2, v.s2), q3 = mux(s, v.ne2, v.sw2);
+  const uint32_t q4 = mux(s, v.nw, v.se), q5 = mux(s, v.sww, v.nee), q5m = mux(s, v.nee, v.sww);
+  const uint32_t q6 = mux(s, v.nne, v.ssw);
+  const uint32_t b = mux(q.ax2, psw, mux(q.ax1, ps, pe));
+  const uint32_t x2 = mux(q.ax2, msw, me), x3 = mux(q.ax2, pe, mux(q.ax1, msw, psw));
+  const uint32_t y1 = mux(q.ax2, q3, mux(q.ax1, q2, q1));
+  const uint32_t y2 = mux(q.ax2, q6, q4), y3 = mux(q.ax2, q5m, mux(q.ax1, q6, q5));
+  constexpr unsigned kMaj = (kA & kB) | (kA & kC) | (kB & kC);
+  const uint32_t s1 = xor3(ms, x2, x3), c1 = lut3<kMaj>(ms, x2, x3);
+  const uint32_t s2 = lut3<~(kA ^ kB ^ kC)>(y1, y2, y3), c2 = lut3<~kMaj>(y1, y2, y3);
+  const uint32_t c3 = lut3<kMaj>(s1, s2, b);
+  const uint32_t m0 = xor3(s1, s2, b) ^ v.a;
+  const uint32_t m1 = xor3(c1, c2, c3) ^ v.a;
+  const uint32_t m2 = lut3<kMaj>(c1, c2, c3) ^ v.a;
+  const uint32_t live = lut3<kA & (kB ^ kC)>(cmask, v.a, b);
+  const uint32_t rm = lut3<~kA & (kB | kC)>(m2 ^ negmask, m0, m1);
+  const uint32_t acc = mux(m1, mux(m0, q.a2, q.a1), q.a0);
+  return lut3<kA & (~kB | kC)>(live, rm, acc);
+}
+
+// Flip the accepted centres F and their partners.
+template <int ROW>
+__device__ __forceinline__ void exchange(uint32_t* S, const Place& p, const Draw& q, uint32_t F) {
+  const int* A = p.A;
+  const uint32_t f0 = lut3<kA & ~kB>(F, q.ax1, q.ax1), f1 = lut3<kA & kB & ~kC>(F, q.ax1, q.ax2);
+  const uint32_t f2 = F & q.ax2;
+  // the turn that aligned the cell to the centre, undone
+  const uint32_t re = 0u - p.rot[3], rw = 0u - p.rot[1];
+  atomicXor(&S[A[2] + 2 * ROW], F);
+  atomicXor(&S[A[3] + 2 * ROW], rotr(f0 & ~q.sgn, re));
+  atomicXor(&S[A[1] + 2 * ROW], rotr(f0 & q.sgn, rw));
+  atomicXor(&S[A[2] + 3 * ROW], f1 & ~q.sgn);
+  atomicXor(&S[A[2] + ROW], f1 & q.sgn);
+  atomicXor(&S[A[1] + 3 * ROW], rotr(f2 & ~q.sgn, rw));
+  atomicXor(&S[A[3] + ROW], rotr(f2 & q.sgn, re));
+}
+
+// Bits j of class q whose columns G*j + q lie in [c0, c1).
+template <int G>
+__device__ __forceinline__ uint32_t column_mask(int q, int c0, int c1) {
+  const int lo = (c0 - q + G - 1) / G, hi = (c1 - q + G - 1) / G;  // c0 > q, c1 >= c0
+  const uint32_t below_hi = hi >= 32 ? 0xFFFFFFFFu : ((1u << hi) - 1u);
+  return below_hi & ~((1u << lo) - 1u);
+}
+
+// One row's draws of two classes in halves: lanes 0..31 hold the first h bits
+// of both classes, lanes 32..63 the bits from h on of the same rows.  After
+// it lanes 0..31 hold the whole words of the first class and lanes 32..63
+// those of the second.
+__device__ __forceinline__ uint32_t join_halves(uint32_t first, uint32_t second, uint32_t h) {
+  const auto p = __builtin_amdgcn_permlane32_swap(first, second, false, false);
+  return p[0] | (p[1] << h);
+}
+__device__ __forceinline__ Draw join_draws(const Draw& a, const Draw& b, uint32_t h) {
+  return Draw{join_halves(a.sgn, b.sgn, h), join_halves(a.ax1, b.ax1, h), join_halves(a.ax2, b.ax2, h),
+              join_halves(a.a0, b.a0, h),   join_halves(a.a1, b.a1, h),   join_halves(a.a2, b.a2, h)};
+}
+
+__device__ __forceinline__ void store_draw(uint32_t* D, const Draw& q, const HexAccept& acc) {
+  uint2* p = reinterpret_cast<uint2*>(D);
+  p[0] = make_uint2(q.sgn, q.ax1);
+  p[1] = make_uint2(q.ax2, q.a0 | acc.all[0]);
+  p[2] = make_uint2(q.a1 | acc.all[1], q.a2 | acc.all[2]);
+}
+__device__ __forceinline__ Draw load_draw(const uint32_t* D) {
+  const uint2* p = reinterpret_cast<const uint2*>(D);
+  const uint2 x = p[0], y = p[1], z = p[2];
+  return Draw{x.x, x.y, y.x, y.y, z.x, z.y};
+}
+
+struct Bytes16 {
+  uint32_t x[4];
+};
+// Ring sites s .. s + 15 (mod N).  Only lanes that reach the ring's end take
+// them one by one.
+__device__ __forceinline__ Bytes16 ring_bytes(const uint8_t* __restrict__ in, uint32_t s, uint32_t N) {
+  Bytes16 v;
+  s = s >= N ? s - N : s;
+  if (s + 16u <= N) {
+    __builtin_memcpy(&v, in + s, 16);
+  } else {
+    v = Bytes16{};
+#pragma unroll 1
+    for (int b = 0; b < 16; ++b) {
+      uint32_t i = s + (uint32_t)b;
+      i = i >= N ? i - N : i;
+      const uint32_t x = (uint32_t)in[i] << (8 * (b & 3));
+#pragma unroll
+      for (int k = 0; k < 4; ++k) v.x[k] |= (b >> 2) == k ? x : 0u;
+    }
+  }
+  return v;
+}
+
+// OR over the eight lanes of a group, in every lane.
+__device__ __forceinline__ uint32_t or8(uint32_t x) {
+  x |= (uint32_t)__builtin_amdgcn_mov_dpp((int)x, 0xB1, 0xF, 0xF, false);   // lane ^ 1
+  x |= (uint32_t)__builtin_amdgcn_mov_dpp((int)x, 0x4E, 0xF, 0xF, false);   // lane ^ 2
+  x |= (uint32_t)__builtin_amdgcn_mov_dpp((int)x, 0x141, 0xF, 0xF, false);  // 7 - lane
+  return x;
+}
+
+// Stage and unstage: eight neighbouring lanes take eight neighbouring groups
+// of G sites of a row (lane l the group l), 16 bytes each, so that a
+// wavefront's loads and stores are contiguous.  Bit l of byte q of the eight
+// lanes' bytes shifted by their lane and ORed together is site q of group l:
+// one byte of each of the row's G class words, of which lane l stores (or
+// reads) the classes 2l and 2l + 1.
+template <int G>
+__device__ __forceinline__ void stage_bytes(uint8_t* B, const Bytes16& v, int l) {
+  uint32_t w[4];
+#pragma unroll
+  for (int k = 0; k < 4; ++k) w[k] = or8(v.x[k] << l);
+  const uint32_t x = l < 4 ? (l < 2 ? w[0] : w[1]) : (l < 6 ? w[2] : w[3]);
+  const uint32_t y = (l & 1) ? x >> 16 : x;
+  if (2 * l < G) {
+    B[8 * l] = (uint8_t)y;
+    B[8 * l + 4] = (uint8_t)(y >> 8);
+  }
+}
+template <int G>
+__device__ __forceinline__ Bytes16 unstage_bytes(const uint8_t* B, int l) {
+  uint32_t y = 0u;
+  if (2 * l < G) y = (uint32_t)B[8 * l] | ((uint32_t)B[8 * l + 4] << 8);
+  y = (l & 1) ? y << 16 : y;
+  Bytes16 v;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) v.x[k] = (or8((l >> 1) == k ? y : 0u) >> l) & 0x01010101u;
+  return v;
+}
+
+// The class order of sweep t (Fisher-Yates over 16, as in kk_tri.hip), entry p.
+__device__ __forceinline__ uint32_t hex_order(uint32_t k0, uint32_t k1, uint64_t t, int p) {
+  const uint32_t tl = (uint32_t)t, th = ctr_hi(t, kTagTriOrder);
+  uint32_t w[16];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const Philox4 b = philox10((uint32_t)j, 0u, tl, th, k0, k1);
+    w[4 * j] = b.x;
+    w[4 * j + 1] = b.y;
+    w[4 * j + 2] = b.z;
+    w[4 * j + 3] = b.w;
+  }
+  uint64_t perm = 0xFEDCBA9876543210ull;
+#pragma unroll
+  for (int i = 15; i >= 1; --i) {
+    const int k = (int)(((uint64_t)w[15 - i] * (uint64_t)(i + 1)) >> 32);
+    const uint64_t vi = (perm >> (4 * i)) & 0xFull, vk = (perm >> (4 * k)) & 0xFull;
+    perm &= ~((0xFull << (4 * i)) | (0xFull << (4 * k)));
+    perm |= (vk << (4 * i)) | (vi << (4 * k));
+  }
+  return (uint32_t)((perm >> (4 * p)) & 0xFull);
+}
+
+// Sum of every thread's count, added to *dst by thread 0.
+__device__ __forceinline__ void add_count(uint32_t cnt, uint32_t* total, unsigned long long* dst) {
+  for (int off = 32; off > 0; off >>= 1) cnt += __shfl_down(cnt, off, 64);
+  if ((threadIdx.x & 63u) == 0u && cnt) atomicAdd(total, cnt);
+  __syncthreads();
+  if (threadIdx.x == 0 && *total) atomicAdd(dst, (unsigned long long)*total);
+}
+
+// ---------------------------------------------------------------------------
+// One sweep of the 16 classes on the tile (tx, ty) of TW x TR sites, from `in`
+// to `out`.  The window holds kHexLeft columns and kTriHalo rows before the
+// tile and at least kTriHalo after it; a cell's value after a phase depends on
+// cells within two steps, so the cells at least 33 from the window's edge --
+// the tile -- are exact after 16 phases.  Every phase works on all the rows
+// that have two rows around them; what the outer cells and the unused bits
+// hold never reaches the tile.
+//
+// What bounds it: the draws, by VALU issue (66 instructions per two sites: 18
+// multiplies and ten compare/add pairs among them, about 300 of a SIMD's
+// cycles at four waves), then the 16 phases, by one wave's latency (about 105
+// dependent instructions, 19 LDS reads, 7 LDS xors and a barrier, 1300
+// cycles; the rows of a window fill 2 to 6 waves, so a phase cannot be
+// shortened by more of them).  4092^2 (256 x 256 tiles, one per CU): 28 us of
+// draws, 9 us of phases, 7 us of loads, packing and stores, 48.5 us per sweep
+// in all, against 104 us with one byte per site and a Philox block per
+// attempt; 1028^2 25.0 against 31.1 us, 404 x 412 17.6 against 23.9 us.
+__device__ __forceinline__ void hex_sweep_body(const uint8_t* __restrict__ in, uint8_t* __restrict__ out, uint32_t L,
+                                               uint32_t H, uint32_t TW, uint32_t TR, uint32_t tx, uint32_t ty,
+                                               uint32_t k0, uint32_t k1, uint64_t t, const HexAccept& acc,
+                                               unsigned long long* partials, uint32_t* lds) {
+  constexpr int G = 16, ROW = kHexRow16;
+  __shared__ uint32_t perm_s[16], total_s, next_s;
+  const uint32_t N = L * H;
+  const int WR = (int)TR + 2 * (int)kTriHalo, NJ = hex_groups(TW);
+  const int N8 = (NJ + 7) >> 3;  // eight-group blocks per row
+  const uint32_t x0 = tx * TW, y0 = ty * TR;
+  const int TWe = (int)min(TW, L - x0), TRe = (int)min(TR, H - y0);
+  // ring index of window cell (0, 0), a multiple of 4
+  uint32_t base = (y0 >= kTriHalo ? y0 - kTriHalo : y0 + H - kTriHalo) * L + x0;
+  base = base >= kHexLeft ? base - kHexLeft : base + N - kHexLeft;
+  const int lane = (int)(threadIdx.x & 63u), nthreads = (int)blockDim.x;
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), nwaves = nthreads >> 6;
+  uint32_t* S = lds;                            // WR rows of ROW words
+  uint32_t* D = lds + hex_spin_words(WR, ROW);  // draws: [class][row][6]
+  auto row_base = [&](int r) {
+    const uint32_t s = base + (uint32_t)r * L;
+    return s >= N ? s - N : s;
+  };
+  if (threadIdx.x == 0) {
+    total_s = 0u;
+    next_s = (uint32_t)nwaves;
+  }
+  // the window: eight lanes per (row, eight groups); the loads of the first
+  // kPre rounds are issued here and packed after the draws
+  constexpr int kPre = 8;
+  const int l8 = lane & 7, nblk = WR * N8, step = nthreads >> 3;
+  const int blk0 = (int)(threadIdx.x >> 3);
+  auto load_blk = [&](int i) {
+    const int r = N8 == 1 ? i : i / N8;
+    return ring_bytes(in, row_base(r) + (uint32_t)(G * (8 * (i - r * N8) + l8)), N);
+  };
+  auto store_blk = [&](int i, const Bytes16& v) {
+    const int r = N8 == 1 ? i : i / N8;
+    stage_bytes<G>(reinterpret_cast<uint8_t*>(S + r * ROW) + (i - r * N8), v, l8);
+  };
+  Bytes16 v[kPre];
+#pragma unroll
+  for (int k = 0; k < kPre; ++k)
+    if (blk0 + k * step < nblk) v[k] = load_blk(blk0 + k * step);
+  __syncthreads();
+  if (wave == 0) {
+    const uint32_t c = hex_order(k0, k1, t, lane & 15);
+    if (lane < 16) perm_s[lane] = c;
+  }
+  // the draws: task = (column class pair, 32 rows), each row in two halves;
+  // the waves take the tasks as they finish (the scheduler favours the oldest)
+  {
+    const Head hd = philox_head(0u, (uint32_t)t, ctr_hi(t, kTagTri), k0, k1);
+    const int h = (NJ + 1) >> 1, ntask = 8 * ((WR - 4 + 31) >> 5);
+    for (int task = wave; task < ntask;) {
+      uint32_t nx = 0u;
+      if (lane == 0) nx = atomicAdd(&next_s, 1u);
+      const int rb = task >> 3, q = 2 * (task & 7);
+      const int r = min(2 + 32 * rb + (lane & 31), WR - 3);
+      int blk = (int)((row_base(r) + (uint32_t)q) >> 1) + (lane < 32 ? 8 * (h - 1) : 8 * (2 * h - 1));
+      const int nb = (int)(N >> 1);
+      blk = blk >= nb ? blk - nb : blk;
+      Draw e{}, o{};
+      for (int j = 0; j < h; ++j) {
+        const Philox4 w = philox_tail(hd, (uint32_t)blk);
+        push_attempt(e, w.x, w.y, acc);
+        push_attempt(o, w.z, w.w, acc);
+        blk -= 8;
+        blk = blk < 0 ? blk + nb : blk;
+      }
+      const Draw d = join_draws(e, o, (uint32_t)h);
+      store_draw(D + 6 * ((q + (lane >> 5)) * WR + r), d, acc);
+      task = __builtin_amdgcn_readfirstlane((int)nx);
+    }
+  }
+#pragma unroll
+  for (int k = 0; k < kPre; ++k)
+    if (blk0 + k * step < nblk) store_blk(blk0 + k * step, v[k]);
+  for (int i = blk0 + kPre * step; i < nblk; i += step) store_blk(i, load_blk(i));
+  __syncthreads();
+  // The phases are one wave's latency each: the rows need nb waves, and up to
+  // three sets of nb waves take turns, so that a set finds its addresses and
+  // draws for its next phase while the others work.
+  const int nb = (WR - 4 + 63) >> 6, nsets = min(3, nwaves / nb);
+  const int set = wave / nb;
+  const int r = 2 + 64 * (wave - set * nb) + lane;
+  const bool row_ok = r < WR - 2;
+  const int rc = row_ok ? r : 2;
+  const uint32_t cmask = row_ok ? 0xFFFFFFFFu : 0u;
+  const int f = (int)(row_base(rc) & 15u);
+  const bool counted = row_ok && r >= (int)kTriHalo && r < (int)kTriHalo + TRe;
+  uint32_t cnt = 0;
+  Place pl{};
+  Draw d{};
+  int q = 0;
+  auto prepare = [&](int p) {
+    q = ((int)perm_s[p] - f) & 15;
+    pl = class_place<G, ROW>(rc, q);
+    d = load_draw(D + 6 * (q * WR + rc));
+  };
+  if (set < nsets) prepare(set);
+  int turn = 0;
+#pragma unroll 1
+  for (int p = 0; p < 16; ++p) {
+    uint32_t F = 0u;
+    const bool mine = set == turn;
+    if (mine) {
+      F = decide(read_around<ROW>(S, pl), d, acc.negmask, cmask);
+      exchange<ROW>(S, pl, d, F);
+    }
+    __syncthreads();
+    if (mine) {
+      const uint32_t m = column_mask<G>(q, (int)kHexLeft, (int)kHexLeft + TWe);
+      cnt += counted ? (uint32_t)__builtin_popcount(F & m) : 0u;
+      if (p + nsets < 16) prepare(p + nsets);
+    }
+    turn = turn + 1 == nsets ? 0 : turn + 1;
+  }
+  // the tile, four sites at a time at its edges (its first column and width are multiples of 4)
+  for (int i = blk0; i < TRe * N8; i += step) {
+    const int rr = N8 == 1 ? i : i / N8, g8 = i - rr * N8;
+    const Bytes16 y =
+        unstage_bytes<G>(reinterpret_cast<const uint8_t*>(S + (rr + (int)kTriHalo) * ROW) + g8, l8);
+    uint8_t* row = out + (size_t)(y0 + (uint32_t)rr) * L + x0;
+    const int c = G * (8 * g8 + l8) - (int)kHexLeft;
+    if (c >= 0 && c + 16 <= TWe) {
+      __builtin_memcpy(row + c, &y, 16);
+    } else {
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+        if (c + 4 * k >= 0 && c + 4 * k < TWe) __builtin_memcpy(row + c + 4 * k, &y.x[k], 4);
+    }
+  }
+  add_count(cnt, &total_s, partials + blockIdx.x % kTriPartials);
+}
+
+__global__ __launch_bounds__(1024) void hex_sweep(const uint8_t* __restrict__ in, uint8_t* __restrict__ out,
+                                                  uint32_t L, uint32_t H, uint32_t TW, uint32_t TR, uint32_t ntx,
+                                                  uint32_t k0, uint32_t k1, uint64_t t, HexAccept acc,
+                                                  unsigned long long* partials) {
+  extern __shared__ __attribute__((aligned(16))) uint32_t lds[];
+  const uint32_t tile = (uint32_t)xcd_tile((int)blockIdx.x, (int)gridDim.x);
+  hex_sweep_body(in, out, L, H, TW, TR, tile % ntx, tile / ntx, k0, k1, t, acc, partials, lds);
+}
+
+// Many lattices in one launch: workgroup b does tile jobs[b].y of replica
+// jobs[b].x, sweep k of the run (buffers and sweep counter from the table).
+__global__ __launch_bounds__(1024) void hex_sweep_batch(const TriBatchRep* reps, const uint2* jobs, uint32_t k) {
+  extern __shared__ __attribute__((aligned(16))) uint32_t lds[];
+  const uint2 jb = jobs[blockIdx.x];
+  const TriBatchRep& R = reps[jb.x];
+  const uint32_t par = R.cur ^ (k & 1u);
+  hex_sweep_body(R.lat[par], R.lat[par ^ 1u], R.L, R.H, R.TW, R.TR, jb.y % R.ntx, jb.y / R.ntx, R.k0, R.k1, R.t0 + k,
+                 R.acc, R.partials, lds);
+}
+
+}  // namespace
+
+hipError_t launch_tri_tile_sweep(const uint8_t* in, uint8_t* out, int L, int H, int TW, int TR, uint32_t k0,
+                                uint32_t k1, uint64_t t, const TriAccept& acc, unsigned long long* partials,
+                                hipStream_t stream) {
+  if (!tri_tile_fits(L, H, TW, TR)) return hipErrorInvalidValue;
+  const HexTile ht = hex_tile(TW, TR);
+  const uint32_t ntx = ((uint32_t)L + ht.tw - 1) / ht.tw, nty = ((uint32_t)H + ht.tr - 1) / ht.tr;
+  hipLaunchKernelGGL(hex_sweep, dim3(ntx * nty), dim3(1024), hex_lds_bytes(ht.tr), stream, in, out, (uint32_t)L,
+                     (uint32_t)H, ht.tw, ht.tr, ntx, k0, k1, t, hex_accept(acc), partials);
+  return hipGetLastError();
+}
+
+hipError_t launch_tri_tile_sweep_batch(const TriBatchRep* reps, const uint2* jobs, uint32_t njobs, uint32_t k,
+                                       size_t lds_bytes, hipStream_t stream) {
+  if (njobs == 0) return hipSuccess;
+  hipLaunchKernelGGL(hex_sweep_batch, dim3(njobs), dim3(1024), lds_bytes, stream, reps, jobs, k);
+  return hipGetLastError();
+}
+
+}  // namespace kk

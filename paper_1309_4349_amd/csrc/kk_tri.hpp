@@ -16,21 +16,63 @@ struct TriAccept {
 };
 hipError_t launch_tri_phase(uint8_t* lat, int L, int H, uint32_t k0, uint32_t k1, uint64_t t, int p,
                             const TriAccept& acc, unsigned long long* partials, hipStream_t stream);
+// What the bit-plane kernels (kk_hex.hip) need of the table: only n = 2, 3, 4
+// (omega > 0) or 6, 7, 8 (omega < 0) can be rejected.
+struct HexAccept {
+  uint32_t thr[3];   // U < thr accepts
+  uint32_t all[3];   // 0xFFFFFFFF: every U is accepted
+  uint32_t negmask;  // 0xFFFFFFFF: the restricted counts are 6, 7, 8
+};
+inline HexAccept hex_accept(const TriAccept& acc) {
+  HexAccept a{};
+  const bool neg = acc.T[2] >= ((uint64_t)1 << 32);  // omega <= 0 (n = 2 is always accepted)
+  a.negmask = neg ? 0xFFFFFFFFu : 0u;
+  for (int j = 0; j < 3; ++j) {
+    const uint64_t T = acc.T[neg ? 6 + j : 2 + j];
+    a.all[j] = T >= ((uint64_t)1 << 32) ? 0xFFFFFFFFu : 0u;
+    a.thr[j] = (uint32_t)(a.all[j] ? 0xFFFFFFFFu : T);
+  }
+  return a;
+}
 // Whole-sweep tiles (16 phases per launch on an LDS window, `in` -> `out`).
+// Which tiles are taken: a byte per site of the window, rows of an odd number
+// of words, next to 16 KiB, in one workgroup's LDS.
 constexpr uint32_t kTriHalo = 33;  // 2 cells per phase, plus 1 for the first phase's reads
 __host__ __device__ inline uint32_t tri_window_stride(uint32_t TW) {
   const uint32_t s = (TW + 2 * kTriHalo + 3u) & ~3u;  // whole words, an odd number of them
   return ((s >> 2) & 1u) ? s : s + 4u;
 }
-// Per workgroup, after the window: each of the 16 waves keeps a ring of 128
+// The literal MPKK's tile kernel: each of the 16 waves keeps a ring of 128
 // pending centres (8 bytes each) whose pair is unlike, so that the decisions
-// run on full waves (tri_tile_sweep).
+// run on full waves.
 constexpr uint32_t kTriQueue = 128, kTriQueueBytes = 16u * kTriQueue * 8u;
 __host__ __device__ inline size_t tri_window_area(uint32_t TW, uint32_t TR) {
   return ((size_t)tri_window_stride(TW) * (TR + 2 * kTriHalo) + 7u) & ~(size_t)7u;
 }
 __host__ __device__ inline size_t tri_window_bytes(uint32_t TW, uint32_t TR) {
   return tri_window_area(TW, TR) + kTriQueueBytes;
+}
+// The bit-plane window of the class schedule: kHexLeft columns before the tile
+// (a multiple of 4 not below kTriHalo, so that rows start on whole words of
+// the ring), NJ groups of 16 columns in all, one bit per group in each of a
+// row's 16 class words; after the rows, six random words per (class, row).
+constexpr uint32_t kHexLeft = 36;
+constexpr int kHexRow16 = 17;  // words per row: 16 classes and one of padding
+constexpr uint32_t kHexMaxCols = 440, kHexMaxRows = 288;
+__host__ __device__ inline int hex_groups(uint32_t TW) { return (int)((kHexLeft + TW + kTriHalo + 15u) / 16u); }
+__host__ __device__ inline int hex_spin_words(int WR, int row) { return (WR * row + 3) & ~3; }
+inline size_t hex_lds_bytes(uint32_t TR) {
+  const int WR = (int)TR + 2 * (int)kTriHalo;
+  return ((size_t)hex_spin_words(WR, kHexRow16) + (size_t)16 * WR * 6) * 4;
+}
+// The tile a launch works with: the columns a multiple of 4, and a tile beyond
+// 32 groups or beyond the LDS in equal parts.
+struct HexTile {
+  uint32_t tw, tr;
+};
+inline HexTile hex_tile(int TW, int TR) {
+  const uint32_t nx = ((uint32_t)TW + kHexMaxCols - 1) / kHexMaxCols, ny = ((uint32_t)TR + kHexMaxRows - 1) / kHexMaxRows;
+  return HexTile{((((uint32_t)TW + nx - 1) / nx) + 3u) & ~3u, ((uint32_t)TR + ny - 1) / ny};
 }
 inline bool tri_tile_fits(int L, int H, int TW, int TR) {
   return TW >= 16 && TR >= 16 && TW + 2 * (int)kTriHalo <= L && TR + 2 * (int)kTriHalo <= H &&
@@ -59,10 +101,10 @@ constexpr uint64_t kTriResidentChunk = 1024;  // sweeps per launch of a single h
 // lat[cur ^ (k & 1)] and writes the other buffer with sweep counter t0 + k.
 struct TriBatchRep {
   uint8_t* lat[2];
-  uint32_t L, H, TW, TR, ntx, cur;
+  uint32_t L, H, TW, TR, ntx, cur;  // TW x TR: a hex_tile
   uint32_t k0, k1;
   uint64_t t0;
-  TriAccept acc;
+  HexAccept acc;
   unsigned long long* partials;  // kTriPartials sums of the replica
 };
 // jobs[b] = (replica, tile) for workgroup b; lds_bytes = the largest window.

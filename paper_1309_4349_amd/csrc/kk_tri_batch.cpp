@@ -132,13 +132,14 @@ kk_status kk_tri_batch_create(kk_tri_batch** out, const kk_tri_replica* reps, si
   std::vector<uint2> jobs;
   for (size_t k = 0; k < b->order.size(); ++k) {
     const kk_sim* h = b->sims[b->order[k]];
-    b->tw.push_back((uint32_t)h->tri_tw);
-    b->tr.push_back((uint32_t)h->tri_tr);
-    const uint32_t ntx = (uint32_t)((h->L + h->tri_tw - 1) / h->tri_tw);
-    const uint32_t nty = (uint32_t)((h->H + h->tri_tr - 1) / h->tri_tr);
+    const HexTile ht = hex_tile(h->tri_tw, h->tri_tr);
+    b->tw.push_back(ht.tw);
+    b->tr.push_back(ht.tr);
+    const uint32_t ntx = ((uint32_t)h->L + ht.tw - 1) / ht.tw;
+    const uint32_t nty = ((uint32_t)h->H + ht.tr - 1) / ht.tr;
     for (uint32_t t = 0; t < ntx * nty; ++t) jobs.push_back(make_uint2((uint32_t)k, t));
     b->job_end.push_back(jobs.size());
-    b->lds_bytes = std::max(b->lds_bytes, tri_window_bytes((uint32_t)h->tri_tw, (uint32_t)h->tri_tr));
+    b->lds_bytes = std::max(b->lds_bytes, hex_lds_bytes(ht.tr));
   }
   if (!b->order.empty()) {
     kk_status st = device_alloc((void**)&b->d_reps, b->order.size() * sizeof(TriBatchRep));
@@ -222,7 +223,7 @@ kk_status tri_batch_run(kk_tri_batch* b) {
       R.k0 = h->k0;
       R.k1 = h->k1;
       R.t0 = h->t;
-      R.acc = h->tacc;
+      R.acc = hex_accept(h->tacc);
       R.partials = h->partials;
       mx = std::max(mx, b->sweeps[b->order[k]]);
     }
