@@ -53,6 +53,36 @@ __host__ __device__ __forceinline__ uint32_t ctr_hi(uint64_t t, uint32_t tag) {
   return (uint32_t)((t >> 32) & 0x0FFFFFFFu) | (tag << 28);
 }
 
+// The same block on the host, for values that are uniform over a launch (the
+// class orders): there they are arguments instead of a wavefront's serial
+// chain at the start of every workgroup.
+inline Philox4 philox10_host(uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3, uint32_t k0, uint32_t k1) {
+  for (int i = 0; i < 10; ++i) {
+    const uint64_t p0 = (uint64_t)c0 * 0xD2511F53u, p1 = (uint64_t)c2 * 0xCD9E8D57u;
+    const uint32_t n0 = (uint32_t)(p1 >> 32) ^ c1 ^ k0, n2 = (uint32_t)(p0 >> 32) ^ c3 ^ k1;
+    c1 = (uint32_t)p1;
+    c3 = (uint32_t)p0;
+    c0 = n0;
+    c2 = n2;
+    k0 += 0x9E3779B9u;
+    k1 += 0xBB67AE85u;
+  }
+  return Philox4{c0, c1, c2, c3};
+}
+
+// Fisher-Yates over n nibbles (entry e of the result in bits 4e .. 4e + 3):
+// step i = n - 1 .. 1 swaps entries i and (w[n - 1 - i] * (i + 1)) >> 32.
+__host__ __device__ __forceinline__ uint64_t shuffle_nibbles(const uint32_t* w, int n) {
+  uint64_t perm = 0xFEDCBA9876543210ull;
+#pragma unroll
+  for (int i = n - 1; i >= 1; --i) {
+    const int k = (int)(((uint64_t)w[n - 1 - i] * (uint64_t)(i + 1)) >> 32);
+    const uint64_t x = ((perm >> (4 * i)) ^ (perm >> (4 * k))) & 0xFull;
+    perm ^= (x << (4 * i)) ^ (x << (4 * k));  // i == k: x is 0
+  }
+  return perm;
+}
+
 __device__ __forceinline__ int imod(int v, int m) {
   int r = v % m;
   return r < 0 ? r + m : r;

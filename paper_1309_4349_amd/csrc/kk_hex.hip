@@ -33,7 +33,7 @@
 namespace kk {
 namespace {
 
-constexpr uint32_t kTagTri = 6u, kTagTriOrder = 7u;
+constexpr uint32_t kTagTri = 6u, kTagTriOrder = 7u, kTagMpkkK = 8u, kTagMpkk = 9u;
 
 // Three-input bitwise functions by truth table, a = 0xF0, b = 0xCC, c = 0xAA.
 constexpr unsigned kA = 0xF0u, kB = 0xCCu, kC = 0xAAu;
@@ -133,7 +133,7 @@ struct Around {
 // Where a lane finds the words around its own: A[d + 2] the word of class
 // q + d mod G two rows above (so that every row offset is a positive
 // immediate), rot[d + 2] the turn that aligns that class's words to the
-// centres (1 where the class passed G - 1, 31 where it passed 0).
+// centres (1 where the class passed G - 1, -1 where it passed 0).
 struct Place {
   int A[5];
   uint32_t rot[5];
@@ -143,10 +143,17 @@ __device__ __forceinline__ Place class_place(int r, int q) {
   Place p;
 #pragma unroll
   for (int d = -2; d <= 2; ++d) {
+    // arithmetic instead of selects: a compare, its scalar mask and the select
+    // that reads it are a longer chain
     const int k = q + d;
-    const bool lo = k < 0, hi = k >= G;
-    p.A[d + 2] = (r - 2) * ROW + (lo ? k + G : (hi ? k - G : k));
-    p.rot[d + 2] = lo ? 31u : (hi ? 1u : 0u);
+    if constexpr (G == 16) {
+      p.A[d + 2] = (r - 2) * ROW + (k & 15);
+      p.rot[d + 2] = (uint32_t)(k >> 4);  // -1 turns by 31
+    } else {
+      const int lo = k >> 31, hi = (G - 1 - k) >> 31;
+      p.A[d + 2] = (r - 2) * ROW + k + (lo & G) - (hi & G);
+      p.rot[d + 2] = (uint32_t)(lo - hi);
+    }
   }
   return p;
 }
@@ -208,7 +215,9 @@ __device__ __forceinline__ uint32_t decide(const Around& v, const Draw& q, uint3
   return lut3<kA & (~kB | kC)>(live, rm, acc);
 }
 
-// Flip the accepted centres F and their partners.
+// Flip the accepted centres F and their partners.  Lanes without a row stay
+// out: their zero flips would all go to one word, and xors of one wave to one
+// word run one after another (62 such lanes cost 1650 cycles per iteration).
 template <int ROW>
 __device__ __forceinline__ void exchange(uint32_t* S, const Place& p, const Draw& q, uint32_t F) {
   const int* A = p.A;
@@ -225,12 +234,11 @@ __device__ __forceinline__ void exchange(uint32_t* S, const Place& p, const Draw
   atomicXor(&S[A[3] + ROW], rotr(f2 & q.sgn, re));
 }
 
-// Bits j of class q whose columns G*j + q lie in [c0, c1).
+// Bits j of class q whose columns G*j + q lie in [c0, c1), c0 >= G > q, at most 31 of them.
 template <int G>
 __device__ __forceinline__ uint32_t column_mask(int q, int c0, int c1) {
-  const int lo = (c0 - q + G - 1) / G, hi = (c1 - q + G - 1) / G;  // c0 > q, c1 >= c0
-  const uint32_t below_hi = hi >= 32 ? 0xFFFFFFFFu : ((1u << hi) - 1u);
-  return below_hi & ~((1u << lo) - 1u);
+  const uint32_t lo = (uint32_t)(c0 + G - 1 - q) / G, hi = (uint32_t)(c1 + G - 1 - q) / G;
+  return ((1u << (hi - lo)) - 1u) << lo;
 }
 
 // One row's draws of two classes in halves: lanes 0..31 hold the first h bits
@@ -246,11 +254,12 @@ __device__ __forceinline__ Draw join_draws(const Draw& a, const Draw& b, uint32_
               join_halves(a.a0, b.a0, h),   join_halves(a.a1, b.a1, h),   join_halves(a.a2, b.a2, h)};
 }
 
-__device__ __forceinline__ void store_draw(uint32_t* D, const Draw& q, const HexAccept& acc) {
+// A draw whose first bit is group j0's.
+__device__ __forceinline__ void store_draw(uint32_t* D, const Draw& q, uint32_t j0, const HexAccept& acc) {
   uint2* p = reinterpret_cast<uint2*>(D);
-  p[0] = make_uint2(q.sgn, q.ax1);
-  p[1] = make_uint2(q.ax2, q.a0 | acc.all[0]);
-  p[2] = make_uint2(q.a1 | acc.all[1], q.a2 | acc.all[2]);
+  p[0] = make_uint2(q.sgn << j0, q.ax1 << j0);
+  p[1] = make_uint2(q.ax2 << j0, (q.a0 << j0) | acc.all[0]);
+  p[2] = make_uint2((q.a1 << j0) | acc.all[1], (q.a2 << j0) | acc.all[2]);
 }
 __device__ __forceinline__ Draw load_draw(const uint32_t* D) {
   const uint2* p = reinterpret_cast<const uint2*>(D);
@@ -319,28 +328,23 @@ __device__ __forceinline__ Bytes16 unstage_bytes(const uint8_t* B, int l) {
   return v;
 }
 
-// The class order of sweep t (Fisher-Yates over 16, as in kk_tri.hip), entry p.
-__device__ __forceinline__ uint32_t hex_order(uint32_t k0, uint32_t k1, uint64_t t, int p) {
-  const uint32_t tl = (uint32_t)t, th = ctr_hi(t, kTagTriOrder);
+// The class order of sweep t: Philox blocks 0 .. 3 of the order's counters,
+// one per lane, and the shuffle in scalar registers.
+__device__ __forceinline__ uint64_t hex_order(uint32_t k0, uint32_t k1, uint64_t t) {
+  const Philox4 b = philox10(threadIdx.x & 3u, 0u, (uint32_t)t, ctr_hi(t, kTagTriOrder), k0, k1);
   uint32_t w[16];
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
-    const Philox4 b = philox10((uint32_t)j, 0u, tl, th, k0, k1);
-    w[4 * j] = b.x;
-    w[4 * j + 1] = b.y;
-    w[4 * j + 2] = b.z;
-    w[4 * j + 3] = b.w;
+    w[4 * j] = (uint32_t)__builtin_amdgcn_readlane((int)b.x, j);
+    w[4 * j + 1] = (uint32_t)__builtin_amdgcn_readlane((int)b.y, j);
+    w[4 * j + 2] = (uint32_t)__builtin_amdgcn_readlane((int)b.z, j);
+    w[4 * j + 3] = (uint32_t)__builtin_amdgcn_readlane((int)b.w, j);
   }
-  uint64_t perm = 0xFEDCBA9876543210ull;
-#pragma unroll
-  for (int i = 15; i >= 1; --i) {
-    const int k = (int)(((uint64_t)w[15 - i] * (uint64_t)(i + 1)) >> 32);
-    const uint64_t vi = (perm >> (4 * i)) & 0xFull, vk = (perm >> (4 * k)) & 0xFull;
-    perm &= ~((0xFull << (4 * i)) | (0xFull << (4 * k)));
-    perm |= (vk << (4 * i)) | (vi << (4 * k));
-  }
-  return (uint32_t)((perm >> (4 * p)) & 0xFull);
+  return shuffle_nibbles(w, 16);
 }
+
+// i / n for 0 <= i < 4096 and n = 1 .. 4, inv = 65536 / n + 1.
+__device__ __forceinline__ int div_small(int i, int inv) { return (int)(((uint32_t)i * (uint32_t)inv) >> 16); }
 
 // Sum of every thread's count, added to *dst by thread 0.
 __device__ __forceinline__ void add_count(uint32_t cnt, uint32_t* total, unsigned long long* dst) {
@@ -362,18 +366,18 @@ __device__ __forceinline__ void add_count(uint32_t cnt, uint32_t* total, unsigne
 // What bounds it: the draws, by VALU issue (66 instructions per two sites: 18
 // multiplies and ten compare/add pairs among them, about 300 of a SIMD's
 // cycles at four waves), then the 16 phases, by one wave's latency (about 105
-// dependent instructions, 19 LDS reads, 7 LDS xors and a barrier, 1300
-// cycles; the rows of a window fill 2 to 6 waves, so a phase cannot be
-// shortened by more of them).  4092^2 (256 x 256 tiles, one per CU): 28 us of
-// draws, 9 us of phases, 7 us of loads, packing and stores, 48.5 us per sweep
-// in all, against 104 us with one byte per site and a Philox block per
-// attempt; 1028^2 25.0 against 31.1 us, 404 x 412 17.6 against 23.9 us.
+// dependent instructions, 19 LDS reads, 7 LDS xors and a barrier, 950 cycles;
+// the rows of a window fill 2 to 6 waves, so a phase cannot be shortened by
+// more of them).  4092^2 (256 x 256 tiles, one per CU): 26 us of draws, 8 us
+// of phases, 8 us of loads, packing and stores, 46 us per sweep in all,
+// against 104 us with one byte per site and a Philox block per attempt;
+// 1028^2 19.0 against 31.1 us, 404 x 412 14.9 against 23.9 us.
 __device__ __forceinline__ void hex_sweep_body(const uint8_t* __restrict__ in, uint8_t* __restrict__ out, uint32_t L,
                                                uint32_t H, uint32_t TW, uint32_t TR, uint32_t tx, uint32_t ty,
-                                               uint32_t k0, uint32_t k1, uint64_t t, const HexAccept& acc,
-                                               unsigned long long* partials, uint32_t* lds) {
+                                               uint32_t k0, uint32_t k1, uint64_t t, uint64_t order,
+                                               const HexAccept& acc, unsigned long long* partials, uint32_t* lds) {
   constexpr int G = 16, ROW = kHexRow16;
-  __shared__ uint32_t perm_s[16], total_s, next_s;
+  __shared__ uint32_t phase_s[16], total_s, next_s;  // phase_s: the phase of each class
   const uint32_t N = L * H;
   const int WR = (int)TR + 2 * (int)kTriHalo, NJ = hex_groups(TW);
   const int N8 = (NJ + 7) >> 3;  // eight-group blocks per row
@@ -390,6 +394,7 @@ __device__ __forceinline__ void hex_sweep_body(const uint8_t* __restrict__ in, u
     const uint32_t s = base + (uint32_t)r * L;
     return s >= N ? s - N : s;
   };
+  if (threadIdx.x < 16) phase_s[(uint32_t)(order >> (4u * threadIdx.x)) & 15u] = threadIdx.x;
   if (threadIdx.x == 0) {
     total_s = 0u;
     next_s = (uint32_t)nwaves;
@@ -398,36 +403,48 @@ __device__ __forceinline__ void hex_sweep_body(const uint8_t* __restrict__ in, u
   // kPre rounds are issued here and packed after the draws
   constexpr int kPre = 8;
   const int l8 = lane & 7, nblk = WR * N8, step = nthreads >> 3;
-  const int blk0 = (int)(threadIdx.x >> 3);
+  const int blk0 = (int)(threadIdx.x >> 3), inv8 = 65536 / N8 + 1;
   auto load_blk = [&](int i) {
-    const int r = N8 == 1 ? i : i / N8;
+    const int r = div_small(i, inv8);
     return ring_bytes(in, row_base(r) + (uint32_t)(G * (8 * (i - r * N8) + l8)), N);
   };
   auto store_blk = [&](int i, const Bytes16& v) {
-    const int r = N8 == 1 ? i : i / N8;
+    const int r = div_small(i, inv8);
     stage_bytes<G>(reinterpret_cast<uint8_t*>(S + r * ROW) + (i - r * N8), v, l8);
   };
   Bytes16 v[kPre];
 #pragma unroll
   for (int k = 0; k < kPre; ++k)
-    if (blk0 + k * step < nblk) v[k] = load_blk(blk0 + k * step);
+    if (k * step < nblk) v[k] = load_blk(min(blk0 + k * step, nblk - 1));  // a uniform test; spare lanes load twice
   __syncthreads();
-  if (wave == 0) {
-    const uint32_t c = hex_order(k0, k1, t, lane & 15);
-    if (lane < 16) perm_s[lane] = c;
-  }
-  // the draws: task = (column class pair, 32 rows), each row in two halves;
-  // the waves take the tasks as they finish (the scheduler favours the oldest)
+  // The draws: task = (pair of classes, 32 rows), each row in two halves.  A
+  // class of phase p is needed within 31 - 2p cells of the tile, a pair as far
+  // as its earlier class.  The waves take the tasks as they finish (the
+  // scheduler favours the oldest).
   {
     const Head hd = philox_head(0u, (uint32_t)t, ctr_hi(t, kTagTri), k0, k1);
-    const int h = (NJ + 1) >> 1, ntask = 8 * ((WR - 4 + 31) >> 5);
-    for (int task = wave; task < ntask;) {
+    const int nb = (int)(N >> 1);
+    auto margin = [&](int pair) { return 31 - 2 * (int)min(phase_s[2 * pair], phase_s[2 * pair + 1]); };
+    int pair = 0, first = 0;  // the pair of the current task and the pair's first task
+    int m = __builtin_amdgcn_readfirstlane(margin(0));
+    for (int task = wave;;) {
+      int blocks = (TRe + 2 * m + 31) >> 5;
+      while (pair < 8 && task >= first + blocks) {
+        first += blocks;
+        if (++pair < 8) {
+          m = __builtin_amdgcn_readfirstlane(margin(pair));
+          blocks = (TRe + 2 * m + 31) >> 5;
+        }
+      }
+      if (pair == 8) break;
       uint32_t nx = 0u;
       if (lane == 0) nx = atomicAdd(&next_s, 1u);
-      const int rb = task >> 3, q = 2 * (task & 7);
-      const int r = min(2 + 32 * rb + (lane & 31), WR - 3);
-      int blk = (int)((row_base(r) + (uint32_t)q) >> 1) + (lane < 32 ? 8 * (h - 1) : 8 * (2 * h - 1));
-      const int nb = (int)(N >> 1);
+      const int j0 = ((int)kHexLeft - m) >> 4, nj = (((int)kHexLeft + TWe + m - 1) >> 4) + 1 - j0;
+      const int h = (nj + 1) >> 1;
+      const int r = min((int)kTriHalo - m + 32 * (task - first) + (lane & 31), (int)kTriHalo + TRe + m - 1);
+      const uint32_t s = row_base(r);
+      const int q = (2 * pair - (int)s) & 15;  // the column class of the pair's even class
+      int blk = (int)((s + (uint32_t)q) >> 1) + 8 * (j0 + (lane < 32 ? h - 1 : 2 * h - 1));
       blk = blk >= nb ? blk - nb : blk;
       Draw e{}, o{};
       for (int j = 0; j < h; ++j) {
@@ -437,8 +454,7 @@ __device__ __forceinline__ void hex_sweep_body(const uint8_t* __restrict__ in, u
         blk -= 8;
         blk = blk < 0 ? blk + nb : blk;
       }
-      const Draw d = join_draws(e, o, (uint32_t)h);
-      store_draw(D + 6 * ((q + (lane >> 5)) * WR + r), d, acc);
+      store_draw(D + 6 * ((q + (lane >> 5)) * WR + r), join_draws(e, o, (uint32_t)h), (uint32_t)j0, acc);
       task = __builtin_amdgcn_readfirstlane((int)nx);
     }
   }
@@ -457,13 +473,13 @@ __device__ __forceinline__ void hex_sweep_body(const uint8_t* __restrict__ in, u
   const int rc = row_ok ? r : 2;
   const uint32_t cmask = row_ok ? 0xFFFFFFFFu : 0u;
   const int f = (int)(row_base(rc) & 15u);
-  const bool counted = row_ok && r >= (int)kTriHalo && r < (int)kTriHalo + TRe;
+  const uint32_t counted = row_ok && r >= (int)kTriHalo && r < (int)kTriHalo + TRe ? 0xFFFFFFFFu : 0u;
   uint32_t cnt = 0;
   Place pl{};
   Draw d{};
   int q = 0;
   auto prepare = [&](int p) {
-    q = ((int)perm_s[p] - f) & 15;
+    q = ((int)(order >> (4 * p)) - f) & 15;
     pl = class_place<G, ROW>(rc, q);
     d = load_draw(D + 6 * (q * WR + rc));
   };
@@ -475,19 +491,19 @@ __device__ __forceinline__ void hex_sweep_body(const uint8_t* __restrict__ in, u
     const bool mine = set == turn;
     if (mine) {
       F = decide(read_around<ROW>(S, pl), d, acc.negmask, cmask);
-      exchange<ROW>(S, pl, d, F);
+      if (row_ok) exchange<ROW>(S, pl, d, F);
     }
     __syncthreads();
     if (mine) {
       const uint32_t m = column_mask<G>(q, (int)kHexLeft, (int)kHexLeft + TWe);
-      cnt += counted ? (uint32_t)__builtin_popcount(F & m) : 0u;
+      cnt += (uint32_t)__builtin_popcount(F & m & counted);
       if (p + nsets < 16) prepare(p + nsets);
     }
     turn = turn + 1 == nsets ? 0 : turn + 1;
   }
   // the tile, four sites at a time at its edges (its first column and width are multiples of 4)
   for (int i = blk0; i < TRe * N8; i += step) {
-    const int rr = N8 == 1 ? i : i / N8, g8 = i - rr * N8;
+    const int rr = div_small(i, inv8), g8 = i - rr * N8;
     const Bytes16 y =
         unstage_bytes<G>(reinterpret_cast<const uint8_t*>(S + (rr + (int)kTriHalo) * ROW) + g8, l8);
     uint8_t* row = out + (size_t)(y0 + (uint32_t)rr) * L + x0;
@@ -505,11 +521,11 @@ __device__ __forceinline__ void hex_sweep_body(const uint8_t* __restrict__ in, u
 
 __global__ __launch_bounds__(1024) void hex_sweep(const uint8_t* __restrict__ in, uint8_t* __restrict__ out,
                                                   uint32_t L, uint32_t H, uint32_t TW, uint32_t TR, uint32_t ntx,
-                                                  uint32_t k0, uint32_t k1, uint64_t t, HexAccept acc,
-                                                  unsigned long long* partials) {
+                                                  uint32_t k0, uint32_t k1, uint64_t t, uint64_t order,
+                                                  HexAccept acc, unsigned long long* partials) {
   extern __shared__ __attribute__((aligned(16))) uint32_t lds[];
   const uint32_t tile = (uint32_t)xcd_tile((int)blockIdx.x, (int)gridDim.x);
-  hex_sweep_body(in, out, L, H, TW, TR, tile % ntx, tile / ntx, k0, k1, t, acc, partials, lds);
+  hex_sweep_body(in, out, L, H, TW, TR, tile % ntx, tile / ntx, k0, k1, t, order, acc, partials, lds);
 }
 
 // Many lattices in one launch: workgroup b does tile jobs[b].y of replica
@@ -520,7 +536,217 @@ __global__ __launch_bounds__(1024) void hex_sweep_batch(const TriBatchRep* reps,
   const TriBatchRep& R = reps[jb.x];
   const uint32_t par = R.cur ^ (k & 1u);
   hex_sweep_body(R.lat[par], R.lat[par ^ 1u], R.L, R.H, R.TW, R.TR, jb.y % R.ntx, jb.y / R.ntx, R.k0, R.k1, R.t0 + k,
-                 R.acc, R.partials, lds);
+                 hex_order(R.k0, R.k1, R.t0 + k), R.acc, R.partials, lds);
+}
+
+// ---------------------------------------------------------------------------
+// One whole literal-MPKK step (7 iterations) on a tile, from `in` to `out`.
+// The window holds kMpkkHalo more cells on every side (a cell's value after an
+// iteration depends on cells within three steps).  Every domain of an
+// iteration decides from the lattice as it stood when the iteration began: the
+// decisions of all words are taken, then a barrier, then the exchanges are
+// written (domains are disjoint).  The centres of an iteration sit every 7
+// sites of the ring; domain m = 2b and m = 2b + 1 take their numbers from
+// Philox block b, so with 14 column classes the even domains of a row are one
+// class, the odd ones the class 7 further on, and one block fills a bit of
+// each.
+//
+// What bounds it: as for the class schedule, the draws by VALU issue and the
+// seven iterations by one wave's latency (1550 cycles each: two barriers).
+// 4098 x 4095 (257 x 256 tiles) 50.6 us per step against 102.8 us with one byte
+// per site; 1027 x 1029 16.3 against 25.1 us; 404 x 420 13.1 against 17.1 us, of
+// which 3 us are the launch, 4 the window and its draws, 5 the iterations.
+__global__ __launch_bounds__(1024) void hex_mpkk_step(const uint8_t* __restrict__ in, uint8_t* __restrict__ out,
+                                                      uint32_t L, uint32_t H, uint32_t TW, uint32_t TR, uint32_t ntx,
+                                                      uint32_t k0, uint32_t k1, uint64_t t, uint32_t covers,
+                                                      HexAccept acc, unsigned long long* partials) {
+  extern __shared__ __attribute__((aligned(16))) uint32_t lds[];
+  constexpr int G = 14, ROW = kHexRow14;
+  __shared__ uint32_t total_s, next_s;
+  const uint32_t N = L * H;
+  const int WR = (int)TR + 2 * (int)kMpkkHalo, NJ = hex_mpkk_groups(TW);
+  const int N8 = (NJ + 7) >> 3;
+  const uint32_t tile = (uint32_t)xcd_tile((int)blockIdx.x, (int)gridDim.x);
+  const uint32_t x0 = (tile % ntx) * TW, y0 = (tile / ntx) * TR;
+  const int TWe = (int)min(TW, L - x0), TRe = (int)min(TR, H - y0);
+  uint32_t base = (y0 >= kMpkkHalo ? y0 - kMpkkHalo : y0 + H - kMpkkHalo) * L + x0;
+  base = base >= kMpkkHalo ? base - kMpkkHalo : base + N - kMpkkHalo;
+  const int lane = (int)(threadIdx.x & 63u), nthreads = (int)blockDim.x;
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), nwaves = nthreads >> 6;
+  uint32_t* S = lds;
+  uint32_t* D = lds + hex_spin_words(WR, ROW);  // draws: [iteration][even or odd domains][row][6]
+  auto row_base = [&](int r) {
+    const uint32_t s = base + (uint32_t)r * L;
+    return s >= N ? s - N : s;
+  };
+  if (threadIdx.x == 0) {
+    total_s = 0u;
+    next_s = (uint32_t)nwaves;
+  }
+  constexpr int kPre = 8;
+  const int l8 = lane & 7, nblk = WR * N8, step = nthreads >> 3;
+  const int blk0 = (int)(threadIdx.x >> 3), inv8 = 65536 / N8 + 1;
+  auto load_blk = [&](int i) {
+    const int r = div_small(i, inv8);
+    return ring_bytes(in, row_base(r) + (uint32_t)(G * (8 * (i - r * N8) + l8)), N);
+  };
+  auto store_blk = [&](int i, const Bytes16& v) {
+    const int r = div_small(i, inv8);
+    stage_bytes<G>(reinterpret_cast<uint8_t*>(S + r * ROW) + (i - r * N8), v, l8);
+  };
+  Bytes16 v[kPre];
+#pragma unroll
+  for (int k = 0; k < kPre; ++k)
+    if (k * step < nblk) v[k] = load_blk(min(blk0 + k * step, nblk - 1));  // a uniform test; spare lanes load twice
+  __syncthreads();
+  // The draws: task = (iteration, 32 rows), the blocks of each row in two
+  // halves.  Iteration i's centres are needed within 19 - 3i cells of the
+  // tile: nj groups from group j0 on.  Bit i of the raw words is block
+  // b0 + j0 - 1 + i, b0 the block of the row's first cell of the even class:
+  // the odd domain of the block before the first group may be the first of its
+  // class.
+  {
+    int m = 19, j0 = 0, h = 0;
+    auto draw = [&](const Head& hd, int blk, Draw& e, Draw& o) {
+      blk += j0 + (lane < 32 ? h - 2 : 2 * h - 2);
+      for (int j = 0; j < h; ++j) {
+        const Philox4 w = philox_tail(hd, (uint32_t)blk);
+        push_attempt(e, w.x, w.y, acc);
+        push_attempt(o, w.z, w.w, acc);
+        --blk;
+      }
+    };
+    auto shifted = [](const Draw& d, uint32_t n) {
+      return Draw{d.sgn >> n, d.ax1 >> n, d.ax2 >> n, d.a0 >> n, d.a1 >> n, d.a2 >> n};
+    };
+    int it = 0, first = 0;  // the current task's iteration and the iteration's first task
+    for (int task = wave;;) {
+      int blocks = (TRe + 2 * m + 31) >> 5;
+      while (it < 7 && task >= first + blocks) {
+        first += blocks;
+        ++it;
+        m -= 3;
+        blocks = (TRe + 2 * m + 31) >> 5;
+      }
+      if (it == 7) break;
+      uint32_t nx = 0u;
+      if (lane == 0) nx = atomicAdd(&next_s, 1u);
+      j0 = ((int)kMpkkHalo - m) / G;
+      h = (((int)kMpkkHalo + TWe + m - 1) / G + 1 - j0 + 2) >> 1;
+      const int r = min((int)kMpkkHalo - m + 32 * (task - first) + (lane & 31), (int)kMpkkHalo + TRe + m - 1);
+      const int k = (int)(covers >> (4 * it)) & 15;
+      const uint32_t s = row_base(r);
+      const Head hd = philox_head((uint32_t)it, (uint32_t)t, ctr_hi(t, kTagMpkk), k0, k1);
+      int ke = k + 14 - (int)(s % 14u);
+      ke = ke >= 14 ? ke - 14 : ke;
+      Draw e{}, o{};
+      draw(hd, (int)((s + (uint32_t)ke - (uint32_t)k) / 14u), e, o);
+      Draw d = shifted(join_draws(e, o, (uint32_t)h), lane < 32 || ke < 7 ? 1u : 0u);
+      // a row that reaches the ring's end goes on with site 0, where domain 0
+      // begins: where N/7 is odd the classes of even and odd domains trade
+      // places there, and the blocks start anew in any case
+      if (__any(s + (uint32_t)(G * NJ) > N)) {
+        const bool swap = N % 14u != 0u;
+        int ke2 = swap ? ke + 7 : ke;
+        ke2 = ke2 >= 14 ? ke2 - 14 : ke2;
+        const int s2 = (int)(s - N);
+        Draw e2{}, o2{};
+        draw(hd, (s2 + ke2 - k) / 14, e2, o2);
+        // lanes 0..31 hold the class of e (the row's first even domains), lanes 32..63 that of o
+        const bool even2 = (lane < 32) != swap;
+        const Draw d2 = shifted(swap ? join_draws(o2, e2, (uint32_t)h) : join_draws(e2, o2, (uint32_t)h),
+                                even2 || ke2 < 7 ? 1u : 0u);
+        int q = lane < 32 ? ke : ke + 7;
+        q = q >= 14 ? q - 14 : q;
+        const int seam = (int)(N - s);  // the first column after the ring's end
+        const int js = max((seam > q ? (seam - q + G - 1) / G : 0) - j0, 0);
+        const uint32_t after = js < 32 ? ~((1u << js) - 1u) : 0u;
+        d = Draw{mux(after, d2.sgn, d.sgn), mux(after, d2.ax1, d.ax1), mux(after, d2.ax2, d.ax2),
+                 mux(after, d2.a0, d.a0),   mux(after, d2.a1, d.a1),   mux(after, d2.a2, d.a2)};
+      }
+      store_draw(D + 6 * ((2 * it + (lane >> 5)) * WR + r), d, (uint32_t)j0, acc);
+      task = __builtin_amdgcn_readfirstlane((int)nx);
+    }
+  }
+#pragma unroll
+  for (int k = 0; k < kPre; ++k)
+    if (blk0 + k * step < nblk) store_blk(blk0 + k * step, v[k]);
+  for (int i = blk0 + kPre * step; i < nblk; i += step) store_blk(i, load_blk(i));
+  __syncthreads();
+  // the even domains' words in the first nb waves, the odd domains' in the next nb
+  const int nb = (WR - 4 + 63) >> 6;
+  const int half = wave >= nb ? 1 : 0;
+  const bool busy = wave < 2 * nb;
+  const int r = 2 + 64 * (wave - half * nb) + lane;
+  const bool row_ok = busy && r < WR - 2;
+  const int rc = row_ok ? r : 2;
+  const uint32_t cmask = row_ok ? 0xFFFFFFFFu : 0u;
+  const int f = (int)(row_base(rc) % 14u);
+  const uint32_t counted = row_ok && r >= (int)kMpkkHalo && r < (int)kMpkkHalo + TRe ? 0xFFFFFFFFu : 0u;
+  uint32_t cnt = 0;
+  Place pl{};
+  Draw d{};
+  int q = 0;
+  auto prepare = [&](int it) {
+    q = ((int)(covers >> (4 * it)) & 15) + 7 * half - f;  // -13 .. 13
+    q += (q >> 31) & 14;
+    pl = class_place<G, ROW>(rc, q);
+    d = load_draw(D + 6 * ((2 * it + half) * WR + rc));
+  };
+  if (busy) prepare(0);
+#pragma unroll 1
+  for (int it = 0; it < 7; ++it) {
+    uint32_t F = 0u;
+    if (busy) F = decide(read_around<ROW>(S, pl), d, acc.negmask, cmask);
+    __syncthreads();
+    if (busy) {
+      if (row_ok) exchange<ROW>(S, pl, d, F);
+      const uint32_t m = column_mask<G>(q, (int)kMpkkHalo, (int)kMpkkHalo + TWe);
+      cnt += (uint32_t)__builtin_popcount(F & m & counted);
+      if (it + 1 < 7) prepare(it + 1);
+    }
+    __syncthreads();
+  }
+  for (int i = blk0; i < TRe * N8; i += step) {
+    const int rr = div_small(i, inv8), g8 = i - rr * N8;
+    const Bytes16 y =
+        unstage_bytes<G>(reinterpret_cast<const uint8_t*>(S + (rr + (int)kMpkkHalo) * ROW) + g8, l8);
+    uint8_t* row = out + (size_t)(y0 + (uint32_t)rr) * L + x0;
+    const int c = G * (8 * g8 + l8) - (int)kMpkkHalo;
+    if (c >= 0 && c + G <= TWe) {
+      __builtin_memcpy(row + c, &y, G);
+    } else {
+#pragma unroll
+      for (int k = 0; k < G; ++k)
+        if (c + k >= 0 && c + k < TWe) row[c + k] = (uint8_t)(y.x[k >> 2] >> (8 * (k & 3)));
+    }
+  }
+  add_count(cnt, &total_s, partials + blockIdx.x % kTriPartials);
+}
+
+// The class order of sweep t, for a launch that holds one sweep.
+uint64_t class_order16(uint32_t k0, uint32_t k1, uint64_t t) {
+  uint32_t w[16];
+  for (uint32_t j = 0; j < 4; ++j) {
+    const Philox4 b = philox10_host(j, 0u, (uint32_t)t, ctr_hi(t, kTagTriOrder), k0, k1);
+    w[4 * j] = b.x;
+    w[4 * j + 1] = b.y;
+    w[4 * j + 2] = b.z;
+    w[4 * j + 3] = b.w;
+  }
+  return shuffle_nibbles(w, 16);
+}
+
+// The domain covers k_j of the seven iterations of step t, nibble j each.
+uint32_t mpkk_covers(uint32_t k0, uint32_t k1, uint64_t t) {
+  uint32_t covers = 0u;
+  for (uint32_t b = 0; b < 2; ++b) {
+    const Philox4 p = philox10_host(b, 2u, (uint32_t)t, ctr_hi(t, kTagMpkkK), k0, k1);
+    const uint32_t w[4] = {p.x, p.y, p.z, p.w};
+    for (uint32_t i = 0; i < 4 && 4 * b + i < 7; ++i)
+      covers |= (uint32_t)(((uint64_t)w[i] * 7u) >> 32) << (4 * (4 * b + i));
+  }
+  return covers;
 }
 
 }  // namespace
@@ -532,7 +758,7 @@ hipError_t launch_tri_tile_sweep(const uint8_t* in, uint8_t* out, int L, int H, 
   const HexTile ht = hex_tile(TW, TR);
   const uint32_t ntx = ((uint32_t)L + ht.tw - 1) / ht.tw, nty = ((uint32_t)H + ht.tr - 1) / ht.tr;
   hipLaunchKernelGGL(hex_sweep, dim3(ntx * nty), dim3(1024), hex_lds_bytes(ht.tr), stream, in, out, (uint32_t)L,
-                     (uint32_t)H, ht.tw, ht.tr, ntx, k0, k1, t, hex_accept(acc), partials);
+                     (uint32_t)H, ht.tw, ht.tr, ntx, k0, k1, t, class_order16(k0, k1, t), hex_accept(acc), partials);
   return hipGetLastError();
 }
 
@@ -540,6 +766,17 @@ hipError_t launch_tri_tile_sweep_batch(const TriBatchRep* reps, const uint2* job
                                        size_t lds_bytes, hipStream_t stream) {
   if (njobs == 0) return hipSuccess;
   hipLaunchKernelGGL(hex_sweep_batch, dim3(njobs), dim3(1024), lds_bytes, stream, reps, jobs, k);
+  return hipGetLastError();
+}
+
+hipError_t launch_mpkk_tile_step(const uint8_t* in, uint8_t* out, int L, int H, int TW, int TR, uint32_t k0,
+                                 uint32_t k1, uint64_t t, const TriAccept& acc, unsigned long long* partials,
+                                 hipStream_t stream) {
+  if (!mpkk_tile_fits(L, H, TW, TR)) return hipErrorInvalidValue;
+  const HexTile ht = hex_mpkk_tile(TW, TR);
+  const uint32_t ntx = ((uint32_t)L + ht.tw - 1) / ht.tw, nty = ((uint32_t)H + ht.tr - 1) / ht.tr;
+  hipLaunchKernelGGL(hex_mpkk_step, dim3(ntx * nty), dim3(1024), hex_mpkk_lds_bytes(ht.tr), stream, in, out,
+                     (uint32_t)L, (uint32_t)H, ht.tw, ht.tr, ntx, k0, k1, t, mpkk_covers(k0, k1, t), hex_accept(acc), partials);
   return hipGetLastError();
 }
 

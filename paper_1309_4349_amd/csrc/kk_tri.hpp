@@ -127,6 +127,21 @@ __host__ __device__ inline size_t mpkk_window_area(uint32_t TW, uint32_t TR) {
 __host__ __device__ inline size_t mpkk_window_bytes(uint32_t TW, uint32_t TR) {
   return mpkk_window_area(TW, TR) + kTriQueueBytes;
 }
+// The bit-plane window of a step: kMpkkHalo columns before the tile, groups of
+// 14 columns (one group of draws before the first, so at most 31), six random
+// words per (iteration, even or odd domains, row).
+constexpr int kHexRow14 = 15;
+constexpr uint32_t kHexMpkkMaxCols = 14 * 31 - 2 * kMpkkHalo, kHexMpkkMaxRows = 368;
+__host__ __device__ inline int hex_mpkk_groups(uint32_t TW) { return (int)((TW + 2 * kMpkkHalo + 13u) / 14u); }
+inline size_t hex_mpkk_lds_bytes(uint32_t TR) {
+  const int WR = (int)TR + 2 * (int)kMpkkHalo;
+  return ((size_t)hex_spin_words(WR, kHexRow14) + (size_t)14 * WR * 6) * 4;
+}
+inline HexTile hex_mpkk_tile(int TW, int TR) {
+  const uint32_t nx = ((uint32_t)TW + kHexMpkkMaxCols - 1) / kHexMpkkMaxCols;
+  const uint32_t ny = ((uint32_t)TR + kHexMpkkMaxRows - 1) / kHexMpkkMaxRows;
+  return HexTile{((uint32_t)TW + nx - 1) / nx, ((uint32_t)TR + ny - 1) / ny};
+}
 inline bool mpkk_tile_fits(int L, int H, int TW, int TR) {
   return TW >= 16 && TR >= 16 && TW + 2 * (int)kMpkkHalo <= L && TR + 2 * (int)kMpkkHalo <= H &&
          mpkk_window_bytes((uint32_t)TW, (uint32_t)TR) <= 160u * 1024u - 1024u;

@@ -36,3 +36,15 @@ def _check(L, H, scheme, tile, x, w, n, t0=0):
 def test_hex_class_tiles_match_oracle(L, H, tile, x, w):
     _check(L, H, "classes", tile, x, w, 3)
     _check(L, H, "classes", tile, x, w, 2, t0=2**32 - 1)
+
+
+# as above for the literal MPKK (31 groups of 14 columns at most), on rings with an even and an odd number of domains:
+# past the ring's end the even and odd domains trade classes
+@pytest.mark.parametrize("L,H,tile,x,w", [
+    (59, 63, (16, 16), 0.5, 0.8), (61, 63, (17, 21), 0.5, 0.5), (437, 119, (392, 40), 0.5, 0.6),
+    (437, 119, (393, 40), 0.4, 0.9), (801, 63, (700, 17), 0.5, 0.6), (157, 448, (57, 400), 0.5, 0.5),
+    (94, 77, (29, 33), 0.3, -0.7), (66, 70, (24, 28), 0.5, 0.0), (59, 70, (16, 27), 0.5, 9.0),
+])
+def test_hex_mpkk_tiles_match_oracle(L, H, tile, x, w):
+    _check(L, H, "mpkk", tile, x, w, 3)
+    _check(L, H, "mpkk", tile, x, w, 2, t0=2**32 - 1)
