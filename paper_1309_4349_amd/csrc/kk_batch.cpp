@@ -7,7 +7,7 @@
 // are "tiled": they are split into a few groups of equal work, and for each
 // group every sweep is one launch over all of the group's halo tiles.
 // Resident replicas of at most kResidentSmallMaxC words per row run in
-// 256-thread workgroups (three per CU), larger ones in 768-thread workgroups.
+// 768-thread workgroups (two per CU), larger ones in 1024-thread workgroups.
 // One HIP graph holds a chunk of kBatchChunk sweeps of everything: a branch
 // per tile group (kBatchChunk chained launches) and a branch per resident
 // kernel (one launch of kBatchChunk sweeps), forked from and joined to one
@@ -97,6 +97,10 @@ namespace {
 bool is_resident(const kk_sim* h) { return h->L % 32 == 0 && h->L >= 64 && h->L / 32 <= kResidentMaxC; }
 
 void clear_plan(kk_batch* b) {
+  // the executable graph must be idle, and finished in the eyes of the runtime,
+  // before it is destroyed: a run waits for its last event on another stream,
+  // which says nothing of the stream that launched the graph
+  if (b->gexec && b->tg_stream[0]) (void)hipStreamSynchronize(b->tg_stream[0]);
   if (b->gexec) (void)hipGraphExecDestroy(b->gexec);
   if (b->graph) (void)hipGraphDestroy(b->graph);
   b->gexec = nullptr;
@@ -425,6 +429,7 @@ kk_status kk_batch_run(kk_batch* b) {
   for (uint64_t r = 0; r < (mx + kBatchChunk - 1) / kBatchChunk; ++r) KB_HIP(hipGraphLaunch(b->gexec, origin));
   KB_HIP(hipEventRecord(b->ev_res, origin));
   KB_HIP(hipStreamWaitEvent(b->sB, b->ev_res, 0));
+  KB_HIP(hipStreamSynchronize(origin));
   KB_HIP(hipStreamSynchronize(b->sB));
   std::vector<unsigned long long> counts(b->ncounts);
   KB_HIP(hipMemcpy(counts.data(), b->d_counts, b->ncounts * sizeof(unsigned long long), hipMemcpyDeviceToHost));

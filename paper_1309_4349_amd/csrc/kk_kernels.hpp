@@ -38,7 +38,7 @@ hipError_t launch_sweep(const SweepParams& p, int layout, bool cyclic, int ku, i
 // p.t0, ping-ponging between p.src (its lattice at the start) and p.dst.  Resident replicas (L % 32 == 0,
 // 2 <= L/32 <= kResidentMaxC): one launch, one workgroup per replica running
 // all of its sweeps with the whole lattice in LDS.
-constexpr int kBatchMaxTww = 16, kBatchTh = 128, kBatchThreads = 768;
+constexpr int kBatchMaxTww = 16, kBatchTh = 128;
 // Tiled replicas run in 512-thread workgroups, ku (1 or 2) units per thread,
 // in tiles 8 or 16 words wide: a tile of tww words by th rows fits when its
 // (th + 28) / 2 computed row pairs times tww + 2 words stay within ku * 512
@@ -54,7 +54,7 @@ struct BatchTileJob {
 hipError_t launch_batch_tiles(const SweepParams* reps, const BatchTileJob* jobs, int njobs, const unsigned* ctl,
                               unsigned rel, int ku, hipStream_t stream);
 hipError_t launch_batch_advance(unsigned* ctl, unsigned step, hipStream_t stream);
-// small: the 256-thread kernel for replicas of at most kResidentSmallMaxC words
+// small: the 768-thread kernel for replicas of at most kResidentSmallMaxC words
 // per row.  A launch runs up to kBatchChunk sweeps from sweep ctl[0] of the run
 // (launch_batch_advance then moves ctl[0] on by kBatchChunk).
 hipError_t launch_batch_resident(const SweepParams* reps, const int* ids, int n, size_t lds_bytes, bool small,
@@ -63,7 +63,7 @@ hipError_t launch_batch_resident(const SweepParams* reps, const int* ids, int n,
 // and one resident launch of kBatchChunk sweeps.
 constexpr int kBatchChunk = 64;
 constexpr int kResidentMaxC = 9;
-constexpr int kResidentSmallMaxC = 5, kResidentSmallThreads = 256;
+constexpr int kResidentSmallMaxC = 4, kResidentSmallThreads = 768, kResidentThreads = 1024;
 size_t batch_tile_lds_bytes();
 size_t batch_resident_lds_bytes(int L);
 

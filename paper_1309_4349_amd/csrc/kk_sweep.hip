@@ -19,6 +19,8 @@
 // (classes 2*((x - y) mod 4) + (y mod 2)), so no pair writes a site that
 // another pair reads: the LDS updates are xor-flips of disjoint bits issued
 // with ds_xor, and a workgroup barrier separates phases.
+#include <type_traits>
+
 #include "kk_common.hpp"
 #include "kk_kernels.hpp"
 
@@ -180,6 +182,45 @@ __device__ __forceinline__ uint32_t load_word_at(const SweepParams& p, int y, in
   return v;
 }
 
+// A word of 32 sites as loaded, packed later, so that the loads of several
+// words are in flight together.  GRID: L % 32 == 0, no word passes the wrap;
+// else an int8 word is eight 4-byte pieces, the start of each wrapped.
+template <int LAYOUT>
+struct RawWord {
+  uint32_t d[LAYOUT == kLayoutBits ? 1 : 8];
+  template <bool GRID>
+  __device__ __forceinline__ void load(const SweepParams& p, int y, int x0) {
+    if constexpr (LAYOUT == kLayoutBits) {
+      d[0] = static_cast<const uint32_t*>(p.src)[(size_t)y * p.wpr + (x0 >> 5)];
+    } else {
+      const uint8_t* row = static_cast<const uint8_t*>(p.src) + (size_t)y * p.L;
+      if constexpr (GRID) {
+        const uint4* q = reinterpret_cast<const uint4*>(row + x0);
+        const uint4 a = q[0], b = q[1];
+        d[0] = a.x, d[1] = a.y, d[2] = a.z, d[3] = a.w, d[4] = b.x, d[5] = b.y, d[6] = b.z, d[7] = b.w;
+      } else {
+        int x = x0;
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+          d[k] = *reinterpret_cast<const uint32_t*>(row + x);
+          x += 4;
+          x = x >= p.L ? x - p.L : x;
+        }
+      }
+    }
+  }
+  __device__ __forceinline__ uint32_t word() const {
+    if constexpr (LAYOUT == kLayoutBits) {
+      return d[0];
+    } else {
+      uint32_t v = 0;
+#pragma unroll
+      for (int k = 0; k < 8; ++k) v |= pack4(d[k]) << (4 * k);
+      return v;
+    }
+  }
+};
+
 // Layout chosen at run time (LAYOUT == 0) or at compile time.
 template <int LAYOUT>
 __device__ __forceinline__ uint32_t load_word_any(const SweepParams& p, int y, int x0) {
@@ -197,22 +238,6 @@ __device__ __forceinline__ void store_word_any(const SweepParams& p, int y, int 
   } else {
     store_word<LAYOUT>(p, y, x0, v, nbits);
   }
-}
-
-// Random planes of the 32 sites starting at true column x0 of true row y.
-__device__ __forceinline__ void gen_planes_at(const SweepParams& p, int y, int x0, int Xw, uint64_t t, uint32_t* pl) {
-  if ((x0 & 31) == 0 && x0 + 32 <= p.L) {
-    const uint32_t tl = (uint32_t)t, thi = ctr_hi(t, kTagSweep);
-    const uint32_t g4 = (uint32_t)(x0 >> 5) * 4u;
-    const Philox4 a = philox10((uint32_t)y, g4 + 0u, tl, thi, p.k0, p.k1);
-    const Philox4 b = philox10((uint32_t)y, g4 + 1u, tl, thi, p.k0, p.k1);
-    const Philox4 c = philox10((uint32_t)y, g4 + 2u, tl, thi, p.k0, p.k1);
-    pl[0] = a.x; pl[1] = a.y; pl[2] = a.z; pl[3] = a.w;
-    pl[4] = b.x; pl[5] = b.y; pl[6] = b.z; pl[7] = b.w;
-    pl[8] = c.x; pl[9] = c.y; pl[10] = c.z; pl[11] = c.w;
-    return;
-  }
-  gen_planes(p, y, Xw, t, pl);
 }
 
 // Three-input bitwise function with a truth table built from the operand
@@ -479,56 +504,102 @@ __device__ __forceinline__ uint32_t opaque_sgpr(uint32_t v) {
   return v;
 }
 
-// Ties: u10 equals a threshold prefix, and the low 32 bits of U decide.  eq[j]
-// holds the tied sites of slot j among the 32 sites from true column xtrue of
-// true row ytrue (xtrue + b may pass the wrap only for L % 32 != 0 or L < 32);
-// the tied sites that lie below the threshold join lt[j].
-__device__ __forceinline__ void resolve_ties(const SweepParams& p, int ytrue, int xtrue, uint64_t t,
-                                             const uint32_t* eq, uint32_t* lt) {
+// Ties: u10 equals a threshold prefix, and the low 32 bits of U decide.  About
+// one row word in eleven has one, so that resolving them where they arise runs
+// a Philox block or two per row word for a few lanes of the wave.  Instead a
+// wave lists the ties of all its row words in LDS and resolves the list once,
+// a tie per lane (six ties per wave and row word on average); a row word's ties
+// share three words of results (one per slot), which its lane then joins to its
+// planes.  No other wave is involved, so no barrier is needed.
+constexpr uint32_t kTieCap = 64;                      // listed ties per wave; further ones are resolved in place
+constexpr uint32_t kTieWaveWords = kTieCap * (2 + 3);  // an entry and three result words each
+struct TieList {
+  uint2* entry;   // site (y << 16 | x); result index << 8 | bit << 3 | slots
+  uint32_t* out;  // three words per result index
+  uint32_t n;     // listed so far (uniform)
+};
+__device__ __forceinline__ TieList tie_list(uint32_t* lds) {  // lds: 8-byte aligned, kTieWaveWords per wave
+  uint32_t* w = lds + kTieWaveWords * (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  return TieList{reinterpret_cast<uint2*>(w), w + 2 * kTieCap, 0u};
+}
+
+__device__ __forceinline__ uint32_t tie_word(const SweepParams& p, uint32_t y, uint32_t x, uint64_t t) {
+  const Philox4 e = philox10(y, x >> 2, (uint32_t)t, ctr_hi(t, kTagExt), p.k0, p.k1);
+  const uint32_t s1 = 0u - (x & 1u), s2 = 0u - ((x >> 1) & 1u);
+  return bsel(s2, bsel(s1, e.w, e.z), bsel(s1, e.y, e.x));
+}
+
+// eq[j] holds the tied sites of slot j among the 32 sites from true column
+// xtrue of true row ytrue (xtrue + b may pass the wrap only for L % 32 != 0 or
+// L < 32).  Returns the result index of the row word, -1 without ties.
+__device__ __forceinline__ int list_ties(const SweepParams& p, TieList& tl, int ytrue, int xtrue, uint64_t t,
+                                         const uint32_t* eq, uint32_t* lt) {
   uint32_t tie = eq[0] | eq[1] | eq[2];
-  while (tie) {
-    const int bp = __builtin_ctz(tie);
-    tie &= tie - 1u;
-    int x = xtrue + bp;
-    if (x >= p.L) x = imod(x, p.L);
-    const Philox4 e = philox10((uint32_t)ytrue, (uint32_t)x >> 2, (uint32_t)t, ctr_hi(t, kTagExt), p.k0, p.k1);
-    const uint32_t xs = (uint32_t)x & 3u;
-    const uint32_t ext = xs == 0 ? e.x : xs == 1 ? e.y : xs == 2 ? e.z : e.w;
+  int idx = -1;
+  for (;;) {
+    const uint64_t m = __ballot(tie != 0u);
+    if (!m) break;
+    if (tie) {
+      const int bp = __builtin_ctz(tie);
+      tie &= tie - 1u;
+      int x = xtrue + bp;
+      if (x >= p.L) x = imod(x, p.L);
+      const uint32_t slots = ((eq[0] >> bp) & 1u) | (((eq[1] >> bp) & 1u) << 1) | (((eq[2] >> bp) & 1u) << 2);
+      const uint32_t pos =
+          tl.n + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+      if (pos < kTieCap) {
+        if (idx < 0) {
+          idx = (int)pos;
+          tl.out[3 * pos] = tl.out[3 * pos + 1] = tl.out[3 * pos + 2] = 0u;
+        }
+        tl.entry[pos] =
+            make_uint2(((uint32_t)ytrue << 16) | (uint32_t)x, ((uint32_t)idx << 8) | ((uint32_t)bp << 3) | slots);
+      } else {
+        const uint32_t ext = tie_word(p, (uint32_t)ytrue, (uint32_t)x, t);
+#pragma unroll
+        for (int j = 0; j < 3; ++j)
+          if (((slots >> j) & 1u) && ext < p.acc.lo[j]) lt[j] |= 1u << bp;
+      }
+    }
+    tl.n += (uint32_t)__popcll(m);
+  }
+  return idx;
+}
+
+// The wave's list, once; after it join_ties may be called.
+__device__ __forceinline__ void resolve_list(const SweepParams& p, const TieList& tl, uint64_t t) {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  const uint32_t i = threadIdx.x & 63u;
+  if (i < min(tl.n, kTieCap)) {
+    const uint2 e = tl.entry[i];
+    const uint32_t ext = tie_word(p, e.x >> 16, e.x & 0xFFFFu, t);
+    uint32_t* out = tl.out + 3 * (e.y >> 8);
 #pragma unroll
     for (int j = 0; j < 3; ++j)
-      if (((eq[j] >> bp) & 1u) && ext < p.acc.lo[j]) lt[j] |= 1u << bp;
+      if (((e.y >> j) & 1u) && ext < p.acc.lo[j]) atomicOr(&out[j], 1u << ((e.y >> 3) & 31u));
+  }
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+}
+
+__device__ __forceinline__ void join_ties(const TieList& tl, int idx, RowRand& q) {
+  if (idx >= 0) {
+    q.acc0 |= tl.out[3 * idx];
+    q.acc1 |= tl.out[3 * idx + 1];
+    q.acc2 |= tl.out[3 * idx + 2];
   }
 }
 
-// pl: the 12 random planes of 32 sites of true row ytrue from true column
-// xtrue (xtrue + b may pass the wrap only for L % 32 != 0 or L < 32).
-__device__ __forceinline__ void row_rand(const uint32_t* pl, const SweepParams& p, int ytrue, int xtrue, uint64_t t,
-                                         RowRand& q) {
-  q.d0 = pl[0];
-  q.d1 = pl[1];
-  uint32_t lt[3], eq[3];
-#pragma unroll
-  for (int j = 0; j < 3; ++j) {
-    if (p.acc.hi[j] < 1024u) cmp10(pl, opaque_sgpr(p.acc.hi[j]), lt[j], eq[j]);
-    else {
-      lt[j] = 0xFFFFFFFFu;
-      eq[j] = 0u;
-    }
-  }
-  resolve_ties(p, ytrue, xtrue, t, eq, lt);
-  q.acc0 = lt[0];
-  q.acc1 = lt[1];
-  q.acc2 = lt[2];
-}
-
-// N Philox4x32-10 blocks at once, round by round across the blocks: the
-// multiplies of different blocks are independent and issue back to back
-// instead of waiting on one block's chain.  c0..c3: counters in, outputs out.
-template <int N>
+// Rounds R0 .. R1 - 1 of N Philox4x32-10 blocks at once, round by round across
+// the blocks: the multiplies of different blocks are independent and issue back
+// to back instead of waiting on one block's chain.  c0..c3: counters in,
+// outputs out.
+template <int N, int R0 = 0, int R1 = 10>
 __device__ __forceinline__ void philox10_n(uint32_t* c0, uint32_t* c1, uint32_t* c2, uint32_t* c3, uint32_t k0,
                                            uint32_t k1) {
+  k0 += (uint32_t)R0 * 0x9E3779B9u;
+  k1 += (uint32_t)R0 * 0xBB67AE85u;
 #pragma unroll
-  for (int r = 0; r < 10; ++r) {
+  for (int r = R0; r < R1; ++r) {
 #pragma unroll
     for (int n = 0; n < N; ++n) {
       const uint64_t p0 = (uint64_t)c0[n] * 0xD2511F53u;
@@ -545,124 +616,61 @@ __device__ __forceinline__ void philox10_n(uint32_t* c0, uint32_t* c1, uint32_t*
   }
 }
 
-// Ties of NR rows on the segment grid (no site index wraps): each pass takes
-// the next tied site of every row and draws the NR extension words together,
-// so the passes follow the largest per-row tie count in the wave (one or two)
-// rather than the sum over rows, and the NR Philox chains overlap.
-template <int NR>
-__device__ __forceinline__ void resolve_ties_grid(const SweepParams& p, const int* y, const int* x, uint64_t t,
-                                                  const uint32_t (*eq)[3], uint32_t (*lt)[3]) {
-  uint32_t tie[NR];
+// u10 < K and u10 == K over the planes (2 .. 11: bits 9 .. 0 of u10) for a
+// slot's threshold prefix K = hi.  Each bit of K becomes one all-zeros /
+// all-ones scalar mask (a signed one-bit field extract) for the borrow chain
+// and the equality chain, one three-input op per bit and chain.  A prefix of
+// 1024 or more accepts every site: its compare runs with a borrow-in (u < 1023
+// + 1) and an empty equality mask instead of a branch.
+__device__ __forceinline__ void compare_slot(const uint32_t* pl, uint32_t hi, bool live, uint32_t& lt, uint32_t& eq) {
+  constexpr unsigned kBorrow = KK_TT((~KK_TA & KK_TB) | (~KK_TA & KK_TC) | (KK_TB & KK_TC));
+  constexpr unsigned kEqStep = KK_TT(KK_TA & ~(KK_TB ^ KK_TC));
+  const bool all = hi >= 1024u;
+  const uint32_t K = opaque_sgpr(all ? 1023u : hi);
+  lt = all ? 0xFFFFFFFFu : 0u;
+  eq = all || !live ? 0u : 0xFFFFFFFFu;
 #pragma unroll
-  for (int i = 0; i < NR; ++i) tie[i] = eq[i][0] | eq[i][1] | eq[i][2];
-  const uint32_t tl = (uint32_t)t, th = ctr_hi(t, kTagExt);
-  for (;;) {
-    uint32_t left = 0u;
-#pragma unroll
-    for (int i = 0; i < NR; ++i) left |= tie[i];
-    if (!left) break;
-    uint32_t c0[NR], c1[NR], c2[NR], c3[NR], bit[NR], xs[NR];
-#pragma unroll
-    for (int i = 0; i < NR; ++i) {
-      const uint32_t m = tie[i];
-      bit[i] = m & (0u - m);  // the next tied site (none: 0, and the draw below is unused)
-      tie[i] = m & (m - 1u);
-      const uint32_t xsite = (uint32_t)x[i] + (uint32_t)(31 - __clz((int)bit[i]));
-      xs[i] = xsite & 3u;
-      c0[i] = (uint32_t)y[i];
-      c1[i] = xsite >> 2;
-      c2[i] = tl;
-      c3[i] = th;
-    }
-    philox10_n<NR>(c0, c1, c2, c3, p.k0, p.k1);
-#pragma unroll
-    for (int i = 0; i < NR; ++i) {
-      // word xs of the block, by bitwise selects (a branch here would split
-      // the NR chains again)
-      const uint32_t s1 = 0u - (xs[i] & 1u), s2 = 0u - (xs[i] >> 1);
-      const uint32_t ext = bsel(s2, bsel(s1, c3[i], c2[i]), bsel(s1, c1[i], c0[i]));
-#pragma unroll
-      for (int j = 0; j < 3; ++j)
-        if (ext < p.acc.lo[j]) lt[i][j] |= eq[i][j] & bit[i];
-    }
+  for (int k = 0; k < 10; ++k) {
+    const uint32_t kb = (uint32_t)((int32_t)(K << (31 - k)) >> 31);
+    lt = bop3<kBorrow>(pl[11 - k], kb, lt);
+    eq = bop3<kEqStep>(eq, pl[11 - k], kb);
   }
 }
 
-// Random state of NR rows whose words sit on the 32-site segment grid
-// (x % 32 == 0 and x + 32 <= L): the 3 NR Philox blocks are drawn together,
-// then the 3 NR compares, then the rare ties.  A slot whose threshold prefix is 1024 or more accepts
-// every site: its compare runs with a borrow-in (u < 1023 + 1) and an empty
-// equality mask instead of a branch.
-template <int NR>
-__device__ __forceinline__ void rand_rows_grid(const SweepParams& p, uint64_t t, const int* y, const int* x,
-                                               RowRand* q) {
+// Random state of the row word of 32 sites from true column x of true row y:
+// its three Philox blocks are drawn together, then its compares.  Off-grid
+// lattices (GRID false: L % 32 != 0) have a few words that do not sit on the
+// 32-site segment grid, next to the wrap; those gather their planes from the
+// segments they cover, where a wave holds any.
+// Returns the index of the row word's tie results, -1 without ties or for a
+// lane that owns no unit (live false).
+template <bool GRID>
+__device__ __forceinline__ int rand_row(const SweepParams& p, TieList& ties, uint64_t t, int y, int x, bool live,
+                                        RowRand& q) {
   const uint32_t tl = (uint32_t)t, thi = ctr_hi(t, kTagSweep);
-  uint32_t c0[NR * 3], c1[NR * 3], c2[NR * 3], c3[NR * 3];
+  uint32_t c0[3], c1[3], c2[3], c3[3];
+  const uint32_t g4 = (uint32_t)(x >> 5) * 4u;
 #pragma unroll
-  for (int i = 0; i < NR; ++i) {
-    const uint32_t g4 = (uint32_t)(x[i] >> 5) * 4u;
-#pragma unroll
-    for (int b = 0; b < 3; ++b) {
-      c0[3 * i + b] = (uint32_t)y[i];
-      c1[3 * i + b] = g4 + (uint32_t)b;
-      c2[3 * i + b] = tl;
-      c3[3 * i + b] = thi;
+  for (int b = 0; b < 3; ++b) {
+    c0[b] = (uint32_t)y;
+    c1[b] = g4 + (uint32_t)b;
+    c2[b] = tl;
+    c3[b] = thi;
+  }
+  philox10_n<3>(c0, c1, c2, c3, p.k0, p.k1);
+  uint32_t pl[kPlanes] = {c0[0], c1[0], c2[0], c3[0], c0[1], c1[1], c2[1], c3[1], c0[2], c1[2], c2[2], c3[2]};
+  if constexpr (!GRID) {
+    const bool gather = live && ((x & 31) != 0 || x + 32 > p.L);
+    if (__any(gather)) {
+      if (gather) gen_planes(p, y, x, t, pl);
     }
   }
-  philox10_n<NR * 3>(c0, c1, c2, c3, p.k0, p.k1);
-  uint32_t pl[NR][kPlanes];
+  uint32_t lt[3], eq[3];
 #pragma unroll
-  for (int i = 0; i < NR; ++i) {
-#pragma unroll
-    for (int b = 0; b < 3; ++b) {
-      pl[i][4 * b] = c0[3 * i + b];
-      pl[i][4 * b + 1] = c1[3 * i + b];
-      pl[i][4 * b + 2] = c2[3 * i + b];
-      pl[i][4 * b + 3] = c3[3 * i + b];
-    }
-  }
-  // The compares run bit by bit across the rows: each bit of a threshold
-  // prefix becomes one all-zeros / all-ones scalar mask (a signed one-bit
-  // field extract), shared by the rows' borrow chains (u < K) and equality
-  // chains (u == K), one three-input op per bit and chain.
-  constexpr unsigned kBorrow = KK_TT((~KK_TA & KK_TB) | (~KK_TA & KK_TC) | (KK_TB & KK_TC));
-  constexpr unsigned kEqStep = KK_TT(KK_TA & ~(KK_TB ^ KK_TC));
-  uint32_t lt[NR][3], eq[NR][3];
-#pragma unroll
-  for (int j = 0; j < 3; ++j) {
-    const uint32_t hi = p.acc.hi[j];
-    const bool all = hi >= 1024u;
-    const uint32_t K = opaque_sgpr(all ? 1023u : hi);
-    const uint32_t bin = all ? 0xFFFFFFFFu : 0u, em = all ? 0u : 0xFFFFFFFFu;
-    uint32_t l[NR], e[NR];
-#pragma unroll
-    for (int i = 0; i < NR; ++i) {
-      l[i] = bin;
-      e[i] = em;
-    }
-#pragma unroll
-    for (int k = 0; k < 10; ++k) {
-      const uint32_t kb = (uint32_t)((int32_t)(K << (31 - k)) >> 31);
-#pragma unroll
-      for (int i = 0; i < NR; ++i) {
-        const uint32_t u = pl[i][11 - k];  // planes 2 .. 11: bits 9 .. 0 of u10
-        l[i] = bop3<kBorrow>(u, kb, l[i]);
-        e[i] = bop3<kEqStep>(e[i], u, kb);
-      }
-    }
-#pragma unroll
-    for (int i = 0; i < NR; ++i) {
-      lt[i][j] = l[i];
-      eq[i][j] = e[i];
-    }
-  }
-  // one test for all rows, so that no Philox block sinks past a tie loop
-  uint32_t anytie = 0u;
-#pragma unroll
-  for (int i = 0; i < NR; ++i) anytie |= eq[i][0] | eq[i][1] | eq[i][2];
-  if (anytie) resolve_ties_grid<NR>(p, y, x, t, eq, lt);
-#pragma unroll
-  for (int i = 0; i < NR; ++i) q[i] = RowRand{pl[i][0], pl[i][1], lt[i][0], lt[i][1], lt[i][2]};
+  for (int j = 0; j < 3; ++j) compare_slot(pl, p.acc.hi[j], live, lt[j], eq[j]);
+  const int idx = list_ties(p, ties, y, x, t, eq, lt);
+  q = RowRand{pl[0], pl[1], lt[0], lt[1], lt[2]};
+  return idx;
 }
 
 
@@ -716,6 +724,13 @@ struct HaloGeom {
   // consecutive words) fall in consecutive LDS banks.
   static constexpr int ST = (C % 2 == 0) ? (C / 2 + 32) : 34;
 };
+
+// LDS words of a halo tile of R rows before the tie lists (an even number):
+// the rows, 16 spare words and the row and column tables.
+template <int TWW>
+__host__ __device__ constexpr int halo_tie_offset(int R) {
+  return (R * HaloGeom<TWW>::ST + 16 + R + HaloGeom<TWW>::C + 1) & ~1;
+}
 
 // One phase of the halo kernel for the thread's units, active row = r0 + H.
 // Branch-free over the units: a unit beyond the tile reads a valid word and
@@ -789,16 +804,22 @@ __device__ __forceinline__ unsigned wave_sum8(unsigned c) {
 // the neighbourhoods of all its units before issuing any exchange (the
 // conflict-free schedule makes that reordering exact), so the LDS latency of
 // the second unit hides behind the first.
-// One sweep of tile `tile` of the lattice described by p (halo mode).
+// One sweep of tile `tile` of the lattice described by p (halo mode), `order`
+// the sweep's class order.  What bounds it: at 4096^2 (256 tiles of 16 x 128) VALU
+// issue, the draws 5 us and the eight phases 5.5 us of the 15.6 us sweep (16.0
+// with three waves per SIMD and ties resolved in place); on small lattices, whose
+// tiles have one or two waves, the chain of staging, draws and phases (400^2 12.9
+// -> 10.2 us, 1036^2 14.7 -> 12.6 us: loads without a branch between them, ties
+// in one list, spare lanes on words of their own).
 // Returns the workgroup's accepted count for the tile interior (the same in
 // every thread).
 
 template <int LAYOUT, int TWW, int KU>
-__device__ __forceinline__ unsigned halo_tile_sweep(uint32_t* S, const SweepParams& p, int tile) {
+__device__ __forceinline__ unsigned halo_tile_sweep(uint32_t* S, const SweepParams& p, int tile, uint32_t order) {
   constexpr int C = HaloGeom<TWW>::C;
   constexpr int ST = HaloGeom<TWW>::ST;
   const int CP = C + 2;       // staged words per row (the pads included)
-  constexpr int NSTG = 6;     // staged global words per thread
+  constexpr int NSTG = 4;     // staged global words per thread
   const int tx = tile % p.tiles_x, ty = tile / p.tiles_x;
   constexpr int TW = TWW;
   const int X0 = tx * TW * 32, Y0 = ty * p.th;
@@ -818,19 +839,27 @@ __device__ __forceinline__ unsigned halo_tile_sweep(uint32_t* S, const SweepPara
     if (i < p.R) ytab[i] = imod(YT + i, p.L);
     else xtab[i - p.R] = imod(XL + 32 * (i - p.R), p.L);
   }
-  // the workgroup's accepted count, in the gap between the rows and the tables
+  // the workgroup's accepted count, in the gap between the rows and the
+  // tables; the tie lists after the tables
   uint32_t* acc_total = S + p.R * ST;
+  TieList ties = tie_list(S + halo_tie_offset<TWW>(p.R));
   if (threadIdx.x == 0) *acc_total = 0u;
   __syncthreads();
 
-  // global loads first; they complete while the random state is computed
-  uint32_t stg[NSTG];
+  // Global loads first; they complete while the random state is computed.  No
+  // branch stands between them (a lane without a word loads a valid one and
+  // drops it), so that all are in flight together.
+  RawWord<LAYOUT> stg[NSTG];
+  auto load_words = [&](auto on_grid) {
 #pragma unroll
-  for (int j = 0; j < NSTG; ++j) {
-    const int i = threadIdx.x + j * blockDim.x;
-    const int r = i / CP, w = i - r * CP - 1;
-    stg[j] = (i < total && w >= 0 && w < wneed) ? load_word_at<LAYOUT>(p, ytab[r], xtab[w]) : 0u;
-  }
+    for (int j = 0; j < NSTG; ++j) {
+      const int i = min((int)(threadIdx.x + j * blockDim.x), total - 1);
+      const int r = i / CP, w = max(i - r * CP - 1, 0);
+      if (j * (int)blockDim.x < total) stg[j].template load<decltype(on_grid)::value>(p, ytab[r], xtab[min(w, wneed - 1)]);
+    }
+  };
+  if ((p.L & 31) == 0) load_words(std::true_type{});
+  else load_words(std::false_type{});
   for (int i = threadIdx.x + NSTG * blockDim.x; i < total; i += blockDim.x) {
     const int r = i / CP, w = i - r * CP - 1;
     S[r * ST + w + 1] = (w >= 0 && w < wneed) ? load_word_at<LAYOUT>(p, ytab[r], xtab[w]) : 0u;
@@ -840,27 +869,31 @@ __device__ __forceinline__ unsigned halo_tile_sweep(uint32_t* S, const SweepPara
   uint32_t okm[KU * 2];                 // class-0 centre pattern of each row (0 for a unit beyond the tile)
   uint32_t imask[KU][2];
   RowRand rr[KU][2];
+  int tie[KU][2];              // index of each row word's tie results
   int ry[KU * 2], rx[KU * 2];  // true row and column of each of the thread's rows
   bool okk[KU];
-  const bool grid = (p.L & 31) == 0;
 #pragma unroll
   for (int k = 0; k < KU; ++k) {
     const int u = threadIdx.x + k * blockDim.x;
     const bool in = u < p.nunits;
+    // A lane beyond the tile's units shares the place of an earlier unit, one
+    // each: its exchanges are empty, but xors of one wave to one LDS word run
+    // one after another, and 40 lanes on one word cost more than the phase.
+    const int v = in ? u : (u - p.nunits < p.nunits ? u - p.nunits : 0);
     int q, wu;
     if ((p.L & 31) == 0) {
-      q = in ? u / C : 0;
-      wu = in ? u - q * C : 0;
+      q = v / C;
+      wu = v - q * C;
     } else {
       // off-grid lattices: the two edge words of every row gather their random
       // planes from two or three segments; numbering them after all inner
       // words confines that slower path to the last waves
       const int nin = p.npairs * (C - 2);
-      if (u < nin) {
-        q = u / (C - 2);
-        wu = 1 + (u - q * (C - 2));
+      if (v < nin) {
+        q = v / (C - 2);
+        wu = 1 + (v - q * (C - 2));
       } else {
-        const int e = in ? u - nin : 0;
+        const int e = v - nin;
         q = e >> 1;
         wu = (e & 1) ? C - 1 : 0;
       }
@@ -868,7 +901,7 @@ __device__ __forceinline__ unsigned halo_tile_sweep(uint32_t* S, const SweepPara
     const bool ok = in && wu < wneed;
     const int w = ok ? wu : 0;
     const int r0 = 2 + 2 * q;
-    base0[k] = r0 * ST + w + 1;
+    base0[k] = r0 * ST + wu + 1;  // also for a word past wneed, which holds the zero pad
     yrow[2 * k] = ytab[r0];
     yrow[2 * k + 1] = ytab[r0 + 1];
     xw[k] = xtab[w];
@@ -890,65 +923,58 @@ __device__ __forceinline__ unsigned halo_tile_sweep(uint32_t* S, const SweepPara
       imask[k][h] = (ok && yv >= Y0 && yv < yend) ? wm : 0u;
       ry[2 * k + h] = ytab[r0 + h];
       rx[2 * k + h] = xtab[w];
-      if (!grid) {
-        if (ok) {
-          uint32_t pl[kPlanes];
-          gen_planes_at(p, ytab[r0 + h], xtab[w], Xw, t, pl);
-          row_rand(pl, p, ytab[r0 + h], xtab[w], t, rr[k][h]);
-        } else {
-          rr[k][h] = RowRand{0u, 0u, 0u, 0u, 0u};
-        }
-      }
     }
   }
-  if (grid) {
-    // row by row (a unit beyond the tile draws for a valid row and decides
-    // nothing: its centre masks are empty); a wave whose units of one index
-    // all lie beyond the tile skips them.  Drawing more rows at once, to
-    // overlap more Philox chains, measured slower: 16.3 us per 4096^2 sweep
-    // for a unit's two rows, 18.7 us for all four rows of a thread, against
-    // 16.2 us row by row.
-    RowRand rq[KU * 2];
+  // row by row (a lane beyond the tile's units draws for a valid row and
+  // decides nothing: its centre masks are empty); a wave whose units of one
+  // index all lie beyond the tile skips them.  Drawing more rows at once, to
+  // overlap more Philox chains, measured slower: 16.3 us per 4096^2 sweep for a
+  // unit's two rows, 18.7 us for all four rows of a thread, against 16.2 us row
+  // by row.
+  auto draw_rows = [&](auto on_grid) {
 #pragma unroll
     for (int k = 0; k < KU; ++k) {
-      if (k == 0 || __any(okk[k])) {
-        rand_rows_grid<1>(p, t, ry + 2 * k, rx + 2 * k, rq + 2 * k);
-        rand_rows_grid<1>(p, t, ry + 2 * k + 1, rx + 2 * k + 1, rq + 2 * k + 1);
+      if (__any(okk[k])) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+          tie[k][h] = rand_row<decltype(on_grid)::value>(p, ties, t, ry[2 * k + h], rx[2 * k + h], okk[k], rr[k][h]);
       } else {
-        rq[2 * k] = rq[2 * k + 1] = RowRand{0u, 0u, 0u, 0u, 0u};
+        rr[k][0] = rr[k][1] = RowRand{0u, 0u, 0u, 0u, 0u};
+        tie[k][0] = tie[k][1] = -1;
       }
     }
+  };
+  if ((p.L & 31) == 0) draw_rows(std::true_type{});
+  else draw_rows(std::false_type{});
+  resolve_list(p, ties, t);
 #pragma unroll
-    for (int k = 0; k < KU; ++k) {
-      rr[k][0] = rq[2 * k];
-      rr[k][1] = rq[2 * k + 1];
-    }
-  }
-  // the class order is the same for the whole workgroup: the first wave
-  // computes it into the word after the column table
-  uint32_t* perm_slot = reinterpret_cast<uint32_t*>(xtab + C);
-  if (threadIdx.x < 64) {
-    const uint32_t pm = class_order(p.k0, p.k1, t);
-    if (threadIdx.x == 0) *perm_slot = pm;
-  }
+  for (int k = 0; k < KU; ++k)
+#pragma unroll
+    for (int h = 0; h < 2; ++h) join_ties(ties, tie[k][h], rr[k][h]);
 #pragma unroll
   for (int j = 0; j < NSTG; ++j) {
     const int i = threadIdx.x + j * blockDim.x;
     const int r = i / CP, w = i - r * CP;
-    if (i < total) S[r * ST + w] = stg[j];
+    if (i < total) S[r * ST + w] = w >= 1 && w <= wneed ? stg[j].word() : 0u;
   }
   __syncthreads();
-  const uint32_t perm = *perm_slot;
+  const uint32_t perm = order;
 
   unsigned count = 0;
+  const bool last = KU == 1 || __any(okk[KU - 1]);  // uniform: this wave has all its units
 #pragma unroll 1
   for (int ph = 0; ph < 8; ++ph) {
     const uint32_t cls = (perm >> (4 * ph)) & 0xFu;
     const int a = (int)(cls >> 1);
     // pairs start on even rows, so the active row of every pair is the class
     // parity: a uniform branch keeps each row's random state in registers
-    if (cls & 1u) count += halo_phase<ST, KU, 1>(S, p, base0, yrow, xw, okm, rr, imask, a, t);
-    else count += halo_phase<ST, KU, 0>(S, p, base0, yrow, xw, okm, rr, imask, a, t);
+    if (last) {
+      if (cls & 1u) count += halo_phase<ST, KU, 1>(S, p, base0, yrow, xw, okm, rr, imask, a, t);
+      else count += halo_phase<ST, KU, 0>(S, p, base0, yrow, xw, okm, rr, imask, a, t);
+    } else {
+      if (cls & 1u) count += halo_phase<ST, 1, 1>(S, p, base0, yrow, xw, okm, rr, imask, a, t);
+      else count += halo_phase<ST, 1, 0>(S, p, base0, yrow, xw, okm, rr, imask, a, t);
+    }
     if (ph == 7) {  // each wave adds its count before the last barrier
       const unsigned ws = wave_sum8(count);
       if ((threadIdx.x & 63) == 0) atomicAdd(acc_total, ws);
@@ -993,179 +1019,261 @@ __device__ __forceinline__ void add_block_count(uint32_t* red_lds, unsigned coun
 }
 
 template <int LAYOUT, int TWW, int KU>
-__global__ __launch_bounds__(KU == 1 ? 1024 : 768)
-__attribute__((amdgpu_waves_per_eu(KU == 1 ? 4 : 3, KU == 1 ? 4 : 3))) void halo_kernel(SweepParams p) {
-  extern __shared__ uint32_t S[];
-  const unsigned total = halo_tile_sweep<LAYOUT, TWW, KU>(S, p, xcd_tile((int)blockIdx.x, (int)gridDim.x));
+__global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 4))) void halo_kernel(SweepParams p,
+                                                                                               uint32_t order) {
+  extern __shared__ __attribute__((aligned(16))) uint32_t S[];
+  const unsigned total = halo_tile_sweep<LAYOUT, TWW, KU>(S, p, xcd_tile((int)blockIdx.x, (int)gridDim.x), order);
   // one workgroup per address: an add without a returned value does not wait
   // for a read of the old sum at the end of the kernel
   if (threadIdx.x == 0) atomicAdd(p.accepted + blockIdx.x, (unsigned long long)total);
 }
 
 // ---------------------------------------------------------------------------
-// Cyclic whole-lattice tile (L % 32 == 0, C = L/32 words per row).  The
-// lattice rows -2..L+1 and words -1..C are all present in LDS: the ones
-// outside 0..L-1 / 0..C-1 are mirror copies of the wrapped sites, so every
-// neighbour read is an immediate offset as in the halo kernel.  Every
-// exchange is written to all LDS copies of the sites it flips; a unit near
-// the wrap carries a small descriptor of which of its targets have a copy.
+// Cyclic lattices (2 .. kResidentMaxC words per row): a sweep is a chain of draws
+// and eight phases, so the draws run ahead of it.  The first PW wavefronts hold
+// KU units per lane and do nothing but phases; RW others draw the next sweep's
+// random state (NT row words per lane) into LDS between the phases' barriers:
+// in eight slices, each shorter than a phase, where a lane draws up to three
+// row words (SLICED), else a whole row word in each of the intervals 1 .. NT.
+// The phase waves take a sweep's draws into registers in the first interval,
+// before any of the next sweep's are written.  The class orders of the launch's
+// sweeps are computed before the first, a sweep per lane.  Rows and words wrap
+// through addresses held per lane, so no cell has a second copy to keep (at two
+// words per row every exchange had up to three).
+//
+// Up to six words per row a phase is one wave's latency (about 600 cycles), with
+// more of them the SIMDs' issue rate bounds it.  Per sweep, one wave set doing
+// draws and phases in turn -> this: 64^2 4.9 -> 2.0 us, 128^2 6.0 -> 2.8, 160^2
+// 7.9 -> 4.4, 192^2 8.2 -> 6.0, 224^2 10.6 -> 7.8, 256^2 9.9 -> 8.9, 288^2 19.7
+// -> 11.5.
 // ---------------------------------------------------------------------------
+constexpr int kPipeMaxSweeps = 256;  // per launch (class orders held in LDS)
 template <int C>
-struct CycGeom {
-  static constexpr int ST = (C % 2 == 0) ? (C / 2 + 32) : 34;  // see HaloGeom
+struct Pipe {
+  static constexpr int RC = 32 * C * C;                       // row words (R = 32 C)
+  static constexpr int KU = C <= 6 ? 1 : (C <= 8 ? 2 : 3);    // units per lane of a phase wave
+  static constexpr int PW = (RC / 2 + 64 * KU - 1) / (64 * KU);
+  static constexpr int T = (RC + 63) / 64;                    // waves of row words
+  static constexpr int NT = C <= 4 ? 1 : (C == 5 ? 2 : (C <= 7 ? 3 : (C == 8 ? 4 : 5)));
+  static constexpr bool SLICED = C <= 6;
+  static constexpr int RW = (T + NT - 1) / NT;
+  static constexpr int kThreads = 64 * (PW + RW);
+  static constexpr int kWords = RC + 5 * RC + kPipeMaxSweeps + RW * (int)kTieWaveWords + 16;
+  static_assert(kThreads <= 1024 && NT <= 7 && kWords % 2 == 0, "wave roles");
 };
 
-// Row copy delta (in LDS rows) of lattice row x in [-2, R+1]: +R, -R or 0.
-__device__ __forceinline__ int row_copy(int x, int R) { return x <= 1 ? R : (x >= R - 2 ? -R : 0); }
-// Word copy delta of word x in [-1, C] (C >= 2): +C, -C or 0.
-template <int C>
-__device__ __forceinline__ int word_copy(int x) { return x <= 0 ? C : (x >= C - 1 ? -C : 0); }
+// A unit's words: row base addresses of rows r0 - 2 .. r0 + 3, word w and its
+// two neighbours.
+struct PipeUnit {
+  int row[6], w, we, ww;
+};
 
-__device__ __forceinline__ void xor_copies(uint32_t* S, int idx, uint32_t m, int dr, int dw) {
-  if (!m) return;
-  if (dr) atomicXor(&S[idx + dr], m);
-  if (dw) atomicXor(&S[idx + dw], m);
-  if (dr && dw) atomicXor(&S[idx + dr + dw], m);
-}
-
-template <int C, int KU, int H>
-__device__ __forceinline__ unsigned cyc_phase(uint32_t* S, const SweepParams& p, const int* base0, const int* yrow,
-                                              const int* xw, const uint32_t* okm, const RowRand (*rr)[2],
-                                              const int* ur, const int* uw, int a, uint64_t t) {
-  constexpr int ST = CycGeom<C>::ST;
+template <int KU, int H>
+__device__ __forceinline__ unsigned pipe_phase(uint32_t* S, const SweepParams& p, const PipeUnit* u,
+                                               const RowRand (*rr)[2], const uint32_t (*ok)[2], const bool* live,
+                                               uint32_t turn) {
   uint32_t v[KU][11];
 #pragma unroll
   for (int k = 0; k < KU; ++k) {
-    const int b = base0[k] + H * ST;
-    v[k][0] = S[b];
-    v[k][1] = S[b - 1];
-    v[k][2] = S[b + 1];
-    v[k][3] = S[b - ST];
-    v[k][4] = S[b - ST - 1];
-    v[k][5] = S[b - ST + 1];
-    v[k][6] = S[b + ST];
-    v[k][7] = S[b + ST - 1];
-    v[k][8] = S[b + ST + 1];
-    v[k][9] = S[b - 2 * ST];
-    v[k][10] = S[b + 2 * ST];
-  }
-  uint32_t F[KU];
-#pragma unroll
-  for (int k = 0; k < KU; ++k) {
-    const uint32_t cmask = __builtin_amdgcn_alignbit(okm[k * 2 + H], okm[k * 2 + H], (32 - a) & 31);
-    F[k] = decide_word(v[k], rr[k][H], p, cmask);
+    const int* r = u[k].row + H;  // rows -2 .. +2 around the active one
+    const int w = u[k].w, we = u[k].we, ww = u[k].ww;
+    v[k][0] = S[r[2] + w];
+    v[k][1] = S[r[2] + ww];
+    v[k][2] = S[r[2] + we];
+    v[k][3] = S[r[1] + w];
+    v[k][4] = S[r[1] + ww];
+    v[k][5] = S[r[1] + we];
+    v[k][6] = S[r[3] + w];
+    v[k][7] = S[r[3] + ww];
+    v[k][8] = S[r[3] + we];
+    v[k][9] = S[r[0] + w];
+    v[k][10] = S[r[4] + w];
   }
   unsigned count = 0;
 #pragma unroll
   for (int k = 0; k < KU; ++k) {
-    const uint32_t d0 = rr[k][H].d0, d1 = rr[k][H].d1;
-    const uint32_t f = F[k];
-    const uint32_t Fpx = bop3<KK_TT(KK_TA & ~KK_TB & ~KK_TC)>(f, d1, d0);
-    const uint32_t Fmx = bop3<KK_TT(KK_TA & ~KK_TB & KK_TC)>(f, d1, d0);
-    const uint32_t Fpy = bop3<KK_TT(KK_TA & KK_TB & ~KK_TC)>(f, d1, d0);
-    const uint32_t Fmy = bop3<KK_TT(KK_TA & KK_TB & KK_TC)>(f, d1, d0);
-    const int b = base0[k] + H * ST;
-    const uint32_t main = f ^ (Fpx << 1) ^ (Fmx >> 1);
-    const uint32_t cr = Fpx >> 31, cl = (Fmx & 1u) << 31;
-    atomicXor(&S[b], main);
-    atomicXor(&S[b + ST], Fpy);
-    atomicXor(&S[b - ST], Fmy);
-    if (cr) atomicXor(&S[b + 1], cr);
-    if (cl) atomicXor(&S[b - 1], cl);
-    const int r = ur[k] + H, w = uw[k];
-    if (f && (r <= 2 || r >= p.R - 3 || w <= 1 || w >= C - 2)) {  // some target has a mirror copy
-      const int R = p.R;
-      const int dr0 = row_copy(r, R) * ST, drp = row_copy(r + 1, R) * ST, drm = row_copy(r - 1, R) * ST;
-      const int dw0 = word_copy<C>(w), dwp = word_copy<C>(w + 1), dwm = word_copy<C>(w - 1);
-      xor_copies(S, b, main, dr0, dw0);
-      xor_copies(S, b + ST, Fpy, drp, dw0);
-      xor_copies(S, b - ST, Fmy, drm, dw0);
-      xor_copies(S, b + 1, cr, dr0, dwp);
-      xor_copies(S, b - 1, cl, dr0, dwm);
+    const int* r = u[k].row + H;
+    const RowRand& q = rr[k][H];
+    const uint32_t f = decide_word(v[k], q, p, __builtin_amdgcn_alignbit(ok[k][H], ok[k][H], turn));
+    if (live[k]) {
+      const uint32_t px = bop3<KK_TT(KK_TA & ~KK_TB & ~KK_TC)>(f, q.d1, q.d0);
+      const uint32_t mx = bop3<KK_TT(KK_TA & ~KK_TB & KK_TC)>(f, q.d1, q.d0);
+      atomicXor(&S[r[2] + u[k].w], (px << 1) | f | (mx >> 1));
+      atomicXor(&S[r[3] + u[k].w], bop3<KK_TT(KK_TA & KK_TB & ~KK_TC)>(f, q.d1, q.d0));
+      atomicXor(&S[r[1] + u[k].w], bop3<KK_TT(KK_TA & KK_TB & KK_TC)>(f, q.d1, q.d0));
+      atomicXor(&S[r[2] + u[k].we], px >> 31);
+      atomicXor(&S[r[2] + u[k].ww], mx << 31);
     }
-    count += (unsigned)__builtin_popcount(f & okm[k * 2 + H + 2 * KU]);
+    count += (unsigned)__builtin_popcount(f);
   }
   return count;
 }
 
-// Whole lattice in one workgroup, p.nsweeps sweeps from p.t0.  Returns the
-// thread's accepted count.
-template <int LAYOUT, int C, int KU>
-__device__ __forceinline__ unsigned cyc_sweeps(uint32_t* S, const SweepParams& p, uint32_t* perm_slot) {
-  constexpr int ST = CycGeom<C>::ST;
-  const int R = p.R;  // == L
-  const int L = p.L;
-  // stage rows -2..R+1, words -1..C (the copies included)
-  const int rows = R + 4, cols = C + 2;
-  for (int i = threadIdx.x; i < rows * cols; i += blockDim.x) {
-    const int rr = i / cols, ww = i - rr * cols;
-    int y = rr - 2, x = ww - 1;
-    y = y < 0 ? y + R : (y >= R ? y - R : y);
-    x = x < 0 ? x + C : (x >= C ? x - C : x);
-    S[rr * ST + ww] = load_word_any<LAYOUT>(p, y, 32 * x);
-  }
-  int base0[KU], yrow[KU * 2], xw[KU], ur[KU], uw[KU];
-  uint32_t okm[KU * 4];  // [0, 2KU): class-0 pattern per row; [2KU, 4KU): count mask per row
-#pragma unroll
-  for (int k = 0; k < KU; ++k) {
-    const int u = threadIdx.x + k * blockDim.x;
-    const bool ok = u < p.nunits;
-    const int q = ok ? u / C : 0, w = ok ? u - q * C : 0;
-    const int r0 = 2 * q;  // lattice row of the pair's first row
-    base0[k] = (r0 + 2) * ST + w + 1;
-    ur[k] = r0;
-    uw[k] = w;
-    yrow[2 * k] = r0;
-    yrow[2 * k + 1] = r0 + 1;
-    xw[k] = 32 * w;
-    okm[2 * k] = ok ? (0x11111111u << (r0 & 3)) : 0u;
-    okm[2 * k + 1] = ok ? (0x11111111u << ((r0 + 1) & 3)) : 0u;
-    okm[2 * KU + 2 * k] = ok ? 0xFFFFFFFFu : 0u;
-    okm[2 * KU + 2 * k + 1] = ok ? 0xFFFFFFFFu : 0u;
-  }
-  (void)L;
+// Whole lattice in one workgroup, p.nsweeps (at most kPipeMaxSweeps) sweeps
+// from p.t0.  Threads beyond Pipe<C>::kThreads only take part in the staging
+// and the barriers.  Returns the thread's accepted count.
+template <int LAYOUT, int C>
+__device__ __forceinline__ unsigned pipe_sweeps(uint32_t* S, const SweepParams& p) {
+  using P = Pipe<C>;
+  constexpr int R = 32 * C, RC = P::RC, KU = P::KU, NT = P::NT;
+  uint32_t* D = S + RC;  // five planes of RC words
+  uint32_t* orders = D + 5 * RC;
+  const int lane = (int)(threadIdx.x & 63u);
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  for (int i = threadIdx.x; i < RC; i += blockDim.x) S[i] = load_word_any<LAYOUT>(p, i / C, 32 * (i % C));
+  for (int i = threadIdx.x; i < p.nsweeps; i += blockDim.x) orders[i] = class_order(p.k0, p.k1, p.t0 + (uint64_t)i);
   unsigned count = 0;
-#pragma unroll 1
-  for (int s = 0; s < p.nsweeps; ++s) {
-    const uint64_t t = p.t0 + (uint64_t)s;
-    // every word sits on the segment grid (L % 32 == 0); a unit beyond the
-    // lattice draws for row 0 and decides nothing
-    RowRand rr[KU][2];
+  if (wave < P::PW) {
+    PipeUnit u[KU];
+    uint32_t ok[KU][2];
+    bool live[KU];
+    int d0[KU];
 #pragma unroll
-    for (int k = 0; k < KU; ++k)
+    for (int k = 0; k < KU; ++k) {
+      const int un = 64 * (wave + k * P::PW) + lane;
+      live[k] = un < RC / 2;
+      const int v = live[k] ? un : un - RC / 2;  // spare lanes: another unit's words, no centres
+      const int q = v / C, w = v - q * C, r0 = 2 * q;
 #pragma unroll
-      for (int h = 0; h < 2; ++h) rand_rows_grid<1>(p, t, yrow + 2 * k + h, xw + k, &rr[k][h]);
-    // one wave computes the sweep's class order; every wave has read the
-    // previous one (right after the previous sweep's first barrier)
-    if (threadIdx.x < 64) {
-      const uint32_t pm = class_order(p.k0, p.k1, t);
-      if (threadIdx.x == 0) *perm_slot = pm;
+      for (int j = 0; j < 6; ++j) {
+        int y = r0 - 2 + j;
+        y = y < 0 ? y + R : (y >= R ? y - R : y);
+        u[k].row[j] = y * C;
+      }
+      u[k].w = w;
+      u[k].we = w + 1 == C ? 0 : w + 1;
+      u[k].ww = w == 0 ? C - 1 : w - 1;
+      ok[k][0] = live[k] ? 0x11111111u << (r0 & 3) : 0u;
+      ok[k][1] = live[k] ? 0x11111111u << ((r0 + 1) & 3) : 0u;
+      d0[k] = r0 * C + w;
     }
-    __syncthreads();  // staging or the previous sweep complete
-    const uint32_t perm = *perm_slot;
 #pragma unroll 1
-    for (int ph = 0; ph < 8; ++ph) {
-      const uint32_t cls = (perm >> (4 * ph)) & 0xFu;
-      const int a = (int)(cls >> 1);
-      if (cls & 1u) count += cyc_phase<C, KU, 1>(S, p, base0, yrow, xw, okm, rr, ur, uw, a, t);
-      else count += cyc_phase<C, KU, 0>(S, p, base0, yrow, xw, okm, rr, ur, uw, a, t);
-      __syncthreads();
+    for (int i = 0; i < 8; ++i) __syncthreads();  // the first sweep's draws
+#pragma unroll 1
+    for (int s = 0; s < p.nsweeps; ++s) {
+      RowRand rr[KU][2];
+#pragma unroll
+      for (int k = 0; k < KU; ++k)
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          const uint32_t* d = D + d0[k] + h * C;
+          rr[k][h] = RowRand{d[0], d[RC], d[2 * RC], d[3 * RC], d[4 * RC]};
+        }
+      const uint32_t perm = (uint32_t)__builtin_amdgcn_readfirstlane((int)orders[s]);
+#pragma unroll 1
+      for (int ph = 0; ph < 8; ++ph) {
+        const uint32_t cls = (perm >> (4 * ph)) & 0xFu, turn = (32u - (cls >> 1)) & 31u;
+        if (cls & 1u) count += pipe_phase<KU, 1>(S, p, u, rr, ok, live, turn);
+        else count += pipe_phase<KU, 0>(S, p, u, rr, ok, live, turn);
+        __syncthreads();
+      }
     }
+  } else if (wave < P::PW + P::RW) {
+    uint32_t* tw = orders + kPipeMaxSweeps + (wave - P::PW) * (int)kTieWaveWords;
+    TieList ties{reinterpret_cast<uint2*>(tw), tw + 2 * kTieCap, 0u};
+    int rid[NT], y[NT], x[NT];
+    bool live[NT];
+#pragma unroll
+    for (int i = 0; i < NT; ++i) {
+      rid[i] = 64 * ((wave - P::PW) * NT + i) + lane;
+      live[i] = rid[i] < RC;
+      rid[i] = live[i] ? rid[i] : RC - 1;
+      y[i] = rid[i] / C;
+      x[i] = 32 * (rid[i] - y[i] * C);
+    }
+    auto store = [&](int i, RowRand q, int tie) {
+      join_ties(ties, tie, q);
+      uint32_t* d = D + rid[i];
+      if (live[i]) {
+        d[0] = q.d0;
+        d[RC] = q.d1;
+        d[2 * RC] = q.acc0;
+        d[3 * RC] = q.acc1;
+        d[4 * RC] = q.acc2;
+      }
+    };
+#pragma unroll 1
+    for (int s = 0; s < p.nsweeps; ++s) {
+      const uint64_t t = p.t0 + (uint64_t)s;
+      if constexpr (P::SLICED) {
+        uint32_t c0[3 * NT], c1[3 * NT], c2[3 * NT], c3[3 * NT];
+        const uint32_t thi = ctr_hi(t, kTagSweep);
+#pragma unroll
+        for (int i = 0; i < NT; ++i)
+#pragma unroll
+          for (int b = 0; b < 3; ++b) {
+            c0[3 * i + b] = (uint32_t)y[i];
+            c1[3 * i + b] = (uint32_t)(x[i] >> 5) * 4u + (uint32_t)b;
+            c2[3 * i + b] = (uint32_t)t;
+            c3[3 * i + b] = thi;
+          }
+        philox10_n<3 * NT, 0, 4>(c0, c1, c2, c3, p.k0, p.k1);
+        __syncthreads();
+        philox10_n<3 * NT, 4, 7>(c0, c1, c2, c3, p.k0, p.k1);
+        __syncthreads();
+        philox10_n<3 * NT, 7, 10>(c0, c1, c2, c3, p.k0, p.k1);
+        __syncthreads();
+        uint32_t pl[NT][kPlanes], lt[NT][3], eq[NT][3];
+        int tie[NT];
+#pragma unroll
+        for (int i = 0; i < NT; ++i) {
+#pragma unroll
+          for (int b = 0; b < 3; ++b) {
+            pl[i][4 * b] = c0[3 * i + b];
+            pl[i][4 * b + 1] = c1[3 * i + b];
+            pl[i][4 * b + 2] = c2[3 * i + b];
+            pl[i][4 * b + 3] = c3[3 * i + b];
+          }
+          compare_slot(pl[i], p.acc.hi[0], live[i], lt[i][0], eq[i][0]);
+        }
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < NT; ++i) {
+          compare_slot(pl[i], p.acc.hi[1], live[i], lt[i][1], eq[i][1]);
+          compare_slot(pl[i], p.acc.hi[2], live[i], lt[i][2], eq[i][2]);
+        }
+        __syncthreads();
+        ties.n = 0u;
+#pragma unroll
+        for (int i = 0; i < NT; ++i) tie[i] = list_ties(p, ties, y[i], x[i], t, eq[i], lt[i]);
+        __syncthreads();
+        resolve_list(p, ties, t);
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < NT; ++i)
+          store(i, RowRand{pl[i][0], pl[i][1], lt[i][0], lt[i][1], lt[i][2]}, tie[i]);
+        __syncthreads();
+      } else {
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < 7; ++i) {
+          if (i < NT) {
+            RowRand q;
+            ties.n = 0u;
+            const int tie = rand_row<true>(p, ties, t, y[i < NT ? i : 0], x[i < NT ? i : 0], live[i < NT ? i : 0], q);
+            resolve_list(p, ties, t);
+            store(i < NT ? i : 0, q, tie);
+          }
+          __syncthreads();
+        }
+      }
+    }
+#pragma unroll 1
+    for (int i = 0; i < 8; ++i) __syncthreads();  // the last sweep's phases
+  } else {
+#pragma unroll 1
+    for (int i = 0; i < 8 * (p.nsweeps + 1); ++i) __syncthreads();
   }
-  for (int i = threadIdx.x; i < R * C; i += blockDim.x) {
-    const int y = i / C, x = i - y * C;
-    store_word_any<LAYOUT>(p, y, 32 * x, S[(y + 2) * ST + x + 1], 32);
-  }
+  for (int i = threadIdx.x; i < RC; i += blockDim.x) store_word_any<LAYOUT>(p, i / C, 32 * (i % C), S[i], 32);
   return count;
 }
 
-template <int LAYOUT, int C, int KU>
-__global__ __launch_bounds__(KU == 1 ? 1024 : 768) void cyc_kernel(SweepParams p) {
-  extern __shared__ uint32_t S[];
-  const unsigned count = cyc_sweeps<LAYOUT, C, KU>(S, p, S + (p.R + 4) * CycGeom<C>::ST + 16);
-  add_block_count(S + (p.R + 4) * CycGeom<C>::ST, count, p.accepted);
+template <int LAYOUT, int C>
+__global__ __launch_bounds__(Pipe<C>::kThreads) void pipe_kernel(SweepParams p) {
+  extern __shared__ __attribute__((aligned(16))) uint32_t S[];
+  const unsigned count = pipe_sweeps<LAYOUT, C>(S, p);
+  add_block_count(S + Pipe<C>::kWords - 16, count, p.accepted);
 }
-
 
 // ---------------------------------------------------------------------------
 // Batch kernels
@@ -1186,7 +1294,7 @@ __global__ void batch_advance_kernel(unsigned* ctl, unsigned step) { ctl[0] += s
 template <int KU>
 __global__ __launch_bounds__(kBatchTileThreads) __attribute__((amdgpu_waves_per_eu(4)))
 void batch_tile_kernel(const SweepParams* reps, const BatchTileJob* jobs, const unsigned* ctl, unsigned rel) {
-  extern __shared__ uint32_t S[];
+  extern __shared__ __attribute__((aligned(16))) uint32_t S[];
   // the sweep index and the job are independent loads; the replica's
   // parameters (sweep count and both buffers included) follow the job
   const unsigned s = __hip_atomic_load(&ctl[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + rel;
@@ -1202,104 +1310,111 @@ void batch_tile_kernel(const SweepParams* reps, const BatchTileJob* jobs, const 
     // compile-time tile width (8 or 16 words: immediate, bank-conflict-free
     // LDS offsets) chosen per replica by a uniform switch; a replica's last
     // tile column may be ragged
+    const uint32_t order = class_order(p.k0, p.k1, p.t0);
     unsigned count;
     if (p.layout == kLayoutBits) {
-      if (p.tww == 8) count = halo_tile_sweep<kLayoutBits, 8, KU>(S, p, job.tile);
-      else count = halo_tile_sweep<kLayoutBits, 16, KU>(S, p, job.tile);
+      if (p.tww == 8) count = halo_tile_sweep<kLayoutBits, 8, KU>(S, p, job.tile, order);
+      else count = halo_tile_sweep<kLayoutBits, 16, KU>(S, p, job.tile, order);
     } else {
-      if (p.tww == 8) count = halo_tile_sweep<kLayoutInt8, 8, KU>(S, p, job.tile);
-      else count = halo_tile_sweep<kLayoutInt8, 16, KU>(S, p, job.tile);
+      if (p.tww == 8) count = halo_tile_sweep<kLayoutInt8, 8, KU>(S, p, job.tile, order);
+      else count = halo_tile_sweep<kLayoutInt8, 16, KU>(S, p, job.tile, order);
     }
     if (threadIdx.x == 0) atomicAdd(p.accepted + job.tile, (unsigned long long)count);
   }
 }
 
-// All resident replicas in one launch, one workgroup each: the width is a
-// uniform run-time switch over per-width instantiations (disjoint code regions
-// share one register allocation) and the layout is a run-time branch of the
-// staging and the final store.  The reduction area sits past the largest
-// resident lattice (rows L+4, stride <= 36).
-__global__ __launch_bounds__(kBatchThreads) void batch_resident_all_kernel(const SweepParams* reps, const int* ids,
-                                                                           const unsigned* ctl) {
-  extern __shared__ uint32_t S[];
+// Resident replicas, one workgroup each: the width is a uniform run-time switch
+// over per-width instantiations (disjoint code regions share one register
+// allocation) and the layout is a run-time branch of the staging and the final
+// store.  Two launches, so that a small replica does not hold the waves and
+// the LDS of a large one.
+template <int C>
+__device__ __forceinline__ void resident_sweeps(uint32_t* S, const SweepParams& p) {
+  const unsigned count = pipe_sweeps<0, C>(S, p);
+  add_block_count(S + Pipe<C>::kWords - 16, count, p.accepted);
+}
+__device__ __forceinline__ bool resident_chunk(SweepParams& p, unsigned s) {
+  if (s >= (unsigned)p.nsweeps) return false;
+  p.t0 += s;  // this launch: up to kBatchChunk sweeps from run sweep s
+  p.nsweeps = min(kBatchChunk, p.nsweeps - (int)s);
+  return true;
+}
+__global__ __launch_bounds__(kResidentThreads) void batch_resident_all_kernel(const SweepParams* reps, const int* ids,
+                                                                              const unsigned* ctl) {
+  extern __shared__ __attribute__((aligned(16))) uint32_t S[];
   const unsigned s = __hip_atomic_load(&ctl[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   SweepParams p = reps[ids[blockIdx.x]];
-  if (s < (unsigned)p.nsweeps) {  // this launch: up to kBatchChunk sweeps from run sweep s
-    p.t0 += s;
-    p.nsweeps = min(kBatchChunk, p.nsweeps - (int)s);
-    uint32_t* slot = S + (p.R + 4) * 36 + 16;  // past the reduction area
-    unsigned count;
-    switch (p.C) {
-      case 2: count = cyc_sweeps<0, 2, 2>(S, p, slot); break;
-      case 3: count = cyc_sweeps<0, 3, 2>(S, p, slot); break;
-      case 4: count = cyc_sweeps<0, 4, 2>(S, p, slot); break;
-      case 5: count = cyc_sweeps<0, 5, 2>(S, p, slot); break;
-      case 6: count = cyc_sweeps<0, 6, 2>(S, p, slot); break;
-      case 7: count = cyc_sweeps<0, 7, 2>(S, p, slot); break;
-      case 8: count = cyc_sweeps<0, 8, 2>(S, p, slot); break;
-      default: count = cyc_sweeps<0, 9, 2>(S, p, slot); break;
-    }
-    add_block_count(S + (p.R + 4) * 36, count, p.accepted);
+  if (!resident_chunk(p, s)) return;
+  switch (p.C) {
+    case 5: resident_sweeps<5>(S, p); break;
+    case 6: resident_sweeps<6>(S, p); break;
+    case 7: resident_sweeps<7>(S, p); break;
+    case 8: resident_sweeps<8>(S, p); break;
+    default: resident_sweeps<9>(S, p); break;
   }
 }
-
-// Small resident replicas (L <= 32 * kResidentSmallMaxC: at most 512 units)
-// in 256-thread workgroups, three per CU.
-__global__ __launch_bounds__(kResidentSmallThreads, 3) void batch_resident_small_kernel(const SweepParams* reps,
-                                                                                       const int* ids,
-                                                                                       const unsigned* ctl) {
-  extern __shared__ uint32_t S[];
+__global__ __launch_bounds__(kResidentSmallThreads) void batch_resident_small_kernel(const SweepParams* reps,
+                                                                                     const int* ids,
+                                                                                     const unsigned* ctl) {
+  extern __shared__ __attribute__((aligned(16))) uint32_t S[];
   const unsigned s = __hip_atomic_load(&ctl[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   SweepParams p = reps[ids[blockIdx.x]];
-  if (s < (unsigned)p.nsweeps) {
-    p.t0 += s;
-    p.nsweeps = min(kBatchChunk, p.nsweeps - (int)s);
-    uint32_t* slot = S + (p.R + 4) * 36 + 16;
-    unsigned count;
-    switch (p.C) {
-      case 2: count = cyc_sweeps<0, 2, 2>(S, p, slot); break;
-      case 3: count = cyc_sweeps<0, 3, 2>(S, p, slot); break;
-      case 4: count = cyc_sweeps<0, 4, 2>(S, p, slot); break;
-      default: count = cyc_sweeps<0, 5, 2>(S, p, slot); break;
-    }
-    add_block_count(S + (p.R + 4) * 36, count, p.accepted);
+  if (!resident_chunk(p, s)) return;
+  switch (p.C) {
+    case 2: resident_sweeps<2>(S, p); break;
+    case 3: resident_sweeps<3>(S, p); break;
+    default: resident_sweeps<4>(S, p); break;
   }
 }
+static_assert(Pipe<4>::kThreads <= kResidentSmallThreads && Pipe<5>::kThreads <= kResidentThreads &&
+              Pipe<7>::kThreads <= kResidentThreads && Pipe<9>::kThreads <= kResidentThreads, "resident threads");
 
+}  // namespace
+
+namespace {
+// class_order on the host.
+uint32_t class_order_host(uint32_t k0, uint32_t k1, uint64_t t) {
+  uint32_t w[8];
+  for (uint32_t j = 0; j < 2; ++j) {
+    const Philox4 b = philox10_host(0u, j, (uint32_t)t, ctr_hi(t, kTagOrder), k0, k1);
+    w[4 * j] = b.x;
+    w[4 * j + 1] = b.y;
+    w[4 * j + 2] = b.z;
+    w[4 * j + 3] = b.w;
+  }
+  return (uint32_t)shuffle_nibbles(w, 8);
+}
 }  // namespace
 
 hipError_t launch_sweep(const SweepParams& p, int layout, bool cyclic, int ku, int threads, hipStream_t stream) {
   const int tiles_y = (p.L + p.th - 1) / p.th;
   const dim3 grid(p.tiles_x * tiles_y), block(threads);
   const size_t lds = (size_t)p.R * (p.C + 2) * sizeof(uint32_t) + 16 * sizeof(unsigned);
-  if (cyclic && p.C >= 2 && p.C <= 11) {
-#define KK_CYC(LY, CC)                                                                            \
-  do {                                                                                            \
-    const size_t cl = ((size_t)(p.R + 4) * CycGeom<CC>::ST + 17) * sizeof(uint32_t);              \
-    if (ku == 1) hipLaunchKernelGGL((cyc_kernel<LY, CC, 1>), grid, block, cl, stream, p);         \
-    else hipLaunchKernelGGL((cyc_kernel<LY, CC, 2>), grid, block, cl, stream, p);                 \
-  } while (0)
-#define KK_CYC_C(LY)                                                                                          \
-  do {                                                                                                        \
-    switch (p.C) {                                                                                            \
-      case 2: KK_CYC(LY, 2); break;   case 3: KK_CYC(LY, 3); break;   case 4: KK_CYC(LY, 4); break;           \
-      case 5: KK_CYC(LY, 5); break;   case 6: KK_CYC(LY, 6); break;   case 7: KK_CYC(LY, 7); break;           \
-      case 8: KK_CYC(LY, 8); break;   case 9: KK_CYC(LY, 9); break;   case 10: KK_CYC(LY, 10); break;         \
-      default: KK_CYC(LY, 11); break;                                                                         \
-    }                                                                                                         \
-  } while (0)
-    if (layout == kLayoutBits) KK_CYC_C(kLayoutBits);
-    else KK_CYC_C(kLayoutInt8);
-#undef KK_CYC_C
-#undef KK_CYC
+  if (cyclic && p.C >= 2 && p.C <= kResidentMaxC && p.nsweeps <= kPipeMaxSweeps) {
+#define KK_PIPE(CC)                                                                                                  \
+  case CC:                                                                                                           \
+    if (layout == kLayoutBits)                                                                                       \
+      hipLaunchKernelGGL((pipe_kernel<kLayoutBits, CC>), grid, dim3(Pipe<CC>::kThreads), Pipe<CC>::kWords * 4, stream, p); \
+    else                                                                                                             \
+      hipLaunchKernelGGL((pipe_kernel<kLayoutInt8, CC>), grid, dim3(Pipe<CC>::kThreads), Pipe<CC>::kWords * 4, stream, p); \
+    break
+    switch (p.C) {
+      KK_PIPE(2); KK_PIPE(3); KK_PIPE(4); KK_PIPE(5); KK_PIPE(6); KK_PIPE(7); KK_PIPE(8); KK_PIPE(9);
+    }
+#undef KK_PIPE
     return hipGetLastError();
   }
   if (!cyclic && (p.tww == 1 || p.tww == 2 || p.tww == 4 || p.tww == 8 || p.tww == 16)) {
+    // two units per thread: four waves per SIMD issue a multiply or a shift
+    // every 4.5 cycles, three (one wave each for 768 threads' units) only every
+    // 5.8, so the first threads take two units and the rest one
+    const dim3 wide(ku == 2 && p.nunits > 1024 ? 1024 : threads);
+    const uint32_t order = class_order_host(p.k0, p.k1, p.t0);
 #define KK_HALO(LY, TW)                                                                                  \
   do {                                                                                                   \
-    const size_t hl = ((size_t)p.R * HaloGeom<TW>::ST + 17 + p.R + HaloGeom<TW>::C) * sizeof(uint32_t);  \
-    if (ku == 1) hipLaunchKernelGGL((halo_kernel<LY, TW, 1>), grid, block, hl, stream, p);               \
-    else hipLaunchKernelGGL((halo_kernel<LY, TW, 2>), grid, block, hl, stream, p);                       \
+    const size_t hl = ((size_t)halo_tie_offset<TW>(p.R) + (wide.x / 64) * kTieWaveWords) * sizeof(uint32_t); \
+    if (ku == 1) hipLaunchKernelGGL((halo_kernel<LY, TW, 1>), grid, block, hl, stream, p, order);        \
+    else hipLaunchKernelGGL((halo_kernel<LY, TW, 2>), grid, wide, hl, stream, p, order);                 \
   } while (0)
 #define KK_HALO_W(LY)                          \
   do {                                         \
@@ -1335,10 +1450,15 @@ namespace kk {
 
 size_t batch_tile_lds_bytes() {
   const int R = kBatchTh + 32;  // the widest tile has the largest stride
-  return ((size_t)R * HaloGeom<kBatchMaxTww>::ST + 17 + R + kBatchMaxTww + 2) * sizeof(uint32_t);
+  return ((size_t)halo_tie_offset<kBatchMaxTww>(R) + (kBatchTileThreads / 64) * kTieWaveWords) * sizeof(uint32_t);
 }
 
-size_t batch_resident_lds_bytes(int L) { return ((size_t)(L + 4) * 36 + 17) * sizeof(uint32_t); }
+size_t batch_resident_lds_bytes(int L) {
+  static constexpr int words[] = {Pipe<2>::kWords, Pipe<3>::kWords, Pipe<4>::kWords, Pipe<5>::kWords,
+                                  Pipe<6>::kWords, Pipe<7>::kWords, Pipe<8>::kWords, Pipe<9>::kWords};
+  static_assert(sizeof words / sizeof words[0] == kResidentMaxC - 1, "one per width");
+  return (size_t)words[L / 32 - 2] * sizeof(uint32_t);
+}
 
 hipError_t launch_batch_tiles(const SweepParams* reps, const BatchTileJob* jobs, int njobs, const unsigned* ctl,
                               unsigned rel, int ku, hipStream_t stream) {
@@ -1362,7 +1482,7 @@ hipError_t launch_batch_resident(const SweepParams* reps, const int* ids, int n,
     hipLaunchKernelGGL(batch_resident_small_kernel, dim3(n), dim3(kResidentSmallThreads), lds_bytes, stream, reps,
                        ids, ctl);
   else
-    hipLaunchKernelGGL(batch_resident_all_kernel, dim3(n), dim3(kBatchThreads), lds_bytes, stream, reps, ids, ctl);
+    hipLaunchKernelGGL(batch_resident_all_kernel, dim3(n), dim3(kResidentThreads), lds_bytes, stream, reps, ids, ctl);
   return hipGetLastError();
 }
 
