@@ -8,16 +8,14 @@
 // group every sweep is one launch over all of the group's halo tiles.
 // Resident replicas of at most kResidentSmallMaxC words per row run in
 // 768-thread workgroups (two per CU), larger ones in 1024-thread workgroups.
-// One HIP graph holds a chunk of kBatchChunk sweeps of everything: a branch
-// per tile group (kBatchChunk chained launches) and a branch per resident
-// kernel (one launch of kBatchChunk sweeps), forked from and joined to one
-// stream; the graph is replayed once per chunk.  Branches of one graph run
-// concurrently, which separate streams replaying their own graphs did not
-// do here (measured).  No slot or replica index
+// Every tile group and every resident kernel has a stream of its own: a run
+// enqueues one launch per sweep for each tile group and one launch per
+// kBatchChunk sweeps for each resident kernel, all streams at once, and waits
+// for all of them.  No slot or replica index
 // enters any random counter, so every replica ends exactly where kk_sweep
 // would have left it.
 //
-// The streams live as long as the batch; the plan (tables, graphs) is rebuilt
+// The streams live as long as the batch; the plan (tables) is rebuilt
 // whenever the replica set changes, which the job server does between steps.
 #include <hip/hip_runtime.h>
 
@@ -35,10 +33,7 @@
 using namespace kk;
 
 namespace {
-constexpr int kMaxTileGroups = 4;
-// sweep hand-off words (two each): one per tile group, then the small and the
-// large resident launch
-constexpr int kCtlSlots = kMaxTileGroups + 2, kCtlSmall = kMaxTileGroups, kCtlLarge = kMaxTileGroups + 1;
+constexpr int kMaxTileGroups = 2;
 // tile workgroups that fill the device once (256 CUs, two per CU)
 constexpr size_t kFillWorkgroups = 512;
 }
@@ -54,14 +49,13 @@ struct kk_batch {
   hipStream_t sA = nullptr, sB = nullptr;  // large resident launch; uploads and joins
   hipStream_t sC = nullptr;                 // small resident launch
   bool own_sB = false;
-  hipEvent_t ev_upload = nullptr, ev_res = nullptr;
+  hipEvent_t ev_upload = nullptr;
   hipStream_t tg_stream[kMaxTileGroups] = {};
   // batched labelling (kk_batch_cluster_hists), made on first use: the table
   // of lattices, the staging rows of the result blocks and their pinned image
   CclRep* d_ccl = nullptr;
   uint32_t* d_hist_stage = nullptr;
   uint32_t* h_hist_stage = nullptr;
-  hipEvent_t tg_done[kMaxTileGroups] = {};
   // plan, rebuilt by batch_plan
   std::vector<int> resident, tiled;
   size_t n_small = 0;  // resident[0, n_small) run in the small kernel, the rest in the large one
@@ -69,15 +63,12 @@ struct kk_batch {
   size_t ncounts = 0;
   std::vector<int> tg_off, tg_n;  // tiled groups: slices of the tile-job table
   std::vector<int> job_rep;       // host copy: replica of every tile job
-  hipGraph_t graph = nullptr;     // one chunk of kBatchChunk sweeps of every branch
-  hipGraphExec_t gexec = nullptr;
-  hipEvent_t ev_fork = nullptr;
   SweepParams* d_params = nullptr;
   BatchTileJob* d_jobs = nullptr;
   int njobs = 0;
   int* d_res = nullptr;
   size_t res_lds = 0, small_lds = 0;
-  unsigned* d_ctl = nullptr;
+  uint32_t* d_orders = nullptr;  // class orders of kBatchChunk sweeps of every replica, per tile group
   unsigned long long* d_counts = nullptr;
   bool poisoned = false;
 };
@@ -97,20 +88,13 @@ namespace {
 bool is_resident(const kk_sim* h) { return h->L % 32 == 0 && h->L >= 64 && h->L / 32 <= kResidentMaxC; }
 
 void clear_plan(kk_batch* b) {
-  // the executable graph must be idle, and finished in the eyes of the runtime,
-  // before it is destroyed: a run waits for its last event on another stream,
-  // which says nothing of the stream that launched the graph
-  if (b->gexec && b->tg_stream[0]) (void)hipStreamSynchronize(b->tg_stream[0]);
-  if (b->gexec) (void)hipGraphExecDestroy(b->gexec);
-  if (b->graph) (void)hipGraphDestroy(b->graph);
-  b->gexec = nullptr;
-  b->graph = nullptr;
-  for (void* p : {(void*)b->d_params, (void*)b->d_jobs, (void*)b->d_res, (void*)b->d_ctl, (void*)b->d_counts})
+  for (void* p : {(void*)b->d_params, (void*)b->d_jobs, (void*)b->d_res, (void*)b->d_orders,
+                  (void*)b->d_counts})
     if (p) (void)hipFree(p);
   b->d_params = nullptr;
   b->d_jobs = nullptr;
   b->d_res = nullptr;
-  b->d_ctl = nullptr;
+  b->d_orders = nullptr;
   b->d_counts = nullptr;
   b->resident.clear();
   b->tiled.clear();
@@ -133,11 +117,8 @@ void free_batch(kk_batch* b) {
   b->sims.clear();
   for (int g = 0; g < kMaxTileGroups; ++g) {
     if (b->tg_stream[g]) (void)hipStreamDestroy(b->tg_stream[g]);
-    if (b->tg_done[g]) (void)hipEventDestroy(b->tg_done[g]);
   }
   if (b->ev_upload) (void)hipEventDestroy(b->ev_upload);
-  if (b->ev_res) (void)hipEventDestroy(b->ev_res);
-  if (b->ev_fork) (void)hipEventDestroy(b->ev_fork);
   if (b->sA) (void)hipStreamDestroy(b->sA);
   if (b->sC) (void)hipStreamDestroy(b->sC);
   if (b->d_ccl) (void)hipFree(b->d_ccl);
@@ -156,13 +137,10 @@ kk_status make_streams(kk_batch* b, void* hip_stream) {
   }
   if ((e = hipStreamCreateWithFlags(&b->sA, hipStreamNonBlocking)) != hipSuccess ||
       (e = hipStreamCreateWithFlags(&b->sC, hipStreamNonBlocking)) != hipSuccess ||
-      (e = hipEventCreateWithFlags(&b->ev_upload, hipEventDisableTiming)) != hipSuccess ||
-      (e = hipEventCreateWithFlags(&b->ev_res, hipEventDisableTiming)) != hipSuccess ||
-      (e = hipEventCreateWithFlags(&b->ev_fork, hipEventDisableTiming)) != hipSuccess)
+      (e = hipEventCreateWithFlags(&b->ev_upload, hipEventDisableTiming)) != hipSuccess)
     return set_error(KK_EDEVICE, "stream/event: %s", hipGetErrorString(e));
   for (int g = 0; g < kMaxTileGroups; ++g)
-    if ((e = hipStreamCreateWithFlags(&b->tg_stream[g], hipStreamNonBlocking)) != hipSuccess ||
-        (e = hipEventCreateWithFlags(&b->tg_done[g], hipEventDisableTiming)) != hipSuccess)
+    if ((e = hipStreamCreateWithFlags(&b->tg_stream[g], hipStreamNonBlocking)) != hipSuccess)
       return set_error(KK_EDEVICE, "stream/event: %s", hipGetErrorString(e));
   return KK_OK;
 }
@@ -197,7 +175,7 @@ void batch_geometry(const kk_sim* h, bool resident, int max_tww, int max_th, int
 
 
 // Plan the current replica set: resident list, tile jobs split into groups of
-// equal work, device tables and one captured graph per group.
+// equal work, device tables.
 kk_status batch_plan(kk_batch* b) {
   clear_plan(b);
   const size_t n = b->sims.size();
@@ -262,9 +240,10 @@ kk_status batch_plan(kk_batch* b) {
   for (const BatchTileJob& j : jobs) b->job_rep.push_back(j.rep);
   kk_status st = KK_OK;
   if (st == KK_OK) st = device_alloc((void**)&b->d_params, n * sizeof(SweepParams));
-  if (st == KK_OK) st = device_alloc((void**)&b->d_ctl, 2 * sizeof(unsigned) * kCtlSlots);
   if (st == KK_OK) st = device_alloc((void**)&b->d_counts, b->ncounts * sizeof(unsigned long long));
   if (st == KK_OK && b->njobs) st = device_alloc((void**)&b->d_jobs, jobs.size() * sizeof(BatchTileJob));
+  if (st == KK_OK && b->njobs)
+    st = device_alloc((void**)&b->d_orders, (size_t)ngroups * n * kBatchChunk * sizeof(uint32_t));
   if (st == KK_OK && !b->resident.empty()) st = device_alloc((void**)&b->d_res, b->resident.size() * sizeof(int));
   if (st != KK_OK) return st;
   hipError_t e;
@@ -274,44 +253,6 @@ kk_status batch_plan(kk_batch* b) {
   if (!b->resident.empty() && (e = hipMemcpy(b->d_res, b->resident.data(), b->resident.size() * sizeof(int),
                                              hipMemcpyHostToDevice)) != hipSuccess)
     return set_error(KK_EDEVICE, "upload ids: %s", hipGetErrorString(e));
-  // one graph: fork from tile group 0's stream, a branch per tile group and
-  // per resident launch, join back
-  const size_t n_small = b->n_small, n_large = b->resident.size() - b->n_small;
-  hipStream_t origin = b->tg_stream[0];
-  if ((e = hipStreamBeginCapture(origin, hipStreamCaptureModeThreadLocal)) != hipSuccess)
-    return set_error(KK_EDEVICE, "capture: %s", hipGetErrorString(e));
-  std::vector<hipStream_t> branches;
-  for (int g = 1; g < ngroups; ++g) branches.push_back(b->tg_stream[g]);
-  if (n_small) branches.push_back(b->sC);
-  if (n_large) branches.push_back(b->sA);
-  e = hipEventRecord(b->ev_fork, origin);
-  for (hipStream_t bs : branches)
-    if (e == hipSuccess) e = hipStreamWaitEvent(bs, b->ev_fork, 0);
-  for (int g = 0; g < ngroups && e == hipSuccess; ++g) {
-    for (int r = 0; r < kBatchChunk && e == hipSuccess; ++r)
-      e = launch_batch_tiles(b->d_params, b->d_jobs + b->tg_off[g], b->tg_n[g], b->d_ctl + 2 * g, (unsigned)r,
-                             b->tile_ku, b->tg_stream[g]);
-    if (e == hipSuccess) e = launch_batch_advance(b->d_ctl + 2 * g, (unsigned)kBatchChunk, b->tg_stream[g]);
-  }
-  if (e == hipSuccess && n_small) {
-    e = launch_batch_resident(b->d_params, b->d_res, (int)n_small, b->small_lds, true, b->d_ctl + 2 * kCtlSmall, b->sC);
-    if (e == hipSuccess) e = launch_batch_advance(b->d_ctl + 2 * kCtlSmall, (unsigned)kBatchChunk, b->sC);
-  }
-  if (e == hipSuccess && n_large) {
-    e = launch_batch_resident(b->d_params, b->d_res + n_small, (int)n_large, b->res_lds, false,
-                              b->d_ctl + 2 * kCtlLarge, b->sA);
-    if (e == hipSuccess) e = launch_batch_advance(b->d_ctl + 2 * kCtlLarge, (unsigned)kBatchChunk, b->sA);
-  }
-  for (size_t i = 0; i < branches.size() && e == hipSuccess; ++i) {
-    e = hipEventRecord(b->tg_done[i % kMaxTileGroups], branches[i]);
-    if (e == hipSuccess) e = hipStreamWaitEvent(origin, b->tg_done[i % kMaxTileGroups], 0);
-  }
-  hipGraph_t graph = nullptr;
-  const hipError_t ee = hipStreamEndCapture(origin, &graph);  // always end the capture
-  if (e == hipSuccess) e = ee;
-  b->graph = graph;
-  if (e == hipSuccess) e = hipGraphInstantiate(&b->gexec, graph, nullptr, nullptr, 0);
-  if (e != hipSuccess) return set_error(KK_EDEVICE, "batch graph: %s", hipGetErrorString(e));
   return KK_OK;
 }
 
@@ -419,17 +360,42 @@ kk_status kk_batch_run(kk_batch* b) {
     if (h->stream != b->sB) KB_HIP(hipStreamSynchronize(h->stream));
   KB_HIP(hipMemcpyAsync(b->d_params, params.data(), n * sizeof(SweepParams), hipMemcpyHostToDevice, b->sB));
   KB_HIP(hipMemsetAsync(b->d_counts, 0, b->ncounts * sizeof(unsigned long long), b->sB));
-  KB_HIP(hipMemsetAsync(b->d_ctl, 0, 2 * sizeof(unsigned) * kCtlSlots, b->sB));
   KB_HIP(hipEventRecord(b->ev_upload, b->sB));
-  // replay the chunk graph until the longest replica is done
-  uint64_t mx = 0;
-  for (size_t i = 0; i < n; ++i) mx = std::max<uint64_t>(mx, nsw[i]);
-  hipStream_t origin = b->tg_stream[0];
-  KB_HIP(hipStreamWaitEvent(origin, b->ev_upload, 0));
-  for (uint64_t r = 0; r < (mx + kBatchChunk - 1) / kBatchChunk; ++r) KB_HIP(hipGraphLaunch(b->gexec, origin));
-  KB_HIP(hipEventRecord(b->ev_res, origin));
-  KB_HIP(hipStreamWaitEvent(b->sB, b->ev_res, 0));
-  KB_HIP(hipStreamSynchronize(origin));
+  // every stream starts after the upload; the resident launches first, then
+  // the tile groups' launches in turn, a sweep of each at a time
+  const size_t n_small = b->n_small, n_large = b->resident.size() - b->n_small;
+  uint64_t res_mx[2] = {0, 0}, tile_mx = 0;
+  for (size_t k = 0; k < b->resident.size(); ++k)
+    res_mx[k < n_small ? 0 : 1] = std::max(res_mx[k < n_small ? 0 : 1], nsw[b->resident[k]]);
+  std::vector<uint64_t> group_mx(b->tg_n.size(), 0);
+  for (size_t g = 0; g < b->tg_n.size(); ++g)
+    for (int j = b->tg_off[g]; j < b->tg_off[g] + b->tg_n[g]; ++j)
+      group_mx[g] = std::max(group_mx[g], nsw[b->job_rep[j]]);
+  for (size_t g = 0; g < group_mx.size(); ++g) {
+    KB_HIP(hipStreamWaitEvent(b->tg_stream[g], b->ev_upload, 0));
+    tile_mx = std::max(tile_mx, group_mx[g]);
+  }
+  KB_HIP(hipStreamWaitEvent(b->sC, b->ev_upload, 0));
+  KB_HIP(hipStreamWaitEvent(b->sA, b->ev_upload, 0));
+  for (uint64_t s = 0; s < std::max(res_mx[0], res_mx[1]); s += kBatchChunk) {
+    if (n_small && s < res_mx[0])
+      KB_HIP(launch_batch_resident(b->d_params, b->d_res, (int)n_small, b->small_lds, true, (unsigned)s, b->sC));
+    if (n_large && s < res_mx[1])
+      KB_HIP(launch_batch_resident(b->d_params, b->d_res + n_small, (int)n_large, b->res_lds, false, (unsigned)s,
+                                   b->sA));
+  }
+  for (uint64_t s = 0; s < tile_mx; ++s)
+    for (size_t g = 0; g < group_mx.size(); ++g)
+      if (s < group_mx[g]) {
+        uint32_t* orders = b->d_orders + g * n * kBatchChunk;
+        if (s % kBatchChunk == 0)
+          KB_HIP(launch_batch_orders(b->d_params, (int)n, (unsigned)s, orders, b->tg_stream[g]));
+        KB_HIP(launch_batch_tiles(b->d_params, b->d_jobs + b->tg_off[g], b->tg_n[g], orders, (unsigned)s, b->tile_ku,
+                                  b->tg_stream[g]));
+      }
+  for (size_t g = 0; g < group_mx.size(); ++g) KB_HIP(hipStreamSynchronize(b->tg_stream[g]));
+  KB_HIP(hipStreamSynchronize(b->sC));
+  KB_HIP(hipStreamSynchronize(b->sA));
   KB_HIP(hipStreamSynchronize(b->sB));
   std::vector<unsigned long long> counts(b->ncounts);
   KB_HIP(hipMemcpy(counts.data(), b->d_counts, b->ncounts * sizeof(unsigned long long), hipMemcpyDeviceToHost));

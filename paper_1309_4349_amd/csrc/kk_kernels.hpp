@@ -31,13 +31,10 @@ struct SweepParams {
 hipError_t launch_sweep(const SweepParams& p, int layout, bool cyclic, int ku, int threads, hipStream_t stream);
 
 // Batch kernels.  Tiled replicas: one workgroup per (replica, tile) job and one
-// launch per sweep; ctl[0] holds the run sweep at which the current chunk of a
-// captured graph starts, each tile launch adds its position `rel` in the chunk,
-// and launch_batch_advance (one thread, the last node of a branch) moves ctl[0]
-// on by the chunk, so the graph replays unchanged.  A replica runs p.nsweeps sweeps from
+// launch per sweep of the run.  A replica runs p.nsweeps sweeps from
 // p.t0, ping-ponging between p.src (its lattice at the start) and p.dst.  Resident replicas (L % 32 == 0,
-// 2 <= L/32 <= kResidentMaxC): one launch, one workgroup per replica running
-// all of its sweeps with the whole lattice in LDS.
+// 2 <= L/32 <= kResidentMaxC): one workgroup per replica with the whole lattice
+// in LDS, kBatchChunk sweeps per launch.
 constexpr int kBatchMaxTww = 16, kBatchTh = 128;
 // Tiled replicas run in 512-thread workgroups, ku (1 or 2) units per thread,
 // in tiles 8 or 16 words wide: a tile of tww words by th rows fits when its
@@ -51,17 +48,16 @@ constexpr bool batch_tile_fits(int tww, int th, int ku = 2) {
 struct BatchTileJob {
   int rep, tile;
 };
-hipError_t launch_batch_tiles(const SweepParams* reps, const BatchTileJob* jobs, int njobs, const unsigned* ctl,
-                              unsigned rel, int ku, hipStream_t stream);
-hipError_t launch_batch_advance(unsigned* ctl, unsigned step, hipStream_t stream);
+// Sweep s of the run; orders[rep * kBatchChunk + s % kBatchChunk] is replica
+// rep's class order of that sweep (launch_batch_orders, once per kBatchChunk sweeps).
+hipError_t launch_batch_tiles(const SweepParams* reps, const BatchTileJob* jobs, int njobs, const uint32_t* orders,
+                              unsigned s, int ku, hipStream_t stream);
+hipError_t launch_batch_orders(const SweepParams* reps, int nreps, unsigned s, uint32_t* orders, hipStream_t stream);
 // small: the 768-thread kernel for replicas of at most kResidentSmallMaxC words
-// per row.  A launch runs up to kBatchChunk sweeps from sweep ctl[0] of the run
-// (launch_batch_advance then moves ctl[0] on by kBatchChunk).
+// per row.  A launch runs up to kBatchChunk sweeps from sweep s of the run.
 hipError_t launch_batch_resident(const SweepParams* reps, const int* ids, int n, size_t lds_bytes, bool small,
-                                 const unsigned* ctl, hipStream_t stream);
-// Sweeps per replay of a batch graph: kBatchChunk tile launches per tile group
-// and one resident launch of kBatchChunk sweeps.
-constexpr int kBatchChunk = 64;
+                                 unsigned s, hipStream_t stream);
+constexpr int kBatchChunk = 256;
 constexpr int kResidentMaxC = 9;
 constexpr int kResidentSmallMaxC = 4, kResidentSmallThreads = 768, kResidentThreads = 1024;
 size_t batch_tile_lds_bytes();

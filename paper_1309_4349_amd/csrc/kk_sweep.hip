@@ -1278,14 +1278,14 @@ __global__ __launch_bounds__(Pipe<C>::kThreads) void pipe_kernel(SweepParams p) 
 // ---------------------------------------------------------------------------
 // Batch kernels
 // ---------------------------------------------------------------------------
-// Sweep hand-off of the batch kernels, which a captured graph replays: ctl[0]
-// holds the run sweep at which the current chunk of the graph starts; a tile
-// launch adds its own position in the chunk (a kernel argument), a resident
-// launch runs the whole chunk, and a one-thread kernel at the end of each
-// branch advances ctl[0] by the chunk for the next replay.  Stream order and
-// the kernel boundaries order every step, so no workgroup touches a shared
-// counter.
-__global__ void batch_advance_kernel(unsigned* ctl, unsigned step) { ctl[0] += step; }
+// The class orders of sweeps s .. s + kBatchChunk - 1 of every replica, one per
+// thread (replica = blockIdx.x): computed by every tile's workgroup they were
+// 150 instructions of each wave.
+__global__ __launch_bounds__(kBatchChunk) void batch_orders_kernel(const SweepParams* reps, unsigned s,
+                                                                   uint32_t* orders) {
+  const SweepParams& p = reps[blockIdx.x];
+  orders[(size_t)blockIdx.x * kBatchChunk + threadIdx.x] = class_order(p.k0, p.k1, p.t0 + s + threadIdx.x);
+}
 
 // KU = 2: tiles of up to 1024 units; KU = 1: up to 512 units, twice the
 // waves per unit, which hides more latency when small tiles spread a batch
@@ -1293,11 +1293,9 @@ __global__ void batch_advance_kernel(unsigned* ctl, unsigned step) { ctl[0] += s
 // Two workgroups per CU: four waves per SIMD, at most 128 VGPRs each.
 template <int KU>
 __global__ __launch_bounds__(kBatchTileThreads) __attribute__((amdgpu_waves_per_eu(4)))
-void batch_tile_kernel(const SweepParams* reps, const BatchTileJob* jobs, const unsigned* ctl, unsigned rel) {
+void batch_tile_kernel(const SweepParams* reps, const BatchTileJob* jobs, const uint32_t* orders, unsigned s) {
   extern __shared__ __attribute__((aligned(16))) uint32_t S[];
-  // the sweep index and the job are independent loads; the replica's
-  // parameters (sweep count and both buffers included) follow the job
-  const unsigned s = __hip_atomic_load(&ctl[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + rel;
+  // sweep s of the run
   const BatchTileJob job = jobs[blockIdx.x];
   SweepParams p = reps[job.rep];
   if (s < (unsigned)p.nsweeps) {
@@ -1310,7 +1308,7 @@ void batch_tile_kernel(const SweepParams* reps, const BatchTileJob* jobs, const 
     // compile-time tile width (8 or 16 words: immediate, bank-conflict-free
     // LDS offsets) chosen per replica by a uniform switch; a replica's last
     // tile column may be ragged
-    const uint32_t order = class_order(p.k0, p.k1, p.t0);
+    const uint32_t order = orders[(size_t)job.rep * kBatchChunk + s % kBatchChunk];
     unsigned count;
     if (p.layout == kLayoutBits) {
       if (p.tww == 8) count = halo_tile_sweep<kLayoutBits, 8, KU>(S, p, job.tile, order);
@@ -1340,9 +1338,8 @@ __device__ __forceinline__ bool resident_chunk(SweepParams& p, unsigned s) {
   return true;
 }
 __global__ __launch_bounds__(kResidentThreads) void batch_resident_all_kernel(const SweepParams* reps, const int* ids,
-                                                                              const unsigned* ctl) {
+                                                                              unsigned s) {
   extern __shared__ __attribute__((aligned(16))) uint32_t S[];
-  const unsigned s = __hip_atomic_load(&ctl[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   SweepParams p = reps[ids[blockIdx.x]];
   if (!resident_chunk(p, s)) return;
   switch (p.C) {
@@ -1354,10 +1351,8 @@ __global__ __launch_bounds__(kResidentThreads) void batch_resident_all_kernel(co
   }
 }
 __global__ __launch_bounds__(kResidentSmallThreads) void batch_resident_small_kernel(const SweepParams* reps,
-                                                                                     const int* ids,
-                                                                                     const unsigned* ctl) {
+                                                                                     const int* ids, unsigned s) {
   extern __shared__ __attribute__((aligned(16))) uint32_t S[];
-  const unsigned s = __hip_atomic_load(&ctl[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   SweepParams p = reps[ids[blockIdx.x]];
   if (!resident_chunk(p, s)) return;
   switch (p.C) {
@@ -1460,29 +1455,29 @@ size_t batch_resident_lds_bytes(int L) {
   return (size_t)words[L / 32 - 2] * sizeof(uint32_t);
 }
 
-hipError_t launch_batch_tiles(const SweepParams* reps, const BatchTileJob* jobs, int njobs, const unsigned* ctl,
-                              unsigned rel, int ku, hipStream_t stream) {
+hipError_t launch_batch_tiles(const SweepParams* reps, const BatchTileJob* jobs, int njobs,
+                              const uint32_t* orders, unsigned s, int ku, hipStream_t stream) {
   if (ku == 1)
     hipLaunchKernelGGL(batch_tile_kernel<1>, dim3(njobs), dim3(kBatchTileThreads), batch_tile_lds_bytes(), stream,
-                       reps, jobs, ctl, rel);
+                       reps, jobs, orders, s);
   else
     hipLaunchKernelGGL(batch_tile_kernel<2>, dim3(njobs), dim3(kBatchTileThreads), batch_tile_lds_bytes(), stream,
-                       reps, jobs, ctl, rel);
+                       reps, jobs, orders, s);
   return hipGetLastError();
 }
 
-hipError_t launch_batch_advance(unsigned* ctl, unsigned step, hipStream_t stream) {
-  hipLaunchKernelGGL(batch_advance_kernel, dim3(1), dim3(1), 0, stream, ctl, step);
+hipError_t launch_batch_orders(const SweepParams* reps, int nreps, unsigned s, uint32_t* orders, hipStream_t stream) {
+  hipLaunchKernelGGL(batch_orders_kernel, dim3(nreps), dim3(kBatchChunk), 0, stream, reps, s, orders);
   return hipGetLastError();
 }
 
 hipError_t launch_batch_resident(const SweepParams* reps, const int* ids, int n, size_t lds_bytes, bool small,
-                                 const unsigned* ctl, hipStream_t stream) {
+                                 unsigned s, hipStream_t stream) {
   if (small)
     hipLaunchKernelGGL(batch_resident_small_kernel, dim3(n), dim3(kResidentSmallThreads), lds_bytes, stream, reps,
-                       ids, ctl);
+                       ids, s);
   else
-    hipLaunchKernelGGL(batch_resident_all_kernel, dim3(n), dim3(kResidentThreads), lds_bytes, stream, reps, ids, ctl);
+    hipLaunchKernelGGL(batch_resident_all_kernel, dim3(n), dim3(kResidentThreads), lds_bytes, stream, reps, ids, s);
   return hipGetLastError();
 }
 
