@@ -179,6 +179,7 @@ void free_all(kk_sim* h) {
   if (h->partials) (void)hipFree(h->partials);
   if (h->ccl.parent) (void)hipFree(h->ccl.parent);
   if (h->ccl.size) (void)hipFree(h->ccl.size);
+  if (h->ccl.border) (void)hipFree(h->ccl.border);
   if (h->ccl.hist) (void)hipFree(h->ccl.hist);  // also holds big_count and big
   if (h->hist_host) (void)hipHostFree(h->hist_host);
   if (h->own_stream && h->stream) (void)hipStreamDestroy(h->stream);
@@ -861,15 +862,18 @@ kk_status kk_energy(kk_sim* h, uint64_t* n_unlike, double* energy_kT) {
 namespace kk {
 
 // Labelling buffers of a handle, made on its first histogram: parent and size
-// (N words each), then one block holding the small-size histogram, the count
-// of large sizes and their list, so that one copy brings back the histogram,
-// the count and the first kHistBigPrefix large sizes; its pinned host image.
+// of the tiles' clusters, the labels along the tiles' edges, then one block
+// holding the small-size histogram, the count of large sizes and their list, so
+// that one copy brings back the histogram, the count and the first
+// kHistBigPrefix large sizes; its pinned host image.
 kk_status hist_buffers(kk_sim* h) {
   if (h->ccl_ready) return KK_OK;
   const size_t N = (size_t)h->L * h->H;
   const unsigned big_cap = (unsigned)(N / kSmallSizes + 1);
-  kk_status st = dmalloc(h, (void**)&h->ccl.parent, N * 4);
-  if (st == KK_OK) st = dmalloc(h, (void**)&h->ccl.size, N * 4);
+  const size_t clusters = ccl_cluster_words(h->L, h->H), border = ccl_border_words(h->L, h->H);
+  kk_status st = dmalloc(h, (void**)&h->ccl.parent, clusters * 4);
+  if (st == KK_OK) st = dmalloc(h, (void**)&h->ccl.size, clusters * 4);
+  if (st == KK_OK) st = dmalloc(h, (void**)&h->ccl.border, border * 4);
   if (st == KK_OK) st = dmalloc(h, (void**)&h->ccl.hist, ((size_t)kSmallSizes + 1 + big_cap) * 4);
   if (st == KK_OK && !h->hist_host) {
     const hipError_t e = hipHostMalloc((void**)&h->hist_host, ((size_t)kSmallSizes + 1 + kHistBigPrefix) * 4,
@@ -881,6 +885,7 @@ kk_status hist_buffers(kk_sim* h) {
     }
   }
   if (st != KK_OK) return st;
+  h->ccl.ncl = h->ccl.border + ccl_tiles(h->L, h->H) * 256;
   h->ccl.big_count = h->ccl.hist + kSmallSizes;
   h->ccl.big = h->ccl.hist + kSmallSizes + 1;
   h->ccl.big_cap = big_cap;

@@ -1,5 +1,7 @@
 // kk_aux.hip -- initial placement, energy, cluster labelling and layout
 // conversion kernels of libkk.
+#include <algorithm>
+
 #include "kk_common.hpp"
 #include "kk_kernels.hpp"
 #include "kk_ccl.hpp"
@@ -9,8 +11,6 @@ namespace kk {
 namespace {
 
 constexpr uint32_t kNone = 0xFFFFFFFFu;
-// workgroups per replica in a many-lattice labelling pass (grid-stride beyond)
-constexpr int kCclManyBlocks = 512;
 
 __device__ __forceinline__ int site_bit(const void* lat, int layout, int L, int x, int y) {
   if (layout == kLayoutBits)
@@ -18,14 +18,33 @@ __device__ __forceinline__ int site_bit(const void* lat, int layout, int L, int 
   return (int)(static_cast<const uint8_t*>(lat)[(size_t)y * L + x] & 1u);
 }
 
+// Sum of a per-thread value over the workgroup (256 threads), added to *out by
+// one atomic.  Atomics on one address run about 12 ns each, one after another:
+// with one per wavefront of 4096 workgroups they were all of the time of the
+// passes below (energy of an int8 lattice 1036^2 200 us, of a 4092^2 triangular
+// ring 400 us; now under 10 and 21 us).
+__device__ __forceinline__ void add_block_sum(unsigned v, unsigned long long* out) {
+  __shared__ unsigned long long part[4];
+  unsigned long long acc = v;
+  for (int off = 32; off > 0; off >>= 1) acc += __shfl_down(acc, off, 64);
+  if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = acc;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    const unsigned long long tot = part[0] + part[1] + part[2] + part[3];
+    if (tot) atomicAdd(out, tot);
+  }
+}
+constexpr int kSumBlocks = 512;  // workgroups of a summing pass (each thread strides)
+
 // ---------------------------------------------------------------------------
 // Energy: N_AB = sum over sites of [s(x,y) != s(x+1,y)] + [s(x,y) != s(x,y+1)]
-// (the Almeida one-parameter model, E/kT = omega * N_AB + const).
+// (the Almeida one-parameter model, E/kT = omega * N_AB + const).  A thread's
+// count stays below 2^32: at most 2 bonds of 2^30 sites over 2^17 threads.
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(256) void energy_bits(const uint32_t* lat, int L, unsigned long long* out) {
   const int wpr = L >> 5;
   const size_t nw = (size_t)L * wpr;
-  unsigned long long acc = 0;
+  unsigned acc = 0;
   for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < nw; i += (size_t)gridDim.x * blockDim.x) {
     const int y = (int)(i / wpr), g = (int)(i - (size_t)y * wpr);
     const uint32_t v = lat[i];
@@ -34,21 +53,24 @@ __global__ __launch_bounds__(256) void energy_bits(const uint32_t* lat, int L, u
     const uint32_t below = lat[(size_t)(y + 1 == L ? 0 : y + 1) * wpr + g];
     acc += (unsigned)__builtin_popcount(v ^ east) + (unsigned)__builtin_popcount(v ^ below);
   }
-  for (int off = 32; off > 0; off >>= 1) acc += __shfl_down(acc, off, 64);
-  if ((threadIdx.x & 63) == 0 && acc) atomicAdd(out, acc);
+  add_block_sum(acc, out);
 }
 
+// Four sites (one per byte) at a time: L is a multiple of 4.
 __global__ __launch_bounds__(256) void energy_int8(const uint8_t* lat, int L, unsigned long long* out) {
-  const size_t n = (size_t)L * L;
-  unsigned long long acc = 0;
-  for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) {
-    const int y = (int)(i / L), x = (int)(i - (size_t)y * L);
-    const uint8_t v = lat[i];
-    acc += (v != lat[(size_t)y * L + (x + 1 == L ? 0 : x + 1)]);
-    acc += (v != lat[(size_t)(y + 1 == L ? 0 : y + 1) * L + x]);
+  const uint32_t* w = reinterpret_cast<const uint32_t*>(lat);
+  const int wpr = L >> 2;
+  const size_t nw = (size_t)L * wpr;
+  unsigned acc = 0;
+  for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < nw; i += (size_t)gridDim.x * blockDim.x) {
+    const int y = (int)(i / wpr), g = (int)(i - (size_t)y * wpr);
+    const uint32_t v = w[i];
+    const uint32_t nxt = w[(size_t)y * wpr + (g + 1 == wpr ? 0 : g + 1)];
+    const uint32_t below = w[(size_t)(y + 1 == L ? 0 : y + 1) * wpr + g];
+    acc += (unsigned)__builtin_popcount(v ^ __builtin_amdgcn_alignbit(nxt, v, 8)) +
+           (unsigned)__builtin_popcount(v ^ below);
   }
-  for (int off = 32; off > 0; off >>= 1) acc += __shfl_down(acc, off, 64);
-  if ((threadIdx.x & 63) == 0 && acc) atomicAdd(out, acc);
+  add_block_sum(acc, out);
 }
 
 // Random-neighbour estimate of the similar first-neighbour fraction: every
@@ -60,7 +82,7 @@ __global__ __launch_bounds__(256) void similar_sampled(const void* lat, int layo
   const int g4 = L >> 2;
   const size_t n = (size_t)L * g4;
   const uint32_t tl = (uint32_t)t, th = ctr_hi(t, kTagObserve);
-  unsigned long long acc = 0;
+  unsigned acc = 0;
   for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) {
     const int y = (int)(i / g4), q = (int)(i - (size_t)y * g4);
     const Philox4 r = philox10((uint32_t)y, (uint32_t)q, tl, th, k0, k1);
@@ -77,8 +99,7 @@ __global__ __launch_bounds__(256) void similar_sampled(const void* lat, int layo
       acc += (site_bit(lat, layout, L, x, y) == site_bit(lat, layout, L, nx, ny));
     }
   }
-  for (int off = 32; off > 0; off >>= 1) acc += __shfl_down(acc, off, 64);
-  if ((threadIdx.x & 63) == 0 && acc) atomicAdd(out, acc);
+  add_block_sum(acc, out);
 }
 
 // ---------------------------------------------------------------------------
@@ -152,13 +173,46 @@ __global__ void set_sites(const uint32_t* idx, unsigned n, int L, int layout, vo
   (void)L;
 }
 
+// Segregated start: the first n1 sites in index order i = y*L + x hold type 1
+// (full rows 0 .. n1/L - 1 and the start of the next one).  Bit-packed words
+// tile rows exactly, so word w holds sites 32w .. 32w + 31.
+__global__ __launch_bounds__(256) void fill_segregated(void* lat, int layout, int L, int H, uint64_t n1) {
+  const size_t n = (size_t)L * H;
+  if (layout == kLayoutBits) {
+    uint32_t* w = static_cast<uint32_t*>(lat);
+    for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < n / 32; i += (size_t)gridDim.x * blockDim.x) {
+      const uint64_t lo = 32 * (uint64_t)i;
+      w[i] = n1 >= lo + 32 ? 0xFFFFFFFFu : (n1 <= lo ? 0u : ((1u << (uint32_t)(n1 - lo)) - 1u));
+    }
+  } else {
+    uint8_t* b = static_cast<uint8_t*>(lat);
+    for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x)
+      b[i] = (uint64_t)i < n1 ? 1 : 0;
+  }
+}
+
 // ---------------------------------------------------------------------------
-// Cluster labelling: lock-free union-find with atomicMin on parent links
-// (parents always point to smaller indices, so no cycle can form), then
-// path flattening, per-root site counts and a size histogram.  Small sizes
-// go to a dense histogram through a per-block LDS copy; the few sizes of
-// kSmallSizes or more are appended to a list.
+// Cluster sizes.  The lattice is cut into tiles of 64 x 64 sites.
+//  1. ccl_tile labels each tile by itself in LDS (union-find over the runs of
+//     each row, found as bits of the row's 64-site mask) and writes its
+//     clusters compactly -- id = (sites of the tiles before) / 2 + k, as a tile
+//     holds at most half as many clusters as sites -- with their sizes, and the
+//     ids of the sites along its four edges.
+//  2. ccl_border unites the clusters across the tiles' edges (lock-free
+//     union-find over the ids: atomicMin links toward smaller ids, so no cycle
+//     can form, and path halving).
+//  3. ccl_sizes adds every cluster's size to its root's.
+//  4. ccl_hist counts the roots by size: small sizes through a dense histogram
+//     per workgroup in LDS, the few of kSmallSizes or more as a list.
+// Only the lattice is read per site; all else is per cluster and per edge site.
+// The per-site labelling before (parent and size words for every site, four
+// passes over them, dependent reads of global memory) took 1.7 ms at 4096^2 and
+// 4.1 ms on a 4092^2 triangular ring; now 0.17 and 0.29 ms, of which the first
+// pass 0.12 and 0.15 (bound by the chains of dependent LDS reads of a tile's
+// unions: 4 tiles per CU hold its 160 KB).
 // ---------------------------------------------------------------------------
+constexpr int kTile = 64;
+
 __device__ __forceinline__ uint32_t ld_parent(const uint32_t* parent, uint32_t x) {
   return __hip_atomic_load(&parent[x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
@@ -193,184 +247,277 @@ __device__ void unite(uint32_t* parent, uint32_t a, uint32_t b) {
   }
 }
 
-// With `runs` (the square torus), a site of the species starts linked
-// straight to the first site of its run: the longest stretch of sites of the
-// species that ends at it, lies in one row and in its 64-site segment (sites
-// 64k .. 64k + 63, one wavefront of the pass: two ballots find it).  The
-// merge pass then needs a horizontal union only at segment ends and across
-// the row's wrap, and the trees it starts from are one level deep.  Without
-// it every site of the species starts as its own root.  Also clears what the
-// later passes accumulate into: the cluster sizes, the small-size histogram
-// and the count of large sizes.
-__device__ __forceinline__ void ccl_init_body(const void* lat, int layout, int L, int H, int species, bool runs,
-                                              uint32_t* parent, uint32_t* size, unsigned* hist, unsigned* big_count) {
-  const size_t n = (size_t)L * H;
-  const size_t tid = blockIdx.x * (size_t)blockDim.x + threadIdx.x, nth = (size_t)gridDim.x * blockDim.x;
-  // the stride is a whole number of wavefronts, so lane l of a wavefront
-  // always holds a site i with i % 64 == l, and the lanes past n are the top ones
-  for (size_t i = tid; i < n; i += nth) {
-    const int y = (int)(i / L), x = (int)(i - (size_t)y * L);
-    const bool me = site_bit(lat, layout, L, x, y) == species;
-    uint32_t pi = me ? (uint32_t)i : kNone;
-    if (runs) {
-      const uint64_t other = __ballot(!me), row0 = __ballot(me && x == 0);
-      const uint32_t lane = (uint32_t)(i & 63u);
-      const uint64_t upto = (2ull << lane) - 1ull;  // lanes 0 .. lane
-      const uint64_t bo = other & upto, bz = row0 & upto;
-      // one past the last lane of another species, and the last row start
-      const uint32_t so = bo ? 64u - (uint32_t)__clzll((long long)bo) : 0u;
-      const uint32_t sz = bz ? 63u - (uint32_t)__clzll((long long)bz) : 0u;
-      if (me) pi = (uint32_t)i - (lane - max(so, sz));
-    }
-    parent[i] = pi;
-    size[i] = 0u;
+// The same within a workgroup, on LDS.
+__device__ __forceinline__ uint32_t lds_root(volatile uint32_t* par, uint32_t x) {
+  uint32_t p = par[x];
+  while (p != x) {
+    x = p;
+    p = par[x];
   }
-  for (size_t i = tid; i < (size_t)kSmallSizes; i += nth) hist[i] = 0u;
-  if (tid == 0) *big_count = 0u;
+  return x;
+}
+__device__ __forceinline__ void lds_unite(uint32_t* par, uint32_t a, uint32_t b) {
+  for (;;) {
+    a = lds_root(par, a);
+    b = lds_root(par, b);
+    if (a == b) return;
+    const uint32_t hi = max(a, b), lo = min(a, b);
+    const uint32_t old = atomicMin(&par[hi], lo);
+    if (old == hi) return;
+    a = lo;
+    b = old;
+  }
 }
 
-__device__ __forceinline__ void ccl_merge_body(const void* lat, int layout, int L, int species, uint32_t* parent) {
-  const size_t n = (size_t)L * L;
+// First site of the run of mask m that holds bit x.
+__device__ __forceinline__ uint32_t run_start(uint64_t m, uint32_t x) {
+  const uint64_t gap = ~m & ((1ull << x) - 1ull);
+  return gap ? 64u - (uint32_t)__clzll((long long)gap) : 0u;
+}
+
+struct CclShape {
+  const void* lat;
+  int layout, L, H;
+};
+
+struct CclTile {
+  int tx, ty, x0, y0, w, h;
+  uint32_t base;  // id of its first cluster
+};
+__device__ __forceinline__ CclTile ccl_place(const CclShape& g, int tile) {
+  const int ntx = (g.L + kTile - 1) / kTile;
+  CclTile t;
+  t.ty = tile / ntx;
+  t.tx = tile - t.ty * ntx;
+  t.x0 = t.tx * kTile;
+  t.y0 = t.ty * kTile;
+  t.w = min(kTile, g.L - t.x0);
+  t.h = min(kTile, g.H - t.y0);
+  t.base = ((uint32_t)t.y0 * (uint32_t)g.L + (uint32_t)t.x0 * (uint32_t)t.h) / 2u;  // both products are even
+  return t;
+}
+
+// One workgroup of 256 threads per tile (strided over the grid).
+template <bool TRI>
+__device__ __forceinline__ void ccl_tile_body(const CclShape& g, int species, const CclBuffers& b) {
+  __shared__ uint64_t rows[kTile];
+  __shared__ uint32_t par[kTile * kTile], cnt[kTile * kTile];
+  __shared__ uint32_t nroot;
+  const int tid = (int)threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const size_t gt = blockIdx.x * (size_t)blockDim.x + threadIdx.x, nth = (size_t)gridDim.x * blockDim.x;
+  for (size_t i = gt; i < (size_t)kSmallSizes; i += nth) b.hist[i] = 0u;
+  if (gt == 0) *b.big_count = 0u;
+  const int ntx = (g.L + kTile - 1) / kTile, nty = (g.H + kTile - 1) / kTile;
+  for (int tile = (int)blockIdx.x; tile < ntx * nty; tile += (int)gridDim.x) {
+    const CclTile t = ccl_place(g, tile);
+    const int x0 = t.x0, y0 = t.y0, w = t.w, h = t.h;
+    if (tid == 0) nroot = 0u;
+    for (int r = wave; r < kTile; r += 4) {
+      const bool me = r < h && lane < w && site_bit(g.lat, g.layout, g.L, x0 + lane, y0 + r) == species;
+      const uint64_t m = __ballot(me);
+      if (lane == 0) rows[r] = m;
+      par[r * kTile + lane] = (uint32_t)(r * kTile + lane);
+      cnt[r * kTile + lane] = 0u;
+    }
+    __syncthreads();
+    // bonds to the row above, one union per stretch of them
+    for (int r = wave == 0 ? 4 : wave; r < h; r += 4) {
+      const uint64_t m = rows[r], mp = rows[r - 1];
+      const uint64_t o = m & mp, os = o & ~(o << 1);
+      if ((os >> lane) & 1ull)
+        lds_unite(par, (uint32_t)(r * kTile) + run_start(m, (uint32_t)lane),
+                  (uint32_t)((r - 1) * kTile) + run_start(mp, (uint32_t)lane));
+      if constexpr (TRI) {  // (r, x) and (r - 1, x + 1)
+        const uint64_t d = m & (mp >> 1), ds = d & ~(d << 1);
+        if ((ds >> lane) & 1ull)
+          lds_unite(par, (uint32_t)(r * kTile) + run_start(m, (uint32_t)lane),
+                    (uint32_t)((r - 1) * kTile) + run_start(mp, (uint32_t)lane + 1u));
+      }
+    }
+    __syncthreads();
+    // run starts: link to the root, add the run's length to it
+    for (int r = wave; r < h; r += 4) {
+      const uint64_t m = rows[r], st = m & ~(m << 1);
+      if ((st >> lane) & 1ull) {
+        const uint64_t run = ~(m >> lane);
+        const uint32_t len = run ? (uint32_t)__ffsll((unsigned long long)run) - 1u : 64u;
+        const uint32_t me = (uint32_t)(r * kTile + lane), root = lds_root(par, me);
+        if (root != me) par[me] = root;
+        atomicAdd(&cnt[root], len);
+      }
+    }
+    __syncthreads();
+    // the tile's clusters, numbered; cnt becomes the number of each root
+    const uint32_t base = t.base;
+    for (int r = wave; r < h; r += 4) {
+      const uint64_t m = rows[r], st = m & ~(m << 1);
+      const uint32_t me = (uint32_t)(r * kTile + lane);
+      if (((st >> lane) & 1ull) && par[me] == me) {
+        const uint32_t k = atomicAdd(&nroot, 1u);
+        b.parent[base + k] = base + k;
+        b.size[base + k] = cnt[me];
+        cnt[me] = k;
+      }
+    }
+    __syncthreads();
+    {  // edges: top, bottom, left, right
+      const int edge = wave;
+      const int er = edge == 0 ? 0 : (edge == 1 ? h - 1 : lane), ec = edge == 2 ? 0 : (edge == 3 ? w - 1 : lane);
+      uint32_t id = kNone;
+      if (er < h && ec < w) {
+        const uint64_t m = rows[er];
+        if ((m >> ec) & 1ull) id = base + cnt[par[(uint32_t)(er * kTile) + run_start(m, (uint32_t)ec)]];
+      }
+      b.border[(size_t)tile * 256 + tid] = id;
+    }
+    if (tid == 0) b.ncl[tile] = nroot;
+    __syncthreads();
+  }
+}
+
+// Unions across the tiles' edges, one thread per tile and edge site.  Square
+// torus: the bonds to the right of the right column and below the bottom row,
+// one per stretch.  Triangular ring (i + 1, i + L, i + L - 1): those of the
+// right column, the bottom row and, for i + L - 1, the left column.
+template <bool TRI>
+__device__ __forceinline__ void ccl_border_body(const CclShape& g, const CclBuffers& b) {
+  const int L = g.L, H = g.H, ntx = (L + kTile - 1) / kTile, nty = (H + kTile - 1) / kTile;
+  const uint32_t* top = b.border;
+  const uint32_t* bottom = b.border + 64;
+  const uint32_t* left = b.border + 128;
+  const uint32_t* right = b.border + 192;
+  constexpr int E = TRI ? 3 : 2;
+  const size_t n = (size_t)ntx * nty * (64 * E);
   for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) {
-    const int y = (int)(i / L), x = (int)(i - (size_t)y * L);
-    if (site_bit(lat, layout, L, x, y) != species) continue;
-    const int xr = (x + 1 == L) ? 0 : x + 1, yd = (y + 1 == L) ? 0 : y + 1;
-    // within a row and a 64-site segment the bond to the right is already a
-    // link of the initial runs
-    if ((xr == 0 || (i & 63u) == 63u) && site_bit(lat, layout, L, xr, y) == species)
-      unite(parent, (uint32_t)i, (uint32_t)((size_t)y * L + xr));
-    if (site_bit(lat, layout, L, x, yd) == species) unite(parent, (uint32_t)i, (uint32_t)((size_t)yd * L + x));
-  }
-}
-
-// Segregated start: the first n1 sites in index order i = y*L + x hold type 1
-// (full rows 0 .. n1/L - 1 and the start of the next one).  Bit-packed words
-// tile rows exactly, so word w holds sites 32w .. 32w + 31.
-__global__ __launch_bounds__(256) void fill_segregated(void* lat, int layout, int L, int H, uint64_t n1) {
-  const size_t n = (size_t)L * H;
-  if (layout == kLayoutBits) {
-    uint32_t* w = static_cast<uint32_t*>(lat);
-    for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < n / 32; i += (size_t)gridDim.x * blockDim.x) {
-      const uint64_t lo = 32 * (uint64_t)i;
-      w[i] = n1 >= lo + 32 ? 0xFFFFFFFFu : (n1 <= lo ? 0u : ((1u << (uint32_t)(n1 - lo)) - 1u));
-    }
-  } else {
-    uint8_t* b = static_cast<uint8_t*>(lat);
-    for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x)
-      b[i] = (uint64_t)i < n1 ? 1 : 0;
-  }
-}
-
-// Triangular lattice, helical boundaries (H rows of L sites, i = y*L + x on one ring of N = L*H):
-// unite i with i+1, i+L and i+L-1 (mod N) when both are of the species; the
-// other three of the six bonds are forward bonds of the neighbours.
-__global__ __launch_bounds__(256) void ccl_merge_tri(const uint8_t* lat, int L, int H, int species, uint32_t* parent) {
-  const uint32_t N = (uint32_t)L * (uint32_t)H;
-  const uint32_t off[3] = {1u, (uint32_t)L, (uint32_t)L - 1u};
-  for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < N; i += gridDim.x * blockDim.x) {
-    if (lat[i] != species) continue;
-#pragma unroll
-    for (int k = 0; k < 3; ++k) {
-      uint32_t j = i + off[k];
-      if (j >= N) j -= N;
-      if (lat[j] == species) unite(parent, i, j);
+    const int tile = (int)(i / (64 * E)), k = (int)(i - (size_t)tile * (64 * E));
+    const int edge = k >> 6, pos = k & 63;
+    const CclTile t = ccl_place(g, tile);
+    const int tx = t.tx, ty = t.ty, y0 = t.y0, w = t.w, h = t.h;
+    auto at = [&](const uint32_t* e, int ttx, int tty, int p) { return e[((size_t)tty * ntx + ttx) * 256 + p]; };
+    auto link = [&](uint32_t a, uint32_t c) {
+      if (a != kNone && c != kNone) unite(b.parent, a, c);
+    };
+    if (edge == 0) {  // right column, row pos: the site to the right
+      if (pos >= h) continue;
+      const uint32_t a = at(right, tx, ty, pos);
+      if (TRI && tx == ntx - 1) {  // the ring goes on in the next row
+        const int y = y0 + pos + 1 == H ? 0 : y0 + pos + 1;
+        link(a, at(left, 0, y / kTile, y % kTile));
+      } else {
+        const int nx = tx + 1 == ntx ? 0 : tx + 1;
+        const uint32_t c = at(left, nx, ty, pos);
+        if (a == kNone || c == kNone) continue;
+        if (pos > 0 && at(right, tx, ty, pos - 1) != kNone && at(left, nx, ty, pos - 1) != kNone) continue;
+        unite(b.parent, a, c);
+      }
+    } else if (edge == 1) {  // bottom row, column pos: the sites below
+      if (pos >= w) continue;
+      const int ny = ty + 1 == nty ? 0 : ty + 1;
+      const uint32_t a = at(bottom, tx, ty, pos), c = at(top, tx, ny, pos);
+      if (a == kNone) continue;
+      const bool stretch = pos > 0 && c != kNone && at(bottom, tx, ty, pos - 1) != kNone &&
+                           at(top, tx, ny, pos - 1) != kNone;
+      if (c != kNone && !stretch) unite(b.parent, a, c);
+      if (TRI && pos > 0 && !(c != kNone && at(top, tx, ny, pos - 1) != kNone)) link(a, at(top, tx, ny, pos - 1));
+    } else {  // left column, row pos: i + L - 1
+      if (pos >= h) continue;
+      const uint32_t a = at(left, tx, ty, pos);
+      if (tx == 0) link(a, at(right, ntx - 1, ty, pos));
+      else {
+        const int y = y0 + pos + 1 == H ? 0 : y0 + pos + 1;
+        link(a, at(right, tx - 1, y / kTile, y % kTile));
+      }
     }
   }
 }
 
-// After all unions: point every site straight at its root.
-__device__ __forceinline__ void ccl_flatten_body(uint32_t* parent, int L, int H) {
-  const size_t n = (size_t)L * H;
-  for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) {
-    if (ld_parent(parent, (uint32_t)i) == kNone) continue;
-    const uint32_t r = find_root_halving(parent, (uint32_t)i);
-    atomicMin(&parent[i], r);
-  }
-}
-
-// Cluster sizes (parents flattened): one add per site onto its root, aggregated over the
-// wavefront first (lanes with the same root add once, by their lowest lane),
-// so a spanning cluster costs one atomic per wave instead of one per site.
-__device__ __forceinline__ void ccl_count_body(uint32_t* parent, int L, int H, uint32_t* size) {
-  const size_t n = (size_t)L * H;
-  const size_t stride = (size_t)gridDim.x * blockDim.x;
-  const int lane = (int)__lane_id();
-  // the loop bound is uniform over the block, so every lane joins every ballot
-  for (size_t base = (size_t)blockIdx.x * blockDim.x; base < n; base += stride) {
-    const size_t i = base + threadIdx.x;
-    bool todo = i < n && parent[i] != kNone;
-    const uint32_t r = todo ? parent[i] : 0u;
-    uint64_t left = __ballot(todo);
-    while (left) {
-      const int leader = __builtin_ctzll(left);
-      const uint32_t rl = __shfl(r, leader);
-      const uint64_t same = __ballot(todo && r == rl);
-      if (lane == leader) atomicAdd(&size[rl], (unsigned)__popcll(same));
-      if (todo && r == rl) todo = false;
-      left &= ~same;
+// Every cluster's size onto its root's.  Most of a tile's additions go to one
+// root (the largest cluster, whose id is among the smallest): those are summed
+// in LDS first, one atomic per tile.
+__device__ __forceinline__ void ccl_sizes_body(const CclShape& g, const CclBuffers& b) {
+  __shared__ uint32_t main_root, main_sum;
+  const int ntiles = ((g.L + kTile - 1) / kTile) * ((g.H + kTile - 1) / kTile);
+  for (int tile = (int)blockIdx.x; tile < ntiles; tile += (int)gridDim.x) {
+    const uint32_t n = b.ncl[tile], base = ccl_place(g, tile).base;
+    if (threadIdx.x == 0) {
+      main_root = kNone;
+      main_sum = 0u;
     }
+    __syncthreads();
+    for (uint32_t k0 = 0; k0 < n; k0 += blockDim.x) {
+      const uint32_t k = k0 + threadIdx.x;
+      uint32_t r = kNone;
+      if (k < n) {
+        r = find_root_halving(b.parent, base + k);
+        if (r == base + k) r = kNone;
+      }
+      if (r != kNone && k0 == 0) atomicMin(&main_root, r);
+      __syncthreads();
+      if (r != kNone) {
+        const uint32_t s = b.size[base + k];  // a cluster that is no root keeps its own size
+        if (r == main_root) atomicAdd(&main_sum, s);
+        else atomicAdd(&b.size[r], s);
+      }
+    }
+    __syncthreads();
+    if (threadIdx.x == 0 && main_sum) atomicAdd(&b.size[main_root], main_sum);
+    __syncthreads();
   }
 }
 
-__device__ __forceinline__ void ccl_hist_body(const uint32_t* size, int L, int H, unsigned* hist, uint32_t* big,
-                                              unsigned* big_count, unsigned big_cap, unsigned* h) {
+__device__ __forceinline__ void ccl_hist_body(const CclShape& g, const CclBuffers& b, unsigned* h) {
   for (int k = threadIdx.x; k < kSmallSizes; k += blockDim.x) h[k] = 0;
   __syncthreads();
-  const size_t n = (size_t)L * H;
-  for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) {
-    const uint32_t s = size[i];
-    if (s == 0) continue;
-    if (s < (uint32_t)kSmallSizes) atomicAdd(&h[s], 1u);
-    else {
-      const unsigned slot = atomicAdd(big_count, 1u);
-      if (slot < big_cap) big[slot] = s;
+  const int ntiles = ((g.L + kTile - 1) / kTile) * ((g.H + kTile - 1) / kTile);
+  for (int tile = (int)blockIdx.x; tile < ntiles; tile += (int)gridDim.x) {
+    const uint32_t n = b.ncl[tile], base = ccl_place(g, tile).base;
+    for (uint32_t k = threadIdx.x; k < n; k += blockDim.x) {
+      if (b.parent[base + k] != base + k) continue;
+      const uint32_t s = b.size[base + k];
+      if (s < (uint32_t)kSmallSizes) atomicAdd(&h[s], 1u);
+      else {
+        const unsigned slot = atomicAdd(b.big_count, 1u);
+        if (slot < b.big_cap) b.big[slot] = s;
+      }
     }
   }
   __syncthreads();
   for (int k = threadIdx.x; k < kSmallSizes; k += blockDim.x)
-    if (h[k]) atomicAdd(&hist[k], h[k]);
+    if (h[k]) atomicAdd(&b.hist[k], h[k]);
 }
 
-// The passes as kernels for one lattice (grid-stride over blockIdx.x), and
-// for many square lattices at once: replica blockIdx.y of a table, each with
-// its own buffers, the same grid-stride over blockIdx.x.
-__global__ __launch_bounds__(256) void ccl_init(const void* lat, int layout, int L, int H, int species, int runs,
-                                                uint32_t* parent, uint32_t* size, unsigned* hist,
-                                                unsigned* big_count) {
-  ccl_init_body(lat, layout, L, H, species, runs != 0, parent, size, hist, big_count);
+// The passes as kernels for one lattice, and for many square lattices at once:
+// replica blockIdx.y of a table, each with its own buffers.
+template <bool TRI>
+__global__ __launch_bounds__(256) void ccl_tile(CclShape g, int species, CclBuffers b) {
+  ccl_tile_body<TRI>(g, species, b);
 }
-__global__ __launch_bounds__(256) void ccl_merge(const void* lat, int layout, int L, int species, uint32_t* parent) {
-  ccl_merge_body(lat, layout, L, species, parent);
+template <bool TRI>
+__global__ __launch_bounds__(256) void ccl_border(CclShape g, CclBuffers b) {
+  ccl_border_body<TRI>(g, b);
 }
-__global__ __launch_bounds__(256) void ccl_flatten(uint32_t* parent, int L, int H) { ccl_flatten_body(parent, L, H); }
-__global__ __launch_bounds__(256) void ccl_count(uint32_t* parent, int L, int H, uint32_t* size) {
-  ccl_count_body(parent, L, H, size);
-}
-__global__ __launch_bounds__(256) void ccl_hist(const uint32_t* size, int L, int H, unsigned* hist, uint32_t* big,
-                                                unsigned* big_count, unsigned big_cap) {
+__global__ __launch_bounds__(256) void ccl_sizes(CclShape g, CclBuffers b) { ccl_sizes_body(g, b); }
+__global__ __launch_bounds__(256) void ccl_hist(CclShape g, CclBuffers b) {
   __shared__ unsigned h[kSmallSizes];
-  ccl_hist_body(size, L, H, hist, big, big_count, big_cap, h);
+  ccl_hist_body(g, b, h);
 }
-__global__ __launch_bounds__(256) void ccl_init_many(const CclRep* reps, int species) {
-  const CclRep& r = reps[blockIdx.y];
-  ccl_init_body(r.lat, r.layout, r.L, r.L, species, true, r.b.parent, r.b.size, r.b.hist, r.b.big_count);
+__device__ __forceinline__ CclShape ccl_shape(const CclRep& r) { return CclShape{r.lat, r.layout, r.L, r.L}; }
+__global__ __launch_bounds__(256) void ccl_tile_many(const CclRep* reps, int species) {
+  const CclRep r = reps[blockIdx.y];
+  ccl_tile_body<false>(ccl_shape(r), species, r.b);
 }
-__global__ __launch_bounds__(256) void ccl_merge_many(const CclRep* reps, int species) {
-  const CclRep& r = reps[blockIdx.y];
-  ccl_merge_body(r.lat, r.layout, r.L, species, r.b.parent);
+__global__ __launch_bounds__(256) void ccl_border_many(const CclRep* reps) {
+  const CclRep r = reps[blockIdx.y];
+  ccl_border_body<false>(ccl_shape(r), r.b);
 }
-__global__ __launch_bounds__(256) void ccl_flatten_many(const CclRep* reps) {
-  const CclRep& r = reps[blockIdx.y];
-  ccl_flatten_body(r.b.parent, r.L, r.L);
-}
-__global__ __launch_bounds__(256) void ccl_count_many(const CclRep* reps) {
-  const CclRep& r = reps[blockIdx.y];
-  ccl_count_body(r.b.parent, r.L, r.L, r.b.size);
+__global__ __launch_bounds__(256) void ccl_sizes_many(const CclRep* reps) {
+  const CclRep r = reps[blockIdx.y];
+  ccl_sizes_body(ccl_shape(r), r.b);
 }
 __global__ __launch_bounds__(256) void ccl_hist_many(const CclRep* reps) {
   __shared__ unsigned h[kSmallSizes];
-  const CclRep& r = reps[blockIdx.y];
-  ccl_hist_body(r.b.size, r.L, r.L, r.b.hist, r.b.big, r.b.big_count, r.b.big_cap, h);
+  const CclRep r = reps[blockIdx.y];
+  ccl_hist_body(ccl_shape(r), r.b, h);
 }
 // Every replica's result block (histogram, large-size count, first large
 // sizes) into row blockIdx.y of one staging array of `words` per replica.
@@ -410,17 +557,17 @@ int grid_for(size_t n, int block) {
 
 hipError_t launch_energy(const void* lat, int layout, int L, unsigned long long* out, hipStream_t stream) {
   if (layout == kLayoutBits)
-    hipLaunchKernelGGL(energy_bits, dim3(grid_for((size_t)L * (L >> 5), 256)), dim3(256), 0, stream,
+    hipLaunchKernelGGL(energy_bits, dim3(std::min(grid_for((size_t)L * (L >> 5), 256), kSumBlocks)), dim3(256), 0, stream,
                        static_cast<const uint32_t*>(lat), L, out);
   else
-    hipLaunchKernelGGL(energy_int8, dim3(grid_for((size_t)L * L, 256)), dim3(256), 0, stream,
+    hipLaunchKernelGGL(energy_int8, dim3(std::min(grid_for((size_t)L * (L >> 2), 256), kSumBlocks)), dim3(256), 0, stream,
                        static_cast<const uint8_t*>(lat), L, out);
   return hipGetLastError();
 }
 
 hipError_t launch_similar_sampled(const void* lat, int layout, int L, uint32_t k0, uint32_t k1, uint64_t t,
                                  unsigned long long* out, hipStream_t stream) {
-  hipLaunchKernelGGL(similar_sampled, dim3(grid_for((size_t)L * (L >> 2), 256)), dim3(256), 0, stream, lat, layout, L,
+  hipLaunchKernelGGL(similar_sampled, dim3(std::min(grid_for((size_t)L * (L >> 2), 256), 4 * kSumBlocks)), dim3(256), 0, stream, lat, layout, L,
                      k0, k1, t, out);
   return hipGetLastError();
 }
@@ -450,42 +597,52 @@ hipError_t launch_set_sites(const uint32_t* idx, unsigned n, int L, int layout, 
   return hipGetLastError();
 }
 
+size_t ccl_tiles(int L, int H) {
+  return (size_t)((L + kTile - 1) / kTile) * (size_t)((H + kTile - 1) / kTile);
+}
+size_t ccl_cluster_words(int L, int H) { return ((size_t)L * (size_t)H + 1) / 2; }
+size_t ccl_border_words(int L, int H) { return ccl_tiles(L, H) * (256 + 1); }
+
+namespace {
+// Workgroups of each pass over n tiles: one per tile up to 4096; a thread per
+// edge site; and few histograms, each of which clears and flushes 4096 bins.
+struct CclGrid {
+  unsigned tile, border, sizes, hist;
+};
+CclGrid ccl_grid(size_t n, bool triangular) {
+  return CclGrid{(unsigned)std::min<size_t>(n, 4096), (unsigned)std::min<size_t>((n * (triangular ? 192 : 128) + 255) / 256, 4096),
+                 (unsigned)std::min<size_t>(n, 4096), (unsigned)std::min<size_t>((n + 7) / 8, 128)};
+}
+}  // namespace
+
 hipError_t launch_ccl(const void* lat, int layout, int L, int H, int species, const CclBuffers& b, bool triangular,
                       hipStream_t stream) {
-  const size_t n = (size_t)L * H;
-  const int g = grid_for(n, 256);
-  hipLaunchKernelGGL(ccl_init, dim3(g), dim3(256), 0, stream, lat, layout, L, H, species, triangular ? 0 : 1,
-                     b.parent, b.size, b.hist, b.big_count);
+  const CclGrid n = ccl_grid(ccl_tiles(L, H), triangular);
+  const CclShape g{lat, layout, L, H};
   if (triangular) {
-    hipLaunchKernelGGL(ccl_merge_tri, dim3(g), dim3(256), 0, stream, static_cast<const uint8_t*>(lat), L, H, species,
-                       b.parent);
+    hipLaunchKernelGGL(ccl_tile<true>, dim3(n.tile), dim3(256), 0, stream, g, species, b);
+    hipLaunchKernelGGL(ccl_border<true>, dim3(n.border), dim3(256), 0, stream, g, b);
   } else {
-    // the square torus: H == L
-    hipLaunchKernelGGL(ccl_merge, dim3(g), dim3(256), 0, stream, lat, layout, L, species, b.parent);
+    hipLaunchKernelGGL(ccl_tile<false>, dim3(n.tile), dim3(256), 0, stream, g, species, b);
+    hipLaunchKernelGGL(ccl_border<false>, dim3(n.border), dim3(256), 0, stream, g, b);
   }
-  hipLaunchKernelGGL(ccl_flatten, dim3(g), dim3(256), 0, stream, b.parent, L, H);
-  hipLaunchKernelGGL(ccl_count, dim3(g), dim3(256), 0, stream, b.parent, L, H, b.size);
-  // each workgroup clears and flushes a whole LDS histogram, and every one of
-  // them adds into the hot small sizes: few workgroups, each streaming many sites
-  hipLaunchKernelGGL(ccl_hist, dim3(g < 128 ? g : 128), dim3(256), 0, stream, b.size, L, H, b.hist, b.big,
-                     b.big_count, b.big_cap);
+  hipLaunchKernelGGL(ccl_sizes, dim3(n.sizes), dim3(256), 0, stream, g, b);
+  hipLaunchKernelGGL(ccl_hist, dim3(n.hist), dim3(256), 0, stream, g, b);
   return hipGetLastError();
 }
 
-hipError_t launch_ccl_many(const CclRep* d_reps, int nreps, size_t max_sites, int species, uint32_t* stage,
-                           uint32_t words, hipStream_t stream) {
+hipError_t launch_ccl_many(const CclRep* d_reps, int nreps, int max_L, int species, uint32_t* stage, uint32_t words,
+                           hipStream_t stream) {
   if (nreps <= 0) return hipSuccess;
-  // every pass strides over its lattice, so a replica needs no more
-  // workgroups than fill the device with the others; workgroups past a
-  // smaller replica's sites exit at once
-  const int g = std::min(grid_for(max_sites, 256), kCclManyBlocks);
-  const dim3 grid((unsigned)g, (unsigned)nreps), hgrid((unsigned)(g < 128 ? g : 128), (unsigned)nreps);
-  hipLaunchKernelGGL(ccl_init_many, grid, dim3(256), 0, stream, d_reps, species);
-  hipLaunchKernelGGL(ccl_merge_many, grid, dim3(256), 0, stream, d_reps, species);
-  hipLaunchKernelGGL(ccl_flatten_many, grid, dim3(256), 0, stream, d_reps);
-  hipLaunchKernelGGL(ccl_count_many, grid, dim3(256), 0, stream, d_reps);
-  hipLaunchKernelGGL(ccl_hist_many, hgrid, dim3(256), 0, stream, d_reps);
-  hipLaunchKernelGGL(ccl_gather_many, dim3(8, (unsigned)nreps), dim3(256), 0, stream, d_reps, stage, words);
+  // every pass strides over its lattice's tiles; workgroups past a smaller
+  // replica's tiles exit at once
+  const CclGrid n = ccl_grid(ccl_tiles(max_L, max_L), false);
+  const unsigned reps = (unsigned)nreps;
+  hipLaunchKernelGGL(ccl_tile_many, dim3(n.tile, reps), dim3(256), 0, stream, d_reps, species);
+  hipLaunchKernelGGL(ccl_border_many, dim3(n.border, reps), dim3(256), 0, stream, d_reps);
+  hipLaunchKernelGGL(ccl_sizes_many, dim3(n.sizes, reps), dim3(256), 0, stream, d_reps);
+  hipLaunchKernelGGL(ccl_hist_many, dim3(n.hist, reps), dim3(256), 0, stream, d_reps);
+  hipLaunchKernelGGL(ccl_gather_many, dim3(8, reps), dim3(256), 0, stream, d_reps, stage, words);
   return hipGetLastError();
 }
 

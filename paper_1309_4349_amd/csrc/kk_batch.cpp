@@ -546,14 +546,14 @@ kk_status kk_batch_cluster_hists(kk_batch* b, int species) {
   // and one wait
   std::vector<kk_sim*> todo;
   std::vector<CclRep> reps;
-  size_t max_sites = 0;
+  int max_L = 0;
   for (kk_sim* h : b->sims) {
     if (hist_cached(h, species)) continue;
     const kk_status st = hist_buffers(h);
     if (st != KK_OK) return st;
     todo.push_back(h);
     reps.push_back(CclRep{h->lat[h->cur], h->layout, h->L, h->ccl});
-    max_sites = std::max(max_sites, (size_t)h->L * (size_t)h->L);
+    max_L = std::max(max_L, h->L);
   }
   if (todo.empty()) return KK_OK;
   const uint32_t words = (uint32_t)kSmallSizes + 1u + kHistBigPrefix;
@@ -565,7 +565,7 @@ kk_status kk_batch_cluster_hists(kk_batch* b, int species) {
     KB_HIP(hipHostMalloc((void**)&b->h_hist_stage, n * words * sizeof(uint32_t), hipHostMallocDefault));
   }
   KB_HIP(hipMemcpyAsync(b->d_ccl, reps.data(), reps.size() * sizeof(CclRep), hipMemcpyHostToDevice, b->sB));
-  KB_HIP(launch_ccl_many(b->d_ccl, (int)reps.size(), max_sites, species, b->d_hist_stage, words, b->sB));
+  KB_HIP(launch_ccl_many(b->d_ccl, (int)reps.size(), max_L, species, b->d_hist_stage, words, b->sB));
   KB_HIP(hipMemcpyAsync(b->h_hist_stage, b->d_hist_stage, todo.size() * words * sizeof(uint32_t),
                         hipMemcpyDeviceToHost, b->sB));
   KB_HIP(hipStreamSynchronize(b->sB));

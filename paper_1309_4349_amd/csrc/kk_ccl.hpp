@@ -17,10 +17,10 @@ struct CclRep {
 };
 
 // Label species on every lattice of the device table d_reps (nreps entries,
-// the largest of max_sites sites), count, build each one's histogram, and
+// the largest of side max_L), count, build each one's histogram, and
 // copy each result block (histogram, large-size count, first large sizes;
 // `words` words) into row i of `stage`.
-hipError_t launch_ccl_many(const CclRep* d_reps, int nreps, size_t max_sites, int species, uint32_t* stage,
-                           uint32_t words, hipStream_t stream);
+hipError_t launch_ccl_many(const CclRep* d_reps, int nreps, int max_L, int species, uint32_t* stage, uint32_t words,
+                           hipStream_t stream);
 
 }  // namespace kk

@@ -80,14 +80,19 @@ hipError_t launch_set_sites(const uint32_t* idx, unsigned n, int L, int layout, 
 
 // Connected components of one species (4-neighbour, periodic) and their size histogram.
 struct CclBuffers {
-  uint32_t* parent;     // N
-  uint32_t* size;       // N
+  uint32_t* parent;     // ccl_cluster_words
+  uint32_t* size;       // ccl_cluster_words
+  uint32_t* border;     // ccl_border_words: 256 edge labels per tile,
+  uint32_t* ncl;        // then the number of clusters per tile
   unsigned* hist;       // small-size histogram, kSmallSizes entries
   uint32_t* big;        // sizes >= kSmallSizes, appended
   unsigned* big_count;  // number of appended sizes
   unsigned big_cap;
 };
 constexpr int kSmallSizes = 4096;
+size_t ccl_tiles(int L, int H);
+size_t ccl_cluster_words(int L, int H);
+size_t ccl_border_words(int L, int H);
 // triangular: six neighbours under helical boundaries (the int8 ring of kk_tri.hip).
 hipError_t launch_ccl(const void* lat, int layout, int L, int H, int species, const CclBuffers& b, bool triangular,
                       hipStream_t stream);

@@ -173,15 +173,40 @@ __global__ __launch_bounds__(256) void mpkk_iter(const uint8_t* __restrict__ in,
   block_count(cnt, red, partials);
 }
 
-// N_AB over the 3N bonds (i, i+1), (i, i+L), (i, i+L-1).
-__global__ __launch_bounds__(256) void tri_energy(const uint8_t* s, uint32_t L, uint32_t N, unsigned long long* out) {
-  unsigned long long a = 0;
-  for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < N; i += gridDim.x * blockDim.x) {
-    const uint8_t v = s[i];
-    a += (v != s[tri_nb(i, 0, L, N)]) + (v != s[tri_nb(i, 2, L, N)]) + (v != s[tri_nb(i, 4, L, N)]);
-  }
+// One atomic per workgroup of 256 threads (see kk_aux.hip's summing passes).
+__device__ __forceinline__ void add_block_sum(uint32_t v, unsigned long long* out) {
+  __shared__ unsigned long long part[4];
+  unsigned long long a = v;
   for (int off = 32; off > 0; off >>= 1) a += __shfl_down(a, off, 64);
-  if ((threadIdx.x & 63) == 0 && a) atomicAdd(out, a);
+  if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = a;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    const unsigned long long tot = part[0] + part[1] + part[2] + part[3];
+    if (tot) atomicAdd(out, tot);
+  }
+}
+
+// N_AB over the 3N bonds (i, i+1), (i, i+L), (i, i+L-1): four sites at a time
+// where their neighbours lie before the ring's end, else one by one.
+__global__ __launch_bounds__(256) void tri_energy(const uint8_t* s, uint32_t L, uint32_t N, unsigned long long* out) {
+  uint32_t a = 0;
+  for (uint32_t q = blockIdx.x * blockDim.x + threadIdx.x; q < (N + 3u) / 4u; q += gridDim.x * blockDim.x) {
+    const uint32_t i = 4u * q;
+    if (i + L + 4u <= N) {
+      uint32_t v, e, d, f;
+      __builtin_memcpy(&v, s + i, 4);
+      __builtin_memcpy(&e, s + i + 1, 4);
+      __builtin_memcpy(&d, s + i + L, 4);
+      __builtin_memcpy(&f, s + i + L - 1, 4);
+      a += (uint32_t)(__builtin_popcount(v ^ e) + __builtin_popcount(v ^ d) + __builtin_popcount(v ^ f));
+    } else {
+      for (uint32_t k = i; k < min(i + 4u, N); ++k) {
+        const uint8_t v = s[k];
+        a += (v != s[tri_nb(k, 0, L, N)]) + (v != s[tri_nb(k, 2, L, N)]) + (v != s[tri_nb(k, 4, L, N)]);
+      }
+    }
+  }
+  add_block_sum(a, out);
 }
 
 // Random-neighbour draw: site i uses word i%4 of block (i/4, 1, t_lo, t_hi28 | 5<<28).
@@ -189,7 +214,7 @@ __global__ __launch_bounds__(256) void tri_similar(const uint8_t* s, uint32_t L,
                                                    uint64_t t, unsigned long long* out) {
   const uint32_t Q = (N + 3u) >> 2;
   const uint32_t tl = (uint32_t)t, th = ctr_hi(t, kTagObserve);
-  unsigned long long a = 0;
+  uint32_t a = 0;
   for (uint32_t q = blockIdx.x * blockDim.x + threadIdx.x; q < Q; q += gridDim.x * blockDim.x) {
     const Philox4 r = philox10(q, 1u, tl, th, k0, k1);
     const uint32_t w[4] = {r.x, r.y, r.z, r.w};
@@ -201,8 +226,7 @@ __global__ __launch_bounds__(256) void tri_similar(const uint8_t* s, uint32_t L,
       a += (s[i] == s[tri_nb(i, d, L, N)]);
     }
   }
-  for (int off = 32; off > 0; off >>= 1) a += __shfl_down(a, off, 64);
-  if ((threadIdx.x & 63) == 0 && a) atomicAdd(out, a);
+  add_block_sum(a, out);
 }
 
 // ---------------------------------------------------------------------------
@@ -322,14 +346,14 @@ hipError_t launch_tri_resident_one(const TriResidentRep& rep, size_t lds_bytes, 
 
 hipError_t launch_tri_energy(const uint8_t* lat, int L, int H, unsigned long long* out, hipStream_t stream) {
   const uint32_t N = (uint32_t)L * (uint32_t)H;
-  hipLaunchKernelGGL(tri_energy, dim3(tri_grid(N)), dim3(256), 0, stream, lat, (uint32_t)L, N, out);
+  hipLaunchKernelGGL(tri_energy, dim3(min(tri_grid((N + 3) / 4), 512)), dim3(256), 0, stream, lat, (uint32_t)L, N, out);
   return hipGetLastError();
 }
 
 hipError_t launch_tri_similar(const uint8_t* lat, int L, int H, uint32_t k0, uint32_t k1, uint64_t t,
                               unsigned long long* out, hipStream_t stream) {
   const uint32_t N = (uint32_t)L * (uint32_t)H;
-  hipLaunchKernelGGL(tri_similar, dim3(tri_grid((N + 3) / 4)), dim3(256), 0, stream, lat, (uint32_t)L, N, k0, k1, t,
+  hipLaunchKernelGGL(tri_similar, dim3(min(tri_grid((N + 3) / 4), 2048)), dim3(256), 0, stream, lat, (uint32_t)L, N, k0, k1, t,
                      out);
   return hipGetLastError();
 }
