@@ -156,7 +156,9 @@ kk_status kk_create_triangular_ex(kk_sim **out, uint32_t L, uint32_t H, uint32_t
  * over the square tiles T x T (T = 320, 256, 192, 160, 128, 96, 64, 48, 32,
  * 16) and the tiles that cut the ring into an nx x ny grid (TW = ceil(L/nx),
  * TR = ceil(H/ny), nx, ny <= 64), or 0 when none fits; class-schedule rings
- * of at most 12288 sites default to the whole ring. */
+ * default to the whole ring up to 12288 sites, up to 26000 where they can be
+ * cut into 3 .. 28 equal segments of a multiple of 16 sites, at least 2L each,
+ * and at any size that fits where they can and no tile does. */
 kk_status kk_tri_set_tile(kk_sim *h, uint32_t cols, uint32_t rows);
 kk_status kk_tri_get_tile(kk_sim *h, uint32_t *cols, uint32_t *rows);
 

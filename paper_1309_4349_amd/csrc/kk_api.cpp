@@ -365,12 +365,13 @@ kk_status enqueue_sweeps(kk_sim* h, uint64_t n, double* kernel_ms, uint64_t* lau
       R.L = (uint32_t)h->L;
       R.H = (uint32_t)h->H;
       R.sweeps = (uint32_t)m;
+      R.seg = ring_segments(h->L, h->H);
       R.k0 = h->k0;
       R.k1 = h->k1;
       R.t0 = h->t;
       R.acc = h->tacc;
       R.partials = h->partials;
-      KK_HIP(launch_tri_resident_one(R, sites, h->stream));
+      KK_HIP(launch_tri_resident_one(R, ring_lds_bytes(h->L, h->H), h->stream));
       nl += 1;
       h->t += m;
       h->attempts += m * sites;
@@ -496,10 +497,14 @@ const int kTriSquareTiles[] = {320, 256, 192, 160, 128, 96, 64, 48, 32, 16};
 void tri_default_tile(int L, int H, bool mpkk, int* tw, int* tr) {
   double best = 0.0;
   *tw = *tr = 0;
-  // rings of up to 12288 sites: the whole ring in one workgroup (measured: 10 us
-  // per sweep at 20^2, 16.7 at 100^2 against 19.9 with tiles; tiles win from
-  // about 13000 sites on)
-  if (!mpkk && (long)L * H <= 12288 && tri_resident_fits(L, H)) {
+  // the whole ring in one workgroup: with equal segments up to 26000 sites (us
+  // per sweep against tiles: 140^2 6.8 and 14.6, 156^2 11.5 and 14.6; level near
+  // 38000, but a batch of few such rings is better off sharing its launches of
+  // tiles), and at any size that no tile fits (380 x 80 12.4 against 64.5 with a
+  // launch per class); a byte per site up to 12288 (its 16.7 at 10000 sites grow
+  // with the sites, 26 at 148^2)
+  const long most = !ring_segments(L, H) ? 12288 : tri_tile_fits(L, H, 16, 16) ? 26000 : (long)kTriResidentMaxBytes;
+  if (!mpkk && (long)L * H <= most && tri_resident_fits(L, H)) {
     *tw = L;
     *tr = H;
     return;

@@ -11,8 +11,9 @@
 // Conflict-free schedule: class(i) = i mod 16, which for L % 8 == 4 and
 // H % 4 == 0 puts two sites of a class at least 4 steps apart, so the
 // exchanges of one class never read a site another writes; a sweep runs the 16
-// classes in a random order.  Whole-sweep tiles are in kk_hex.hip; here one
-// launch per class, in place, or the whole ring in one workgroup.  Random numbers:
+// classes in a random order.  Whole-sweep tiles are in kk_hex.hip, the whole
+// ring in one workgroup in kk_ring.hip; here one launch per class, in place.
+// Random numbers:
 //   site i at sweep t: Philox block (i/2, 0, t_lo, t_hi28 | 6<<28), words
 //   2(i%2) (direction, d = (w * 6) >> 32 picks +1, -1, +L, -L, +(L-1),
 //   -(L-1)) and 2(i%2)+1 (the 32-bit uniform U);
@@ -36,44 +37,10 @@
 #include "kk_common.hpp"
 #include "kk_kernels.hpp"
 #include "kk_tri.hpp"
+#include "kk_tri_dev.hpp"
 
 namespace kk {
 namespace {
-
-constexpr uint32_t kTagTri = 6u, kTagTriOrder = 7u, kTagMpkkK = 8u, kTagMpkk = 9u;
-
-__device__ __forceinline__ uint32_t tri_nb(uint32_t i, uint32_t d, uint32_t L, uint32_t N) {
-  // +1, -1, +L, -L, +(L-1), -(L-1) on the ring of N sites
-  const uint32_t mag = d < 2 ? 1u : (d < 4 ? L : L - 1u);
-  if ((d & 1u) == 0u) {
-    const uint32_t j = i + mag;
-    return j >= N ? j - N : j;
-  }
-  return i >= mag ? i - mag : i + N - mag;
-}
-
-__device__ __forceinline__ uint32_t tri_order(uint32_t k0, uint32_t k1, uint64_t t, int p) {
-  const uint32_t tl = (uint32_t)t, th = ctr_hi(t, kTagTriOrder);
-  uint32_t w[16];
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    const Philox4 b = philox10((uint32_t)j, 0u, tl, th, k0, k1);
-    w[4 * j] = b.x;
-    w[4 * j + 1] = b.y;
-    w[4 * j + 2] = b.z;
-    w[4 * j + 3] = b.w;
-  }
-  // the permutation as 16 nibbles of one 64-bit word (nibble e = entry e)
-  uint64_t perm = 0xFEDCBA9876543210ull;
-#pragma unroll
-  for (int i = 15; i >= 1; --i) {
-    const int k = (int)(((uint64_t)w[15 - i] * (uint64_t)(i + 1)) >> 32);
-    const uint64_t vi = (perm >> (4 * i)) & 0xFull, vk = (perm >> (4 * k)) & 0xFull;
-    perm &= ~((0xFull << (4 * i)) | (0xFull << (4 * k)));
-    perm |= (vk << (4 * i)) | (vi << (4 * k));
-  }
-  return (uint32_t)((perm >> (4 * p)) & 0xFull);
-}
 
 __device__ __forceinline__ int tri_unlike_except(const uint8_t* s, uint32_t i, uint32_t other, uint32_t L,
                                                  uint32_t N) {
@@ -104,7 +71,7 @@ __global__ __launch_bounds__(256) void tri_phase(uint8_t* s, uint32_t L, uint32_
   __shared__ uint32_t cls_s;
   __shared__ unsigned long long red[4];
   if (threadIdx.x < 64) {
-    const uint32_t c = tri_order(k0, k1, t, p);
+    const uint32_t c = (uint32_t)(hex_order(k0, k1, t) >> (4 * p)) & 15u;
     if (threadIdx.x == 0) cls_s = c;
   }
   __syncthreads();
@@ -229,87 +196,6 @@ __global__ __launch_bounds__(256) void tri_similar(const uint8_t* s, uint32_t L,
   add_block_sum(a, out);
 }
 
-// ---------------------------------------------------------------------------
-// Small lattices: the whole ring of one replica in one workgroup's LDS (no
-// halo), all of its sweeps in one launch, written back in place.  The 16
-// classes of a sweep run in the sweep's order with a barrier between them;
-// neighbours wrap modulo N inside LDS.  Workgroup b runs replica b of the
-// table.
-__device__ __forceinline__ void tri_resident_body(const TriResidentRep& R, uint8_t* ring) {
-  __shared__ uint32_t perm_s[16], thr_s[11];
-  __shared__ uint32_t all_s;
-  __shared__ unsigned long long red[16];
-  const uint32_t L = R.L, N = R.L * R.H;
-  uint8_t* lat = R.lat;
-  const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6, nwaves = blockDim.x >> 6;
-  if (threadIdx.x >= 64 && threadIdx.x < 64 + 11) {
-    const uint32_t n = threadIdx.x - 64;
-    const uint64_t T = R.acc.T[n];
-    thr_s[n] = T >= 0xFFFFFFFFull ? 0xFFFFFFFFu : (uint32_t)T;
-    const uint32_t always = (uint32_t)__ballot(T >= 0x100000000ull);  // lanes 0..10 of wave 1
-    if (n == 0) all_s = always;
-  }
-  for (uint32_t i = threadIdx.x; i < N; i += blockDim.x) ring[i] = lat[i];
-  unsigned long long cnt = 0;
-  const uint32_t M = N >> 4;
-  for (uint32_t s = 0; s < R.sweeps; ++s) {
-    const uint64_t t = R.t0 + s;
-    __syncthreads();  // the previous sweep's last phase (and the load) are complete
-    if (threadIdx.x < 64) {
-      const uint32_t c = tri_order(R.k0, R.k1, t, (int)(threadIdx.x & 15u));
-      if (threadIdx.x < 16) perm_s[threadIdx.x] = c;
-    }
-    __syncthreads();
-    const uint32_t always = all_s;
-    const uint32_t tl = (uint32_t)t, th = ctr_hi(t, kTagTri);
-    for (int p = 0; p < 16; ++p) {
-      const uint32_t cls = perm_s[p];
-      for (uint32_t j = threadIdx.x; j < M; j += blockDim.x) {
-        const uint32_t i = cls + 16u * j;
-        const Philox4 r = philox10(i >> 1, 0u, tl, th, R.k0, R.k1);
-        const uint32_t wd = (i & 1u) ? r.z : r.x, u = (i & 1u) ? r.w : r.y;
-        const uint32_t d = (uint32_t)(((uint64_t)wd * 6u) >> 32);
-        const uint32_t b = tri_nb(i, d, L, N);
-        const uint32_t vi = ring[i], vb = ring[b];
-        if (vi == vb) continue;
-        // the i-b bond is unlike and appears once in each neighbourhood
-        uint32_t n = 0;
-#pragma unroll
-        for (uint32_t e = 0; e < 6; ++e) n += ring[tri_nb(i, e, L, N)] != vi;
-#pragma unroll
-        for (uint32_t e = 0; e < 6; ++e) n += ring[tri_nb(b, e, L, N)] != vb;
-        n -= 2u;
-        if (u < thr_s[n] || ((always >> n) & 1u)) {
-          ring[i] = (uint8_t)vb;
-          ring[b] = (uint8_t)vi;
-          ++cnt;
-        }
-      }
-      __syncthreads();
-    }
-  }
-  __syncthreads();
-  for (uint32_t i = threadIdx.x; i < N; i += blockDim.x) lat[i] = ring[i];
-  for (int off = 32; off > 0; off >>= 1) cnt += __shfl_down(cnt, off, 64);
-  if (lane == 0) red[wave] = cnt;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    unsigned long long tot = 0;
-    for (uint32_t w = 0; w < nwaves; ++w) tot += red[w];
-    if (tot) atomicAdd(&R.partials[0], tot);
-  }
-}
-
-__global__ __launch_bounds__(1024) void tri_resident(const TriResidentRep* reps) {
-  extern __shared__ uint8_t ring[];
-  tri_resident_body(reps[blockIdx.x], ring);
-}
-
-__global__ __launch_bounds__(1024) void tri_resident_one(TriResidentRep R) {
-  extern __shared__ uint8_t ring[];
-  tri_resident_body(R, ring);
-}
-
 int tri_grid(size_t n) {
   const size_t g = (n + 255) / 256;
   return (int)(g < 8192 ? (g < 1 ? 1 : g) : 8192);
@@ -330,17 +216,6 @@ hipError_t launch_mpkk_iteration(const uint8_t* in, uint8_t* out, int L, int H, 
   const uint32_t N = (uint32_t)L * (uint32_t)H;
   hipLaunchKernelGGL(mpkk_iter, dim3(tri_grid(N / 7)), dim3(256), 0, stream, in, out, (uint32_t)L, N, k0, k1, t, j,
                      acc, partials);
-  return hipGetLastError();
-}
-
-hipError_t launch_tri_resident(const TriResidentRep* reps, uint32_t nreps, size_t lds_bytes, hipStream_t stream) {
-  if (nreps == 0) return hipSuccess;
-  hipLaunchKernelGGL(tri_resident, dim3(nreps), dim3(1024), lds_bytes, stream, reps);
-  return hipGetLastError();
-}
-
-hipError_t launch_tri_resident_one(const TriResidentRep& rep, size_t lds_bytes, hipStream_t stream) {
-  hipLaunchKernelGGL(tri_resident_one, dim3(1), dim3(1024), lds_bytes, stream, rep);
   return hipGetLastError();
 }
 

@@ -1,4 +1,4 @@
-// kk_tri.hpp -- launchers of the triangular-lattice kernels (kk_tri.hip).
+// kk_tri.hpp -- launchers of the triangular-lattice kernels (kk_tri.hip, kk_hex.hip, kk_ring.hip).
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -23,7 +23,7 @@ struct HexAccept {
   uint32_t all[3];   // 0xFFFFFFFF: every U is accepted
   uint32_t negmask;  // 0xFFFFFFFF: the restricted counts are 6, 7, 8
 };
-inline HexAccept hex_accept(const TriAccept& acc) {
+__host__ __device__ inline HexAccept hex_accept(const TriAccept& acc) {
   HexAccept a{};
   const bool neg = acc.T[2] >= ((uint64_t)1 << 32);  // omega <= 0 (n = 2 is always accepted)
   a.negmask = neg ? 0xFFFFFFFFu : 0u;
@@ -78,20 +78,45 @@ inline bool tri_tile_fits(int L, int H, int TW, int TR) {
   return TW >= 16 && TR >= 16 && TW + 2 * (int)kTriHalo <= L && TR + 2 * (int)kTriHalo <= H &&
          tri_window_bytes((uint32_t)TW, (uint32_t)TR) <= 160u * 1024u - 1024u;
 }
-// The whole ring in one workgroup's LDS (small lattices): N = L * H bytes.
+// The whole ring in one workgroup's LDS (kk_ring.hip): up to a byte per site.
 constexpr size_t kTriResidentMaxBytes = 160u * 1024u - 1024u;
 inline bool tri_resident_fits(int L, int H) {
   return (size_t)L * (size_t)H <= kTriResidentMaxBytes;
 }
+// The segments of kk_ring.hip's bit planes (0: the ring has none and is held a
+// byte per site): B equal parts of 16 W sites, B <= 28 bits of a word, at least
+// 2L sites each, W such that two buffers of draws fit the LDS.  The fewest that
+// leave one wave per class (more words, hence more lanes for the draws), else
+// the most.
+constexpr int kRingMaxBits = 28, kRingMaxWords = 194;
+constexpr int kRingStride = 196;  // words per class, fixed so that a class's place is part of an instruction
+inline uint32_t ring_segments(int L, int H) {
+  const int M = L * H / 16;
+  uint32_t best = 0;
+  for (int B = 3; B <= kRingMaxBits && 2 * B <= H; ++B) {
+    if (M % B != 0 || M / B > kRingMaxWords) continue;
+    best = (uint32_t)B;
+    if (M / B <= 64) break;
+  }
+  return best;
+}
+// LDS of a whole ring: words, two buffers of draws and 128 class orders; or bytes.
+inline size_t ring_lds_bytes(int L, int H) {
+  const uint32_t B = ring_segments(L, H);
+  const size_t N = (size_t)L * (size_t)H;
+  return B ? 16u * 4u * kRingStride + 12u * 4u * (N / B) + 1024u : N;
+}
 struct TriResidentRep {
   uint8_t* lat;  // the current buffer, updated in place
   uint32_t L, H, sweeps;
+  uint32_t seg;  // ring_segments(L, H)
   uint32_t k0, k1;
   uint64_t t0;
   TriAccept acc;
   unsigned long long* partials;
 };
-// Workgroup b runs replica b (reps[b].sweeps sweeps); lds_bytes = the largest N.
+// Workgroup b runs replica b (reps[b].sweeps sweeps); lds_bytes = the largest
+// ring_lds_bytes.
 hipError_t launch_tri_resident(const TriResidentRep* reps, uint32_t nreps, size_t lds_bytes, hipStream_t stream);
 // One replica, its descriptor passed by value.
 hipError_t launch_tri_resident_one(const TriResidentRep& rep, size_t lds_bytes, hipStream_t stream);

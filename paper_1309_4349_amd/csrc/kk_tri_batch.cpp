@@ -37,7 +37,7 @@ struct kk_tri_batch {
   bool own_stream = false;
   bool poisoned = false;
   std::vector<size_t> res;       // resident replicas
-  size_t res_lds = 0;            // largest resident ring
+  size_t res_lds = 0;            // the largest resident ring's LDS
   TriResidentRep* d_res = nullptr;
   std::vector<size_t> order;     // tiled replicas, sweeps descending
   std::vector<uint32_t> tw, tr;  // their tiles, fixed at creation (the job table depends on them)
@@ -115,7 +115,7 @@ kk_status kk_tri_batch_create(kk_tri_batch** out, const kk_tri_replica* reps, si
     const bool whole = h->tri_tw == h->L && h->tri_tr == h->H;
     if (h->geom == 1 && fits >= kMinResident && tri_resident_fits(h->L, h->H)) {
       b->res.push_back(i);
-      b->res_lds = std::max(b->res_lds, (size_t)h->L * (size_t)h->H);
+      b->res_lds = std::max(b->res_lds, ring_lds_bytes(h->L, h->H));
     } else if (h->geom == 1 && h->tri_tw > 0 && !whole) {
       b->order.push_back(i);
     } else {
@@ -188,6 +188,7 @@ kk_status tri_batch_run(kk_tri_batch* b) {
       R.L = (uint32_t)h->L;
       R.H = (uint32_t)h->H;
       R.sweeps = (uint32_t)b->sweeps[b->res[k]];
+      R.seg = ring_segments(h->L, h->H);
       R.k0 = h->k0;
       R.k1 = h->k1;
       R.t0 = h->t;
