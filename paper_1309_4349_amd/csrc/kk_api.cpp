@@ -177,11 +177,8 @@ void free_all(kk_sim* h) {
     if (h->lat[i]) (void)hipFree(h->lat[i]);
   if (h->counters) (void)hipFree(h->counters);
   if (h->partials) (void)hipFree(h->partials);
-  if (h->ccl.parent) (void)hipFree(h->ccl.parent);
-  if (h->ccl.size) (void)hipFree(h->ccl.size);
-  if (h->ccl.border) (void)hipFree(h->ccl.border);
-  if (h->ccl.hist) (void)hipFree(h->ccl.hist);  // also holds big_count and big
-  if (h->hist_host) (void)hipHostFree(h->hist_host);
+  if (h->ccl.parent) (void)hipFree(h->ccl.parent);  // all labelling buffers
+  if (h->in_pool) pinned_handles(-1);
   if (h->own_stream && h->stream) (void)hipStreamDestroy(h->stream);
 }
 
@@ -292,11 +289,22 @@ size_t tile_count(int L, const TileConfig& tc) {
 }
 
 uint64_t sum_partials(kk_sim* h, kk_status* st) {
-  std::vector<unsigned long long> v(h->npartials);
+  std::vector<unsigned long long> v(1);
   *st = KK_OK;
-  hipError_t e = hipMemcpyAsync(v.data(), h->partials, h->npartials * sizeof(unsigned long long),
-                                hipMemcpyDeviceToHost, h->stream);
+  Pinned pin;
+  hipError_t e;
+  if (pin) {
+    e = launch_sum_words(h->partials, h->npartials, pin.sums(0), h->stream);
+  } else {
+    v.resize(h->npartials);
+    e = hipMemcpyAsync(v.data(), h->partials, h->npartials * sizeof(unsigned long long), hipMemcpyDeviceToHost,
+                       h->stream);
+  }
   if (e == hipSuccess) e = hipStreamSynchronize(h->stream);
+  if (e == hipSuccess && pin) {
+    pin.drained();
+    v[0] = pin.sums(0)[0];
+  }
   if (e != hipSuccess) {
     h->poisoned = true;
     *st = set_error(KK_EDEVICE, "reading accepted counts: %s", hipGetErrorString(e));
@@ -445,16 +453,49 @@ kk_status enqueue_sweeps(kk_sim* h, uint64_t n, double* kernel_ms, uint64_t* lau
 }  // namespace
 
 namespace kk {
-kk_status device_alloc(void** p, size_t bytes) { return dmalloc(nullptr, p, bytes); }
+namespace {
+std::mutex pinned_mu;
+std::vector<uint8_t*> pinned_kept;  // idle blocks
+long pinned_users = 0;              // handles alive
+}  // namespace
 
-kk_status fold_accepted(kk_sim* h, const unsigned long long* dev_counts, size_t n) {
-  if (n == 0) return KK_OK;
-  std::vector<unsigned long long> v(n);
-  KK_HIP(hipMemcpyAsync(v.data(), dev_counts, n * sizeof(unsigned long long), hipMemcpyDeviceToHost, h->stream));
-  KK_HIP(hipStreamSynchronize(h->stream));
-  for (auto x : v) h->accepted_base += x;
-  return KK_OK;
+Pinned::Pinned() : p_(nullptr) {
+  {
+    std::lock_guard<std::mutex> lock(pinned_mu);
+    if (!pinned_kept.empty()) {
+      p_ = pinned_kept.back();
+      pinned_kept.pop_back();
+      return;
+    }
+  }
+  void* p = nullptr;
+  if (hipHostMalloc(&p, kPinnedBytes, hipHostMallocPortable) == hipSuccess) p_ = static_cast<uint8_t*>(p);
+  else (void)hipGetLastError();  // the caller does without
 }
+
+Pinned::~Pinned() {
+  if (!p_) return;
+  if (idle_) {
+    std::lock_guard<std::mutex> lock(pinned_mu);
+    if (pinned_users > 0 && pinned_kept.size() < kPinnedKept) {
+      pinned_kept.push_back(p_);
+      return;
+    }
+  }
+  (void)hipHostFree(p_);
+}
+
+void pinned_handles(int change) {
+  std::vector<uint8_t*> gone;
+  {
+    std::lock_guard<std::mutex> lock(pinned_mu);
+    pinned_users += change;
+    if (pinned_users == 0) gone.swap(pinned_kept);
+  }
+  for (uint8_t* p : gone) (void)hipHostFree(p);
+}
+
+kk_status device_alloc(void** p, size_t bytes) { return dmalloc(nullptr, p, bytes); }
 
 // Whole-sweep (or whole-step) tile of a triangular lattice.  Small rings of
 // the class schedule take the whole ring in one workgroup.  Otherwise a workgroup
@@ -603,6 +644,8 @@ kk_status create_handle(kk_sim** out, uint32_t L, uint32_t H, int geom, double c
     }
     h->own_stream = true;
   }
+  pinned_handles(1);
+  h->in_pool = true;
   const size_t bytes = lattice_bytes(h);
   for (int i = 0; i < 2 && st == KK_OK; ++i) st = dmalloc(h, &h->lat[i], bytes);
   if (st == KK_OK) st = dmalloc(h, (void**)&h->counters, 2 * sizeof(unsigned long long));
@@ -622,6 +665,42 @@ kk_status create_handle(kk_sim** out, uint32_t L, uint32_t H, int geom, double c
 }
 
 }  // namespace kk
+
+namespace {
+// The sums over the lattice that are read back: N_AB, or the sampled
+// neighbours of the same type.
+enum SumKind { kSumEnergy, kSumSimilar };
+hipError_t launch_sum(kk_sim* h, SumKind kind, unsigned long long* out, int* nsum) {
+  const void* lat = h->lat[h->cur];
+  const uint8_t* ring = static_cast<const uint8_t*>(lat);
+  if (kind == kSumEnergy)
+    return h->geom != 0 ? launch_tri_energy(ring, h->L, h->H, out, nsum, h->stream)
+                        : launch_energy(lat, h->layout, h->L, out, nsum, h->stream);
+  return h->geom != 0 ? launch_tri_similar(ring, h->L, h->H, h->k0, h->k1, h->t, out, nsum, h->stream)
+                      : launch_similar_sampled(lat, h->layout, h->L, h->k0, h->k1, h->t, out, nsum, h->stream);
+}
+uint64_t add_up(const unsigned long long* v, int n) {
+  uint64_t s = 0;
+  for (int i = 0; i < n; ++i) s += v[i];
+  return s;
+}
+kk_status read_sum(kk_sim* h, SumKind kind, unsigned long long* sum) {
+  Pinned pin;
+  int n = 0;
+  if (pin) {
+    KK_HIP(launch_sum(h, kind, pin.sums(0), &n));
+    KK_HIP(hipStreamSynchronize(h->stream));
+    pin.drained();
+    *sum = add_up(pin.sums(0), n);
+    return KK_OK;
+  }
+  KK_HIP(hipMemsetAsync(h->counters, 0, sizeof(unsigned long long), h->stream));
+  KK_HIP(launch_sum(h, kind, h->counters, nullptr));
+  KK_HIP(hipMemcpyAsync(sum, h->counters, sizeof *sum, hipMemcpyDeviceToHost, h->stream));
+  KK_HIP(hipStreamSynchronize(h->stream));
+  return KK_OK;
+}
+}  // namespace
 
 extern "C" {
 
@@ -849,14 +928,9 @@ kk_status kk_sweep_timed(kk_sim* h, uint64_t n, double* kernel_ms, uint64_t* lau
 
 kk_status kk_energy(kk_sim* h, uint64_t* n_unlike, double* energy_kT) {
   KK_GUARD(h);
-  KK_HIP(hipMemsetAsync(h->counters + 1, 0, sizeof(unsigned long long), h->stream));
-  if (h->geom != 0)
-    KK_HIP(launch_tri_energy(static_cast<const uint8_t*>(h->lat[h->cur]), h->L, h->H, h->counters + 1, h->stream));
-  else
-    KK_HIP(launch_energy(h->lat[h->cur], h->layout, h->L, h->counters + 1, h->stream));
   unsigned long long v = 0;
-  KK_HIP(hipMemcpyAsync(&v, h->counters + 1, sizeof v, hipMemcpyDeviceToHost, h->stream));
-  KK_HIP(hipStreamSynchronize(h->stream));
+  const kk_status st = read_sum(h, kSumEnergy, &v);
+  if (st != KK_OK) return st;
   if (n_unlike) *n_unlike = v;
   if (energy_kT) *energy_kT = h->omega * (double)v;
   return KK_OK;
@@ -866,31 +940,24 @@ kk_status kk_energy(kk_sim* h, uint64_t* n_unlike, double* energy_kT) {
 
 namespace kk {
 
-// Labelling buffers of a handle, made on its first histogram: parent and size
-// of the tiles' clusters, the labels along the tiles' edges, then one block
-// holding the small-size histogram, the count of large sizes and their list, so
-// that one copy brings back the histogram, the count and the first
-// kHistBigPrefix large sizes; its pinned host image.
+// Labelling buffers of a handle, one allocation made on its first histogram:
+// parent and size of the tiles' clusters, the labels along the tiles' edges,
+// then one block holding the small-size histogram, the count of large sizes
+// and their list, so that one copy brings back the histogram, the count and the
+// first kHistBigPrefix large sizes.
 kk_status hist_buffers(kk_sim* h) {
   if (h->ccl_ready) return KK_OK;
   const size_t N = (size_t)h->L * h->H;
   const unsigned big_cap = (unsigned)(N / kSmallSizes + 1);
-  const size_t clusters = ccl_cluster_words(h->L, h->H), border = ccl_border_words(h->L, h->H);
-  kk_status st = dmalloc(h, (void**)&h->ccl.parent, clusters * 4);
-  if (st == KK_OK) st = dmalloc(h, (void**)&h->ccl.size, clusters * 4);
-  if (st == KK_OK) st = dmalloc(h, (void**)&h->ccl.border, border * 4);
-  if (st == KK_OK) st = dmalloc(h, (void**)&h->ccl.hist, ((size_t)kSmallSizes + 1 + big_cap) * 4);
-  if (st == KK_OK && !h->hist_host) {
-    const hipError_t e = hipHostMalloc((void**)&h->hist_host, ((size_t)kSmallSizes + 1 + kHistBigPrefix) * 4,
-                                       hipHostMallocDefault);
-    if (e != hipSuccess) {
-      (void)hipGetLastError();
-      h->hist_host = nullptr;
-      st = set_error(KK_ENOMEM, "hipHostMalloc: %s", hipGetErrorString(e));
-    }
-  }
+  auto whole = [](size_t words) { return (words + 63) & ~(size_t)63; };
+  const size_t clusters = whole(ccl_cluster_words(h->L, h->H)), border = whole(ccl_border_words(h->L, h->H));
+  const kk_status st = dmalloc(h, (void**)&h->ccl.parent,
+                               (2 * clusters + border + (size_t)kSmallSizes + 1 + big_cap) * sizeof(uint32_t));
   if (st != KK_OK) return st;
+  h->ccl.size = h->ccl.parent + clusters;
+  h->ccl.border = h->ccl.size + clusters;
   h->ccl.ncl = h->ccl.border + ccl_tiles(h->L, h->H) * 256;
+  h->ccl.hist = h->ccl.border + border;
   h->ccl.big_count = h->ccl.hist + kSmallSizes;
   h->ccl.big = h->ccl.hist + kSmallSizes + 1;
   h->ccl.big_cap = big_cap;
@@ -900,21 +967,25 @@ kk_status hist_buffers(kk_sim* h) {
 
 bool hist_cached(const kk_sim* h, int species) { return h->hist_epoch == h->epoch && h->hist_species == species; }
 
-// Label species, count and histogram on `stream`, and copy the result block
-// to the pinned image.  The result is read by hist_finish once the stream has
-// drained.
-kk_status hist_enqueue(kk_sim* h, int species, hipStream_t stream) {
-  kk_status st = hist_buffers(h);
-  if (st != KK_OK) return st;
-  KK_HIP(launch_ccl(h->lat[h->cur], h->layout, h->L, h->H, species, h->ccl, h->geom != 0, stream));
-  const size_t words = (size_t)kSmallSizes + 1 + std::min<size_t>(h->ccl.big_cap, kHistBigPrefix);
-  KK_HIP(hipMemcpyAsync(h->hist_host, h->ccl.hist, words * 4, hipMemcpyDeviceToHost, stream));
-  return KK_OK;
+namespace {
+size_t image_words(const kk_sim* h) {
+  return (size_t)kSmallSizes + 1 + std::min<size_t>(h->ccl.big_cap, kHistBigPrefix);
 }
 
-// Turn the pinned image into the handle's cached histogram (sizes ascending).
-kk_status hist_finish(kk_sim* h, int species) {
-  const uint32_t* hs = h->hist_host;
+// Label species and count, the result block into `image` (pinned), on the
+// handle's stream.
+kk_status hist_enqueue(kk_sim* h, int species, uint32_t* image) {
+  const kk_status st = hist_buffers(h);
+  if (st != KK_OK) return st;
+  KK_HIP(launch_ccl(h->lat[h->cur], h->layout, h->L, h->H, species, h->ccl, h->geom != 0, h->stream));
+  KK_HIP(launch_copy_bytes(h->ccl.hist, image, image_words(h) * sizeof(uint32_t), h->stream));
+  return KK_OK;
+}
+}  // namespace
+
+// Turn the image of the result block into the handle's cached histogram (sizes
+// ascending).
+kk_status hist_finish(kk_sim* h, int species, const uint32_t* hs) {
   const unsigned nbig = hs[kSmallSizes];
   if (nbig > h->ccl.big_cap) return set_error(KK_EDEVICE, "cluster list overflow (%u > %u)", nbig, h->ccl.big_cap);
   std::vector<uint32_t> big(hs + kSmallSizes + 1, hs + kSmallSizes + 1 + std::min<unsigned>(nbig, kHistBigPrefix));
@@ -947,10 +1018,13 @@ kk_status kk_cluster_hist(kk_sim* h, int species, kk_hist_entry* out, size_t cap
   if (!hist_cached(h, species)) {
     // the result is cached until the lattice changes, so a size query
     // followed by the fill labels only once
-    kk_status st = hist_enqueue(h, species, h->stream);
+    Pinned pin;
+    if (!pin) return set_error(KK_ENOMEM, "hipHostMalloc of %zu bytes failed", kPinnedBytes);
+    kk_status st = hist_enqueue(h, species, pin.image());
     if (st != KK_OK) return st;
     KK_HIP(hipStreamSynchronize(h->stream));
-    st = hist_finish(h, species);
+    pin.drained();
+    st = hist_finish(h, species, pin.image());
     if (st != KK_OK) return st;
   }
   const size_t n = h->hist_cache.size();
@@ -966,26 +1040,28 @@ kk_status kk_observe(kk_sim* h, int species, kk_observables* out) {
   if (species != 0 && species != 1) return set_error(KK_EINVAL, "species must be 0 or 1");
   kk_observables o{};
   o.sweep = h->t;
-  kk_status st = kk_energy(h, &o.n_unlike, &o.energy_kT);
-  if (st != KK_OK) return st;
   const uint64_t N = (uint64_t)h->L * (uint64_t)h->H;
+  uint64_t same = 0;
+  Pinned pin;  // all three results in one wait
+  if (!pin) return set_error(KK_ENOMEM, "hipHostMalloc of %zu bytes failed", kPinnedBytes);
+  const bool label = !hist_cached(h, species);
+  int ne = 0, ns = 0;
+  KK_HIP(launch_sum(h, kSumEnergy, pin.sums(0), &ne));
+  KK_HIP(launch_sum(h, kSumSimilar, pin.sums(1), &ns));
+  kk_status st = label ? hist_enqueue(h, species, pin.image()) : KK_OK;
+  if (st != KK_OK) return st;
+  KK_HIP(hipStreamSynchronize(h->stream));
+  pin.drained();
+  o.n_unlike = add_up(pin.sums(0), ne);
+  o.energy_kT = h->omega * (double)o.n_unlike;
+  same = add_up(pin.sums(1), ns);
+  st = label ? hist_finish(h, species, pin.image()) : KK_OK;
+  if (st != KK_OK) return st;
   // the lattice has 2N bonds (square) or 3N (triangular)
   o.similar_exact = 1.0 - (double)o.n_unlike / (double)((h->geom != 0 ? 3 : 2) * N);
-  KK_HIP(hipMemsetAsync(h->counters, 0, sizeof(unsigned long long), h->stream));
-  if (h->geom != 0)
-    KK_HIP(launch_tri_similar(static_cast<const uint8_t*>(h->lat[h->cur]), h->L, h->H, h->k0, h->k1, h->t,
-                              h->counters, h->stream));
-  else
-    KK_HIP(launch_similar_sampled(h->lat[h->cur], h->layout, h->L, h->k0, h->k1, h->t, h->counters, h->stream));
-  unsigned long long same = 0;
-  KK_HIP(hipMemcpyAsync(&same, h->counters, sizeof same, hipMemcpyDeviceToHost, h->stream));
-  KK_HIP(hipStreamSynchronize(h->stream));
   o.similar_sampled = (double)same / (double)N;
-  size_t n = 0;
-  st = kk_cluster_hist(h, species, nullptr, 0, &n);
-  if (st != KK_OK && st != KK_ETRUNC) return st;
   uint64_t nc = 0, s1 = 0, s2 = 0, smax = 0;
-  for (const kk_hist_entry& e : h->hist_cache) {  // filled by the call above
+  for (const kk_hist_entry& e : h->hist_cache) {
     nc += e.count;
     s1 += e.size * e.count;
     s2 += e.size * e.size * e.count;
@@ -1018,6 +1094,17 @@ kk_status kk_get_lattice(kk_sim* h, uint8_t* host_out, size_t n) {
   KK_GUARD(h);
   const size_t N = (size_t)h->L * h->H;
   if (!host_out || n != N) return set_error(KK_EINVAL, "need a buffer of exactly L*H = %zu bytes", N);
+  if (N <= kPinnedLattice) {
+    Pinned pin;
+    if (pin) {
+      if (h->layout == kLayoutInt8) KK_HIP(launch_copy_bytes(h->lat[h->cur], pin.sites(), N, h->stream));
+      else KK_HIP(launch_unpack(static_cast<const uint32_t*>(h->lat[h->cur]), pin.sites(), h->L, h->stream));
+      KK_HIP(hipStreamSynchronize(h->stream));
+      pin.drained();
+      std::memcpy(host_out, pin.sites(), N);
+      return KK_OK;
+    }
+  }
   if (h->layout == kLayoutInt8) {
     KK_HIP(hipMemcpyAsync(host_out, h->lat[h->cur], N, hipMemcpyDeviceToHost, h->stream));
     KK_HIP(hipStreamSynchronize(h->stream));

@@ -18,12 +18,13 @@ __device__ __forceinline__ int site_bit(const void* lat, int layout, int L, int 
   return (int)(static_cast<const uint8_t*>(lat)[(size_t)y * L + x] & 1u);
 }
 
-// Sum of a per-thread value over the workgroup (256 threads), added to *out by
+// Sum of a per-thread value over the workgroup (256 threads): each workgroup's
+// into its own word (`spread`: host memory, added up there), or added to *out by
 // one atomic.  Atomics on one address run about 12 ns each, one after another:
 // with one per wavefront of 4096 workgroups they were all of the time of the
 // passes below (energy of an int8 lattice 1036^2 200 us, of a 4092^2 triangular
 // ring 400 us; now under 10 and 21 us).
-__device__ __forceinline__ void add_block_sum(unsigned v, unsigned long long* out) {
+__device__ __forceinline__ void add_block_sum(unsigned long long v, unsigned long long* out, bool spread) {
   __shared__ unsigned long long part[4];
   unsigned long long acc = v;
   for (int off = 32; off > 0; off >>= 1) acc += __shfl_down(acc, off, 64);
@@ -31,7 +32,8 @@ __device__ __forceinline__ void add_block_sum(unsigned v, unsigned long long* ou
   __syncthreads();
   if (threadIdx.x == 0) {
     const unsigned long long tot = part[0] + part[1] + part[2] + part[3];
-    if (tot) atomicAdd(out, tot);
+    if (spread) out[blockIdx.x] = tot;
+    else if (tot) atomicAdd(out, tot);
   }
 }
 constexpr int kSumBlocks = 512;  // workgroups of a summing pass (each thread strides)
@@ -41,7 +43,8 @@ constexpr int kSumBlocks = 512;  // workgroups of a summing pass (each thread st
 // (the Almeida one-parameter model, E/kT = omega * N_AB + const).  A thread's
 // count stays below 2^32: at most 2 bonds of 2^30 sites over 2^17 threads.
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void energy_bits(const uint32_t* lat, int L, unsigned long long* out) {
+__global__ __launch_bounds__(256) void energy_bits(const uint32_t* lat, int L, unsigned long long* out,
+                                                   bool spread) {
   const int wpr = L >> 5;
   const size_t nw = (size_t)L * wpr;
   unsigned acc = 0;
@@ -53,11 +56,12 @@ __global__ __launch_bounds__(256) void energy_bits(const uint32_t* lat, int L, u
     const uint32_t below = lat[(size_t)(y + 1 == L ? 0 : y + 1) * wpr + g];
     acc += (unsigned)__builtin_popcount(v ^ east) + (unsigned)__builtin_popcount(v ^ below);
   }
-  add_block_sum(acc, out);
+  add_block_sum(acc, out, spread);
 }
 
 // Four sites (one per byte) at a time: L is a multiple of 4.
-__global__ __launch_bounds__(256) void energy_int8(const uint8_t* lat, int L, unsigned long long* out) {
+__global__ __launch_bounds__(256) void energy_int8(const uint8_t* lat, int L, unsigned long long* out,
+                                                   bool spread) {
   const uint32_t* w = reinterpret_cast<const uint32_t*>(lat);
   const int wpr = L >> 2;
   const size_t nw = (size_t)L * wpr;
@@ -70,7 +74,7 @@ __global__ __launch_bounds__(256) void energy_int8(const uint8_t* lat, int L, un
     acc += (unsigned)__builtin_popcount(v ^ __builtin_amdgcn_alignbit(nxt, v, 8)) +
            (unsigned)__builtin_popcount(v ^ below);
   }
-  add_block_sum(acc, out);
+  add_block_sum(acc, out, spread);
 }
 
 // Random-neighbour estimate of the similar first-neighbour fraction: every
@@ -78,7 +82,7 @@ __global__ __launch_bounds__(256) void energy_int8(const uint8_t* lat, int L, un
 // (y, x / 4, t, tag 5): +x, -x, +y, -y) and counts when both are of the same
 // type.  One thread per 4-site group (one Philox block); L % 4 == 0.
 __global__ __launch_bounds__(256) void similar_sampled(const void* lat, int layout, int L, uint32_t k0, uint32_t k1,
-                                                       uint64_t t, unsigned long long* out) {
+                                                       uint64_t t, unsigned long long* out, bool spread) {
   const int g4 = L >> 2;
   const size_t n = (size_t)L * g4;
   const uint32_t tl = (uint32_t)t, th = ctr_hi(t, kTagObserve);
@@ -99,7 +103,7 @@ __global__ __launch_bounds__(256) void similar_sampled(const void* lat, int layo
       acc += (site_bit(lat, layout, L, x, y) == site_bit(lat, layout, L, nx, ny));
     }
   }
-  add_block_sum(acc, out);
+  add_block_sum(acc, out, spread);
 }
 
 // ---------------------------------------------------------------------------
@@ -538,12 +542,32 @@ __global__ __launch_bounds__(256) void pack_bits(const uint8_t* in, uint32_t* ou
   }
 }
 
+// Sixteen sites (a half word of the lattice) per thread, one 16-byte store each:
+// a wavefront's stores are one stretch, also where `out` is host memory.
 __global__ __launch_bounds__(256) void unpack_bits(const uint32_t* in, uint8_t* out, int L) {
-  const size_t nw = (size_t)L * (L >> 5);
-  for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < nw; i += (size_t)gridDim.x * blockDim.x) {
-    const uint32_t v = in[i];
-    for (int b = 0; b < 32; ++b) out[i * 32 + b] = (uint8_t)((v >> b) & 1u);
+  const uint16_t* h = reinterpret_cast<const uint16_t*>(in);
+  uint4* o = reinterpret_cast<uint4*>(out);
+  const size_t n = (size_t)L * (L >> 4);
+  auto spread = [](uint32_t nibble) { return (nibble * 0x00204081u) & 0x01010101u; };
+  for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) {
+    const uint32_t v = h[i];
+    o[i] = make_uint4(spread(v & 15u), spread((v >> 4) & 15u), spread((v >> 8) & 15u), spread(v >> 12));
   }
+}
+
+// Read-back into host memory: a copy and a sum.  A copy command of the runtime
+// takes about 8 us longer than a kernel that writes the bytes itself.
+__global__ __launch_bounds__(256) void copy_bytes(const uint8_t* in, uint8_t* out, size_t n) {
+  const uint4* v = reinterpret_cast<const uint4*>(in);
+  uint4* o = reinterpret_cast<uint4*>(out);
+  const size_t i0 = blockIdx.x * (size_t)blockDim.x + threadIdx.x, step = (size_t)gridDim.x * blockDim.x;
+  for (size_t i = i0; i < n / 16; i += step) o[i] = v[i];
+  for (size_t i = (n & ~(size_t)15) + i0; i < n; i += step) out[i] = in[i];
+}
+__global__ __launch_bounds__(256) void sum_words(const unsigned long long* in, size_t n, unsigned long long* out) {
+  unsigned long long acc = 0;
+  for (size_t i = threadIdx.x; i < n; i += 256) acc += in[i];
+  add_block_sum(acc, out, true);
 }
 
 int grid_for(size_t n, int block) {
@@ -555,20 +579,35 @@ int grid_for(size_t n, int block) {
 
 }  // namespace
 
-hipError_t launch_energy(const void* lat, int layout, int L, unsigned long long* out, hipStream_t stream) {
-  if (layout == kLayoutBits)
-    hipLaunchKernelGGL(energy_bits, dim3(std::min(grid_for((size_t)L * (L >> 5), 256), kSumBlocks)), dim3(256), 0, stream,
-                       static_cast<const uint32_t*>(lat), L, out);
+hipError_t launch_energy(const void* lat, int layout, int L, unsigned long long* out, int* nsum, hipStream_t stream) {
+  const bool bits = layout == kLayoutBits;
+  const int n = std::min(grid_for((size_t)L * (L >> (bits ? 5 : 2)), 256), kSumBlocks);
+  if (nsum) *nsum = n;
+  if (bits)
+    hipLaunchKernelGGL(energy_bits, dim3(n), dim3(256), 0, stream, static_cast<const uint32_t*>(lat), L, out,
+                       nsum != nullptr);
   else
-    hipLaunchKernelGGL(energy_int8, dim3(std::min(grid_for((size_t)L * (L >> 2), 256), kSumBlocks)), dim3(256), 0, stream,
-                       static_cast<const uint8_t*>(lat), L, out);
+    hipLaunchKernelGGL(energy_int8, dim3(n), dim3(256), 0, stream, static_cast<const uint8_t*>(lat), L, out,
+                       nsum != nullptr);
   return hipGetLastError();
 }
 
 hipError_t launch_similar_sampled(const void* lat, int layout, int L, uint32_t k0, uint32_t k1, uint64_t t,
-                                 unsigned long long* out, hipStream_t stream) {
-  hipLaunchKernelGGL(similar_sampled, dim3(std::min(grid_for((size_t)L * (L >> 2), 256), 4 * kSumBlocks)), dim3(256), 0, stream, lat, layout, L,
-                     k0, k1, t, out);
+                                  unsigned long long* out, int* nsum, hipStream_t stream) {
+  const int n = std::min(grid_for((size_t)L * (L >> 2), 256), 4 * kSumBlocks);
+  if (nsum) *nsum = n;
+  hipLaunchKernelGGL(similar_sampled, dim3(n), dim3(256), 0, stream, lat, layout, L, k0, k1, t, out, nsum != nullptr);
+  return hipGetLastError();
+}
+
+hipError_t launch_sum_words(const unsigned long long* in, size_t n, unsigned long long* out, hipStream_t stream) {
+  hipLaunchKernelGGL(sum_words, dim3(1), dim3(256), 0, stream, in, n, out);
+  return hipGetLastError();
+}
+
+hipError_t launch_copy_bytes(const void* in, void* out, size_t n, hipStream_t stream) {
+  hipLaunchKernelGGL(copy_bytes, dim3(grid_for((n + 15) / 16, 256)), dim3(256), 0, stream,
+                     static_cast<const uint8_t*>(in), static_cast<uint8_t*>(out), n);
   return hipGetLastError();
 }
 
@@ -652,7 +691,7 @@ hipError_t launch_pack(const uint8_t* in, uint32_t* out, int L, hipStream_t stre
 }
 
 hipError_t launch_unpack(const uint32_t* in, uint8_t* out, int L, hipStream_t stream) {
-  hipLaunchKernelGGL(unpack_bits, dim3(grid_for((size_t)L * (L >> 5), 256)), dim3(256), 0, stream, in, out, L);
+  hipLaunchKernelGGL(unpack_bits, dim3(grid_for((size_t)L * (L >> 4), 256)), dim3(256), 0, stream, in, out, L);
   return hipGetLastError();
 }
 

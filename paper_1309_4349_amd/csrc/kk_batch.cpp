@@ -569,10 +569,8 @@ kk_status kk_batch_cluster_hists(kk_batch* b, int species) {
   KB_HIP(hipMemcpyAsync(b->h_hist_stage, b->d_hist_stage, todo.size() * words * sizeof(uint32_t),
                         hipMemcpyDeviceToHost, b->sB));
   KB_HIP(hipStreamSynchronize(b->sB));
-  for (size_t i = 0; i < todo.size(); ++i)
-    std::memcpy(todo[i]->hist_host, b->h_hist_stage + i * words, words * sizeof(uint32_t));
-  for (kk_sim* h : todo) {
-    const kk_status st = hist_finish(h, species);
+  for (size_t i = 0; i < todo.size(); ++i) {
+    const kk_status st = hist_finish(todo[i], species, b->h_hist_stage + i * words);
     if (st != KK_OK) return st;
   }
   return KK_OK;

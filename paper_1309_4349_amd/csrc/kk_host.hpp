@@ -43,7 +43,8 @@ struct kk_sim {
   uint64_t attempts = 0;
   void* lat[2] = {nullptr, nullptr};
   int cur = 0;
-  unsigned long long* counters = nullptr;  // [0] unused, [1] energy scratch
+  unsigned long long* counters = nullptr;  // sums, where no pinned block can be had
+  bool in_pool = false;                    // counted by pinned_handles
   unsigned long long* partials = nullptr;  // accepted moves, one running sum per sweep tile
   size_t npartials = 0;
   uint64_t accepted_base = 0;              // accepted moves folded in from earlier tile shapes
@@ -55,7 +56,6 @@ struct kk_sim {
   kk::TileConfig tile{};
   kk::CclBuffers ccl{};
   bool ccl_ready = false;
-  uint32_t* hist_host = nullptr;  // pinned image of the histogram block (hist_enqueue)
   int geom = 0;                          // 0 square torus; triangular helical int8 ring: 1 with the
                                          // conflict-free 16 classes, 2 with the literal MPKK cover
   kk::TriAccept tacc{};                  // triangular thresholds
@@ -69,16 +69,40 @@ struct kk_sim {
 };
 
 namespace kk {
+// A block of pinned host memory that kernels write results into, leased for
+// one call: at most kPinnedKept are kept between calls, for all handles,
+// threads and streams together, and none once the last handle is gone.  A lease
+// that ends before its stream has drained frees the block instead.
+constexpr size_t kPinnedLattice = (size_t)1 << 20;  // lattices up to this many sites are read back through it
+constexpr size_t kPinnedSums = 0, kPinnedImage = 65536, kPinnedSites = 131072;  // offsets in a block
+constexpr size_t kPinnedBytes = kPinnedSites + kPinnedLattice;
+constexpr size_t kPinnedKept = 4;
+class Pinned {
+ public:
+  Pinned();
+  ~Pinned();
+  Pinned(const Pinned&) = delete;
+  Pinned& operator=(const Pinned&) = delete;
+  explicit operator bool() const { return p_ != nullptr; }
+  unsigned long long* sums(int i) const { return reinterpret_cast<unsigned long long*>(p_ + kPinnedSums) + i * kMaxSums; }
+  uint32_t* image() const { return reinterpret_cast<uint32_t*>(p_ + kPinnedImage); }
+  uint8_t* sites() const { return p_ + kPinnedSites; }
+  void drained() { idle_ = true; }  // nothing on the device writes into it any more
+
+ private:
+  uint8_t* p_;
+  bool idle_ = false;
+};
+void pinned_handles(int change);  // handles created less destroyed
+
 // helpers shared with the batch engine (kk_api.cpp)
 kk_status device_alloc(void** p, size_t bytes);
 // cluster histograms: a handle's labelling is enqueued on a stream and read
 // back after that stream drains, so that many handles share one wait
 constexpr unsigned kHistBigPrefix = 1024;  // large sizes copied back with the histogram
 bool hist_cached(const kk_sim* h, int species);
-kk_status hist_buffers(kk_sim* h);  // the labelling buffers and the pinned image, made once
-kk_status hist_enqueue(kk_sim* h, int species, hipStream_t stream);
-kk_status hist_finish(kk_sim* h, int species);
-kk_status fold_accepted(kk_sim* h, const unsigned long long* dev_counts, size_t n);
+kk_status hist_buffers(kk_sim* h);  // the labelling buffers, made once
+kk_status hist_finish(kk_sim* h, int species, const uint32_t* image);  // image: the result block on the host
 
 // batch engine over borrowed handles (kk_batch.cpp), used by the job server:
 // the batch never destroys these sims; replan after the set changes.

@@ -64,11 +64,14 @@ size_t batch_tile_lds_bytes();
 size_t batch_resident_lds_bytes(int L);
 
 // N_AB (unlike nearest-neighbour bonds) added into *out.
-hipError_t launch_energy(const void* lat, int layout, int L, unsigned long long* out, hipStream_t stream);
+// nsum NULL: the sum is added to *out.  Else each of the *nsum workgroups (at most
+// kMaxSums) writes its own word of out, host memory that the caller adds up.
+constexpr int kMaxSums = 2048;
+hipError_t launch_energy(const void* lat, int layout, int L, unsigned long long* out, int* nsum, hipStream_t stream);
 
 // Count of sites whose randomly drawn neighbour has the same type, added into *out.
 hipError_t launch_similar_sampled(const void* lat, int layout, int L, uint32_t k0, uint32_t k1, uint64_t t,
-                                 unsigned long long* out, hipStream_t stream);
+                                 unsigned long long* out, int* nsum, hipStream_t stream);
 
 // Initial placement.
 hipError_t launch_init_keys(uint64_t* keys, int L, int H, uint32_t k0, uint32_t k1, hipStream_t stream);
@@ -102,6 +105,8 @@ hipError_t launch_fill_segregated(void* lat, int layout, int L, int H, uint64_t 
 
 // int8 <-> bit-packed conversion on the device (bit-packed needs L % 32 == 0).
 hipError_t launch_pack(const uint8_t* in, uint32_t* out, int L, hipStream_t stream);
+hipError_t launch_sum_words(const unsigned long long* in, size_t n, unsigned long long* out, hipStream_t stream);
+hipError_t launch_copy_bytes(const void* in, void* out, size_t n, hipStream_t stream);  // both 16-byte aligned
 hipError_t launch_unpack(const uint32_t* in, uint8_t* out, int L, hipStream_t stream);
 
 }  // namespace kk

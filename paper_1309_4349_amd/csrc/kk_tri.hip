@@ -140,8 +140,8 @@ __global__ __launch_bounds__(256) void mpkk_iter(const uint8_t* __restrict__ in,
   block_count(cnt, red, partials);
 }
 
-// One atomic per workgroup of 256 threads (see kk_aux.hip's summing passes).
-__device__ __forceinline__ void add_block_sum(uint32_t v, unsigned long long* out) {
+// One word or one atomic per workgroup of 256 threads, as kk_aux.hip's summing passes.
+__device__ __forceinline__ void add_block_sum(uint32_t v, unsigned long long* out, bool spread) {
   __shared__ unsigned long long part[4];
   unsigned long long a = v;
   for (int off = 32; off > 0; off >>= 1) a += __shfl_down(a, off, 64);
@@ -149,13 +149,15 @@ __device__ __forceinline__ void add_block_sum(uint32_t v, unsigned long long* ou
   __syncthreads();
   if (threadIdx.x == 0) {
     const unsigned long long tot = part[0] + part[1] + part[2] + part[3];
-    if (tot) atomicAdd(out, tot);
+    if (spread) out[blockIdx.x] = tot;
+    else if (tot) atomicAdd(out, tot);
   }
 }
 
 // N_AB over the 3N bonds (i, i+1), (i, i+L), (i, i+L-1): four sites at a time
 // where their neighbours lie before the ring's end, else one by one.
-__global__ __launch_bounds__(256) void tri_energy(const uint8_t* s, uint32_t L, uint32_t N, unsigned long long* out) {
+__global__ __launch_bounds__(256) void tri_energy(const uint8_t* s, uint32_t L, uint32_t N, unsigned long long* out,
+                                                  bool spread) {
   uint32_t a = 0;
   for (uint32_t q = blockIdx.x * blockDim.x + threadIdx.x; q < (N + 3u) / 4u; q += gridDim.x * blockDim.x) {
     const uint32_t i = 4u * q;
@@ -173,12 +175,12 @@ __global__ __launch_bounds__(256) void tri_energy(const uint8_t* s, uint32_t L, 
       }
     }
   }
-  add_block_sum(a, out);
+  add_block_sum(a, out, spread);
 }
 
 // Random-neighbour draw: site i uses word i%4 of block (i/4, 1, t_lo, t_hi28 | 5<<28).
 __global__ __launch_bounds__(256) void tri_similar(const uint8_t* s, uint32_t L, uint32_t N, uint32_t k0, uint32_t k1,
-                                                   uint64_t t, unsigned long long* out) {
+                                                   uint64_t t, unsigned long long* out, bool spread) {
   const uint32_t Q = (N + 3u) >> 2;
   const uint32_t tl = (uint32_t)t, th = ctr_hi(t, kTagObserve);
   uint32_t a = 0;
@@ -193,7 +195,7 @@ __global__ __launch_bounds__(256) void tri_similar(const uint8_t* s, uint32_t L,
       a += (s[i] == s[tri_nb(i, d, L, N)]);
     }
   }
-  add_block_sum(a, out);
+  add_block_sum(a, out, spread);
 }
 
 int tri_grid(size_t n) {
@@ -219,17 +221,20 @@ hipError_t launch_mpkk_iteration(const uint8_t* in, uint8_t* out, int L, int H, 
   return hipGetLastError();
 }
 
-hipError_t launch_tri_energy(const uint8_t* lat, int L, int H, unsigned long long* out, hipStream_t stream) {
+hipError_t launch_tri_energy(const uint8_t* lat, int L, int H, unsigned long long* out, int* nsum, hipStream_t stream) {
   const uint32_t N = (uint32_t)L * (uint32_t)H;
-  hipLaunchKernelGGL(tri_energy, dim3(min(tri_grid((N + 3) / 4), 512)), dim3(256), 0, stream, lat, (uint32_t)L, N, out);
+  const int n = min(tri_grid((N + 3) / 4), 512);
+  if (nsum) *nsum = n;
+  hipLaunchKernelGGL(tri_energy, dim3(n), dim3(256), 0, stream, lat, (uint32_t)L, N, out, nsum != nullptr);
   return hipGetLastError();
 }
 
 hipError_t launch_tri_similar(const uint8_t* lat, int L, int H, uint32_t k0, uint32_t k1, uint64_t t,
-                              unsigned long long* out, hipStream_t stream) {
+                              unsigned long long* out, int* nsum, hipStream_t stream) {
   const uint32_t N = (uint32_t)L * (uint32_t)H;
-  hipLaunchKernelGGL(tri_similar, dim3(min(tri_grid((N + 3) / 4), 2048)), dim3(256), 0, stream, lat, (uint32_t)L, N, k0, k1, t,
-                     out);
+  const int n = min(tri_grid((N + 3) / 4), 2048);
+  if (nsum) *nsum = n;
+  hipLaunchKernelGGL(tri_similar, dim3(n), dim3(256), 0, stream, lat, (uint32_t)L, N, k0, k1, t, out, nsum != nullptr);
   return hipGetLastError();
 }
 

@@ -176,8 +176,9 @@ hipError_t launch_mpkk_tile_step(const uint8_t* in, uint8_t* out, int L, int H, 
                                  hipStream_t stream);
 hipError_t launch_mpkk_iteration(const uint8_t* in, uint8_t* out, int L, int H, uint32_t k0, uint32_t k1, uint64_t t,
                                  int j, const TriAccept& acc, unsigned long long* partials, hipStream_t stream);
-hipError_t launch_tri_energy(const uint8_t* lat, int L, int H, unsigned long long* out, hipStream_t stream);
+// Sums as launch_energy's (kk_kernels.hpp).
+hipError_t launch_tri_energy(const uint8_t* lat, int L, int H, unsigned long long* out, int* nsum, hipStream_t stream);
 hipError_t launch_tri_similar(const uint8_t* lat, int L, int H, uint32_t k0, uint32_t k1, uint64_t t,
-                              unsigned long long* out, hipStream_t stream);
+                              unsigned long long* out, int* nsum, hipStream_t stream);
 
 }  // namespace kk
