@@ -193,8 +193,8 @@ kk_status dmalloc(kk_sim* h, void** p, size_t bytes) {
   return KK_OK;
 }
 
-// Uniform random subset of exactly n1 sites: radix select of the n1-th
-// smallest Philox key, then ties (equal 64-bit keys) broken by site index.
+// Uniform random subset of exactly n1 sites: those of the n1 smallest Philox
+// keys, ties (equal 64-bit keys) broken by site index.
 kk_status place_initial(kk_sim* h) {
   const int L = h->L, H = h->H;
   const size_t N = (size_t)L * H;
@@ -211,74 +211,30 @@ kk_status place_initial(kk_sim* h) {
     KK_HIP(hipStreamSynchronize(h->stream));
     return KK_OK;
   }
-  uint64_t* keys = nullptr;
-  unsigned* hist = nullptr;
-  kk_status st = dmalloc(h, (void**)&keys, N * sizeof(uint64_t));
+  uint8_t* scratch = nullptr;
+  const size_t sbytes = (place_bytes(N) + 15) & ~(size_t)15;
+  kk_status st = dmalloc(h, (void**)&scratch, sbytes + sizeof(uint32_t));
   if (st != KK_OK) return st;
-  const unsigned eq_cap = 4096;
-  st = dmalloc(h, (void**)&hist, (256 + 1 + eq_cap) * sizeof(unsigned));
-  if (st != KK_OK) {
-    (void)hipFree(keys);
-    return st;
-  }
-  unsigned* eq_count = hist + 256;
-  uint32_t* eq_list = reinterpret_cast<uint32_t*>(hist + 257);
-  auto fail = [&](const char* what, hipError_t e) {
-    (void)hipFree(keys);
-    (void)hipFree(hist);
-    h->poisoned = true;
-    return set_error(KK_EDEVICE, "%s failed: %s", what, hipGetErrorString(e));
-  };
-  hipError_t e = launch_init_keys(keys, L, H, h->k0, h->k1, h->stream);
-  if (e != hipSuccess) return fail("init_keys", e);
-  uint64_t prefix = 0, need = n1;
-  for (int shift = 56; shift >= 0; shift -= 8) {
-    unsigned hh[256];
-    if ((e = hipMemsetAsync(hist, 0, 256 * sizeof(unsigned), h->stream)) != hipSuccess) return fail("memset", e);
-    if ((e = launch_radix_hist(keys, N, prefix, shift, hist, h->stream)) != hipSuccess) return fail("radix_hist", e);
-    if ((e = hipMemcpyAsync(hh, hist, sizeof hh, hipMemcpyDeviceToHost, h->stream)) != hipSuccess)
-      return fail("copy hist", e);
-    if ((e = hipStreamSynchronize(h->stream)) != hipSuccess) return fail("sync", e);
-    uint64_t cum = 0;
-    int d = 0;
-    for (; d < 256; ++d) {
-      if (cum + hh[d] >= need) break;
-      cum += hh[d];
+  uint32_t* dlen = reinterpret_cast<uint32_t*>(scratch + sbytes);
+  uint32_t len = 0;
+  hipError_t e;
+  {
+    Pinned pin;
+    e = launch_place(L, H, h->layout, n1, h->k0, h->k1, dst, scratch, pin ? pin.image() : dlen, h->stream);
+    if (e == hipSuccess && !pin) e = hipMemcpyAsync(&len, dlen, sizeof len, hipMemcpyDeviceToHost, h->stream);
+    if (e == hipSuccess) e = hipStreamSynchronize(h->stream);
+    if (e == hipSuccess && pin) {
+      pin.drained();
+      len = *pin.image();
     }
-    prefix |= (uint64_t)d << shift;
-    need -= cum;
   }
-  // sites with key < prefix are ones; `need` of the sites with key == prefix too
-  if ((e = hipMemsetAsync(eq_count, 0, sizeof(unsigned), h->stream)) != hipSuccess) return fail("memset", e);
-  if ((e = launch_init_mark(keys, L, H, h->layout, prefix, dst, eq_count, eq_list, eq_cap, h->stream)) != hipSuccess)
-    return fail("init_mark", e);
-  unsigned neq = 0;
-  if ((e = hipMemcpyAsync(&neq, eq_count, sizeof neq, hipMemcpyDeviceToHost, h->stream)) != hipSuccess)
-    return fail("copy eq", e);
-  if ((e = hipStreamSynchronize(h->stream)) != hipSuccess) return fail("sync", e);
-  if (neq > eq_cap || need > neq) {
-    (void)hipFree(keys);
-    (void)hipFree(hist);
-    return set_error(KK_EDEVICE, "initial placement: %u equal keys (cap %u), need %llu", neq, eq_cap,
-                     (unsigned long long)need);
+  (void)hipFree(scratch);
+  if (e != hipSuccess) {
+    h->poisoned = true;
+    return set_error(KK_EDEVICE, "initial placement failed: %s", hipGetErrorString(e));
   }
-  std::vector<uint32_t> idx(neq);
-  if (neq) {
-    if ((e = hipMemcpyAsync(idx.data(), eq_list, neq * sizeof(uint32_t), hipMemcpyDeviceToHost, h->stream)) !=
-        hipSuccess)
-      return fail("copy eq list", e);
-    if ((e = hipStreamSynchronize(h->stream)) != hipSuccess) return fail("sync", e);
-    std::sort(idx.begin(), idx.end());
-    idx.resize((size_t)need);
-    if ((e = hipMemcpyAsync(eq_list, idx.data(), idx.size() * sizeof(uint32_t), hipMemcpyHostToDevice,
-                            h->stream)) != hipSuccess)
-      return fail("upload ties", e);
-    if ((e = launch_set_sites(eq_list, (unsigned)idx.size(), L, h->layout, dst, h->stream)) != hipSuccess)
-      return fail("set_sites", e);
-  }
-  if ((e = hipStreamSynchronize(h->stream)) != hipSuccess) return fail("sync", e);
-  (void)hipFree(keys);
-  (void)hipFree(hist);
+  if (len > place_cap(N))
+    return set_error(KK_EDEVICE, "initial placement: %u sites to order (cap %zu)", len, place_cap(N));
   return KK_OK;
 }
 

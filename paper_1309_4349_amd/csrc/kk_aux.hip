@@ -109,72 +109,167 @@ __global__ __launch_bounds__(256) void similar_sampled(const void* lat, int layo
 // ---------------------------------------------------------------------------
 // Initial placement: each site's 64-bit key is Philox block (y, x, 0, tag 4)
 // words 0 and 1; the n1 sites with the smallest (key, index) get type 1.
-// The n1-th smallest key is found by an 8-pass MSB-first radix select.
+//  1. place_count_keys counts the keys by their top 10 bits.
+//  2. place_mark finds the bin that holds the n1-th smallest key, gives the sites
+//     below it type 1 and lists the sites in it (one in 1024).
+//  3. place_select, one workgroup, takes the rest of them by a radix select over
+//     the remaining key bits, then the index.
+// The keys are computed again in the second pass instead of being kept: a block
+// of Philox per site is cheaper than 8 bytes written and read.  Nothing returns
+// to the host between the passes.  Eight passes over stored keys, each with its
+// histogram on the host, made a 64^2 handle 0.46 ms and a 4096^2 one 1.3 ms to
+// create; now 0.25 and 0.74, allocations for the most part.
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void init_keys(uint64_t* keys, int L, int H, uint32_t k0, uint32_t k1) {
-  const size_t n = (size_t)L * H;
-  for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) {
-    const uint32_t y = (uint32_t)(i / L), x = (uint32_t)(i - (size_t)y * L);
-    const Philox4 r = philox10(y, x, 0u, kTagInit << 28, k0, k1);
-    keys[i] = ((uint64_t)r.x << 32) | (uint64_t)r.y;
-  }
+constexpr int kPlaceBins = 1024;
+
+struct PlaceList {
+  uint64_t* key;
+  uint32_t* idx;
+  unsigned* count;
+  uint32_t cap;
+};
+
+__device__ __forceinline__ uint64_t place_key(uint32_t i, uint32_t L, uint32_t k0, uint32_t k1) {
+  const uint32_t y = i / L;
+  const Philox4 r = philox10(y, i - y * L, 0u, kTagInit << 28, k0, k1);
+  return ((uint64_t)r.x << 32) | (uint64_t)r.y;
 }
 
-__global__ __launch_bounds__(256) void radix_hist(const uint64_t* keys, size_t n, uint64_t prefix, int shift,
-                                                  unsigned* hist) {
-  __shared__ unsigned h[256];
-  h[threadIdx.x] = 0;
+__global__ __launch_bounds__(1024) void place_count_keys(uint32_t L, uint32_t n, uint32_t k0, uint32_t k1,
+                                                         unsigned* hist) {
+  __shared__ unsigned h[kPlaceBins];
+  h[threadIdx.x] = 0u;
   __syncthreads();
-  const int hs = shift + 8;
-  for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) {
-    const uint64_t k = keys[i];
-    if (hs >= 64 || (k >> hs) == (prefix >> hs)) atomicAdd(&h[(k >> shift) & 0xFFu], 1u);
-  }
+  for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x)
+    atomicAdd(&h[place_key(i, L, k0, k1) >> 54], 1u);
   __syncthreads();
   if (h[threadIdx.x]) atomicAdd(&hist[threadIdx.x], h[threadIdx.x]);
 }
 
-__global__ __launch_bounds__(256) void init_mark(const uint64_t* keys, int L, int H, int layout, uint64_t kth,
-                                                 void* lat, unsigned* eq_count, uint32_t* eq_list,
-                                                 unsigned eq_cap) {
-  if (layout == kLayoutBits) {
-    const int wpr = L >> 5;
-    const size_t nw = (size_t)H * wpr;
-    for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < nw; i += (size_t)gridDim.x * blockDim.x) {
-      uint32_t v = 0;
-      const size_t base = i * 32;  // words tile rows exactly, so site index = 32 * word + bit
-      for (int b = 0; b < 32; ++b) {
-        const uint64_t k = keys[base + b];
-        if (k < kth) v |= 1u << b;
-        else if (k == kth) {
-          const unsigned slot = atomicAdd(eq_count, 1u);
-          if (slot < eq_cap) eq_list[slot] = (uint32_t)(base + b);
-        }
-      }
-      static_cast<uint32_t*>(lat)[i] = v;
-    }
-  } else {
-    const size_t n = (size_t)L * H;
-    for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) {
-      const uint64_t k = keys[i];
-      uint8_t v = 0;
-      if (k < kth) v = 1;
-      else if (k == kth) {
-        const unsigned slot = atomicAdd(eq_count, 1u);
-        if (slot < eq_cap) eq_list[slot] = (uint32_t)i;
-      }
-      static_cast<uint8_t*>(lat)[i] = v;
-    }
+// Of NB counts (one per thread of the first NB), the bin that holds the
+// need-th entry, and how many of its entries are needed.
+struct PlaceBin {
+  uint32_t bin, need, count;
+};
+template <int NB>
+__device__ __forceinline__ PlaceBin place_bin(unsigned c, uint32_t need) {
+  __shared__ uint32_t sum[NB / 64];
+  __shared__ PlaceBin found;
+  const int tid = (int)threadIdx.x, lane = tid & 63;
+  uint32_t upto = c;
+  for (int off = 1; off < 64; off <<= 1) {
+    const uint32_t o = __shfl_up(upto, off, 64);
+    upto += lane >= off ? o : 0u;
   }
+  if (tid < NB && lane == 63) sum[tid >> 6] = upto;
+  __syncthreads();
+  if (tid < NB) {
+    for (int w = 0; w < (tid >> 6); ++w) upto += sum[w];
+    if (upto >= need && upto - c < need) found = PlaceBin{(uint32_t)tid, need - (upto - c), c};
+  }
+  __syncthreads();
+  const PlaceBin f = found;
+  __syncthreads();
+  return f;
 }
 
-__global__ void set_sites(const uint32_t* idx, unsigned n, int L, int layout, void* lat) {
-  const unsigned i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  const uint32_t s = idx[i];
-  if (layout == kLayoutBits) atomicOr(&static_cast<uint32_t*>(lat)[s >> 5], 1u << (s & 31u));
-  else static_cast<uint8_t*>(lat)[s] = 1;
-  (void)L;
+// The list of sites in the bin: key and index.  A workgroup gathers its own
+// first (one addition to the list's length instead of one per site).
+__global__ __launch_bounds__(1024) void place_mark(uint32_t L, uint32_t n, int layout, uint32_t n1, uint32_t k0,
+                                                   uint32_t k1, const unsigned* hist, void* lat, PlaceList list) {
+  constexpr uint32_t kMine = 1024;
+  __shared__ uint64_t key_s[kMine];
+  __shared__ uint32_t idx_s[kMine];
+  __shared__ uint32_t mine, base;
+  if (threadIdx.x == 0) mine = 0u;
+  const PlaceBin b = place_bin<kPlaceBins>(hist[threadIdx.x], n1);
+  for (uint32_t i0 = blockIdx.x * blockDim.x; i0 < n; i0 += gridDim.x * blockDim.x) {
+    const uint32_t i = i0 + threadIdx.x;
+    const uint64_t k = i < n ? place_key(i, L, k0, k1) : ~0ull;
+    const uint32_t top = (uint32_t)(k >> 54);
+    const bool one = i < n && top < b.bin;
+    if (layout == kLayoutBits) {  // L is a multiple of 32: half a wavefront per word, all of it in range or none
+      const uint64_t m = __ballot(one);
+      if ((threadIdx.x & 31u) == 0u && i < n) static_cast<uint32_t*>(lat)[i >> 5] = (uint32_t)(m >> (threadIdx.x & 32u));
+    } else if (i < n) {
+      static_cast<uint8_t*>(lat)[i] = (uint8_t)one;
+    }
+    if (i < n && top == b.bin) {
+      const uint32_t s = atomicAdd(&mine, 1u);
+      if (s < kMine) {
+        key_s[s] = k;
+        idx_s[s] = i;
+      } else {
+        const uint32_t g = atomicAdd(list.count, 1u);
+        if (g < list.cap) {
+          list.key[g] = k;
+          list.idx[g] = i;
+        }
+      }
+    }
+  }
+  __syncthreads();
+  const uint32_t m = min(mine, kMine);
+  if (threadIdx.x == 0) base = atomicAdd(list.count, m);
+  __syncthreads();
+  for (uint32_t s = threadIdx.x; s < m; s += blockDim.x)
+    if (base + s < list.cap) {
+      list.key[base + s] = key_s[s];
+      list.idx[base + s] = idx_s[s];
+    }
+}
+
+// One workgroup: digits of 8 bits, first the key's lower 56, then the index's
+// 32, until a digit's bin is needed whole.  *length is the list's full length.
+__global__ __launch_bounds__(1024) void place_select(int layout, uint32_t n1, const unsigned* hist, void* lat,
+                                                     PlaceList list, uint32_t* length) {
+  __shared__ unsigned h[256];
+  uint32_t need = place_bin<kPlaceBins>(hist[threadIdx.x], n1).need;
+  const uint32_t m = min(*list.count, list.cap);
+  if (threadIdx.x == 0) *length = *list.count;
+  uint64_t pk = m ? list.key[0] & 0xFF00000000000000ull : 0ull;  // the digits found so far (the bin has the first)
+  uint32_t pi = 0u;
+  // whether an entry agrees with the digits before this level, and its digit
+  auto digit = [&](int level, uint64_t k, uint32_t i, bool& in) {
+    if (level < 7) {
+      in = ((k ^ pk) >> (56 - 8 * level)) == 0;
+      return (uint32_t)(k >> (48 - 8 * level)) & 255u;
+    }
+    const int sh = 24 - 8 * (level - 7);
+    in = k == pk && ((uint64_t)(i ^ pi) >> (sh + 8)) == 0;
+    return (i >> sh) & 255u;
+  };
+  int level = 0;
+  for (; level < 11; ++level) {
+    if (threadIdx.x < 256) h[threadIdx.x] = 0u;
+    __syncthreads();
+    for (uint32_t s = threadIdx.x; s < m; s += blockDim.x) {
+      bool in;
+      const uint32_t d = digit(level, list.key[s], list.idx[s], in);
+      if (in) atomicAdd(&h[d], 1u);
+    }
+    __syncthreads();
+    const PlaceBin f = place_bin<256>(threadIdx.x < 256 ? h[threadIdx.x] : 0u, need);
+    if (level < 7) pk |= (uint64_t)f.bin << (48 - 8 * level);
+    else pi |= f.bin << (24 - 8 * (level - 7));
+    need = f.need;
+    if (f.need == f.count) break;
+  }
+  level = min(level, 10);
+  for (uint32_t s = threadIdx.x; s < m; s += blockDim.x) {
+    const uint64_t k = list.key[s];
+    const uint32_t i = list.idx[s];
+    bool take;
+    if (level < 7) {
+      take = (k >> (48 - 8 * level)) <= (pk >> (48 - 8 * level));
+    } else {
+      const int sh = 24 - 8 * (level - 7);
+      take = k < pk || (k == pk && (i >> sh) <= (pi >> sh));
+    }
+    if (!take) continue;
+    if (layout == kLayoutBits) atomicOr(&static_cast<uint32_t*>(lat)[i >> 5], 1u << (i & 31u));
+    else static_cast<uint8_t*>(lat)[i] = 1;
+  }
 }
 
 // Segregated start: the first n1 sites in index order i = y*L + x hold type 1
@@ -611,28 +706,26 @@ hipError_t launch_copy_bytes(const void* in, void* out, size_t n, hipStream_t st
   return hipGetLastError();
 }
 
-hipError_t launch_init_keys(uint64_t* keys, int L, int H, uint32_t k0, uint32_t k1, hipStream_t stream) {
-  hipLaunchKernelGGL(init_keys, dim3(grid_for((size_t)L * H, 256)), dim3(256), 0, stream, keys, L, H, k0, k1);
-  return hipGetLastError();
-}
+size_t place_cap(size_t n) { return n / (kPlaceBins / 2) + 1024; }
+// key and index of every listed site, the list's length and the key counts
+size_t place_bytes(size_t n) { return place_cap(n) * 12 + (kPlaceBins + 2) * sizeof(unsigned); }
 
-hipError_t launch_radix_hist(const uint64_t* keys, size_t n, uint64_t prefix, int shift, unsigned* hist256,
-                             hipStream_t stream) {
-  hipLaunchKernelGGL(radix_hist, dim3(grid_for(n, 256)), dim3(256), 0, stream, keys, n, prefix, shift, hist256);
-  return hipGetLastError();
-}
-
-hipError_t launch_init_mark(const uint64_t* keys, int L, int H, int layout, uint64_t kth, void* lat, unsigned* eq_count,
-                            uint32_t* eq_list, unsigned eq_cap, hipStream_t stream) {
-  const size_t n = layout == kLayoutBits ? (size_t)H * (L >> 5) : (size_t)L * H;
-  hipLaunchKernelGGL(init_mark, dim3(grid_for(n, 256)), dim3(256), 0, stream, keys, L, H, layout, kth, lat, eq_count,
-                     eq_list, eq_cap);
-  return hipGetLastError();
-}
-
-hipError_t launch_set_sites(const uint32_t* idx, unsigned n, int L, int layout, void* lat, hipStream_t stream) {
-  if (n == 0) return hipSuccess;
-  hipLaunchKernelGGL(set_sites, dim3((n + 255) / 256), dim3(256), 0, stream, idx, n, L, layout, lat);
+hipError_t launch_place(int L, int H, int layout, size_t n1, uint32_t k0, uint32_t k1, void* lat, void* scratch,
+                        uint32_t* length, hipStream_t stream) {
+  const uint32_t n = (uint32_t)L * (uint32_t)H;
+  PlaceList list;
+  list.cap = (uint32_t)place_cap(n);
+  list.key = static_cast<uint64_t*>(scratch);
+  unsigned* hist = reinterpret_cast<unsigned*>(list.key + list.cap);
+  list.count = hist + kPlaceBins;
+  list.idx = list.count + 2;
+  hipError_t e = hipMemsetAsync(hist, 0, (kPlaceBins + 1) * sizeof(unsigned), stream);
+  if (e != hipSuccess) return e;
+  const int grid = std::min(grid_for(n, 1024), 512);
+  hipLaunchKernelGGL(place_count_keys, dim3(grid), dim3(1024), 0, stream, (uint32_t)L, n, k0, k1, hist);
+  hipLaunchKernelGGL(place_mark, dim3(grid), dim3(1024), 0, stream, (uint32_t)L, n, layout, (uint32_t)n1, k0, k1, hist,
+                     lat, list);
+  hipLaunchKernelGGL(place_select, dim3(1), dim3(1024), 0, stream, layout, (uint32_t)n1, hist, lat, list, length);
   return hipGetLastError();
 }
 

@@ -73,13 +73,13 @@ hipError_t launch_energy(const void* lat, int layout, int L, unsigned long long*
 hipError_t launch_similar_sampled(const void* lat, int layout, int L, uint32_t k0, uint32_t k1, uint64_t t,
                                  unsigned long long* out, int* nsum, hipStream_t stream);
 
-// Initial placement.
-hipError_t launch_init_keys(uint64_t* keys, int L, int H, uint32_t k0, uint32_t k1, hipStream_t stream);
-hipError_t launch_radix_hist(const uint64_t* keys, size_t n, uint64_t prefix, int shift, unsigned* hist256,
-                             hipStream_t stream);
-hipError_t launch_init_mark(const uint64_t* keys, int L, int H, int layout, uint64_t kth, void* lat, unsigned* eq_count,
-                            uint32_t* eq_list, unsigned eq_cap, hipStream_t stream);
-hipError_t launch_set_sites(const uint32_t* idx, unsigned n, int L, int layout, void* lat, hipStream_t stream);
+// Initial placement: n1 of the L x H sites (0 < n1 < L H).  scratch: place_bytes.
+// *length (device or pinned memory) becomes the number of sites the selection
+// had to order; beyond place_cap the placement is incomplete.
+size_t place_cap(size_t n);
+size_t place_bytes(size_t n);
+hipError_t launch_place(int L, int H, int layout, size_t n1, uint32_t k0, uint32_t k1, void* lat, void* scratch,
+                        uint32_t* length, hipStream_t stream);
 
 // Connected components of one species (4-neighbour, periodic) and their size histogram.
 struct CclBuffers {

@@ -69,10 +69,12 @@ int resolve_layout(const kk_replica& r) {
 // Upper bound of the device bytes a job's handle holds at any time.  Always:
 // two lattice buffers, the energy counters and one accepted-move sum per
 // sweep tile.  On top, the larger of the two phases that need scratch:
-// placement (8-byte keys per site and the radix tables, freed after it) and
-// retirement (the cluster-labelling arrays, 4 bytes per site and 1 KiB per
-// 64 x 64 tile -- counted as 8 bytes per site -- plus the size tables, and for a bit-packed lattice kept on the host the N-byte unpack
-// buffer of kk_get_lattice, taken while the labelling arrays are still held).
+// placement (its list, 12 bytes per 512 sites, and key counts, freed after it)
+// and retirement (the cluster-labelling arrays, 4 bytes per site and 1 KiB per
+// 64 x 64 tile, plus the size tables, and for a bit-packed lattice kept on the
+// host the N-byte unpack buffer of kk_get_lattice, taken while the labelling
+// arrays are still held).  Both are counted as 8 bytes per site, more than
+// either takes.
 // 64 KiB of slack covers the job's share of the batch tables.
 size_t job_footprint(const kk_replica& r, bool keep_lattice) {
   const int layout = resolve_layout(r);
