@@ -75,27 +75,30 @@ void default_tile(int L, int layout, TileConfig* tc) {
     tc->ku = units > max_threads(1) ? 2 : 1;
     return;
   }
-  // Largest tile (least halo work) that still gives the GPU enough workgroups;
-  // two units per thread only when the tiles saturate the device.
-  static const int cand[][2] = {{16, 128}, {8, 128}, {8, 64}, {4, 64}, {2, 64}, {2, 32}, {2, 16}, {1, 16}};
-  const int ncand = (int)(sizeof cand / sizeof cand[0]);
-  int pick = ncand - 1;
-  long tiles = 0;
-  for (int i = 0; i < ncand; ++i) {
-    const int tww = std::min(cand[i][0], (L + 31) / 32);
-    const int th = std::min(cand[i][1], L);
-    tiles = (long)((L + 32 * tww - 1) / (32 * tww)) * ((L + th - 1) / th);
-    if (tiles >= 128) {
-      pick = i;
-      break;
+  // The tile of least modelled time for a launch of two sweeps: rounds of 256
+  // workgroups (one per CU), each a fixed part -- launch, staging, one row of
+  // draws, 16 phases of latency -- plus its units of both sweeps; 1000 units take
+  // as long as the fixed part.  Against the widest tile that made 128 workgroups
+  // (us per sweep, both with two sweeps per launch): 1536^2 (8, 64) 9.3, (4, 76)
+  // 6.6; 2048^2 (8, 128) 10.9, (4, 128) 8.7; 1700^2 int8 14.2 and 10.3; 1024^2
+  // (4, 64) 6.4, (2, 64) 5.5; 6144^2 40.6 and 35.4; level below 1000 and at
+  // 4096^2.  Sides of 2692 .. 3968 had no tile that a launch could take.
+  long best = 0;
+  tc->cyclic = false;
+  for (int tww = 1; tww <= 16; tww *= 2) {
+    if (tww > (L + 31) / 32) break;
+    for (int th = 4 * std::min(3, L / 4); th <= std::min(L, 256); th += 4) {
+      const int C = tww + 2, first = (th + 60) / 2 * C, second = (th + 28) / 2 * C;  // units of the two sweeps
+      if (first > 2048 || second > 2 * max_threads(2)) break;
+      const long tiles = (long)((L + 32 * tww - 1) / (32 * tww)) * ((L + th - 1) / th);
+      const long cost = (tiles + 255) / 256 * (1000 + first + second);
+      if (best != 0 && cost >= best) continue;
+      best = cost;
+      tc->tww = tww;
+      tc->th = th;
+      tc->ku = second > max_threads(1) ? 2 : 1;
     }
   }
-  tc->cyclic = false;
-  tc->tww = std::min(cand[pick][0], (L + 31) / 32);
-  tc->th = std::min(cand[pick][1], L);
-  // Two units per thread pay off only when the tiles oversubscribe the device;
-  // small lattices are latency-bound and run faster with one.
-  tc->ku = (tiles >= 256 && L >= 2048) ? 2 : 1;
 }
 
 // Fill the geometry fields of p for lattice side L and tile config tc.
@@ -378,7 +381,7 @@ kk_status enqueue_sweeps(kk_sim* h, uint64_t n, double* kernel_ms, uint64_t* lau
     p.k0 = h->k0;
     p.k1 = h->k1;
     p.acc = h->acc;
-    const uint64_t per_launch = h->tile.cyclic ? 256 : 1;
+    const uint64_t per_launch = (uint64_t)sweeps_per_launch(p, h->tile.cyclic, h->tile.ku);
     while (n > 0) {
       const uint64_t k = n < per_launch ? n : per_launch;
       p.src = h->lat[h->cur];

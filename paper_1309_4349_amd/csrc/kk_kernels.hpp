@@ -29,6 +29,8 @@ struct SweepParams {
 };
 
 hipError_t launch_sweep(const SweepParams& p, int layout, bool cyclic, int ku, int threads, hipStream_t stream);
+// Sweeps that one launch_sweep takes at most (p.nsweeps).
+int sweeps_per_launch(const SweepParams& p, bool cyclic, int ku);
 
 // Batch kernels.  Tiled replicas: one workgroup per (replica, tile) job and one
 // launch per sweep of the run.  A replica runs p.nsweeps sweeps from

@@ -121,7 +121,7 @@ extern "C" kk_status kk_sweep_noalloc(void* lattice, uint32_t L, uint32_t layout
   void* buf[2] = {lattice, other};
   int cur = 0;
   uint64_t t = t0, n = n_sweeps;
-  const uint64_t per_launch = tc.cyclic ? 256 : 1;
+  const uint64_t per_launch = (uint64_t)kk::sweeps_per_launch(p, tc.cyclic, tc.ku);
   while (n > 0) {
     const uint64_t k = n < per_launch ? n : per_launch;
     p.src = buf[cur];

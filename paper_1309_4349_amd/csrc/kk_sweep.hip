@@ -811,11 +811,29 @@ __device__ __forceinline__ unsigned wave_sum8(unsigned c) {
 // tiles have one or two waves, the chain of staging, draws and phases (400^2 12.9
 // -> 10.2 us, 1036^2 14.7 -> 12.6 us: loads without a branch between them, ties
 // in one list, spare lanes on words of their own).
+// Two sweeps in one launch: the window has 16 more rows on each side (its halo
+// columns, 32, are enough for two sweeps as they are), and the launch, the
+// staging and the stores are paid once.
+// kSideBySide: the first half_threads threads hold the first sweep's units,
+// which reach 16 rows beyond the tile's own halo, the rest the second's, so that
+// both sweeps' draws run at once (400^2 10.2 -> 6.6 us per sweep, 1036^2 12.6 ->
+// 9.2, 1024^2 9.3 -> 6.4, tiles unchanged).  kInTurn: all threads do one sweep,
+// then the other, for tiles whose two sweeps need more threads than a workgroup
+// has (4096^2 15.6 -> 14.3 us per sweep).
+enum HaloMode { kOneSweep, kSideBySide, kInTurn };
 // Returns the workgroup's accepted count for the tile interior (the same in
 // every thread).
+__host__ __device__ constexpr int halo_rows(int th, int ns) { return th + 32 * ns; }
+__host__ __device__ constexpr int halo_pairs(int th, int ns, int sweep) { return (halo_rows(th, ns - sweep) - 4) / 2; }
+// Threads for the units of one of the two sweeps.
+__host__ __device__ constexpr int half_threads(int th, int C, int KU, int sweep) {
+  return ((halo_pairs(th, 2, sweep) * C + KU - 1) / KU + 63) & ~63;
+}
 
-template <int LAYOUT, int TWW, int KU>
-__device__ __forceinline__ unsigned halo_tile_sweep(uint32_t* S, const SweepParams& p, int tile, uint32_t order) {
+template <int LAYOUT, int TWW, int KU, HaloMode MODE>
+__device__ __forceinline__ unsigned halo_tile_sweep(uint32_t* S, const SweepParams& p, int tile, uint32_t order0,
+                                                    uint32_t order1) {
+  constexpr int NS = MODE == kOneSweep ? 1 : 2;
   constexpr int C = HaloGeom<TWW>::C;
   constexpr int ST = HaloGeom<TWW>::ST;
   const int CP = C + 2;       // staged words per row (the pads included)
@@ -823,26 +841,34 @@ __device__ __forceinline__ unsigned halo_tile_sweep(uint32_t* S, const SweepPara
   const int tx = tile % p.tiles_x, ty = tile / p.tiles_x;
   constexpr int TW = TWW;
   const int X0 = tx * TW * 32, Y0 = ty * p.th;
-  const int XL = X0 - 32, YT = Y0 - 16;
+  const int XL = X0 - 32, YT = Y0 - 16 * NS;
   const int xend = min(X0 + TW * 32, p.L), yend = min(Y0 + p.th, p.L);
-  const int total = p.R * CP;
-  const uint64_t t = p.t0;
+  const int R = halo_rows(p.th, NS);
+  const int total = R * CP;
+  // side by side: the sweep this thread's units belong to, and its place among their threads
+  int mine = 0, tid = (int)threadIdx.x, nthreads = (int)blockDim.x;
+  if constexpr (MODE == kSideBySide) {
+    const int ta = half_threads(p.th, C, KU, 0);
+    mine = __builtin_amdgcn_readfirstlane(tid >= ta ? 1 : 0);
+    tid -= mine ? ta : 0;
+    nthreads = mine ? nthreads - ta : ta;
+  }
   // LDS words that can reach the interior: the left halo word, the interior
   // words and one halo word past them.  In a ragged last tile the words after
   // that behave like the zero pad of a full tile: they are neither loaded nor
   // computed (for L % 32 != 0 they would also sit off the 32-site segment grid).
   const int wneed = min(C, (xend - X0 + 31) / 32 + 2);
   // true (wrapped) row of every LDS row and true column of every LDS word
-  int* ytab = reinterpret_cast<int*>(S + p.R * ST + 16);
-  int* xtab = ytab + p.R;
-  for (int i = threadIdx.x; i < p.R + C; i += blockDim.x) {
-    if (i < p.R) ytab[i] = imod(YT + i, p.L);
-    else xtab[i - p.R] = imod(XL + 32 * (i - p.R), p.L);
+  int* ytab = reinterpret_cast<int*>(S + R * ST + 16);
+  int* xtab = ytab + R;
+  for (int i = threadIdx.x; i < R + C; i += blockDim.x) {
+    if (i < R) ytab[i] = imod(YT + i, p.L);
+    else xtab[i - R] = imod(XL + 32 * (i - R), p.L);
   }
   // the workgroup's accepted count, in the gap between the rows and the
   // tables; the tie lists after the tables
-  uint32_t* acc_total = S + p.R * ST;
-  TieList ties = tie_list(S + halo_tie_offset<TWW>(p.R));
+  uint32_t* acc_total = S + R * ST;
+  TieList ties = tie_list(S + halo_tie_offset<TWW>(R));
   if (threadIdx.x == 0) *acc_total = 0u;
   __syncthreads();
 
@@ -865,84 +891,89 @@ __device__ __forceinline__ unsigned halo_tile_sweep(uint32_t* S, const SweepPara
     S[r * ST + w + 1] = (w >= 0 && w < wneed) ? load_word_at<LAYOUT>(p, ytab[r], xtab[w]) : 0u;
   }
 
-  int base0[KU], yrow[KU * 2], xw[KU];  // LDS base; true row of each of the pair's rows; true x of bit 0
-  uint32_t okm[KU * 2];                 // class-0 centre pattern of each row (0 for a unit beyond the tile)
-  uint32_t imask[KU][2];
-  RowRand rr[KU][2];
-  int tie[KU][2];              // index of each row word's tie results
-  int ry[KU * 2], rx[KU * 2];  // true row and column of each of the thread's rows
-  bool okk[KU];
-#pragma unroll
-  for (int k = 0; k < KU; ++k) {
-    const int u = threadIdx.x + k * blockDim.x;
-    const bool in = u < p.nunits;
-    // A lane beyond the tile's units shares the place of an earlier unit, one
-    // each: its exchanges are empty, but xors of one wave to one LDS word run
-    // one after another, and 40 lanes on one word cost more than the phase.
-    const int v = in ? u : (u - p.nunits < p.nunits ? u - p.nunits : 0);
-    int q, wu;
-    if ((p.L & 31) == 0) {
-      q = v / C;
-      wu = v - q * C;
-    } else {
-      // off-grid lattices: the two edge words of every row gather their random
-      // planes from two or three segments; numbering them after all inner
-      // words confines that slower path to the last waves
-      const int nin = p.npairs * (C - 2);
-      if (v < nin) {
-        q = v / (C - 2);
-        wu = 1 + (v - q * (C - 2));
-      } else {
-        const int e = v - nin;
-        q = e >> 1;
-        wu = (e & 1) ? C - 1 : 0;
-      }
-    }
-    const bool ok = in && wu < wneed;
-    const int w = ok ? wu : 0;
-    const int r0 = 2 + 2 * q;
-    base0[k] = r0 * ST + wu + 1;  // also for a word past wneed, which holds the zero pad
-    yrow[2 * k] = ytab[r0];
-    yrow[2 * k + 1] = ytab[r0 + 1];
-    xw[k] = xtab[w];
-    // class a = 0 centres of a row with virtual y sit at x = y (mod 4); the
-    // virtual x of bit 0 is a multiple of 32
-    okm[2 * k] = ok ? (0x11111111u << ((YT + r0) & 3)) : 0u;
-    okm[2 * k + 1] = ok ? (0x11111111u << ((YT + r0 + 1) & 3)) : 0u;
-    const int Xw = XL + 32 * w;
-    uint32_t wm = 0u;
-    if (Xw + 32 > X0 && Xw < xend) {
-      const int lo = max(Xw, X0), hi = min(Xw + 32, xend);
-      const int n = hi - lo;
-      wm = (n == 32 ? 0xFFFFFFFFu : ((1u << n) - 1u)) << (lo - Xw);
-    }
-    okk[k] = ok;
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const int yv = YT + r0 + h;
-      imask[k][h] = (ok && yv >= Y0 && yv < yend) ? wm : 0u;
-      ry[2 * k + h] = ytab[r0 + h];
-      rx[2 * k + h] = xtab[w];
-    }
-  }
-  // row by row (a lane beyond the tile's units draws for a valid row and
-  // decides nothing: its centre masks are empty); a wave whose units of one
-  // index all lie beyond the tile skips them.  Drawing more rows at once, to
-  // overlap more Philox chains, measured slower: 16.3 us per 4096^2 sweep for a
-  // unit's two rows, 18.7 us for all four rows of a thread, against 16.2 us row
-  // by row.
-  auto draw_rows = [&](auto on_grid) {
+  // one sweep of the window: the thread's units, their draws, the phases
+  auto sweep = [&](int sw, auto first) {
+    const int npairs = halo_pairs(p.th, NS, sw), nunits = npairs * C;
+    const uint64_t t = p.t0 + (uint64_t)sw;
+    ties.n = 0u;
+    int base0[KU], yrow[KU * 2], xw[KU];  // LDS base; true row of each of the pair's rows; true x of bit 0
+    uint32_t okm[KU * 2];                 // class-0 centre pattern of each row (0 for a unit beyond the tile)
+    uint32_t imask[KU][2];
+    RowRand rr[KU][2];
+    int tie[KU][2];              // index of each row word's tie results
+    int ry[KU * 2], rx[KU * 2];  // true row and column of each of the thread's rows
+    bool okk[KU];
 #pragma unroll
     for (int k = 0; k < KU; ++k) {
-      if (__any(okk[k])) {
-#pragma unroll
-        for (int h = 0; h < 2; ++h)
-          tie[k][h] = rand_row<decltype(on_grid)::value>(p, ties, t, ry[2 * k + h], rx[2 * k + h], okk[k], rr[k][h]);
+      const int u = tid + k * nthreads;
+      const bool in = u < nunits;
+      // A lane beyond the tile's units shares the place of an earlier unit, one
+      // each: its exchanges are empty, but xors of one wave to one LDS word run
+      // one after another, and 40 lanes on one word cost more than the phase.
+      const int v = in ? u : (u - nunits < nunits ? u - nunits : 0);
+      int q, wu;
+      if ((p.L & 31) == 0) {
+        q = v / C;
+        wu = v - q * C;
       } else {
-        rr[k][0] = rr[k][1] = RowRand{0u, 0u, 0u, 0u, 0u};
-        tie[k][0] = tie[k][1] = -1;
+        // off-grid lattices: the two edge words of every row gather their random
+        // planes from two or three segments; numbering them after all inner
+        // words confines that slower path to the last waves
+        const int nin = npairs * (C - 2);
+        if (v < nin) {
+          q = v / (C - 2);
+          wu = 1 + (v - q * (C - 2));
+        } else {
+          const int e = v - nin;
+          q = e >> 1;
+          wu = (e & 1) ? C - 1 : 0;
+        }
+      }
+      const bool ok = in && wu < wneed;
+      const int w = ok ? wu : 0;
+      const int r0 = 2 + 16 * sw + 2 * q;
+      base0[k] = r0 * ST + wu + 1;  // also for a word past wneed, which holds the zero pad
+      yrow[2 * k] = ytab[r0];
+      yrow[2 * k + 1] = ytab[r0 + 1];
+      xw[k] = xtab[w];
+      // class a = 0 centres of a row with virtual y sit at x = y (mod 4); the
+      // virtual x of bit 0 is a multiple of 32
+      okm[2 * k] = ok ? (0x11111111u << ((YT + r0) & 3)) : 0u;
+      okm[2 * k + 1] = ok ? (0x11111111u << ((YT + r0 + 1) & 3)) : 0u;
+      const int Xw = XL + 32 * w;
+      uint32_t wm = 0u;
+      if (Xw + 32 > X0 && Xw < xend) {
+        const int lo = max(Xw, X0), hi = min(Xw + 32, xend);
+        const int n = hi - lo;
+        wm = (n == 32 ? 0xFFFFFFFFu : ((1u << n) - 1u)) << (lo - Xw);
+      }
+      okk[k] = ok;
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const int yv = YT + r0 + h;
+        imask[k][h] = (ok && yv >= Y0 && yv < yend) ? wm : 0u;
+        ry[2 * k + h] = ytab[r0 + h];
+        rx[2 * k + h] = xtab[w];
       }
     }
+    // row by row (a lane beyond the tile's units draws for a valid row and
+    // decides nothing: its centre masks are empty); a wave whose units of one
+    // index all lie beyond the tile skips them.  Drawing more rows at once, to
+    // overlap more Philox chains, measured slower: 16.3 us per 4096^2 sweep for a
+    // unit's two rows, 18.7 us for all four rows of a thread, against 16.2 us row
+    // by row.
+    auto draw_rows = [&](auto on_grid) {
+#pragma unroll
+      for (int k = 0; k < KU; ++k) {
+        if (__any(okk[k])) {
+#pragma unroll
+          for (int h = 0; h < 2; ++h)
+            tie[k][h] = rand_row<decltype(on_grid)::value>(p, ties, t, ry[2 * k + h], rx[2 * k + h], okk[k], rr[k][h]);
+        } else {
+          rr[k][0] = rr[k][1] = RowRand{0u, 0u, 0u, 0u, 0u};
+          tie[k][0] = tie[k][1] = -1;
+        }
+      }
   };
   if ((p.L & 31) == 0) draw_rows(std::true_type{});
   else draw_rows(std::false_type{});
@@ -951,20 +982,26 @@ __device__ __forceinline__ unsigned halo_tile_sweep(uint32_t* S, const SweepPara
   for (int k = 0; k < KU; ++k)
 #pragma unroll
     for (int h = 0; h < 2; ++h) join_ties(ties, tie[k][h], rr[k][h]);
+  if constexpr (decltype(first)::value) {
 #pragma unroll
-  for (int j = 0; j < NSTG; ++j) {
-    const int i = threadIdx.x + j * blockDim.x;
-    const int r = i / CP, w = i - r * CP;
-    if (i < total) S[r * ST + w] = w >= 1 && w <= wneed ? stg[j].word() : 0u;
+    for (int j = 0; j < NSTG; ++j) {
+      const int i = threadIdx.x + j * blockDim.x;
+      const int r = i / CP, w = i - r * CP;
+      if (i < total) S[r * ST + w] = w >= 1 && w <= wneed ? stg[j].word() : 0u;
+    }
+    __syncthreads();
   }
-  __syncthreads();
-  const uint32_t perm = order;
+  const uint32_t perm = sw ? order1 : order0;
 
   unsigned count = 0;
   const bool last = KU == 1 || __any(okk[KU - 1]);  // uniform: this wave has all its units
 #pragma unroll 1
-  for (int ph = 0; ph < 8; ++ph) {
-    const uint32_t cls = (perm >> (4 * ph)) & 0xFu;
+  for (int ph = 0; ph < (MODE == kSideBySide ? 16 : 8); ++ph) {
+    if (MODE == kSideBySide && (ph >> 3) != sw) {  // the other sweep's phase
+      __syncthreads();
+      continue;
+    }
+    const uint32_t cls = (perm >> (4 * (ph & 7))) & 0xFu;
     const int a = (int)(cls >> 1);
     // pairs start on even rows, so the active row of every pair is the class
     // parity: a uniform branch keeps each row's random state in registers
@@ -975,26 +1012,29 @@ __device__ __forceinline__ unsigned halo_tile_sweep(uint32_t* S, const SweepPara
       if (cls & 1u) count += halo_phase<ST, 1, 1>(S, p, base0, yrow, xw, okm, rr, imask, a, t);
       else count += halo_phase<ST, 1, 0>(S, p, base0, yrow, xw, okm, rr, imask, a, t);
     }
-    if (ph == 7) {  // each wave adds its count before the last barrier
+    if ((ph & 7) == 7) {  // each wave adds its count before the last barrier
       const unsigned ws = wave_sum8(count);
       if ((threadIdx.x & 63) == 0) atomicAdd(acc_total, ws);
     }
     __syncthreads();
   }
+  };
+  sweep(mine, std::true_type{});
+  if constexpr (MODE == kInTurn) sweep(1, std::false_type{});
 
   // write the interior back (a full-width tile divides by a constant)
   const int iw = (xend - X0 + 31) / 32, ih = yend - Y0;
   if (xend - X0 == TW * 32) {
     for (int i = threadIdx.x; i < TW * ih; i += blockDim.x) {
       const int rr2 = i / TW, ww = i - rr2 * TW;
-      store_word<LAYOUT>(p, Y0 + rr2, X0 + 32 * ww, S[(16 + rr2) * ST + 1 + ww + 1], 32);
+      store_word<LAYOUT>(p, Y0 + rr2, X0 + 32 * ww, S[(16 * NS + rr2) * ST + 1 + ww + 1], 32);
     }
   } else {
     for (int i = threadIdx.x; i < iw * ih; i += blockDim.x) {
       const int rr2 = i / iw, ww = i - rr2 * iw;
       const int x0 = X0 + 32 * ww;
       const int nb = min(32, xend - x0);
-      const uint32_t val = S[(16 + rr2) * ST + 1 + ww + 1];
+      const uint32_t val = S[(16 * NS + rr2) * ST + 1 + ww + 1];
       store_word<LAYOUT>(p, Y0 + rr2, x0, nb == 32 ? val : (val & ((1u << nb) - 1u)), nb);
     }
   }
@@ -1018,11 +1058,13 @@ __device__ __forceinline__ void add_block_count(uint32_t* red_lds, unsigned coun
   }
 }
 
-template <int LAYOUT, int TWW, int KU>
+template <int LAYOUT, int TWW, int KU, HaloMode MODE>
 __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 4))) void halo_kernel(SweepParams p,
-                                                                                               uint32_t order) {
+                                                                                               uint32_t order0,
+                                                                                               uint32_t order1) {
   extern __shared__ __attribute__((aligned(16))) uint32_t S[];
-  const unsigned total = halo_tile_sweep<LAYOUT, TWW, KU>(S, p, xcd_tile((int)blockIdx.x, (int)gridDim.x), order);
+  const unsigned total =
+      halo_tile_sweep<LAYOUT, TWW, KU, MODE>(S, p, xcd_tile((int)blockIdx.x, (int)gridDim.x), order0, order1);
   // one workgroup per address: an add without a returned value does not wait
   // for a read of the old sum at the end of the kernel
   if (threadIdx.x == 0) atomicAdd(p.accepted + blockIdx.x, (unsigned long long)total);
@@ -1311,11 +1353,11 @@ void batch_tile_kernel(const SweepParams* reps, const BatchTileJob* jobs, const 
     const uint32_t order = orders[(size_t)job.rep * kBatchChunk + s % kBatchChunk];
     unsigned count;
     if (p.layout == kLayoutBits) {
-      if (p.tww == 8) count = halo_tile_sweep<kLayoutBits, 8, KU>(S, p, job.tile, order);
-      else count = halo_tile_sweep<kLayoutBits, 16, KU>(S, p, job.tile, order);
+      if (p.tww == 8) count = halo_tile_sweep<kLayoutBits, 8, KU, kOneSweep>(S, p, job.tile, order, 0u);
+      else count = halo_tile_sweep<kLayoutBits, 16, KU, kOneSweep>(S, p, job.tile, order, 0u);
     } else {
-      if (p.tww == 8) count = halo_tile_sweep<kLayoutInt8, 8, KU>(S, p, job.tile, order);
-      else count = halo_tile_sweep<kLayoutInt8, 16, KU>(S, p, job.tile, order);
+      if (p.tww == 8) count = halo_tile_sweep<kLayoutInt8, 8, KU, kOneSweep>(S, p, job.tile, order, 0u);
+      else count = halo_tile_sweep<kLayoutInt8, 16, KU, kOneSweep>(S, p, job.tile, order, 0u);
     }
     if (threadIdx.x == 0) atomicAdd(p.accepted + job.tile, (unsigned long long)count);
   }
@@ -1381,6 +1423,39 @@ uint32_t class_order_host(uint32_t k0, uint32_t k1, uint64_t t) {
 }
 }  // namespace
 
+namespace {
+// How a halo tile is launched: the mode, units per thread, threads.
+struct HaloPlan {
+  HaloMode mode;
+  int ku, threads;
+};
+template <int TWW>
+size_t halo_lds_bytes(int th, const HaloPlan& pl) {
+  return ((size_t)halo_tie_offset<TWW>(halo_rows(th, pl.mode == kOneSweep ? 1 : 2)) +
+          (size_t)(pl.threads / 64) * kTieWaveWords) * sizeof(uint32_t);
+}
+HaloPlan halo_plan(const SweepParams& p, int ku, bool two, int threads) {
+  const bool rows_fit = (size_t)halo_rows(p.th, 2) * HaloGeom<16>::ST * 4 + 32768 <= 160 * 1024;  // the widest stride
+  if (two && rows_fit) {
+    for (int k = 1; k <= 2; ++k) {
+      const int n = half_threads(p.th, p.C, k, 0) + half_threads(p.th, p.C, k, 1);
+      if (n <= 1024) return HaloPlan{kSideBySide, k, n};
+    }
+    if (half_threads(p.th, p.C, 2, 0) <= 1024) return HaloPlan{kInTurn, 2, 1024};
+  }
+  // two units per thread: four waves per SIMD issue a multiply or a shift
+  // every 4.5 cycles, three (one wave each for 768 threads' units) only every
+  // 5.8, so the first threads take two units and the rest one
+  return HaloPlan{kOneSweep, ku, ku == 2 && p.nunits > 1024 ? 1024 : threads};
+}
+bool halo_width(const SweepParams& p) { return p.tww == 1 || p.tww == 2 || p.tww == 4 || p.tww == 8 || p.tww == 16; }
+}  // namespace
+
+int sweeps_per_launch(const SweepParams& p, bool cyclic, int ku) {
+  if (cyclic) return 256;
+  return halo_width(p) && halo_plan(p, ku, true, 0).mode != kOneSweep ? 2 : 1;
+}
+
 hipError_t launch_sweep(const SweepParams& p, int layout, bool cyclic, int ku, int threads, hipStream_t stream) {
   const int tiles_y = (p.L + p.th - 1) / p.th;
   const dim3 grid(p.tiles_x * tiles_y), block(threads);
@@ -1399,17 +1474,21 @@ hipError_t launch_sweep(const SweepParams& p, int layout, bool cyclic, int ku, i
 #undef KK_PIPE
     return hipGetLastError();
   }
-  if (!cyclic && (p.tww == 1 || p.tww == 2 || p.tww == 4 || p.tww == 8 || p.tww == 16)) {
-    // two units per thread: four waves per SIMD issue a multiply or a shift
-    // every 4.5 cycles, three (one wave each for 768 threads' units) only every
-    // 5.8, so the first threads take two units and the rest one
-    const dim3 wide(ku == 2 && p.nunits > 1024 ? 1024 : threads);
-    const uint32_t order = class_order_host(p.k0, p.k1, p.t0);
-#define KK_HALO(LY, TW)                                                                                  \
-  do {                                                                                                   \
-    const size_t hl = ((size_t)halo_tie_offset<TW>(p.R) + (wide.x / 64) * kTieWaveWords) * sizeof(uint32_t); \
-    if (ku == 1) hipLaunchKernelGGL((halo_kernel<LY, TW, 1>), grid, block, hl, stream, p, order);        \
-    else hipLaunchKernelGGL((halo_kernel<LY, TW, 2>), grid, wide, hl, stream, p, order);                 \
+  if (!cyclic && halo_width(p)) {
+    const HaloPlan pl = halo_plan(p, ku, p.nsweeps == 2, threads);
+    const uint32_t o0 = class_order_host(p.k0, p.k1, p.t0);
+    const uint32_t o1 = pl.mode == kOneSweep ? 0u : class_order_host(p.k0, p.k1, p.t0 + 1);
+#define KK_HALO(LY, TW)                                                                                              \
+  do {                                                                                                               \
+    const size_t hl = halo_lds_bytes<TW>(p.th, pl);                                                                  \
+    const dim3 nt(pl.threads);                                                                                       \
+    if (pl.mode == kInTurn) hipLaunchKernelGGL((halo_kernel<LY, TW, 2, kInTurn>), grid, nt, hl, stream, p, o0, o1);  \
+    else if (pl.mode == kSideBySide && pl.ku == 1)                                                                   \
+      hipLaunchKernelGGL((halo_kernel<LY, TW, 1, kSideBySide>), grid, nt, hl, stream, p, o0, o1);                    \
+    else if (pl.mode == kSideBySide)                                                                                 \
+      hipLaunchKernelGGL((halo_kernel<LY, TW, 2, kSideBySide>), grid, nt, hl, stream, p, o0, o1);                    \
+    else if (pl.ku == 1) hipLaunchKernelGGL((halo_kernel<LY, TW, 1, kOneSweep>), grid, nt, hl, stream, p, o0, o1);   \
+    else hipLaunchKernelGGL((halo_kernel<LY, TW, 2, kOneSweep>), grid, nt, hl, stream, p, o0, o1);                   \
   } while (0)
 #define KK_HALO_W(LY)                          \
   do {                                         \

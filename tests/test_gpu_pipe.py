@@ -42,3 +42,14 @@ def test_whole_lattice_matches_oracle(L, layout, w, n):
 def test_halo_tiles_match_oracle(L, layout, tile):
     _check(L, layout, 0.8, 3, tile)
     _check(L, layout, -0.5, 2, tile)
+
+
+# two sweeps in one launch: side by side with one and with two units per thread, in turn, windows taller and wider than
+# the lattice, one sweep left over, and the counter's 2^32 between the two
+@pytest.mark.parametrize("L,layout,tile", [(416, "bitpacked", (2, 20, 1)), (404, "int8", (8, 64, 1)),
+                                           (512, "bitpacked", (16, 128, 2)), (576, "int8", (8, 256, 2)),
+                                           (404, "int8", (16, 96, 2)), (36, "int8", (1, 12, 1)), (36, "int8", (2, 36, 1)),
+                                           (320, "int8", (4, 160, 2)), (4, "int8", None), (2724, "int8", None)])
+def test_two_sweeps_per_launch_match_oracle(L, layout, tile):
+    _check(L, layout, 0.8, 5 if L < 1000 else 2, tile)
+    _check(L, layout, -0.5, 2, tile, t0=2**32 - 1)
