@@ -45,6 +45,7 @@ struct kk_batch {
   int tile_th = kBatchTh;        // largest tile height of tiled replicas (rows, even)
   int tile_tww = kBatchMaxTww / 2;  // largest tile width of tiled replicas (words)
   int tile_ku = 2;                  // units per thread of the tile kernel (1 or 2)
+  bool tile_auto = true;            // the three above follow the replicas (choose_tile)
   // streams and events, created once
   hipStream_t sA = nullptr, sB = nullptr;  // large resident launch; uploads and joins
   hipStream_t sC = nullptr;                 // small resident launch
@@ -57,6 +58,7 @@ struct kk_batch {
   uint32_t* d_hist_stage = nullptr;
   uint32_t* h_hist_stage = nullptr;
   // plan, rebuilt by batch_plan
+  BatchTilePlan plan{};
   std::vector<int> resident, tiled;
   size_t n_small = 0;  // resident[0, n_small) run in the small kernel, the rest in the large one
   std::vector<size_t> count_off, count_n;
@@ -174,12 +176,63 @@ void batch_geometry(const kk_sim* h, bool resident, int max_tww, int max_th, int
 }
 
 
+// Tiles of a batch that was neither tuned nor given a tile: 8 words wide and the
+// lowest that leave one workgroup per CU (256) if both sweeps fit side by side
+// (48 rows), else from 64 rows on two (us per sweep: twelve lattices of 400^2 at
+// 100 rows 17.9, 40 rows 11.5, 36 rows -- 288 workgroups -- 16.4; two of 2048^2 at
+// 128 rows 12.8, 64 rows 11.0; five of 2048^2 at 128 rows 22.9, 64 rows -- 1280
+// workgroups -- 28.5).
+void choose_tile(kk_batch* b) {
+  b->tile_tww = kBatchMaxTww / 2;
+  b->tile_ku = 2;
+  auto jobs = [&](int th) {
+    size_t n = 0;
+    for (const kk_sim* h : b->sims) {
+      if (is_resident(h)) continue;
+      SweepParams p{};
+      batch_geometry(h, false, b->tile_tww, th, b->tile_ku, &p);
+      n += (size_t)p.tiles_x * (size_t)((h->L + p.th - 1) / p.th);
+    }
+    return n;
+  };
+  for (int th = 16; th < kBatchTh; th += 4) {
+    if (jobs(th) > (th <= 48 ? kFillWorkgroups / 2 : kFillWorkgroups) || (th > 48 && th < 64)) continue;
+    b->tile_th = th;
+    return;
+  }
+  b->tile_th = kBatchTh;
+}
+
+// Two sweeps per launch where it pays: side by side with at most one workgroup
+// per CU; in turn up to 1024 workgroups, or if no lattice is bit-packed (us per
+// sweep, one and two: 2048^2 x 5 29.0 and 22.9; bits 4096^2 x 2 27.8 and 28.2,
+// 320^2 x 200 28.5 and 30.7, the 256-replica table 41.3 and 43.2; int8 1024^2 x 48
+// 60.8 and 47.7): with the device full of workgroups the launch and the staging
+// hide behind other tiles' phases, and the taller window is what is left.
+BatchTilePlan tile_plan(const kk_batch* b, size_t jobs) {
+  BatchTilePlan pl{1, false, b->tile_ku, kBatchTileThreads, 0};
+  int side = 0;
+  bool turn = true, bits = false;
+  for (int i : b->tiled) {
+    SweepParams p{};
+    batch_geometry(b->sims[i], false, b->tile_tww, b->tile_th, b->tile_ku, &p);
+    pl.max_th = std::max(pl.max_th, p.th);
+    side = std::max(side, batch_tile_threads(p.tww, p.th));
+    turn = turn && batch_tile_in_turn(p.tww, p.th);
+    bits = bits || b->sims[i]->layout == kLayoutBits;
+  }
+  if (side <= 1024 && jobs <= kFillWorkgroups / 2) return BatchTilePlan{2, true, 1, side, pl.max_th};
+  if (turn && (jobs <= 2 * kFillWorkgroups || !bits)) return BatchTilePlan{2, false, 2, kBatchTileThreads, pl.max_th};
+  return pl;
+}
+
 // Plan the current replica set: resident list, tile jobs split into groups of
 // equal work, device tables.
 kk_status batch_plan(kk_batch* b) {
   clear_plan(b);
   const size_t n = b->sims.size();
   if (n == 0) return KK_OK;
+  if (b->tile_auto) choose_tile(b);
   std::vector<BatchTileJob> jobs;
   for (size_t i = 0; i < n; ++i) {
     kk_sim* h = b->sims[i];
@@ -214,6 +267,7 @@ kk_status batch_plan(kk_batch* b) {
   // fifth branch serialises behind another).
   size_t tile_jobs = 0;
   for (int i : b->tiled) tile_jobs += b->count_n[i];
+  b->plan = tile_plan(b, tile_jobs);
   const int ngroups = (int)std::min<size_t>(tile_jobs >= kFillWorkgroups ? 2 : 1, b->tiled.size());
   std::vector<std::vector<int>> groups(ngroups);
   {
@@ -362,7 +416,7 @@ kk_status kk_batch_run(kk_batch* b) {
   KB_HIP(hipMemsetAsync(b->d_counts, 0, b->ncounts * sizeof(unsigned long long), b->sB));
   KB_HIP(hipEventRecord(b->ev_upload, b->sB));
   // every stream starts after the upload; the resident launches first, then
-  // the tile groups' launches in turn, a sweep of each at a time
+  // the tile groups' launches, one of each at a time
   const size_t n_small = b->n_small, n_large = b->resident.size() - b->n_small;
   uint64_t res_mx[2] = {0, 0}, tile_mx = 0;
   for (size_t k = 0; k < b->resident.size(); ++k)
@@ -384,13 +438,13 @@ kk_status kk_batch_run(kk_batch* b) {
       KB_HIP(launch_batch_resident(b->d_params, b->d_res + n_small, (int)n_large, b->res_lds, false, (unsigned)s,
                                    b->sA));
   }
-  for (uint64_t s = 0; s < tile_mx; ++s)
+  for (uint64_t s = 0; s < tile_mx; s += (uint64_t)b->plan.sweeps)
     for (size_t g = 0; g < group_mx.size(); ++g)
       if (s < group_mx[g]) {
         uint32_t* orders = b->d_orders + g * n * kBatchChunk;
         if (s % kBatchChunk == 0)
           KB_HIP(launch_batch_orders(b->d_params, (int)n, (unsigned)s, orders, b->tg_stream[g]));
-        KB_HIP(launch_batch_tiles(b->d_params, b->d_jobs + b->tg_off[g], b->tg_n[g], orders, (unsigned)s, b->tile_ku,
+        KB_HIP(launch_batch_tiles(b->d_params, b->d_jobs + b->tg_off[g], b->tg_n[g], orders, (unsigned)s, b->plan,
                                   b->tg_stream[g]));
       }
   for (size_t g = 0; g < group_mx.size(); ++g) KB_HIP(hipStreamSynchronize(b->tg_stream[g]));
@@ -405,7 +459,8 @@ kk_status kk_batch_run(kk_batch* b) {
     h->t += b->sweeps[i];
     if (b->sweeps[i]) h->epoch += 1;
     h->attempts += b->sweeps[i] * (uint64_t)h->L * (uint64_t)h->L;
-    if (!is_resident(h)) h->cur ^= (int)(b->sweeps[i] & 1u);
+    const uint64_t per = (uint64_t)b->plan.sweeps;  // the buffers change places with every launch
+    if (!is_resident(h)) h->cur ^= (int)((b->sweeps[i] + per - 1) / per & 1u);
   }
   return KK_OK;
 }
@@ -467,14 +522,17 @@ kk_status kk_batch_autotune(kk_batch* b, uint32_t trial_sweeps, uint32_t* tile_w
   };
   const std::vector<uint64_t> sweeps0 = b->sweeps;
   const int th0 = b->tile_th, tw0 = b->tile_tww, ku0 = b->tile_ku;
+  const bool auto0 = b->tile_auto;
   int best_th = th0, best_tw = tw0, best_ku = ku0;
   double best_ms = 1e300;
   kk_status st = KK_OK;
-  // (words, rows, units per thread): large tiles for batches that fill the
-  // device, small one-unit-per-thread tiles that spread a few mid-sized
-  // replicas over many workgroups
-  static const int cand[][3] = {{8, 128, 2}, {16, 84, 2}, {8, 64, 2}, {16, 42, 2}, {8, 32, 2}, {8, 16, 2},
-                                {16, 28, 1}, {16, 20, 1}, {8, 72, 1}, {8, 50, 1}, {8, 32, 1}};
+  // (words, rows, units per thread): the tile that suits the replicas, large
+  // tiles for batches that fill the device, small one-unit-per-thread tiles that
+  // spread a few mid-sized replicas over many workgroups
+  choose_tile(b);
+  const int cand[][3] = {{b->tile_tww, b->tile_th, b->tile_ku}, {8, 128, 2}, {16, 84, 2}, {8, 64, 2}, {16, 42, 2},
+                         {8, 32, 2}, {8, 16, 2}, {16, 28, 1}, {16, 20, 1}, {8, 72, 1}, {8, 50, 1}, {8, 32, 1}};
+  b->tile_auto = false;
   for (const auto& c : cand) {
     const int tw = c[0], th = c[1];
     b->tile_th = th;
@@ -502,6 +560,7 @@ kk_status kk_batch_autotune(kk_batch* b, uint32_t trial_sweeps, uint32_t* tile_w
   b->tile_th = st == KK_OK ? best_th : th0;
   b->tile_tww = st == KK_OK ? best_tw : tw0;
   b->tile_ku = st == KK_OK ? best_ku : ku0;
+  b->tile_auto = st == KK_OK ? false : auto0;
   const kk_status ps = batch_replan(b, b->sims, sweeps0);
   if (st == KK_OK) st = ps;
   if (st != KK_OK) return st;
@@ -529,6 +588,7 @@ kk_status kk_batch_set_tile(kk_batch* b, uint32_t tile_words, uint32_t tile_rows
   b->tile_tww = (int)tile_words;
   b->tile_th = (int)tile_rows;
   b->tile_ku = (int)units_per_thread;
+  b->tile_auto = false;
   return batch_replan(b, b->sims, b->sweeps);
 }
 

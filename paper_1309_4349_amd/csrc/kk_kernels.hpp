@@ -50,10 +50,19 @@ constexpr bool batch_tile_fits(int tww, int th, int ku = 2) {
 struct BatchTileJob {
   int rep, tile;
 };
-// Sweep s of the run; orders[rep * kBatchChunk + s % kBatchChunk] is replica
+// How the tiles of a batch are launched.
+struct BatchTilePlan {
+  int sweeps;         // per launch, 1 or 2
+  bool side_by_side;  // with two: both sweeps' units at once, else in turn
+  int ku, threads;
+  int max_th;         // rows of the tallest tile
+};
+int batch_tile_threads(int tww, int th);   // side by side, one unit per thread
+bool batch_tile_in_turn(int tww, int th);  // fits 512 threads of two units
+// Sweep s of the run, or s and s + 1; orders[rep * kBatchChunk + s % kBatchChunk] is replica
 // rep's class order of that sweep (launch_batch_orders, once per kBatchChunk sweeps).
 hipError_t launch_batch_tiles(const SweepParams* reps, const BatchTileJob* jobs, int njobs, const uint32_t* orders,
-                              unsigned s, int ku, hipStream_t stream);
+                              unsigned s, const BatchTilePlan& plan, hipStream_t stream);
 hipError_t launch_batch_orders(const SweepParams* reps, int nreps, unsigned s, uint32_t* orders, hipStream_t stream);
 // small: the 768-thread kernel for replicas of at most kResidentSmallMaxC words
 // per row.  A launch runs up to kBatchChunk sweeps from sweep s of the run.
@@ -62,7 +71,6 @@ hipError_t launch_batch_resident(const SweepParams* reps, const int* ids, int n,
 constexpr int kBatchChunk = 256;
 constexpr int kResidentMaxC = 9;
 constexpr int kResidentSmallMaxC = 4, kResidentSmallThreads = 768, kResidentThreads = 1024;
-size_t batch_tile_lds_bytes();
 size_t batch_resident_lds_bytes(int L);
 
 // N_AB (unlike nearest-neighbour bonds) added into *out.

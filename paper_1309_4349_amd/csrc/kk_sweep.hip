@@ -821,6 +821,7 @@ __device__ __forceinline__ unsigned wave_sum8(unsigned c) {
 // then the other, for tiles whose two sweeps need more threads than a workgroup
 // has (4096^2 15.6 -> 14.3 us per sweep).
 enum HaloMode { kOneSweep, kSideBySide, kInTurn };
+// With `sweeps` 1 the second is left out (a batch's replica whose run ends).
 // Returns the workgroup's accepted count for the tile interior (the same in
 // every thread).
 __host__ __device__ constexpr int halo_rows(int th, int ns) { return th + 32 * ns; }
@@ -832,7 +833,7 @@ __host__ __device__ constexpr int half_threads(int th, int C, int KU, int sweep)
 
 template <int LAYOUT, int TWW, int KU, HaloMode MODE>
 __device__ __forceinline__ unsigned halo_tile_sweep(uint32_t* S, const SweepParams& p, int tile, uint32_t order0,
-                                                    uint32_t order1) {
+                                                    uint32_t order1, int sweeps = 2) {
   constexpr int NS = MODE == kOneSweep ? 1 : 2;
   constexpr int C = HaloGeom<TWW>::C;
   constexpr int ST = HaloGeom<TWW>::ST;
@@ -929,7 +930,7 @@ __device__ __forceinline__ unsigned halo_tile_sweep(uint32_t* S, const SweepPara
           wu = (e & 1) ? C - 1 : 0;
         }
       }
-      const bool ok = in && wu < wneed;
+      const bool ok = in && wu < wneed && (MODE != kSideBySide || sw < sweeps);
       const int w = ok ? wu : 0;
       const int r0 = 2 + 16 * sw + 2 * q;
       base0[k] = r0 * ST + wu + 1;  // also for a word past wneed, which holds the zero pad
@@ -996,7 +997,7 @@ __device__ __forceinline__ unsigned halo_tile_sweep(uint32_t* S, const SweepPara
   unsigned count = 0;
   const bool last = KU == 1 || __any(okk[KU - 1]);  // uniform: this wave has all its units
 #pragma unroll 1
-  for (int ph = 0; ph < (MODE == kSideBySide ? 16 : 8); ++ph) {
+  for (int ph = 0; ph < (MODE == kSideBySide ? 8 * sweeps : 8); ++ph) {
     if (MODE == kSideBySide && (ph >> 3) != sw) {  // the other sweep's phase
       __syncthreads();
       continue;
@@ -1020,7 +1021,7 @@ __device__ __forceinline__ unsigned halo_tile_sweep(uint32_t* S, const SweepPara
   }
   };
   sweep(mine, std::true_type{});
-  if constexpr (MODE == kInTurn) sweep(1, std::false_type{});
+  if (MODE == kInTurn && sweeps == 2) sweep(1, std::false_type{});
 
   // write the interior back (a full-width tile divides by a constant)
   const int iw = (xend - X0 + 31) / 32, ih = yend - Y0;
@@ -1329,19 +1330,18 @@ __global__ __launch_bounds__(kBatchChunk) void batch_orders_kernel(const SweepPa
   orders[(size_t)blockIdx.x * kBatchChunk + threadIdx.x] = class_order(p.k0, p.k1, p.t0 + s + threadIdx.x);
 }
 
-// KU = 2: tiles of up to 1024 units; KU = 1: up to 512 units, twice the
-// waves per unit, which hides more latency when small tiles spread a batch
-// over many workgroups.
-// Two workgroups per CU: four waves per SIMD, at most 128 VGPRs each.
-template <int KU>
-__global__ __launch_bounds__(kBatchTileThreads) __attribute__((amdgpu_waves_per_eu(4)))
+// A launch does sweep s of the run, or s and s + 1 (MODE); the buffers change
+// places with every launch.  512 threads, two workgroups per CU (four waves per
+// SIMD, at most 128 VGPRs each), or up to 1024 side by side.
+template <int KU, HaloMode MODE>
+__global__ __launch_bounds__(MODE == kSideBySide ? 1024 : kBatchTileThreads) __attribute__((amdgpu_waves_per_eu(4)))
 void batch_tile_kernel(const SweepParams* reps, const BatchTileJob* jobs, const uint32_t* orders, unsigned s) {
   extern __shared__ __attribute__((aligned(16))) uint32_t S[];
-  // sweep s of the run
+  constexpr unsigned NS = MODE == kOneSweep ? 1 : 2;
   const BatchTileJob job = jobs[blockIdx.x];
   SweepParams p = reps[job.rep];
   if (s < (unsigned)p.nsweeps) {
-    if (s & 1u) {  // p.src holds the lattice at the start of the run, p.dst the other buffer
+    if ((s / NS) & 1u) {  // p.src holds the lattice at the start of the run, p.dst the other buffer
       const void* t = p.src;
       p.src = p.dst;
       p.dst = const_cast<void*>(t);
@@ -1350,14 +1350,16 @@ void batch_tile_kernel(const SweepParams* reps, const BatchTileJob* jobs, const 
     // compile-time tile width (8 or 16 words: immediate, bank-conflict-free
     // LDS offsets) chosen per replica by a uniform switch; a replica's last
     // tile column may be ragged
-    const uint32_t order = orders[(size_t)job.rep * kBatchChunk + s % kBatchChunk];
+    const uint32_t* o = orders + (size_t)job.rep * kBatchChunk + s % kBatchChunk;
+    const uint32_t o0 = o[0], o1 = NS == 2 ? o[1] : 0u;  // s is even with two
+    const int sweeps = min((int)NS, p.nsweeps - (int)s);
     unsigned count;
     if (p.layout == kLayoutBits) {
-      if (p.tww == 8) count = halo_tile_sweep<kLayoutBits, 8, KU, kOneSweep>(S, p, job.tile, order, 0u);
-      else count = halo_tile_sweep<kLayoutBits, 16, KU, kOneSweep>(S, p, job.tile, order, 0u);
+      if (p.tww == 8) count = halo_tile_sweep<kLayoutBits, 8, KU, MODE>(S, p, job.tile, o0, o1, sweeps);
+      else count = halo_tile_sweep<kLayoutBits, 16, KU, MODE>(S, p, job.tile, o0, o1, sweeps);
     } else {
-      if (p.tww == 8) count = halo_tile_sweep<kLayoutInt8, 8, KU, kOneSweep>(S, p, job.tile, order, 0u);
-      else count = halo_tile_sweep<kLayoutInt8, 16, KU, kOneSweep>(S, p, job.tile, order, 0u);
+      if (p.tww == 8) count = halo_tile_sweep<kLayoutInt8, 8, KU, MODE>(S, p, job.tile, o0, o1, sweeps);
+      else count = halo_tile_sweep<kLayoutInt8, 16, KU, MODE>(S, p, job.tile, o0, o1, sweeps);
     }
     if (threadIdx.x == 0) atomicAdd(p.accepted + job.tile, (unsigned long long)count);
   }
@@ -1522,11 +1524,6 @@ hipError_t launch_sweep(const SweepParams& p, int layout, bool cyclic, int ku, i
 
 namespace kk {
 
-size_t batch_tile_lds_bytes() {
-  const int R = kBatchTh + 32;  // the widest tile has the largest stride
-  return ((size_t)halo_tie_offset<kBatchMaxTww>(R) + (kBatchTileThreads / 64) * kTieWaveWords) * sizeof(uint32_t);
-}
-
 size_t batch_resident_lds_bytes(int L) {
   static constexpr int words[] = {Pipe<2>::kWords, Pipe<3>::kWords, Pipe<4>::kWords, Pipe<5>::kWords,
                                   Pipe<6>::kWords, Pipe<7>::kWords, Pipe<8>::kWords, Pipe<9>::kWords};
@@ -1534,14 +1531,21 @@ size_t batch_resident_lds_bytes(int L) {
   return (size_t)words[L / 32 - 2] * sizeof(uint32_t);
 }
 
-hipError_t launch_batch_tiles(const SweepParams* reps, const BatchTileJob* jobs, int njobs,
-                              const uint32_t* orders, unsigned s, int ku, hipStream_t stream) {
-  if (ku == 1)
-    hipLaunchKernelGGL(batch_tile_kernel<1>, dim3(njobs), dim3(kBatchTileThreads), batch_tile_lds_bytes(), stream,
-                       reps, jobs, orders, s);
-  else
-    hipLaunchKernelGGL(batch_tile_kernel<2>, dim3(njobs), dim3(kBatchTileThreads), batch_tile_lds_bytes(), stream,
-                       reps, jobs, orders, s);
+int batch_tile_threads(int tww, int th) { return half_threads(th, tww + 2, 1, 0) + half_threads(th, tww + 2, 1, 1); }
+bool batch_tile_in_turn(int tww, int th) { return half_threads(th, tww + 2, 2, 0) <= kBatchTileThreads; }
+
+hipError_t launch_batch_tiles(const SweepParams* reps, const BatchTileJob* jobs, int njobs, const uint32_t* orders,
+                              unsigned s, const BatchTilePlan& pl, hipStream_t stream) {
+  const size_t lds = ((size_t)halo_tie_offset<kBatchMaxTww>(halo_rows(pl.max_th, pl.sweeps)) +  // the widest tile's stride
+                      (size_t)(pl.threads / 64) * kTieWaveWords) * sizeof(uint32_t);
+  const dim3 grid(njobs), block(pl.threads);
+#define KK_BATCH(KU, MODE) \
+  hipLaunchKernelGGL((batch_tile_kernel<KU, MODE>), grid, block, lds, stream, reps, jobs, orders, s)
+  if (pl.sweeps == 2 && pl.side_by_side) KK_BATCH(1, kSideBySide);
+  else if (pl.sweeps == 2) KK_BATCH(2, kInTurn);
+  else if (pl.ku == 1) KK_BATCH(1, kOneSweep);
+  else KK_BATCH(2, kOneSweep);
+#undef KK_BATCH
   return hipGetLastError();
 }
 
