@@ -67,7 +67,9 @@ void default_tile(int L, int layout, TileConfig* tc) {
       return;
     }
   }
-  if (cyclic_fits(L)) {
+  // the whole lattice in one workgroup up to 160 (4.4 us per sweep against 4.8 ..
+  // 5.0 with tiles; 192 6.0 and 4.8, 288 11.5 and 4.9)
+  if (cyclic_fits(L) && L <= 160) {
     tc->cyclic = true;
     tc->tww = L / 32;
     tc->th = L;

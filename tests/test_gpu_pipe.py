@@ -30,8 +30,10 @@ def _check(L, layout, w, n, tile=None, t0=0):
                                           (160, "bitpacked", 0.0, 5), (192, "int8", 1.2, 5), (224, "bitpacked", 0.4, 5),
                                           (256, "int8", 0.88, 4), (288, "bitpacked", -1.1, 4)])
 def test_whole_lattice_matches_oracle(L, layout, w, n):
-    _check(L, layout, w, n)
-    _check(L, layout, w, 3, t0=2**32 - 2)
+    whole = (0, 0, 2)  # the whole lattice in one workgroup
+    _check(L, layout, w, n, whole)
+    _check(L, layout, w, 3, whole, t0=2**32 - 2)
+    _check(L, layout, w, 4)
 
 
 # halo tiles whose last wave is mostly spare lanes, with two units per thread of which most threads hold one, and off
