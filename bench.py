@@ -92,29 +92,25 @@ def roofline_alu(mix, weights, attempts_per_s):
             "instruction_mix": {k: round(v, 4) for k, v in mix.items()}}
 
 
-# HBM-side bytes per launch of the sweep kernel on this workload, from the
-# rocprofv3 FETCH_SIZE / WRITE_SIZE passes recorded in
-# profiles/halo_kernel_4096_bitpacked.md (counters scaled by what they read for
-# a plain copy kernel of known size).  Valid only for the kernel sources that
-# were profiled: the line reports null once they change.
-PROFILED_TRAFFIC = {"sources_sha256_prefix": "b3cfdf93ff201d3a", "tile": (16, 128, 2),
-                    "bytes_per_launch": 4721976}
+# HBM-side bytes per launch (two sweeps) of the sweep kernel on this workload,
+# from the rocprofv3 FETCH_SIZE / WRITE_SIZE passes recorded in
+# profiles/kernels_by_case.md (counters scaled by what they read for a plain
+# copy kernel of known size).  Valid only for the kernel sources that were
+# profiled: the line reports null once they change.
+PROFILED_TRAFFIC = {"sources_sha256_prefix": "ecbbe6fda177cc9b", "tile": (8, 256, 2),
+                    "bytes_per_launch": 5113312}
 KERNEL_SOURCES = ["kk_sweep.hip", "kk_common.hpp", "kk_kernels.hpp"]
 # The same for the triangular whole-sweep tile kernel on the 4092^2 lattice with
-# 256 x 256 tiles (profiles/tri_tile_sweep_4092.md).
-TRI_PROFILED_TRAFFIC = {"sources_sha256_prefix": "acfed7f9645a8c30", "tile": (256, 256),
-                        "bytes_per_launch": 35863064}
-TRI_KERNEL_SOURCES = ["kk_tri.hip", "kk_tri.hpp", "kk_common.hpp"]
-# And for the literal-MPKK whole-step tile kernel on the 4098 x 4095 ring with
-# 257 x 256 tiles (profiles/mpkk_tile_step_4098x4095.md).
-MPKK_PROFILED_TRAFFIC = {"sources_sha256_prefix": "acfed7f9645a8c30", "tile": (257, 256),
-                         "bytes_per_launch": 35132607}
-# The 400^2 int8 paths (profiles/halo_kernel_400_int8.md): the plain sweep
-# kernel with 2 x 16 tiles, and the batch tile kernel at the autotuner's 16 x 28
-# tiles, one unit per thread, over the 12 runs.
-GRID_PROFILED_TRAFFIC = {"sources_sha256_prefix": "b3cfdf93ff201d3a", "plain_tile": (2, 16, 1),
-                         "plain_bytes_per_launch": 886838, "batch_tile": (16, 28),
-                         "batch_bytes_per_launch": 6599810}
+# 256 x 256 tiles, and for the literal-MPKK whole-step tile kernel on the
+# 4098 x 4095 ring with 257 x 256 tiles (one sweep or step per launch).
+TRI_KERNEL_SOURCES = ["kk_hex.hip", "kk_tri_dev.hpp", "kk_tri.hpp", "kk_common.hpp"]
+TRI_PROFILED_TRAFFIC = {"sources_sha256_prefix": "1f4f1e74803ff6df", "tile": (256, 256),
+                        "bytes_per_launch": 35863661}
+MPKK_PROFILED_TRAFFIC = {"sources_sha256_prefix": "1f4f1e74803ff6df", "tile": (257, 256),
+                         "bytes_per_launch": 35164111}
+# The plain sweep kernel on one 400^2 int8 lattice (two sweeps per launch).
+GRID_PROFILED_TRAFFIC = {"sources_sha256_prefix": "ecbbe6fda177cc9b", "plain_tile": (1, 24, 1),
+                         "plain_bytes_per_launch": 949263}
 
 
 def kernel_sources_sha(files=KERNEL_SOURCES) -> str:
@@ -324,7 +320,7 @@ def triangular(sweeps: int, profile_sweeps: int, cpu: bool, batch_sweeps: int = 
     out = {"workload": f"triangular helical {L}x{L} int8, x={x}, omega={w}, {sweeps} sweeps",
            "value": rate, "unit": "attempts/s", "n_unlike_over_3N": nab / (3 * N),
            "roofline": {**roofline_alu(TRI_MIX, weights, per_launch / per_launch_s),
-                        "traffic": traffic, "kernel": "tri_tile_sweep" if sim_tile[0] else "tri_phase",
+                        "traffic": traffic, "kernel": "hex_sweep" if sim_tile[0] else "tri_phase",
                         "kernel_us": round(per_launch_s * 1e6, 3), "launches": int(launches),
                         "tile": {"cols": sim_tile[0], "rows": sim_tile[1]},
                         "hbm_achieved_GBps": round(hbm, 1), "hbm_frac": round(hbm / HBM_PEAK_GBS, 5)}}
@@ -387,7 +383,7 @@ def mpkk(steps: int, bias_steps: int, cpu: bool, weights=None):
     out = {"workload": f"literal MPKK, triangular helical {L}x{H} int8, x={x}, omega={w}, {steps} steps",
            "value": rate, "unit": "attempts/s",
            "roofline": {**roofline_alu(MPKK_MIX, weights, per_launch / per_launch_s),
-                        "traffic": traffic, "kernel": "mpkk_tile_step" if mp_tile[0] else "mpkk_iter",
+                        "traffic": traffic, "kernel": "hex_mpkk_step" if mp_tile[0] else "mpkk_iter",
                         "kernel_us": round(per_launch_s * 1e6, 3), "launches": int(launches),
                         "tile": {"cols": mp_tile[0], "rows": mp_tile[1]},
                         "hbm_achieved_GBps": round(hbm, 1), "hbm_frac": round(hbm / HBM_PEAK_GBS, 5)}}
@@ -543,30 +539,29 @@ def grid_400(rounds: int, every: int, weights=None, tile=None):
     # the plain path's sweep kernel on one 400^2 lattice, timed on the library's stream
     ms, launches = sims[5].sweep_timed(500)
     per_launch_s = ms / 1e3 / launches
+    per_launch = jobs[5].L * jobs[5].L * 500 / launches  # attempts
     ptile = sims[5].get_tile()
     for s in sims:
         s.close()
     plain = sites * every / tp
-    n1 = jobs[0].L * jobs[0].L
     same_src = kernel_sources_sha() == GRID_PROFILED_TRAFFIC["sources_sha256_prefix"]
-    plain_roof = {**roofline_alu(SQUARE_MIX, weights, n1 / per_launch_s),
+    plain_roof = {**roofline_alu(SQUARE_MIX, weights, per_launch / per_launch_s),
                   "traffic": GRID_PROFILED_TRAFFIC["plain_bytes_per_launch"]
                   if same_src and tuple(ptile) == GRID_PROFILED_TRAFFIC["plain_tile"] else None,
                   "kernel": f"halo_kernel<int8, {ptile[0]}, {ptile[2]}>", "kernel_us": round(per_launch_s * 1e6, 3),
                   "launches": int(launches), "tile": {"words": ptile[0], "rows": ptile[1], "units_per_thread": ptile[2]},
-                  "algorithmic_bytes_per_launch": int(BYTES_PER_ATTEMPT_INT8 * n1),
-                  "hbm_achieved_GBps": round(BYTES_PER_ATTEMPT_INT8 * n1 / per_launch_s / 1e9, 1),
-                  "hbm_frac": round(BYTES_PER_ATTEMPT_INT8 * n1 / per_launch_s / 1e9 / HBM_PEAK_GBS, 5)}
+                  "algorithmic_bytes_per_launch": int(BYTES_PER_ATTEMPT_INT8 * per_launch),
+                  "hbm_achieved_GBps": round(BYTES_PER_ATTEMPT_INT8 * per_launch / per_launch_s / 1e9, 1),
+                  "hbm_frac": round(BYTES_PER_ATTEMPT_INT8 * per_launch / per_launch_s / 1e9 / HBM_PEAK_GBS, 5)}
     batch_sweep_rate = sites * every / tsw
     batch_roof = {**roofline_alu(SQUARE_MIX, weights, batch_sweep_rate),
-                  "traffic": GRID_PROFILED_TRAFFIC["batch_bytes_per_launch"]
-                  if same_src and (tw, th) == GRID_PROFILED_TRAFFIC["batch_tile"] else None,
+                  "traffic": None,
                   "algorithmic_bytes_per_launch": int(BYTES_PER_ATTEMPT_INT8 * sites),
                   "kernel": "batch_tile_kernel (whole batch run of the 12 lattices, launch gaps included)",
                   "us_per_sweep": round(tsw / every * 1e6, 3), "plan": plan}
     log(f"[bench] 400^2 grid: batched {rate:.3e} attempts/s (tiles <= {tw}x{th}; sweeps alone "
         f"{batch_sweep_rate:.3e}, {tsw / every * 1e6:.1f} us per sweep of all 12), one after another {plain:.3e}; "
-        f"plain sweep kernel {per_launch_s * 1e6:.2f} us per 400^2 sweep")
+        f"plain sweep kernel {ms * 2:.2f} us per 400^2 sweep")
     return {"workload": "12 runs of 400x400 int8, x in {0.3,0.5,0.7} x omega in {0.3,0.6,0.9,1.2}, "
                         f"histogram of every run every {every} sweeps",
             "batched_attempts_per_s": rate, "rounds": rounds, "sweeps_per_round": every,

@@ -307,8 +307,8 @@ void kk_destroy(kk_sim *h);
  * Batches: many independent replicas (uneven L, composition, omega, seed)
  * advanced together.  Replicas with L % 32 == 0 and 64 <= L <= 288 run in
  * persistent launches (one for L <= 128, one for the rest) with the whole
- * lattice held in LDS; the others run as one launch per sweep over all their
- * tiles.  A replica's result equals what kk_create_ex + kk_sweep gives for the
+ * lattice held in LDS; the others run as one launch per sweep, or per two,
+ * over all their tiles.  A replica's result equals what kk_create_ex + kk_sweep gives for the
  * same parameters (no replica or slot index enters any random number).
  * ------------------------------------------------------------------------- */
 typedef struct kk_batch kk_batch;
@@ -476,11 +476,10 @@ kk_status kk_server_now(kk_server *s, double *t);
 
 /* The device bytes a job is charged at admission (an upper bound of what it
  * holds at any time): two lattice buffers, the energy counters and one
- * accepted-move sum per sweep tile, plus the larger of the placement scratch
- * (8 bytes per site and the radix tables) and the retirement scratch (the
- * cluster-labelling arrays, 8 bytes per site and the size tables, and with
- * keep_lattice on a bit-packed job the N-byte unpack buffer of the lattice
- * copy), plus 64 KiB for the job's share of the batch tables.  Host-only: no
+ * accepted-move sum per sweep tile, plus the larger of the placement and the
+ * retirement scratch (cluster labelling), both counted as 8 bytes per site and
+ * their tables, retirement of a bit-packed job with keep_lattice as N bytes more
+ * (the unpack buffer of the lattice copy), plus 64 KiB for the job's share of the batch tables.  Host-only: no
  * device call.  KK_EINVAL for a NULL argument, a bad L or layout. */
 kk_status kk_server_job_bytes(const kk_replica *job, uint32_t keep_lattice, uint64_t *bytes);
 

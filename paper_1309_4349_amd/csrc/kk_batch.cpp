@@ -5,15 +5,15 @@
 // 32 * kResidentMaxC) are "resident": one persistent launch gives each its own
 // workgroup, which keeps the lattice in LDS for all of its sweeps.  The others
 // are "tiled": they are split into a few groups of equal work, and for each
-// group every sweep is one launch over all of the group's halo tiles.
+// group every sweep, or every two, is one launch over all of the group's halo
+// tiles.
 // Resident replicas of at most kResidentSmallMaxC words per row run in
 // 768-thread workgroups (two per CU), larger ones in 1024-thread workgroups.
 // Every tile group and every resident kernel has a stream of its own: a run
-// enqueues one launch per sweep for each tile group and one launch per
-// kBatchChunk sweeps for each resident kernel, all streams at once, and waits
-// for all of them.  No slot or replica index
-// enters any random counter, so every replica ends exactly where kk_sweep
-// would have left it.
+// enqueues the launches of each tile group and one launch per kBatchChunk sweeps
+// for each resident kernel, all streams at once, and waits for all of them.  No
+// slot or replica index enters any random counter, so every replica ends
+// exactly where kk_sweep would have left it.
 //
 // The streams live as long as the batch; the plan (tables) is rebuilt
 // whenever the replica set changes, which the job server does between steps.
@@ -261,10 +261,10 @@ kk_status batch_plan(kk_batch* b) {
   for (int i : b->resident) b->n_small += b->sims[i]->L / 32 <= kResidentSmallMaxC;
   // longest-processing-time split of the tiled replicas by work per run.  Two
   // tile chains fill each other's launch tails when the tiles can fill the
-  // device; fewer tiles run best as one chain.  Graph branches run
+  // device; fewer tiles run best as one chain.  Streams run
   // concurrently only up to the device's hardware queues (four): the two tile
   // chains plus at most two resident launches stay within that (measured: a
-  // fifth branch serialises behind another).
+  // fifth serialises behind another).
   size_t tile_jobs = 0;
   for (int i : b->tiled) tile_jobs += b->count_n[i];
   b->plan = tile_plan(b, tile_jobs);

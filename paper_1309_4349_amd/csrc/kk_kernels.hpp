@@ -33,12 +33,12 @@ hipError_t launch_sweep(const SweepParams& p, int layout, bool cyclic, int ku, i
 int sweeps_per_launch(const SweepParams& p, bool cyclic, int ku);
 
 // Batch kernels.  Tiled replicas: one workgroup per (replica, tile) job and one
-// launch per sweep of the run.  A replica runs p.nsweeps sweeps from
-// p.t0, ping-ponging between p.src (its lattice at the start) and p.dst.  Resident replicas (L % 32 == 0,
-// 2 <= L/32 <= kResidentMaxC): one workgroup per replica with the whole lattice
-// in LDS, kBatchChunk sweeps per launch.
+// launch per sweep, or per two, of the run.  A replica runs p.nsweeps sweeps from
+// p.t0, ping-ponging between p.src (its lattice at the start) and p.dst.
+// Resident replicas (L % 32 == 0, 2 <= L/32 <= kResidentMaxC): one workgroup per
+// replica with the whole lattice in LDS, kBatchChunk sweeps per launch.
 constexpr int kBatchMaxTww = 16, kBatchTh = 128;
-// Tiled replicas run in 512-thread workgroups, ku (1 or 2) units per thread,
+// Tiled replicas run in 512-thread workgroups (more with two sweeps side by side), ku (1 or 2) units per thread,
 // in tiles 8 or 16 words wide: a tile of tww words by th rows fits when its
 // (th + 28) / 2 computed row pairs times tww + 2 words stay within ku * 512
 // units.

@@ -42,9 +42,7 @@ __host__ __device__ inline uint32_t tri_window_stride(uint32_t TW) {
   const uint32_t s = (TW + 2 * kTriHalo + 3u) & ~3u;  // whole words, an odd number of them
   return ((s >> 2) & 1u) ? s : s + 4u;
 }
-// The literal MPKK's tile kernel: each of the 16 waves keeps a ring of 128
-// pending centres (8 bytes each) whose pair is unlike, so that the decisions
-// run on full waves.
+// The 16 KiB: they belong to the rule of which tiles are accepted.
 constexpr uint32_t kTriQueue = 128, kTriQueueBytes = 16u * kTriQueue * 8u;
 __host__ __device__ inline size_t tri_window_area(uint32_t TW, uint32_t TR) {
   return ((size_t)tri_window_stride(TW) * (TR + 2 * kTriHalo) + 7u) & ~(size_t)7u;
@@ -144,8 +142,7 @@ __host__ __device__ inline uint32_t mpkk_window_stride(uint32_t TW) {
   const uint32_t s = (TW + 2 * kMpkkHalo + 3u) & ~3u;  // whole words, an odd number of them
   return ((s >> 2) & 1u) ? s : s + 4u;
 }
-// The window, then the per-wave rings of pending attempts (as for the class
-// schedule's tile kernel).
+// Which tiles are taken, as for the class schedule.
 __host__ __device__ inline size_t mpkk_window_area(uint32_t TW, uint32_t TR) {
   return ((size_t)mpkk_window_stride(TW) * (TR + 2 * kMpkkHalo) + 15u) & ~(size_t)15u;
 }
