@@ -82,7 +82,7 @@ void default_tile(int L, int layout, TileConfig* tc) {
   // draws, 16 phases of latency -- plus its units of both sweeps; 1000 units take
   // as long as the fixed part.  Against the widest tile that made 128 workgroups
   // (us per sweep, both with two sweeps per launch): 1536^2 (8, 64) 9.3, (4, 76)
-  // 6.6; 2048^2 (8, 128) 10.9, (4, 128) 8.7; 1700^2 int8 14.2 and 10.3; 1024^2
+  // 6.6; 2048^2 (8, 128) 10.9, (4, 128) 8.7; 1700^2 int8 12.8 and 9.6; 1024^2
   // (4, 64) 6.4, (2, 64) 5.5; 6144^2 40.6 and 35.4; level below 1000 and at
   // 4096^2.  Sides of 2692 .. 3968 had no tile that a launch could take.
   long best = 0;

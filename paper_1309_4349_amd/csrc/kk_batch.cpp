@@ -179,7 +179,7 @@ void batch_geometry(const kk_sim* h, bool resident, int max_tww, int max_th, int
 // Tiles of a batch that was neither tuned nor given a tile: 8 words wide and the
 // lowest that leave one workgroup per CU (256) if both sweeps fit side by side
 // (48 rows), else from 64 rows on two (us per sweep: twelve lattices of 400^2 at
-// 100 rows 17.9, 40 rows 11.5, 36 rows -- 288 workgroups -- 16.4; two of 2048^2 at
+// 100 rows 14.7, 40 rows 10.1, 36 rows -- 288 workgroups -- 14.6; two of 2048^2 at
 // 128 rows 12.8, 64 rows 11.0; five of 2048^2 at 128 rows 22.9, 64 rows -- 1280
 // workgroups -- 28.5).
 void choose_tile(kk_batch* b) {
