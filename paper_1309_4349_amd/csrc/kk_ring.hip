@@ -102,8 +102,7 @@ struct RingLane {
   uint32_t* x[11];  // own; one word on, one back; a and a + 1 on; a + 1 and a back; 2L likewise on, back
   uint32_t rot[11];
 };
-// A lane without a word (w >= W) gets places of its own past the class's words:
-// its flips are zero, and xors of one wave to one word run one after another.
+// A lane without a word (w >= W) works at ring_word(w) of every class instead.
 template <int M>
 __device__ __forceinline__ RingLane ring_lane(uint32_t* S, int w, int W, int L) {
   const int a = L >> 4, b = 2 * a + (M == 12 ? 1 : 0);
@@ -111,7 +110,7 @@ __device__ __forceinline__ RingLane ring_lane(uint32_t* S, int w, int W, int L) 
   RingLane z;
 #pragma unroll
   for (int i = 0; i < 11; ++i) {
-    const int x = w < W ? w + by[i] : w;
+    const int x = w < W ? w + by[i] : ring_word(w);
     const int turn = w < W ? (x >= W ? 1 : (x < 0 ? -1 : 0)) : 0;
     z.x[i] = S + (x - turn * W);
     z.rot[i] = (uint32_t)turn;

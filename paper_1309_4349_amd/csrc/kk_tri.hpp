@@ -88,6 +88,13 @@ inline bool tri_resident_fits(int L, int H) {
 // the most.
 constexpr int kRingMaxBits = 28, kRingMaxWords = 194;
 constexpr int kRingStride = 196;  // words per class, fixed so that a class's place is part of an instruction
+// The word of a class at which lane w of the phase waves works.  The lanes past
+// the last word decide nothing and flip no bit, but they read and xor too: the
+// word is inside the class for all of them and another one for each lane of a
+// wave, as xors of one wave to one word run one after another.
+// Lanes up to kRingStride take the spare words there are, the rest (W = 193 or
+// 194 only: four waves) the class's first words, which they xor with zero.
+__host__ __device__ constexpr int ring_word(int w) { return w < kRingStride ? w : w - kRingStride; }
 inline uint32_t ring_segments(int L, int H) {
   const int M = L * H / 16;
   uint32_t best = 0;

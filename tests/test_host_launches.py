@@ -1,0 +1,67 @@
+"""CPU checks of what the library's host side launches: small programs linked
+against libkk.so and a stand-in for the HIP runtime (host_runtime.hpp), which
+records every kernel launch and runs none."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+from paper_1309_4349_amd import kk
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_1309_4349_amd", "csrc")
+ROCM = os.environ.get("ROCM_PATH", "/opt/rocm")
+CXX = shutil.which("g++")
+
+
+def _run(tmp_path, program):
+    if CXX is None:
+        pytest.skip("no C++ compiler")
+    kk.load()  # builds the library if nothing is built
+    src, exe = tmp_path / "p.cpp", tmp_path / "p"
+    src.write_text('#include "host_runtime.hpp"\n#include "kk.h"\n' + program)
+    lib = os.path.dirname(kk.LIB_PATH)
+    subprocess.run([CXX, "-std=c++17", "-O1", "-w", "-rdynamic", "-D__HIP_PLATFORM_AMD__",
+                    *(f"-I{d}" for d in (os.path.join(ROOT, "tests"), os.path.join(ROOT, "include"), CSRC,
+                                         os.path.join(ROCM, "include"))),
+                    str(src), "-o", str(exe), f"-L{lib}", "-l:" + os.path.basename(kk.LIB_PATH), f"-Wl,-rpath,{lib}",
+                    "-Wl,--allow-shlib-undefined"], check=True)
+    r = subprocess.run([str(exe)], capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0, (r.stdout + r.stderr)[-2000:]
+
+
+# The lanes of a whole ring's phase waves: each at a word of its class, the lanes of a wave at different ones, a lane that
+# has a word of the ring at its own.
+RING = r"""
+#include <set>
+#include "kk_tri.hpp"
+using namespace kk;
+int main() {
+  int rings = 0, most = 0;
+  for (int L = 4; L <= 13568; L += 8)
+    for (int H = 4; (size_t)L * H <= kTriResidentMaxBytes; H += 4) {
+      const int B = (int)ring_segments(L, H);
+      if (B == 0) continue;
+      ++rings;
+      const int W = L * H / (16 * B);
+      REQUIRE(W * 16 * B == L * H && W <= kRingStride && 16 * W >= 2 * L);
+      REQUIRE(ring_lds_bytes(L, H) + 1024 <= 160 * 1024);
+      most = W > most ? W : most;
+      for (int wave = 0; wave < (W + 63) / 64; ++wave) {
+        std::set<int> at;
+        for (int w = 64 * wave; w < 64 * wave + 64; ++w) {
+          REQUIRE(ring_word(w) >= 0 && ring_word(w) < kRingStride && (w >= W || ring_word(w) == w));
+          at.insert(ring_word(w));
+        }
+        REQUIRE(at.size() == 64);
+      }
+    }
+  REQUIRE(rings > 1000 && most == kRingMaxWords);
+  return 0;
+}
+"""
+
+
+def test_every_lane_of_a_whole_ring_works_inside_its_class(tmp_path):
+    _run(tmp_path, RING)
