@@ -747,21 +747,19 @@ __device__ __forceinline__ uint32_t decide_word(const uint32_t* v, const RowRand
   return bop3<KK_TT(KK_TA & (~KK_TB | KK_TC))>(A, rm, accsel);
 }
 
+// LDS row stride of a row of C words: at least C + 2 (one pad word each side),
+// and congruent to C/2 modulo 32 so that the words a phase touches (every other
+// row, consecutive words) fall in consecutive LDS banks.
+__host__ __device__ constexpr int halo_stride(int C) { return C % 2 == 0 ? C / 2 + 32 : 34; }
 template <int TWW>
 struct HaloGeom {
   static constexpr int C = TWW + 2;  // LDS words per row: the tile plus one halo word each side
-  // Row stride: at least C + 2 (one pad word each side), and congruent to
-  // C/2 modulo 32 so that the words a phase touches (every other row,
-  // consecutive words) fall in consecutive LDS banks.
-  static constexpr int ST = (C % 2 == 0) ? (C / 2 + 32) : 34;
+  static constexpr int ST = halo_stride(C);
 };
 
-// LDS words of a halo tile of R rows before the tie lists (an even number):
-// the rows, 16 spare words and the row and column tables.
-template <int TWW>
-__host__ __device__ constexpr int halo_tie_offset(int R) {
-  return (R * HaloGeom<TWW>::ST + 16 + R + HaloGeom<TWW>::C + 1) & ~1;
-}
+// LDS words of a halo tile of R rows of C words before the tie lists (an even
+// number): the rows, 16 spare words and the row and column tables.
+__host__ __device__ constexpr int halo_tie_offset(int R, int C) { return (R * halo_stride(C) + 16 + R + C + 1) & ~1; }
 
 // One phase of the halo kernel for the thread's units, active row = r0 + H.
 // Branch-free over the units: a unit beyond the tile reads a valid word and
@@ -900,7 +898,7 @@ __device__ __forceinline__ unsigned halo_tile_sweep(uint32_t* S, const SweepPara
   // the workgroup's accepted count, in the gap between the rows and the
   // tables; the tie lists after the tables
   uint32_t* acc_total = S + R * ST;
-  TieList ties = tie_list(S + halo_tie_offset<TWW>(R));
+  TieList ties = tie_list(S + halo_tie_offset(R, C));
   if (threadIdx.x == 0) *acc_total = 0u;
   __syncthreads();
 
@@ -1462,9 +1460,8 @@ struct HaloPlan {
   HaloMode mode;
   int ku, threads;
 };
-template <int TWW>
-size_t halo_lds_bytes(int th, const HaloPlan& pl) {
-  return ((size_t)halo_tie_offset<TWW>(halo_rows(th, pl.mode == kOneSweep ? 1 : 2)) +
+size_t halo_lds_bytes(const SweepParams& p, const HaloPlan& pl) {
+  return ((size_t)halo_tie_offset(halo_rows(p.th, pl.mode == kOneSweep ? 1 : 2), p.C) +
           (size_t)(pl.threads / 64) * kTieWaveWords) * sizeof(uint32_t);
 }
 HaloPlan halo_plan(const SweepParams& p, int ku, bool two, int threads) {
@@ -1478,8 +1475,11 @@ HaloPlan halo_plan(const SweepParams& p, int ku, bool two, int threads) {
   }
   // two units per thread: four waves per SIMD issue a multiply or a shift
   // every 4.5 cycles, three (one wave each for 768 threads' units) only every
-  // 5.8, so the first threads take two units and the rest one
-  return HaloPlan{kOneSweep, ku, ku == 2 && p.nunits > 1024 ? 1024 : threads};
+  // 5.8, so the first threads take two units and the rest one -- but for tiles
+  // whose rows leave no room for the tie lists of 16 waves (one word wide, 992
+  // rows or more: 992 take 143440 B, a wave's list 1280)
+  const HaloPlan full{kOneSweep, ku, ku == 2 && p.nunits > 1024 ? 1024 : threads};
+  return halo_lds_bytes(p, full) <= 160 * 1024 ? full : HaloPlan{kOneSweep, ku, threads};
 }
 bool halo_width(const SweepParams& p) { return p.tww == 1 || p.tww == 2 || p.tww == 4 || p.tww == 8 || p.tww == 16; }
 }  // namespace
@@ -1513,7 +1513,7 @@ hipError_t launch_sweep(const SweepParams& p, int layout, bool cyclic, int ku, i
     const uint32_t o1 = pl.mode == kOneSweep ? 0u : class_order_host(p.k0, p.k1, p.t0 + 1);
 #define KK_HALO(LY, TW)                                                                                              \
   do {                                                                                                               \
-    const size_t hl = halo_lds_bytes<TW>(p.th, pl);                                                                  \
+    const size_t hl = halo_lds_bytes(p, pl);                                                                          \
     const dim3 nt(pl.threads);                                                                                       \
     if (pl.mode == kInTurn) hipLaunchKernelGGL((halo_kernel<LY, TW, 2, kInTurn>), grid, nt, hl, stream, p, o0, o1);  \
     else if (pl.mode == kSideBySide && pl.ku == 1)                                                                   \
@@ -1567,7 +1567,7 @@ bool batch_tile_in_turn(int tww, int th) { return half_threads(th, tww + 2, 2, 0
 
 hipError_t launch_batch_tiles(const SweepParams* reps, const BatchTileJob* jobs, int njobs, const uint32_t* orders,
                               unsigned s, const BatchTilePlan& pl, hipStream_t stream) {
-  const size_t lds = ((size_t)halo_tie_offset<kBatchMaxTww>(halo_rows(pl.max_th, pl.sweeps)) +  // the widest tile's stride
+  const size_t lds = ((size_t)halo_tie_offset(halo_rows(pl.max_th, pl.sweeps), kBatchMaxTww + 2) +  // the widest tile's stride
                       (size_t)(pl.threads / 64) * kTieWaveWords) * sizeof(uint32_t);
   const dim3 grid(njobs), block(pl.threads);
 #define KK_BATCH(KU, MODE) \

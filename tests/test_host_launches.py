@@ -65,3 +65,34 @@ int main() {
 
 def test_every_lane_of_a_whole_ring_works_inside_its_class(tmp_path):
     _run(tmp_path, RING)
+
+
+# Every tile that kk_set_tile accepts can be launched, for a single sweep and for two.
+SET_TILE = r"""
+int main() {
+  for (unsigned L : {1024u, 1036u}) {
+    kk_sim* h = nullptr;
+    REQUIRE(kk_create_ex(&h, L, 0.5, 0.5, 1, L % 32 ? KK_LAYOUT_INT8 : KK_LAYOUT_BITPACKED, nullptr) == KK_OK);
+    int accepted = 0;
+    for (unsigned words = 1; words <= 32; ++words)
+      for (unsigned rows = 2; rows <= 1200; rows += 2)
+        for (unsigned units = 1; units <= 2; ++units) {
+          if (kk_set_tile(h, words, rows, units) != KK_OK) continue;
+          ++accepted;
+          for (unsigned n = 1; n <= 2; ++n)
+            if (kk_sweep(h, n) != KK_OK) {
+              printf("tile %u x %u at %u units, %u sweeps: %s\n", words, rows, units, n, kk_last_error());
+              return 1;
+            }
+        }
+    REQUIRE(accepted > 2000);
+    REQUIRE(kk_set_tile(h, 1, 996, 2) == KK_OK && kk_set_tile(h, 1, 998, 2) == KK_EINVAL);  // 1536 units, and 1539
+    kk_destroy(h);
+  }
+  return 0;
+}
+"""
+
+
+def test_every_accepted_tile_can_be_launched(tmp_path):
+    _run(tmp_path, SET_TILE)
