@@ -306,9 +306,14 @@ __global__ __launch_bounds__(256) void fill_segregated(void* lat, int layout, in
 // Only the lattice is read per site; all else is per cluster and per edge site.
 // The per-site labelling before (parent and size words for every site, four
 // passes over them, dependent reads of global memory) took 1.7 ms at 4096^2 and
-// 4.1 ms on a 4092^2 triangular ring; now 0.17 and 0.29 ms, of which the first
-// pass 0.12 and 0.15 (bound by the chains of dependent LDS reads of a tile's
-// unions: 4 tiles per CU hold its 160 KB).
+// 4.1 ms on a 4092^2 triangular ring; now 0.16 and 0.28 ms, of which the first
+// pass 0.10 and 0.14 (bound by the chains of dependent LDS reads of a tile's
+// unions: 4 tiles per CU hold its 160 KB).  On lattices of a few tiles each pass
+// is one workgroup's latency: 400^2 at omega -1.2, whose clusters are single
+// sites for the most part, 12 + 4 + 6 + 7 us.  (27, 5, 6 and 30 us with four
+// wavefronts per tile that load one row after another, a histogram workgroup for
+// every 8 tiles, and an LDS addition for every cluster, nearly all on one word:
+// slower than the labelling before up to 800^2.)
 // ---------------------------------------------------------------------------
 constexpr int kTile = 64;
 
@@ -396,8 +401,8 @@ __device__ __forceinline__ CclTile ccl_place(const CclShape& g, int tile) {
   return t;
 }
 
-// One workgroup of 256 threads per tile (strided over the grid).
-template <bool TRI>
+// One workgroup of NW wavefronts per tile (strided over the grid).
+template <bool TRI, int NW>
 __device__ __forceinline__ void ccl_tile_body(const CclShape& g, int species, const CclBuffers& b) {
   __shared__ uint64_t rows[kTile];
   __shared__ uint32_t par[kTile * kTile], cnt[kTile * kTile];
@@ -411,16 +416,34 @@ __device__ __forceinline__ void ccl_tile_body(const CclShape& g, int species, co
     const CclTile t = ccl_place(g, tile);
     const int x0 = t.x0, y0 = t.y0, w = t.w, h = t.h;
     if (tid == 0) nroot = 0u;
-    for (int r = wave; r < kTile; r += 4) {
-      const bool me = r < h && lane < w && site_bit(g.lat, g.layout, g.L, x0 + lane, y0 + r) == species;
-      const uint64_t m = __ballot(me);
-      if (lane == 0) rows[r] = m;
+    // a wave's rows, with all of its loads in flight at once
+    if (g.layout == kLayoutBits) {  // a row per lane, one word (w == 32) or two
+      if (lane < kTile / NW) {
+        const int r = wave + NW * lane;
+        const uint32_t* q =
+            static_cast<const uint32_t*>(g.lat) + (size_t)(y0 + min(r, h - 1)) * (g.L >> 5) + (x0 >> 5);
+        const uint64_t flip = species ? 0ull : ~0ull, in = w > 32 ? ~0ull : 0xFFFFFFFFull;
+        const uint64_t m = (uint64_t)q[0] | ((uint64_t)q[w > 32 ? 1 : 0] << 32);
+        rows[r] = r < h ? (m ^ flip) & in : 0ull;
+      }
+    } else {
+      const uint8_t* q = static_cast<const uint8_t*>(g.lat) + (size_t)x0 + min(lane, w - 1);
+      int site[kTile / NW];
+#pragma unroll
+      for (int k = 0; k < kTile / NW; ++k) site[k] = q[(size_t)(y0 + min(wave + NW * k, h - 1)) * g.L] & 1;
+#pragma unroll
+      for (int k = 0; k < kTile / NW; ++k) {
+        const uint64_t m = __ballot(wave + NW * k < h && lane < w && site[k] == species);
+        if (lane == 0) rows[wave + NW * k] = m;
+      }
+    }
+    for (int r = wave; r < kTile; r += NW) {
       par[r * kTile + lane] = (uint32_t)(r * kTile + lane);
       cnt[r * kTile + lane] = 0u;
     }
     __syncthreads();
     // bonds to the row above, one union per stretch of them
-    for (int r = wave == 0 ? 4 : wave; r < h; r += 4) {
+    for (int r = wave == 0 ? NW : wave; r < h; r += NW) {
       const uint64_t m = rows[r], mp = rows[r - 1];
       const uint64_t o = m & mp, os = o & ~(o << 1);
       if ((os >> lane) & 1ull)
@@ -435,7 +458,7 @@ __device__ __forceinline__ void ccl_tile_body(const CclShape& g, int species, co
     }
     __syncthreads();
     // run starts: link to the root, add the run's length to it
-    for (int r = wave; r < h; r += 4) {
+    for (int r = wave; r < h; r += NW) {
       const uint64_t m = rows[r], st = m & ~(m << 1);
       if ((st >> lane) & 1ull) {
         const uint64_t run = ~(m >> lane);
@@ -448,7 +471,7 @@ __device__ __forceinline__ void ccl_tile_body(const CclShape& g, int species, co
     __syncthreads();
     // the tile's clusters, numbered; cnt becomes the number of each root
     const uint32_t base = t.base;
-    for (int r = wave; r < h; r += 4) {
+    for (int r = wave; r < h; r += NW) {
       const uint64_t m = rows[r], st = m & ~(m << 1);
       const uint32_t me = (uint32_t)(r * kTile + lane);
       if (((st >> lane) & 1ull) && par[me] == me) {
@@ -463,11 +486,11 @@ __device__ __forceinline__ void ccl_tile_body(const CclShape& g, int species, co
       const int edge = wave;
       const int er = edge == 0 ? 0 : (edge == 1 ? h - 1 : lane), ec = edge == 2 ? 0 : (edge == 3 ? w - 1 : lane);
       uint32_t id = kNone;
-      if (er < h && ec < w) {
+      if (wave < 4 && er < h && ec < w) {
         const uint64_t m = rows[er];
         if ((m >> ec) & 1ull) id = base + cnt[par[(uint32_t)(er * kTile) + run_start(m, (uint32_t)ec)]];
       }
-      b.border[(size_t)tile * 256 + tid] = id;
+      if (wave < 4) b.border[(size_t)tile * 256 + tid] = id;
     }
     if (tid == 0) b.ncl[tile] = nroot;
     __syncthreads();
@@ -565,21 +588,26 @@ __device__ __forceinline__ void ccl_sizes_body(const CclShape& g, const CclBuffe
 }
 
 __device__ __forceinline__ void ccl_hist_body(const CclShape& g, const CclBuffers& b, unsigned* h) {
+  const int ntiles = ((g.L + kTile - 1) / kTile) * ((g.H + kTile - 1) / kTile);
+  if ((int)blockIdx.x >= ntiles) return;
   for (int k = threadIdx.x; k < kSmallSizes; k += blockDim.x) h[k] = 0;
   __syncthreads();
-  const int ntiles = ((g.L + kTile - 1) / kTile) * ((g.H + kTile - 1) / kTile);
+  unsigned ones = 0;  // clusters of one site, the most frequent: additions to one word run one after another
   for (int tile = (int)blockIdx.x; tile < ntiles; tile += (int)gridDim.x) {
     const uint32_t n = b.ncl[tile], base = ccl_place(g, tile).base;
     for (uint32_t k = threadIdx.x; k < n; k += blockDim.x) {
       if (b.parent[base + k] != base + k) continue;
       const uint32_t s = b.size[base + k];
-      if (s < (uint32_t)kSmallSizes) atomicAdd(&h[s], 1u);
+      if (s == 1u) ++ones;
+      else if (s < (uint32_t)kSmallSizes) atomicAdd(&h[s], 1u);
       else {
         const unsigned slot = atomicAdd(b.big_count, 1u);
         if (slot < b.big_cap) b.big[slot] = s;
       }
     }
   }
+  for (int off = 32; off > 0; off >>= 1) ones += __shfl_down(ones, off, 64);
+  if ((threadIdx.x & 63) == 0) atomicAdd(&h[1], ones);
   __syncthreads();
   for (int k = threadIdx.x; k < kSmallSizes; k += blockDim.x)
     if (h[k]) atomicAdd(&b.hist[k], h[k]);
@@ -587,9 +615,9 @@ __device__ __forceinline__ void ccl_hist_body(const CclShape& g, const CclBuffer
 
 // The passes as kernels for one lattice, and for many square lattices at once:
 // replica blockIdx.y of a table, each with its own buffers.
-template <bool TRI>
-__global__ __launch_bounds__(256) void ccl_tile(CclShape g, int species, CclBuffers b) {
-  ccl_tile_body<TRI>(g, species, b);
+template <bool TRI, int NW>
+__global__ __launch_bounds__(64 * NW) void ccl_tile(CclShape g, int species, CclBuffers b) {
+  ccl_tile_body<TRI, NW>(g, species, b);
 }
 template <bool TRI>
 __global__ __launch_bounds__(256) void ccl_border(CclShape g, CclBuffers b) {
@@ -603,7 +631,7 @@ __global__ __launch_bounds__(256) void ccl_hist(CclShape g, CclBuffers b) {
 __device__ __forceinline__ CclShape ccl_shape(const CclRep& r) { return CclShape{r.lat, r.layout, r.L, r.L}; }
 __global__ __launch_bounds__(256) void ccl_tile_many(const CclRep* reps, int species) {
   const CclRep r = reps[blockIdx.y];
-  ccl_tile_body<false>(ccl_shape(r), species, r.b);
+  ccl_tile_body<false, 4>(ccl_shape(r), species, r.b);
 }
 __global__ __launch_bounds__(256) void ccl_border_many(const CclRep* reps) {
   const CclRep r = reps[blockIdx.y];
@@ -737,13 +765,13 @@ size_t ccl_border_words(int L, int H) { return ccl_tiles(L, H) * (256 + 1); }
 
 namespace {
 // Workgroups of each pass over n tiles: one per tile up to 4096; a thread per
-// edge site; and few histograms, each of which clears and flushes 4096 bins.
+// edge site; and up to 128 histograms, each of which clears and flushes 4096 bins.
 struct CclGrid {
   unsigned tile, border, sizes, hist;
 };
 CclGrid ccl_grid(size_t n, bool triangular) {
   return CclGrid{(unsigned)std::min<size_t>(n, 4096), (unsigned)std::min<size_t>((n * (triangular ? 192 : 128) + 255) / 256, 4096),
-                 (unsigned)std::min<size_t>(n, 4096), (unsigned)std::min<size_t>((n + 7) / 8, 128)};
+                 (unsigned)std::min<size_t>(n, 4096), (unsigned)std::min<size_t>(n, 128)};
 }
 }  // namespace
 
@@ -751,11 +779,17 @@ hipError_t launch_ccl(const void* lat, int layout, int L, int H, int species, co
                       hipStream_t stream) {
   const CclGrid n = ccl_grid(ccl_tiles(L, H), triangular);
   const CclShape g{lat, layout, L, H};
+  // Up to a tile per CU, 16 wavefronts per tile: a wavefront's rows come one after
+  // another (us of the first pass with 4 and with 16: 64^2 17.5 and 8.4, 400^2 22.2
+  // and 11.9); with more tiles the four that share a CU fill it.
+  const bool wide = n.tile <= 256;
   if (triangular) {
-    hipLaunchKernelGGL(ccl_tile<true>, dim3(n.tile), dim3(256), 0, stream, g, species, b);
+    if (wide) hipLaunchKernelGGL((ccl_tile<true, 16>), dim3(n.tile), dim3(1024), 0, stream, g, species, b);
+    else hipLaunchKernelGGL((ccl_tile<true, 4>), dim3(n.tile), dim3(256), 0, stream, g, species, b);
     hipLaunchKernelGGL(ccl_border<true>, dim3(n.border), dim3(256), 0, stream, g, b);
   } else {
-    hipLaunchKernelGGL(ccl_tile<false>, dim3(n.tile), dim3(256), 0, stream, g, species, b);
+    if (wide) hipLaunchKernelGGL((ccl_tile<false, 16>), dim3(n.tile), dim3(1024), 0, stream, g, species, b);
+    else hipLaunchKernelGGL((ccl_tile<false, 4>), dim3(n.tile), dim3(256), 0, stream, g, species, b);
     hipLaunchKernelGGL(ccl_border<false>, dim3(n.border), dim3(256), 0, stream, g, b);
   }
   hipLaunchKernelGGL(ccl_sizes, dim3(n.sizes), dim3(256), 0, stream, g, b);

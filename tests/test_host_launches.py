@@ -96,3 +96,32 @@ int main() {
 
 def test_every_accepted_tile_can_be_launched(tmp_path):
     _run(tmp_path, SET_TILE)
+
+
+# Each pass of a cluster histogram has the workgroups to work on all tiles (64 x 64 sites) of a small lattice at once.
+HIST = r"""
+int main() {
+  for (unsigned L : {64u, 256u, 400u, 640u}) {
+    kk_sim* h = nullptr;
+    REQUIRE(kk_create_ex(&h, L, 0.5, 0.5, 1, KK_LAYOUT_INT8, nullptr) == KK_OK);
+    g_launches.clear();
+    size_t n = 0;
+    REQUIRE(kk_cluster_hist(h, 1, nullptr, 0, &n) == KK_OK);
+    const unsigned tiles = ((L + 63) / 64) * ((L + 63) / 64);
+    size_t seen = 0;
+    for (const Launch& l : g_launches)
+      for (const char* pass : {"ccl_tile", "ccl_sizes", "ccl_hist"})
+        if (l.kernel.find(pass) != std::string::npos) {
+          REQUIRE(l.blocks == tiles);
+          ++seen;
+        }
+    REQUIRE(seen == 3);
+    kk_destroy(h);
+  }
+  return 0;
+}
+"""
+
+
+def test_histogram_passes_take_all_tiles_at_once(tmp_path):
+    _run(tmp_path, HIST)
