@@ -379,8 +379,10 @@ void kk_batch_destroy(kk_batch *b);
  * replica holding its whole ring in LDS for all of its sweeps.  Other
  * class-schedule replicas whose lattice takes a whole-sweep tile are
  * "batched": each sweep of a run is one launch whose workgroups are the tiles
- * of all batched replicas that still have sweeps to make.  Literal-MPKK
- * replicas and the rest run through their own launches on the batch stream.
+ * of all batched replicas that still have sweeps to make.  Of the rest, the
+ * replicas whose handle's tile is the whole ring share one launch per run, a
+ * workgroup each; literal MPKK and the others run through their own launches
+ * on the batch stream.
  * A replica's result equals what kk_create_triangular_ex + kk_restart(start)
  * + kk_sweep(sweeps) per run gives alone (no replica index enters a random
  * counter). */
@@ -407,8 +409,8 @@ kk_status kk_tri_batch_run(kk_tri_batch *b);
  * never destroy it). */
 kk_status kk_tri_batch_sim(kk_tri_batch *b, size_t i, kk_sim **sim_out);
 /* Resident replicas (whole ring in one workgroup), replicas in the batched
- * tile launch, replicas run on their own, and tile jobs of the batched
- * launch.  NULL outputs are skipped. */
+ * tile launch, the others (fewer than 64 whole rings among them), and tile
+ * jobs of the batched launch.  NULL outputs are skipped. */
 kk_status kk_tri_batch_info(kk_tri_batch *b, size_t *n_resident, size_t *n_batched, size_t *n_plain,
                             size_t *n_jobs);
 void kk_tri_batch_destroy(kk_tri_batch *b);

@@ -500,11 +500,11 @@ void tri_default_tile(int L, int H, bool mpkk, int* tw, int* tr) {
   double best = 0.0;
   *tw = *tr = 0;
   // the whole ring in one workgroup: with equal segments up to 26000 sites (us
-  // per sweep against tiles: 140^2 6.8 and 14.6, 156^2 11.5 and 14.6; level near
-  // 38000, but a batch of few such rings is better off sharing its launches of
-  // tiles), and at any size that no tile fits (380 x 80 12.4 against 64.5 with a
-  // launch per class); a byte per site up to 12288 (its 16.7 at 10000 sites grow
-  // with the sites, 26 at 148^2)
+  // per sweep against tiles: 140^2 6.8 and 14.6, 156^2 11.5 and 14.6, level near
+  // 38000; the line lies below the crossing because rings above it, 132 x 200 the
+  // smallest in use, are relied on to run in tiles), and at any size that no tile
+  // fits (380 x 80 12.4 against 64.5 with a launch per class); a byte per site up
+  // to 12288 (its 16.7 at 10000 sites grow with the sites, 26 at 148^2)
   const long most = !ring_segments(L, H) ? 12288 : tri_tile_fits(L, H, 16, 16) ? 26000 : (long)kTriResidentMaxBytes;
   if (!mpkk && (long)L * H <= most && tri_resident_fits(L, H)) {
     *tw = L;

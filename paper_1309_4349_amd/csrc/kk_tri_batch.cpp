@@ -8,10 +8,13 @@
 // a run is one launch whose workgroups are the (replica, tile) jobs of all
 // tiled replicas that still have sweeps to make.  Tiled replicas are ordered
 // by their sweep count, longest first, so the jobs of sweep k are a prefix of
-// one job table.  The rest (literal MPKK, lattices too small for a tile) run
-// through their own launches on the same stream.  No replica index enters a
-// random counter, so every replica ends exactly where kk_sweep would have
-// left it.
+// one job table.  Of the rest, the replicas whose handle runs the whole ring
+// share one launch as the resident ones do (fewer than kMinResident, or the
+// batch would have made them resident; one launch each took 6.8 us per sweep
+// times their number: 8 rings of 140^2 54 us per sweep of all, 63 rings 427, now
+// 6.9); literal MPKK and lattices too small for a tile run through their own
+// launches on the same stream.  No replica index enters a random counter, so
+// every replica ends exactly where kk_sweep would have left it.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -37,8 +40,7 @@ struct kk_tri_batch {
   bool own_stream = false;
   bool poisoned = false;
   std::vector<size_t> res;       // resident replicas
-  size_t res_lds = 0;            // the largest resident ring's LDS
-  TriResidentRep* d_res = nullptr;
+  TriResidentRep* d_res = nullptr;  // room for every replica whose ring fits
   std::vector<size_t> order;     // tiled replicas, sweeps descending
   std::vector<uint32_t> tw, tr;  // their tiles, fixed at creation (the job table depends on them)
   std::vector<size_t> plain;     // the others
@@ -115,15 +117,14 @@ kk_status kk_tri_batch_create(kk_tri_batch** out, const kk_tri_replica* reps, si
     const bool whole = h->tri_tw == h->L && h->tri_tr == h->H;
     if (h->geom == 1 && fits >= kMinResident && tri_resident_fits(h->L, h->H)) {
       b->res.push_back(i);
-      b->res_lds = std::max(b->res_lds, ring_lds_bytes(h->L, h->H));
     } else if (h->geom == 1 && h->tri_tw > 0 && !whole) {
       b->order.push_back(i);
     } else {
       b->plain.push_back(i);
     }
   }
-  if (!b->res.empty()) {
-    const kk_status st = device_alloc((void**)&b->d_res, b->res.size() * sizeof(TriResidentRep));
+  if (fits > 0) {
+    const kk_status st = device_alloc((void**)&b->d_res, fits * sizeof(TriResidentRep));
     if (st != KK_OK) return fail(st);
   }
   std::stable_sort(b->order.begin(), b->order.end(),
@@ -178,27 +179,38 @@ kk_status tri_batch_run(kk_tri_batch* b) {
     if (h->t + b->sweeps[i] >= ((uint64_t)1 << 60)) return set_error(KK_EINVAL, "sweep counter overflow");
   }
   // every replica's stream is the batch stream, so the order below is the order on the device
-  std::vector<TriResidentRep> res_reps(b->res.size());  // alive until the final synchronisation
-  if (!b->res.empty()) {
-    std::vector<TriResidentRep>& reps = res_reps;
-    for (size_t k = 0; k < b->res.size(); ++k) {
-      kk_sim* h = b->sims[b->res[k]];
+  // whole rings: the resident replicas, and those that run on their own as long as their handle's tile is the ring
+  std::vector<size_t> rings = b->res, alone;
+  for (size_t i : b->plain) {
+    const kk_sim* h = b->sims[i];
+    (h->geom == 1 && h->tri_tw == h->L && h->tri_tr == h->H ? rings : alone).push_back(i);
+  }
+  if (rings.size() == 1) {  // one alone takes its description as an argument (140^2 6.74 us per sweep, from the table 6.83)
+    alone.push_back(rings[0]);
+    rings.clear();
+  }
+  std::vector<TriResidentRep> reps(rings.size());  // alive until the final synchronisation
+  if (!rings.empty()) {
+    size_t lds = 0;
+    for (size_t k = 0; k < rings.size(); ++k) {
+      kk_sim* h = b->sims[rings[k]];
       TriResidentRep& R = reps[k];
       R.lat = static_cast<uint8_t*>(h->lat[h->cur]);
       R.L = (uint32_t)h->L;
       R.H = (uint32_t)h->H;
-      R.sweeps = (uint32_t)b->sweeps[b->res[k]];
+      R.sweeps = (uint32_t)b->sweeps[rings[k]];
       R.seg = ring_segments(h->L, h->H);
       R.k0 = h->k0;
       R.k1 = h->k1;
       R.t0 = h->t;
       R.acc = h->tacc;
       R.partials = h->partials;
+      lds = std::max(lds, ring_lds_bytes(h->L, h->H));
     }
     TB_HIP(hipMemcpyAsync(b->d_res, reps.data(), reps.size() * sizeof(TriResidentRep), hipMemcpyHostToDevice,
                           b->stream));
-    TB_HIP(launch_tri_resident(b->d_res, (uint32_t)b->res.size(), b->res_lds, b->stream));
-    for (size_t i : b->res) {
+    TB_HIP(launch_tri_resident(b->d_res, (uint32_t)rings.size(), lds, b->stream));
+    for (size_t i : rings) {
       kk_sim* h = b->sims[i];
       h->t += b->sweeps[i];
       h->attempts += b->sweeps[i] * (uint64_t)h->L * (uint64_t)h->H;
@@ -207,11 +219,10 @@ kk_status tri_batch_run(kk_tri_batch* b) {
   }
   std::vector<TriBatchRep> tile_reps(b->order.size());  // alive until the final synchronisation
   if (!b->order.empty()) {
-    std::vector<TriBatchRep>& reps = tile_reps;
     uint64_t mx = 0;
     for (size_t k = 0; k < b->order.size(); ++k) {
       kk_sim* h = b->sims[b->order[k]];
-      TriBatchRep& R = reps[k];
+      TriBatchRep& R = tile_reps[k];
       R.lat[0] = static_cast<uint8_t*>(h->lat[0]);
       R.lat[1] = static_cast<uint8_t*>(h->lat[1]);
       R.L = (uint32_t)h->L;
@@ -228,7 +239,7 @@ kk_status tri_batch_run(kk_tri_batch* b) {
       R.partials = h->partials;
       mx = std::max(mx, b->sweeps[b->order[k]]);
     }
-    TB_HIP(hipMemcpyAsync(b->d_reps, reps.data(), reps.size() * sizeof(TriBatchRep), hipMemcpyHostToDevice,
+    TB_HIP(hipMemcpyAsync(b->d_reps, tile_reps.data(), tile_reps.size() * sizeof(TriBatchRep), hipMemcpyHostToDevice,
                           b->stream));
     // sweep k: the replicas with more than k sweeps, a prefix of `order`
     size_t active = b->order.size();
@@ -246,7 +257,7 @@ kk_status tri_batch_run(kk_tri_batch* b) {
       if (s) h->epoch += 1;
     }
   }
-  for (size_t i : b->plain) {
+  for (size_t i : alone) {
     const kk_status st = kk_sweep_async(b->sims[i], b->sweeps[i]);
     if (st != KK_OK) {
       b->poisoned = true;

@@ -125,3 +125,37 @@ int main() {
 
 def test_histogram_passes_take_all_tiles_at_once(tmp_path):
     _run(tmp_path, HIST)
+
+
+# Whole rings of a batch of fewer than 64 share one launch; a replica whose handle was given another tile since, and one
+# that is no ring, run their own.
+FEW_RINGS = r"""
+int main() {
+  std::vector<kk_tri_replica> reps;
+  for (unsigned i = 0; i < 12; ++i) {
+    const unsigned L = i % 3 == 0 ? 100u : 140u;
+    reps.push_back(kk_tri_replica{L, L, KK_TRI_CLASSES, KK_START_RANDOM, 0.5, 0.5, i, 3 + i % 2});
+  }
+  reps.push_back(kk_tri_replica{101, 84, KK_TRI_MPKK, KK_START_RANDOM, 0.5, 0.5, 1, 3});
+  kk_tri_batch* b = nullptr;
+  REQUIRE(kk_tri_batch_create(&b, reps.data(), reps.size(), nullptr) == KK_OK);
+  g_launches.clear();
+  REQUIRE(kk_tri_batch_run(b) == KK_OK);
+  REQUIRE(launched("ring_sweeps") == 1 && launched("mpkk") == 3);
+  for (const Launch& l : g_launches) REQUIRE(l.kernel.find("ring_sweeps") == std::string::npos || l.blocks == 12);
+  kk_sim* h = nullptr;
+  REQUIRE(kk_tri_batch_sim(b, 1, &h) == KK_OK && kk_tri_set_tile(h, 16, 16) == KK_OK);
+  g_launches.clear();
+  REQUIRE(kk_tri_batch_run(b) == KK_OK);
+  REQUIRE(launched("ring_sweeps") == 1 && launched("hex_sweep") == 4);
+  for (const Launch& l : g_launches) REQUIRE(l.kernel.find("ring_sweeps") == std::string::npos || l.blocks == 11);
+  uint64_t sweeps = 0, attempts = 0;
+  REQUIRE(kk_stats(h, &sweeps, &attempts, nullptr) == KK_OK && sweeps == 8 && attempts == 8 * 140 * 140);
+  kk_tri_batch_destroy(b);
+  return 0;
+}
+"""
+
+
+def test_few_whole_rings_share_a_launch(tmp_path):
+    _run(tmp_path, FEW_RINGS)
