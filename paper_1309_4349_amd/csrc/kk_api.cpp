@@ -58,15 +58,9 @@ bool cyclic_fits(int L) {
 std::mutex g_tuned_mu;
 std::map<std::pair<int, int>, TileConfig> g_tuned;
 
-void default_tile(int L, int layout, TileConfig* tc) {
-  {
-    std::lock_guard<std::mutex> lk(g_tuned_mu);
-    auto it = g_tuned.find({L, layout});
-    if (it != g_tuned.end()) {
-      *tc = it->second;
-      return;
-    }
-  }
+namespace {
+// The tile of a lattice that no autotuner has looked at.
+void modelled_tile(int L, TileConfig* tc) {
   // the whole lattice in one workgroup up to 160 (4.4 us per sweep against 4.8 ..
   // 5.0 with tiles; 192 6.0 and 4.8, 288 11.5 and 4.9)
   if (cyclic_fits(L) && L <= 160) {
@@ -101,6 +95,19 @@ void default_tile(int L, int layout, TileConfig* tc) {
       tc->ku = second > max_threads(1) ? 2 : 1;
     }
   }
+}
+}  // namespace
+
+void default_tile(int L, int layout, TileConfig* tc) {
+  {
+    std::lock_guard<std::mutex> lk(g_tuned_mu);
+    auto it = g_tuned.find({L, layout});
+    if (it != g_tuned.end()) {
+      *tc = it->second;
+      return;
+    }
+  }
+  modelled_tile(L, tc);
 }
 
 // Fill the geometry fields of p for lattice side L and tile config tc.
@@ -1165,29 +1172,36 @@ kk_status kk_autotune(kk_sim* h, uint32_t trial_sweeps, uint32_t* tile_words, ui
   if (h->geom != 0) return set_error(KK_EINVAL, "the triangular lattice has no sweep tiles");
   if (trial_sweeps == 0) trial_sweeps = 20;
   if (trial_sweeps > 100000) return set_error(KK_EINVAL, "trial_sweeps must be at most 100000");
+  trial_sweeps += trial_sweeps & 1;  // whole launches of two sweeps, which runs are made of
   const int L = h->L;
-  // candidates: the cyclic tile when it fits, and halo tiles of the compiled widths
+  // candidates: the tile the handle has, the one it would have untuned, the
+  // cyclic tile when it fits, and halo tiles of the compiled widths
   std::vector<TileConfig> cands;
-  for (int ku = 1; ku <= 2; ++ku) {
-    TileConfig tc;
-    tc.ku = ku;
+  auto add = [&](const TileConfig& tc) {
     std::string why;
+    for (const TileConfig& c : cands)
+      if (c.cyclic == tc.cyclic && c.tww == tc.tww && c.th == tc.th && c.ku == tc.ku) return;
+    if (tile_valid(L, tc, &why)) cands.push_back(tc);
+  };
+  add(h->tile);
+  TileConfig tc;
+  modelled_tile(L, &tc);
+  add(tc);
+  for (int ku = 1; ku <= 2; ++ku) {
+    tc.ku = ku;
     if (cyclic_fits(L)) {
       tc.cyclic = true;
       tc.tww = L / 32;
       tc.th = L;
-      if (tile_valid(L, tc, &why)) cands.push_back(tc);
+      add(tc);
     }
+    tc.cyclic = false;
     for (int tww : {16, 8, 4, 2, 1}) {
       if (tww > (L + 31) / 32) continue;
       for (int th : {32, 48, 64, 96, 128, 192, 256}) {
-        tc.cyclic = false;
         tc.tww = tww;
         tc.th = std::min(th, L);
-        bool dup = false;
-        for (const TileConfig& c : cands)
-          dup |= !c.cyclic && c.tww == tc.tww && c.th == tc.th && c.ku == tc.ku;
-        if (!dup && tile_valid(L, tc, &why)) cands.push_back(tc);
+        add(tc);
       }
     }
   }

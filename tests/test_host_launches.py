@@ -2,7 +2,6 @@
 against libkk.so and a stand-in for the HIP runtime (host_runtime.hpp), which
 records every kernel launch and runs none."""
 import os
-import shutil
 import subprocess
 
 import pytest
@@ -11,20 +10,18 @@ from paper_1309_4349_amd import kk
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 CSRC = os.path.join(ROOT, "paper_1309_4349_amd", "csrc")
-ROCM = os.environ.get("ROCM_PATH", "/opt/rocm")
-CXX = shutil.which("g++")
+HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 
 def _run(tmp_path, program):
-    if CXX is None:
-        pytest.skip("no C++ compiler")
+    if not os.path.exists(HIPCC):
+        pytest.skip("no hipcc")
     kk.load()  # builds the library if nothing is built
     src, exe = tmp_path / "p.cpp", tmp_path / "p"
     src.write_text('#include "host_runtime.hpp"\n#include "kk.h"\n' + program)
     lib = os.path.dirname(kk.LIB_PATH)
-    subprocess.run([CXX, "-std=c++17", "-O1", "-w", "-rdynamic", "-D__HIP_PLATFORM_AMD__",
-                    *(f"-I{d}" for d in (os.path.join(ROOT, "tests"), os.path.join(ROOT, "include"), CSRC,
-                                         os.path.join(ROCM, "include"))),
+    subprocess.run([HIPCC, "--offload-arch=gfx950", "--offload-host-only", "-std=c++17", "-O1", "-w", "-rdynamic",
+                    *(f"-I{d}" for d in (os.path.join(ROOT, "tests"), os.path.join(ROOT, "include"), CSRC)),
                     str(src), "-o", str(exe), f"-L{lib}", "-l:" + os.path.basename(kk.LIB_PATH), f"-Wl,-rpath,{lib}",
                     "-Wl,--allow-shlib-undefined"], check=True)
     r = subprocess.run([str(exe)], capture_output=True, text=True, timeout=120)
@@ -159,3 +156,45 @@ int main() {
 
 def test_few_whole_rings_share_a_launch(tmp_path):
     _run(tmp_path, FEW_RINGS)
+
+
+# kk_autotune times the tile the handle has and the untuned default, also once another tile is the default of the process,
+# and ranks by launches of two sweeps whatever the number of trial sweeps.
+AUTOTUNE = r"""
+#include "kk_kernels.hpp"
+static unsigned fast[2];  // words and rows of the tile that is quicker than all others
+static double cost(const Launch& l) {
+  if (l.kernel.find("halo_kernel") == std::string::npos && l.kernel.find("sweep_kernel") == std::string::npos &&
+      l.kernel.find("pipe_kernel") == std::string::npos)
+    return 0.0;
+  const kk::SweepParams& p = *static_cast<const kk::SweepParams*>(l.args[0]);
+  return (p.nsweeps == 1 ? 50.0 : p.nsweeps) * ((unsigned)p.tww == fast[0] && (unsigned)p.th == fast[1] ? 0.5 : 1.0);
+}
+int main() {
+  g_cost = cost;
+  for (unsigned L : {300u, 400u, 1036u, 2048u}) {
+    const unsigned layout = L % 32 ? KK_LAYOUT_INT8 : KK_LAYOUT_BITPACKED;
+    kk_sim *h = nullptr, *g = nullptr, *f = nullptr;
+    uint32_t words, rows, units;
+    double us = 0.0;
+    REQUIRE(kk_create_ex(&h, L, 0.5, 0.5, 1, layout, nullptr) == KK_OK);
+    uint32_t untuned[3];
+    REQUIRE(kk_get_tile(h, &untuned[0], &untuned[1], &untuned[2]) == KK_OK);
+    fast[0] = 2, fast[1] = 64;  // one of the list
+    REQUIRE(kk_autotune(h, 1, &words, &rows, &units, &us) == KK_OK && words == 2 && rows == 64 && us == 500.0);
+    fast[0] = untuned[0], fast[1] = untuned[1];  // only the rule's; the process's default is the list's now
+    REQUIRE(kk_create_ex(&g, L, 0.5, 0.5, 1, layout, nullptr) == KK_OK);
+    REQUIRE(kk_autotune(g, 5, &words, &rows, &units, &us) == KK_OK);
+    REQUIRE(words == untuned[0] && rows == untuned[1] && units == untuned[2] && us == 500.0);
+    fast[0] = 1, fast[1] = 22;  // only the handle's
+    REQUIRE(kk_create_ex(&f, L, 0.5, 0.5, 1, layout, nullptr) == KK_OK && kk_set_tile(f, 1, 22, 1) == KK_OK);
+    REQUIRE(kk_autotune(f, 4, &words, &rows, &units, nullptr) == KK_OK && words == 1 && rows == 22 && units == 1);
+    for (kk_sim* s : {h, g, f}) kk_destroy(s);
+  }
+  return 0;
+}
+"""
+
+
+def test_autotune_times_the_tile_it_replaces(tmp_path):
+    _run(tmp_path, AUTOTUNE)
