@@ -123,8 +123,17 @@ def kernel_sources_sha(files=KERNEL_SOURCES) -> str:
     return h.hexdigest()[:16]
 
 
-BYTES_PER_ATTEMPT_BITS = 0.25   # read + write one bit per site per sweep
-BYTES_PER_ATTEMPT_INT8 = 2.0
+# A launch reads and writes the lattice once, however many sweeps it makes.
+BYTES_PER_SITE_BITS = 0.25
+BYTES_PER_SITE_INT8 = 2.0
+
+
+def hbm_fields(sites: int, bytes_per_site: float, launch_s: float) -> dict:
+    """What one launch cannot do without moving, and the rate that makes."""
+    moved = int(bytes_per_site * sites)
+    rate = moved / launch_s / 1e9
+    return {"algorithmic_bytes_per_launch": moved, "hbm_achieved_GBps": round(rate, 1),
+            "hbm_frac": round(rate / HBM_PEAK_GBS, 5)}
 
 
 def log(*a):
@@ -310,7 +319,6 @@ def triangular(sweeps: int, profile_sweeps: int, cpu: bool, batch_sweeps: int = 
     ms, launches = sim.sweep_timed(profile_sweeps)
     per_launch_s = ms / 1e3 / launches
     per_launch = N * profile_sweeps / launches
-    hbm = BYTES_PER_ATTEMPT_INT8 * per_launch / per_launch_s / 1e9
     nab, _ = sim.energy()
     sim.close()
     traffic = None
@@ -323,7 +331,7 @@ def triangular(sweeps: int, profile_sweeps: int, cpu: bool, batch_sweeps: int = 
                         "traffic": traffic, "kernel": "hex_sweep" if sim_tile[0] else "tri_phase",
                         "kernel_us": round(per_launch_s * 1e6, 3), "launches": int(launches),
                         "tile": {"cols": sim_tile[0], "rows": sim_tile[1]},
-                        "hbm_achieved_GBps": round(hbm, 1), "hbm_frac": round(hbm / HBM_PEAK_GBS, 5)}}
+                        **hbm_fields(N, BYTES_PER_SITE_INT8, per_launch_s)}}
     log(f"[bench] triangular {L}^2: {rate:.3e} attempts/s, {per_launch_s * 1e6:.2f} us/launch")
     out["batch"] = tri_batch(256, 100, batch_sweeps, 32)
     if cpu:
@@ -374,7 +382,6 @@ def mpkk(steps: int, bias_steps: int, cpu: bool, weights=None):
     ms, launches = sim.sweep_timed(50)
     per_launch_s = ms / 1e3 / launches
     per_launch = N * 50 / launches
-    hbm = BYTES_PER_ATTEMPT_INT8 * per_launch / per_launch_s / 1e9
     sim.close()
     traffic = None
     if (kernel_sources_sha(TRI_KERNEL_SOURCES) == MPKK_PROFILED_TRAFFIC["sources_sha256_prefix"]
@@ -386,7 +393,7 @@ def mpkk(steps: int, bias_steps: int, cpu: bool, weights=None):
                         "traffic": traffic, "kernel": "hex_mpkk_step" if mp_tile[0] else "mpkk_iter",
                         "kernel_us": round(per_launch_s * 1e6, 3), "launches": int(launches),
                         "tile": {"cols": mp_tile[0], "rows": mp_tile[1]},
-                        "hbm_achieved_GBps": round(hbm, 1), "hbm_frac": round(hbm / HBM_PEAK_GBS, 5)}}
+                        **hbm_fields(N, BYTES_PER_SITE_INT8, per_launch_s)}}
     log(f"[bench] mpkk {L}x{H}: {rate:.3e} attempts/s, {per_launch_s * 1e6:.2f} us/launch")
     if cpu:
         threads = int(os.environ.get("OMP_NUM_THREADS", os.cpu_count() or 1))
@@ -550,13 +557,11 @@ def grid_400(rounds: int, every: int, weights=None, tile=None):
                   if same_src and tuple(ptile) == GRID_PROFILED_TRAFFIC["plain_tile"] else None,
                   "kernel": f"halo_kernel<int8, {ptile[0]}, {ptile[2]}>", "kernel_us": round(per_launch_s * 1e6, 3),
                   "launches": int(launches), "tile": {"words": ptile[0], "rows": ptile[1], "units_per_thread": ptile[2]},
-                  "algorithmic_bytes_per_launch": int(BYTES_PER_ATTEMPT_INT8 * per_launch),
-                  "hbm_achieved_GBps": round(BYTES_PER_ATTEMPT_INT8 * per_launch / per_launch_s / 1e9, 1),
-                  "hbm_frac": round(BYTES_PER_ATTEMPT_INT8 * per_launch / per_launch_s / 1e9 / HBM_PEAK_GBS, 5)}
+                  **hbm_fields(jobs[5].L * jobs[5].L, BYTES_PER_SITE_INT8, per_launch_s)}
     batch_sweep_rate = sites * every / tsw
     batch_roof = {**roofline_alu(SQUARE_MIX, weights, batch_sweep_rate),
                   "traffic": None,
-                  "algorithmic_bytes_per_launch": int(BYTES_PER_ATTEMPT_INT8 * sites),
+                  "algorithmic_bytes_per_launch": int(BYTES_PER_SITE_INT8 * sites),
                   "kernel": "batch_tile_kernel (whole batch run of the 12 lattices, launch gaps included)",
                   "us_per_sweep": round(tsw / every * 1e6, 3), "plan": plan}
     log(f"[bench] 400^2 grid: batched {rate:.3e} attempts/s (tiles <= {tw}x{th}; sweeps alone "
@@ -692,7 +697,7 @@ def main():
     ms, launches = sim.sweep_timed(args.profile_sweeps)
     per_launch_s = ms / 1e3 / launches
     attempts_per_launch = N * args.profile_sweeps / launches
-    hbm = BYTES_PER_ATTEMPT_BITS * attempts_per_launch / per_launch_s / 1e9
+    hbm = hbm_fields(N, BYTES_PER_SITE_BITS, per_launch_s)
     tw, th, ku = sim.get_tile()
     traffic = None
     if (kernel_sources_sha() == PROFILED_TRAFFIC["sources_sha256_prefix"]
@@ -700,16 +705,14 @@ def main():
         traffic = PROFILED_TRAFFIC["bytes_per_launch"]
     roofline = {**roofline_alu(SQUARE_MIX, weights, attempts_per_launch / per_launch_s), "traffic": traffic,
                 "traffic_unit": "bytes per launch (rocprofv3 FETCH_SIZE + WRITE_SIZE, copy-calibrated)",
-                "algorithmic_bytes_per_launch": int(BYTES_PER_ATTEMPT_BITS * attempts_per_launch),
                 "kernel": f"halo_kernel<bitpacked, {tw}, {ku}>",
                 "kernel_us": round(per_launch_s * 1e6, 3), "launches": int(launches),
-                "hbm_achieved_GBps": round(hbm, 1), "hbm_peak_GBps": HBM_PEAK_GBS,
-                "hbm_frac": round(hbm / HBM_PEAK_GBS, 5),
+                "hbm_peak_GBps": HBM_PEAK_GBS, **hbm,
                 "tile": {"words": tw, "rows": th, "units_per_thread": ku},
                 "valu_issue_cycles": {k: round(v, 3) for k, v in (cycles or {}).items()},
                 "weights_rel_fma": {k: round(v, 3) for k, v in weights.items()}}
     log(f"[bench] sweep kernel {per_launch_s * 1e6:.2f} us/launch, frac {roofline['frac']}, "
-        f"{hbm:.1f} GB/s algorithmic")
+        f"{hbm['hbm_achieved_GBps']} GB/s algorithmic")
     # observables of the final state (labelling, N_AB and the random-neighbour draw)
     sim.sweep(1)
     torch.cuda.synchronize()
