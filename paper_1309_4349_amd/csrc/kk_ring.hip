@@ -102,7 +102,8 @@ struct RingLane {
   uint32_t* x[11];  // own; one word on, one back; a and a + 1 on; a + 1 and a back; 2L likewise on, back
   uint32_t rot[11];
 };
-// A lane without a word (w >= W) works at ring_word(w) of every class instead.
+// A lane without a word (w >= W) has the words w of all classes for its own
+// (kRingWords): its flips are zero.
 template <int M>
 __device__ __forceinline__ RingLane ring_lane(uint32_t* S, int w, int W, int L) {
   const int a = L >> 4, b = 2 * a + (M == 12 ? 1 : 0);
@@ -110,7 +111,7 @@ __device__ __forceinline__ RingLane ring_lane(uint32_t* S, int w, int W, int L) 
   RingLane z;
 #pragma unroll
   for (int i = 0; i < 11; ++i) {
-    const int x = w < W ? w + by[i] : ring_word(w);
+    const int x = w < W ? w + by[i] : w;
     const int turn = w < W ? (x >= W ? 1 : (x < 0 ? -1 : 0)) : 0;
     z.x[i] = S + (x - turn * W);
     z.rot[i] = (uint32_t)turn;
@@ -268,7 +269,7 @@ __device__ __forceinline__ void hex_ring(const TriResidentRep& R, uint32_t* lds,
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), nwaves = nthreads >> 6;
   const int nb = (W + 63) >> 6, ndraw = nwaves - nb;
   uint32_t* S = lds;                      // [class][kRingStride]
-  uint32_t* D = S + 16 * kRingStride;     // [buffer][class][W][6]
+  uint32_t* D = S + kRingWords;           // [buffer][class][W][6]
   uint64_t* orders = reinterpret_cast<uint64_t*>(D + 12 * K);  // of 128 sweeps
   const HexAccept acc = hex_accept(R.acc);
   for (int k = (int)threadIdx.x; k < K; k += nthreads) {

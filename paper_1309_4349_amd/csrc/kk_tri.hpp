@@ -88,13 +88,13 @@ inline bool tri_resident_fits(int L, int H) {
 // the most.
 constexpr int kRingMaxBits = 28, kRingMaxWords = 194;
 constexpr int kRingStride = 196;  // words per class, fixed so that a class's place is part of an instruction
-// The word of a class at which lane w of the phase waves works.  The lanes past
-// the last word decide nothing and flip no bit, but they read and xor too: the
-// word is inside the class for all of them and another one for each lane of a
-// wave, as xors of one wave to one word run one after another.
-// Lanes up to kRingStride take the spare words there are, the rest (W = 193 or
-// 194 only: four waves) the class's first words, which they xor with zero.
-__host__ __device__ constexpr int ring_word(int w) { return w < kRingStride ? w : w - kRingStride; }
+// Lane w of the phase waves works at word w of a class, also past the class's
+// last word: such a lane decides nothing and flips no bit, but it reads and xors
+// too, at a word that no other lane of its wave has (xors of one wave to one word
+// run one after another).  With 193 or 194 words there are four waves, whose last
+// lanes reach into the next class, and past the last class into spare words.
+constexpr int kRingLanes = (kRingMaxWords + 63) / 64 * 64;
+constexpr int kRingWords = 16 * kRingStride + (kRingLanes - kRingStride);  // of LDS before the draws; an even number
 inline uint32_t ring_segments(int L, int H) {
   const int M = L * H / 16;
   uint32_t best = 0;
@@ -109,7 +109,7 @@ inline uint32_t ring_segments(int L, int H) {
 inline size_t ring_lds_bytes(int L, int H) {
   const uint32_t B = ring_segments(L, H);
   const size_t N = (size_t)L * (size_t)H;
-  return B ? 16u * 4u * kRingStride + 12u * 4u * (N / B) + 1024u : N;
+  return B ? 4u * kRingWords + 12u * 4u * (N / B) + 1024u : N;
 }
 struct TriResidentRep {
   uint8_t* lat;  // the current buffer, updated in place

@@ -28,10 +28,9 @@ def _run(tmp_path, program):
     assert r.returncode == 0, (r.stdout + r.stderr)[-2000:]
 
 
-# The lanes of a whole ring's phase waves: each at a word of its class, the lanes of a wave at different ones, a lane that
-# has a word of the ring at its own.
+# The lanes of a whole ring's phase waves stay, in every class, before the words where other waves store the draws, and
+# the ring, two buffers of draws and 128 class orders fit the LDS next to what the kernel holds there besides (under 1 KiB).
 RING = r"""
-#include <set>
 #include "kk_tri.hpp"
 using namespace kk;
 int main() {
@@ -45,14 +44,9 @@ int main() {
       REQUIRE(W * 16 * B == L * H && W <= kRingStride && 16 * W >= 2 * L);
       REQUIRE(ring_lds_bytes(L, H) + 1024 <= 160 * 1024);
       most = W > most ? W : most;
-      for (int wave = 0; wave < (W + 63) / 64; ++wave) {
-        std::set<int> at;
-        for (int w = 64 * wave; w < 64 * wave + 64; ++w) {
-          REQUIRE(ring_word(w) >= 0 && ring_word(w) < kRingStride && (w >= W || ring_word(w) == w));
-          at.insert(ring_word(w));
-        }
-        REQUIRE(at.size() == 64);
-      }
+      const int lanes = (W + 63) / 64 * 64;
+      REQUIRE(15 * kRingStride + lanes <= kRingWords && kRingWords % 2 == 0);
+      REQUIRE(ring_lds_bytes(L, H) >= 4u * kRingWords + 12u * 16u * W * 4u + 128u * 8u);
     }
   REQUIRE(rings > 1000 && most == kRingMaxWords);
   return 0;
@@ -60,7 +54,7 @@ int main() {
 """
 
 
-def test_every_lane_of_a_whole_ring_works_inside_its_class(tmp_path):
+def test_every_lane_of_a_whole_ring_stays_off_the_draws(tmp_path):
     _run(tmp_path, RING)
 
 
