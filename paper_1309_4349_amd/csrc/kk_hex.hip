@@ -576,15 +576,9 @@ __global__ __launch_bounds__(1024) void hex_mpkk_step(const uint8_t* __restrict_
 
 // The class order of sweep t, for a launch that holds one sweep.
 uint64_t class_order16(uint32_t k0, uint32_t k1, uint64_t t) {
-  uint32_t w[16];
-  for (uint32_t j = 0; j < 4; ++j) {
-    const Philox4 b = philox10_host(j, 0u, (uint32_t)t, ctr_hi(t, kTagTriOrder), k0, k1);
-    w[4 * j] = b.x;
-    w[4 * j + 1] = b.y;
-    w[4 * j + 2] = b.z;
-    w[4 * j + 3] = b.w;
-  }
-  return shuffle_nibbles(w, 16);
+  return order_of([&](int j) {
+    return philox10_host((uint32_t)j, 0u, (uint32_t)t, ctr_hi(t, kTagTriOrder), k0, k1);
+  });
 }
 
 // The domain covers k_j of the seven iterations of step t, nibble j each.

@@ -289,16 +289,8 @@ __device__ __forceinline__ void hex_ring(const TriResidentRep& R, uint32_t* lds,
   } else {
     auto draw_orders = [&](uint32_t first) {
       const uint64_t t = R.t0 + first + (uint32_t)lane;
-      uint32_t w[16];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const Philox4 b = philox10((uint32_t)j, 0u, (uint32_t)t, ctr_hi(t, kTagTriOrder), R.k0, R.k1);
-        w[4 * j] = b.x;
-        w[4 * j + 1] = b.y;
-        w[4 * j + 2] = b.z;
-        w[4 * j + 3] = b.w;
-      }
-      orders[(first + (uint32_t)lane) & 127u] = shuffle_nibbles(w, 16);
+      orders[(first + (uint32_t)lane) & 127u] = order_of(
+          [&](int j) { return philox10((uint32_t)j, 0u, (uint32_t)t, ctr_hi(t, kTagTriOrder), R.k0, R.k1); });
     };
     const int inv = (1 << 20) / W + 1, ntask = (8 * W + 63) >> 6;
     // blocks of the longest wave's tasks per part of a sweep

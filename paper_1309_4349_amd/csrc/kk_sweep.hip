@@ -765,9 +765,9 @@ __host__ __device__ constexpr int halo_tie_offset(int R, int C) { return (R * ha
 // Branch-free over the units: a unit beyond the tile reads a valid word and
 // has an empty centre mask, so it decides nothing and writes nothing.
 template <int ST, int KU, int H>
-__device__ __forceinline__ unsigned halo_phase(uint32_t* S, const SweepParams& p, const int* base0, const int* yrow,
-                                               const int* xw, const uint32_t* okm, const RowRand (*rr)[2],
-                                               const uint32_t (*imask)[2], int a, uint64_t t) {
+__device__ __forceinline__ unsigned halo_phase(uint32_t* S, const SweepParams& p, const int* base0,
+                                               const uint32_t* okm, const RowRand (*rr)[2],
+                                               const uint32_t (*imask)[2], int a) {
   uint32_t v[KU][11];
 #pragma unroll
   for (int k = 0; k < KU; ++k) {
@@ -926,8 +926,8 @@ __device__ __forceinline__ unsigned halo_tile_sweep(uint32_t* S, const SweepPara
     const int npairs = halo_pairs(p.th, NS, sw), nunits = npairs * C;
     const uint64_t t = p.t0 + (uint64_t)sw;
     ties.n = 0u;
-    int base0[KU], yrow[KU * 2], xw[KU];  // LDS base; true row of each of the pair's rows; true x of bit 0
-    uint32_t okm[KU * 2];                 // class-0 centre pattern of each row (0 for a unit beyond the tile)
+    int base0[KU];         // LDS base
+    uint32_t okm[KU * 2];  // class-0 centre pattern of each row (0 for a unit beyond the tile)
     uint32_t imask[KU][2];
     RowRand rr[KU][2];
     int tie[KU][2];              // index of each row word's tie results
@@ -963,9 +963,6 @@ __device__ __forceinline__ unsigned halo_tile_sweep(uint32_t* S, const SweepPara
       const int w = ok ? wu : 0;
       const int r0 = 2 + 16 * sw + 2 * q;
       base0[k] = r0 * ST + wu + 1;  // also for a word past wneed, which holds the zero pad
-      yrow[2 * k] = ytab[r0];
-      yrow[2 * k + 1] = ytab[r0 + 1];
-      xw[k] = xtab[w];
       // class a = 0 centres of a row with virtual y sit at x = y (mod 4); the
       // virtual x of bit 0 is a multiple of 32
       okm[2 * k] = ok ? (0x11111111u << ((YT + r0) & 3)) : 0u;
@@ -1036,11 +1033,11 @@ __device__ __forceinline__ unsigned halo_tile_sweep(uint32_t* S, const SweepPara
     // pairs start on even rows, so the active row of every pair is the class
     // parity: a uniform branch keeps each row's random state in registers
     if (last) {
-      if (cls & 1u) count += halo_phase<ST, KU, 1>(S, p, base0, yrow, xw, okm, rr, imask, a, t);
-      else count += halo_phase<ST, KU, 0>(S, p, base0, yrow, xw, okm, rr, imask, a, t);
+      if (cls & 1u) count += halo_phase<ST, KU, 1>(S, p, base0, okm, rr, imask, a);
+      else count += halo_phase<ST, KU, 0>(S, p, base0, okm, rr, imask, a);
     } else {
-      if (cls & 1u) count += halo_phase<ST, 1, 1>(S, p, base0, yrow, xw, okm, rr, imask, a, t);
-      else count += halo_phase<ST, 1, 0>(S, p, base0, yrow, xw, okm, rr, imask, a, t);
+      if (cls & 1u) count += halo_phase<ST, 1, 1>(S, p, base0, okm, rr, imask, a);
+      else count += halo_phase<ST, 1, 0>(S, p, base0, okm, rr, imask, a);
     }
     if ((ph & 7) == 7) {  // each wave adds its count before the last barrier
       const unsigned ws = wave_sum8(count);

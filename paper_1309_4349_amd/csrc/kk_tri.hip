@@ -140,20 +140,6 @@ __global__ __launch_bounds__(256) void mpkk_iter(const uint8_t* __restrict__ in,
   block_count(cnt, red, partials);
 }
 
-// One word or one atomic per workgroup of 256 threads, as kk_aux.hip's summing passes.
-__device__ __forceinline__ void add_block_sum(uint32_t v, unsigned long long* out, bool spread) {
-  __shared__ unsigned long long part[4];
-  unsigned long long a = v;
-  for (int off = 32; off > 0; off >>= 1) a += __shfl_down(a, off, 64);
-  if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = a;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    const unsigned long long tot = part[0] + part[1] + part[2] + part[3];
-    if (spread) out[blockIdx.x] = tot;
-    else if (tot) atomicAdd(out, tot);
-  }
-}
-
 // N_AB over the 3N bonds (i, i+1), (i, i+L), (i, i+L-1): four sites at a time
 // where their neighbours lie before the ring's end, else one by one.
 __global__ __launch_bounds__(256) void tri_energy(const uint8_t* s, uint32_t L, uint32_t N, unsigned long long* out,

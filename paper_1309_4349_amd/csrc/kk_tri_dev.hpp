@@ -58,7 +58,7 @@ struct Draw {
 // that follows from them, stay in scalar registers, which leaves 18 multiplies
 // per block.
 struct Head {
-  uint32_t u0c, u1, u2x, u3;  // round 1: hi(t_lo M1) ^ j ^ k0 multiplied out, lo(t_lo M1)
+  uint32_t u0c, u2x, u3;  // round 1: hi(t_lo M1) ^ j ^ k0 multiplied out, lo(t_lo M1)
   uint32_t th1, k0, k1;
 };
 __device__ __forceinline__ Head philox_head(uint32_t j, uint32_t tl, uint32_t th, uint32_t k0, uint32_t k1) {
@@ -68,7 +68,6 @@ __device__ __forceinline__ Head philox_head(uint32_t j, uint32_t tl, uint32_t th
   h.u0c = (uint32_t)p1 ^ (k0 + 0x9E3779B9u);              // round 2's c1 ^ k0
   h.u2x = (uint32_t)(p0 >> 32) ^ (k1 + 0xBB67AE85u);      // round 2's hi(p0) ^ k1
   h.u3 = (uint32_t)p0;                                    // round 2's new c3
-  h.u1 = 0u;
   h.th1 = th ^ k1;                                        // round 1's c3 ^ k1
   h.k0 = k0;
   h.k1 = k1;
@@ -151,19 +150,27 @@ __device__ __forceinline__ uint32_t decide(const Around& v, const Draw& q, uint3
   return lut3<kA & (~kB | kC)>(live, rm, acc);
 }
 
-// The class order of sweep t: Philox blocks 0 .. 3 of the order's counters,
-// one per lane, and the shuffle in scalar registers.
-__device__ __forceinline__ uint64_t hex_order(uint32_t k0, uint32_t k1, uint64_t t) {
-  const Philox4 b = philox10(threadIdx.x & 3u, 0u, (uint32_t)t, ctr_hi(t, kTagTriOrder), k0, k1);
+// The class order of a sweep from Philox blocks 0 .. 3 of the order's counters.
+template <class Block>
+__host__ __device__ __forceinline__ uint64_t order_of(Block block) {
   uint32_t w[16];
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
-    w[4 * j] = (uint32_t)__builtin_amdgcn_readlane((int)b.x, j);
-    w[4 * j + 1] = (uint32_t)__builtin_amdgcn_readlane((int)b.y, j);
-    w[4 * j + 2] = (uint32_t)__builtin_amdgcn_readlane((int)b.z, j);
-    w[4 * j + 3] = (uint32_t)__builtin_amdgcn_readlane((int)b.w, j);
+    const Philox4 b = block(j);
+    w[4 * j] = b.x;
+    w[4 * j + 1] = b.y;
+    w[4 * j + 2] = b.z;
+    w[4 * j + 3] = b.w;
   }
   return shuffle_nibbles(w, 16);
+}
+// Of sweep t, for a wavefront: a block per lane, and the shuffle in scalar registers.
+__device__ __forceinline__ uint64_t hex_order(uint32_t k0, uint32_t k1, uint64_t t) {
+  const Philox4 b = philox10(threadIdx.x & 3u, 0u, (uint32_t)t, ctr_hi(t, kTagTriOrder), k0, k1);
+  return order_of([&](int j) {
+    return Philox4{(uint32_t)__builtin_amdgcn_readlane((int)b.x, j), (uint32_t)__builtin_amdgcn_readlane((int)b.y, j),
+                   (uint32_t)__builtin_amdgcn_readlane((int)b.z, j), (uint32_t)__builtin_amdgcn_readlane((int)b.w, j)};
+  });
 }
 
 // Sum of every thread's count, added to *dst by thread 0.
