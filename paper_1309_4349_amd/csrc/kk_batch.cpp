@@ -205,10 +205,18 @@ void choose_tile(kk_batch* b) {
 
 // Two sweeps per launch where it pays: side by side with at most one workgroup
 // per CU; in turn up to 1024 workgroups, or if no lattice is bit-packed (us per
-// sweep, one and two: 2048^2 x 5 29.0 and 22.9; bits 4096^2 x 2 27.8 and 28.2,
-// 320^2 x 200 28.5 and 30.7, the 256-replica table 41.3 and 43.2; int8 1024^2 x 48
-// 60.8 and 47.7): with the device full of workgroups the launch and the staging
-// hide behind other tiles' phases, and the taller window is what is left.
+// sweep, one and two: 2048^2 x 5 29.0 and 22.9).  With the device full of
+// workgroups the launch hides behind other tiles' phases; what two sweeps save
+// then is one of two stagings and stores, 64 bytes and their packing per word of
+// int8 but 8 bytes per word of bits, and what they cost is 32 more rows of
+// window, most for the low tiles of small lattices.  So all-int8 sets gain
+// (1024^2 x 48 61.2 and 48.1, 4096^2 x 3 75.3 and 54.9, 320^2 x 200 35.2 and 34.0),
+// bits lose or are level (320^2 x 200 28.5 and 30.3, 2048^2 x 12 42.4 and 42.1),
+// and so do the sets of mixed layouts and many small sides that batches are made
+// of (the 256-replica table 41.3 and 42.9, its off-grid form 45.3 and 46.2).  One
+// launch makes the same number of sweeps of all its replicas, so one bit-packed
+// replica decides for the set; mixed sets of one large side would gain (half of
+// 1024^2 x 48 in int8 52.5 and 45.4).
 BatchTilePlan tile_plan(const kk_batch* b, size_t jobs) {
   BatchTilePlan pl{1, false, b->tile_ku, kBatchTileThreads, 0};
   int side = 0;

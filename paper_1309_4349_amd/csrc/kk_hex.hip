@@ -216,12 +216,14 @@ __device__ __forceinline__ int div_small(int i, int inv) { return (int)(((uint32
 // What bounds it: the draws, by VALU issue (66 instructions per two sites: 18
 // multiplies and ten compare/add pairs among them, about 300 of a SIMD's
 // cycles at four waves), then the 16 phases, by one wave's latency (about 105
-// dependent instructions, 19 LDS reads, 7 LDS xors and a barrier, 950 cycles;
-// the rows of a window fill 2 to 6 waves, so a phase cannot be shortened by
-// more of them).  4092^2 (256 x 256 tiles, one per CU): 26 us of draws, 8 us
-// of phases, 8 us of loads, packing and stores, 46 us per sweep in all,
-// against 104 us with one byte per site and a Philox block per attempt;
-// 1028^2 19.0 against 31.1 us, 404 x 412 14.9 against 23.9 us.
+// dependent instructions, 19 LDS reads, 7 LDS xors and a barrier; the rows of a
+// window fill 2 to 6 waves, so a phase cannot be shortened by more of them).
+// 4092^2 (256 x 256 tiles, one per CU): of a workgroup's 99000 cycles 5000 go by
+// until the loads are issued, the draws and the packing end at 70500, 16 phases
+// of 1240 follow, and the stores take the rest: 46.4 us per sweep against 104 us
+// with one byte per site and a Philox block per attempt.  404 x 412 (29 x 23
+// tiles), 27000 cycles: 2200, 9100, 16 x 970, 1000: 14.9 against 23.9 us;
+// 1028^2 18.6 against 31.1 us.
 __device__ __forceinline__ void hex_sweep_body(const uint8_t* __restrict__ in, uint8_t* __restrict__ out, uint32_t L,
                                                uint32_t H, uint32_t TW, uint32_t TR, uint32_t tx, uint32_t ty,
                                                uint32_t k0, uint32_t k1, uint64_t t, uint64_t order,
@@ -402,10 +404,12 @@ __global__ __launch_bounds__(1024) void hex_sweep_batch(const TriBatchRep* reps,
 // each.
 //
 // What bounds it: as for the class schedule, the draws by VALU issue and the
-// seven iterations by one wave's latency (1550 cycles each: two barriers).
-// 4098 x 4095 (257 x 256 tiles) 50.6 us per step against 102.8 us with one byte
-// per site; 1027 x 1029 16.3 against 25.1 us; 404 x 420 13.1 against 17.1 us, of
-// which 3 us are the launch, 4 the window and its draws, 5 the iterations.
+// seven iterations by one wave's latency (two barriers each).  4098 x 4095 (257 x
+// 256 tiles), 100000 cycles: 8000 until the loads are issued, 55000 draws and
+// packing, 7 x 2670, 18000 stores (of single bytes at a tile's edges): 50.6 us
+// per step against 102.8 us with one byte per site.  404 x 420 (24 x 28 tiles),
+// 22000 cycles: 2700, 6800, 7 x 1580, 1700: 13.1 against 17.1 us; 1027 x 1029
+// 16.3 against 25.1 us.
 __global__ __launch_bounds__(1024) void hex_mpkk_step(const uint8_t* __restrict__ in, uint8_t* __restrict__ out,
                                                       uint32_t L, uint32_t H, uint32_t TW, uint32_t TR, uint32_t ntx,
                                                       uint32_t k0, uint32_t k1, uint64_t t, uint32_t covers,

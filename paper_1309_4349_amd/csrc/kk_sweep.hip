@@ -7,11 +7,13 @@
 // (SWAR) logic against the word's 12 bit-sliced random planes.
 //
 // Two tile modes:
-//  * halo tiles (hx = 1 word, hy = 16 rows on each side): one sweep per
-//    launch.  A phase's dependency radius is 2 sites, so after 8 phases the
-//    interior is exact while the outermost 16 rows / 16 bits of the halo
-//    may be stale; the counter-based random numbers make the redundant halo
-//    work reproduce exactly what the neighbouring tile computes.
+//  * halo tiles (one word and 16 rows per sweep on each side): two sweeps per
+//    launch with 32 rows, or one with 16.  A phase's dependency radius is 2
+//    sites, so a sweep's 8 phases leave the interior exact while the outermost
+//    16 rows / 16 bits of the halo may be stale (32 of both after two sweeps:
+//    the one word is enough for them); the counter-based random numbers make
+//    the redundant halo work reproduce exactly what the neighbouring tile
+//    computes.
 //  * cyclic tile (whole lattice, L % 32 == 0): rows and words wrap inside
 //    LDS, so no halo exists and any number of sweeps runs in one launch.
 //
@@ -806,7 +808,8 @@ __device__ __forceinline__ unsigned halo_phase(uint32_t* S, const SweepParams& p
     // every update goes out unconditionally (the two carries into the
     // neighbouring words are mostly zero, but a masked store costs more issue
     // slots than an xor with zero, and skipping a wave's carries when none is
-    // set measured slower: 16.45 against 16.1 us per 4096^2 sweep)
+    // set measured slower: 16.45 against 16.1 us per 4096^2 sweep at one sweep
+    // per launch of 16 x 128 tiles)
     atomicXor(&S[b], (Fpx << 1) | f | (Fmx >> 1));
     atomicXor(&S[b + ST], Fpy);
     atomicXor(&S[b - ST], Fmy);
@@ -834,12 +837,14 @@ __device__ __forceinline__ unsigned wave_sum8(unsigned c) {
 // conflict-free schedule makes that reordering exact), so the LDS latency of
 // the second unit hides behind the first.
 // One sweep of tile `tile` of the lattice described by p (halo mode), `order`
-// the sweep's class order.  What bounds it: at 4096^2 (256 tiles of 16 x 128) VALU
-// issue, the draws 5 us and the eight phases 5.5 us of the 15.6 us sweep (16.0
-// with three waves per SIMD and ties resolved in place); on small lattices, whose
-// tiles have one or two waves, the chain of staging, draws and phases (400^2 12.9
-// -> 10.2 us, 1036^2 14.7 -> 12.6 us: loads without a branch between them, ties
-// in one list, spare lanes on words of their own).
+// the sweep's class order.  What bounds it: at 4096^2 (256 tiles of 8 x 256, in
+// turn, 28.3 us per launch) VALU issue: of a workgroup's 63000 cycles 3000 are
+// staging, 29000 the two sweeps' draws, 30000 their phases, 1000 the stores.  On
+// small lattices, whose tiles have one or two waves per sweep, the chain of them:
+// 400^2 (tiles of 1 x 24, side by side, 11.7 us per launch), 24400 cycles: 3500
+// tables and loads, 8500 draws, ties and packing, 12300 the 16 phases (with one
+// sweep per launch 12.9 -> 10.2 us, 1036^2 14.7 -> 12.6 us: loads without a branch
+// between them, ties in one list, spare lanes on words of their own).
 // Two sweeps in one launch: the window has 16 more rows on each side (its halo
 // columns, 32, are enough for two sweeps as they are), and the launch, the
 // staging and the stores are paid once.
@@ -988,7 +993,7 @@ __device__ __forceinline__ unsigned halo_tile_sweep(uint32_t* S, const SweepPara
     // index all lie beyond the tile skips them.  Drawing more rows at once, to
     // overlap more Philox chains, measured slower: 16.3 us per 4096^2 sweep for a
     // unit's two rows, 18.7 us for all four rows of a thread, against 16.2 us row
-    // by row.
+    // by row (at one sweep per launch of 16 x 128 tiles).
     auto draw_rows = [&](auto on_grid) {
 #pragma unroll
       for (int k = 0; k < KU; ++k) {
@@ -1564,8 +1569,8 @@ bool batch_tile_in_turn(int tww, int th) { return half_threads(th, tww + 2, 2, 0
 
 hipError_t launch_batch_tiles(const SweepParams* reps, const BatchTileJob* jobs, int njobs, const uint32_t* orders,
                               unsigned s, const BatchTilePlan& pl, hipStream_t stream) {
-  const size_t lds = ((size_t)halo_tie_offset(halo_rows(pl.max_th, pl.sweeps), kBatchMaxTww + 2) +  // the widest tile's stride
-                      (size_t)(pl.threads / 64) * kTieWaveWords) * sizeof(uint32_t);
+  const int rows = halo_tie_offset(halo_rows(pl.max_th, pl.sweeps), kBatchMaxTww + 2);  // the widest tile's stride
+  const size_t lds = ((size_t)rows + (size_t)(pl.threads / 64) * kTieWaveWords) * sizeof(uint32_t);
   const dim3 grid(njobs), block(pl.threads);
 #define KK_BATCH(KU, MODE) \
   hipLaunchKernelGGL((batch_tile_kernel<KU, MODE>), grid, block, lds, stream, reps, jobs, orders, s)
