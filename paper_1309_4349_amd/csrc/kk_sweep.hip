@@ -21,6 +21,7 @@
 // (classes 2*((x - y) mod 4) + (y mod 2)), so no pair writes a site that
 // another pair reads: the LDS updates are xor-flips of disjoint bits issued
 // with ds_xor, and a workgroup barrier separates phases.
+#include <algorithm>
 #include <type_traits>
 
 #include "kk_common.hpp"
@@ -1466,15 +1467,8 @@ size_t halo_lds_bytes(const SweepParams& p, const HaloPlan& pl) {
   return ((size_t)halo_tie_offset(halo_rows(p.th, pl.mode == kOneSweep ? 1 : 2), p.C) +
           (size_t)(pl.threads / 64) * kTieWaveWords) * sizeof(uint32_t);
 }
-HaloPlan halo_plan(const SweepParams& p, int ku, bool two, int threads) {
-  const bool rows_fit = (size_t)halo_rows(p.th, 2) * HaloGeom<16>::ST * 4 + 32768 <= 160 * 1024;  // the widest stride
-  if (two && rows_fit) {
-    for (int k = 1; k <= 2; ++k) {
-      const int n = half_threads(p.th, p.C, k, 0) + half_threads(p.th, p.C, k, 1);
-      if (n <= 1024) return HaloPlan{kSideBySide, k, n};
-    }
-    if (half_threads(p.th, p.C, 2, 0) <= 1024) return HaloPlan{kInTurn, 2, 1024};
-  }
+HaloPlan one_sweep_plan(const SweepParams& p, int ku) {
+  const int threads = ((p.nunits + ku - 1) / ku + 63) & ~63;
   // two units per thread: four waves per SIMD issue a multiply or a shift
   // every 4.5 cycles, three (one wave each for 768 threads' units) only every
   // 5.8, so the first threads take two units and the rest one -- but for tiles
@@ -1483,12 +1477,41 @@ HaloPlan halo_plan(const SweepParams& p, int ku, bool two, int threads) {
   const HaloPlan full{kOneSweep, ku, ku == 2 && p.nunits > 1024 ? 1024 : threads};
   return halo_lds_bytes(p, full) <= 160 * 1024 ? full : HaloPlan{kOneSweep, ku, threads};
 }
+// Rounds of workgroups that a launch takes: 16 wavefronts (halo_kernel's
+// registers) and 160 KiB of LDS per CU.
+int halo_rounds(const SweepParams& p, const HaloPlan& pl) {
+  const int tiles = p.tiles_x * ((p.L + p.th - 1) / p.th);
+  const int per_cu = std::min(1024 / pl.threads, (int)(160 * 1024 / halo_lds_bytes(p, pl)));
+  return (tiles + 256 * per_cu - 1) / (256 * per_cu);
+}
+// How pairs of sweeps are launched: two per launch if that takes no more rounds
+// of workgroups than one, and with several rounds only from 56 rows on, where
+// the window of two sweeps has at most a fifth more units than two of one.  us
+// per sweep, one and two per launch: bits 4096^2 in tiles of 16 x 128 (one round
+// either way) 15.9 and 14.4, of 8 x 64 (one round becomes four) 21.5 and 34.5, of
+// 16 x 40 (four rounds either way) 36.0 and 40.5; 2048^2 in tiles of 2 x 32 (one
+// becomes three) 11.3 and 24.9.  Over 2349 tiles on sides of 64 .. 8192 the choice
+// is within 1.14 of the better but for a few int8 tiles, 0.7 % from it on average;
+// tiles of the default rule always take two.
+HaloPlan pair_plan(const SweepParams& p, int ku) {
+  const HaloPlan one = one_sweep_plan(p, ku);
+  const bool rows_fit = (size_t)halo_rows(p.th, 2) * HaloGeom<16>::ST * 4 + 32768 <= 160 * 1024;  // the widest stride
+  if (!rows_fit) return one;
+  HaloPlan two = one;
+  for (int k = 2; k >= 1; --k) {
+    const int n = half_threads(p.th, p.C, k, 0) + half_threads(p.th, p.C, k, 1);
+    if (n <= 1024) two = HaloPlan{kSideBySide, k, n};
+  }
+  if (two.mode == kOneSweep && half_threads(p.th, p.C, 2, 0) <= 1024) two = HaloPlan{kInTurn, 2, 1024};
+  const int rounds = halo_rounds(p, one);
+  return halo_rounds(p, two) <= rounds && (rounds == 1 || p.th >= 56) ? two : one;
+}
 bool halo_width(const SweepParams& p) { return p.tww == 1 || p.tww == 2 || p.tww == 4 || p.tww == 8 || p.tww == 16; }
 }  // namespace
 
 int sweeps_per_launch(const SweepParams& p, bool cyclic, int ku) {
   if (cyclic) return 256;
-  return halo_width(p) && halo_plan(p, ku, true, 0).mode != kOneSweep ? 2 : 1;
+  return halo_width(p) && pair_plan(p, ku).mode != kOneSweep ? 2 : 1;
 }
 
 hipError_t launch_sweep(const SweepParams& p, int layout, bool cyclic, int ku, int threads, hipStream_t stream) {
@@ -1510,7 +1533,7 @@ hipError_t launch_sweep(const SweepParams& p, int layout, bool cyclic, int ku, i
     return hipGetLastError();
   }
   if (!cyclic && halo_width(p)) {
-    const HaloPlan pl = halo_plan(p, ku, p.nsweeps == 2, threads);
+    const HaloPlan pl = p.nsweeps == 2 ? pair_plan(p, ku) : one_sweep_plan(p, ku);
     const uint32_t o0 = class_order_host(p.k0, p.k1, p.t0);
     const uint32_t o1 = pl.mode == kOneSweep ? 0u : class_order_host(p.k0, p.k1, p.t0 + 1);
 #define KK_HALO(LY, TW)                                                                                              \

@@ -174,15 +174,15 @@ int main() {
     REQUIRE(kk_create_ex(&h, L, 0.5, 0.5, 1, layout, nullptr) == KK_OK);
     uint32_t untuned[3];
     REQUIRE(kk_get_tile(h, &untuned[0], &untuned[1], &untuned[2]) == KK_OK);
-    fast[0] = 2, fast[1] = 64;  // one of the list
-    REQUIRE(kk_autotune(h, 1, &words, &rows, &units, &us) == KK_OK && words == 2 && rows == 64 && us == 500.0);
+    fast[0] = 8, fast[1] = 96;  // one of the list
+    REQUIRE(kk_autotune(h, 1, &words, &rows, &units, &us) == KK_OK && words == 8 && rows == 96 && us == 500.0);
     fast[0] = untuned[0], fast[1] = untuned[1];  // only the rule's; the process's default is the list's now
     REQUIRE(kk_create_ex(&g, L, 0.5, 0.5, 1, layout, nullptr) == KK_OK);
     REQUIRE(kk_autotune(g, 5, &words, &rows, &units, &us) == KK_OK);
     REQUIRE(words == untuned[0] && rows == untuned[1] && units == untuned[2] && us == 500.0);
-    fast[0] = 1, fast[1] = 22;  // only the handle's
-    REQUIRE(kk_create_ex(&f, L, 0.5, 0.5, 1, layout, nullptr) == KK_OK && kk_set_tile(f, 1, 22, 1) == KK_OK);
-    REQUIRE(kk_autotune(f, 4, &words, &rows, &units, nullptr) == KK_OK && words == 1 && rows == 22 && units == 1);
+    fast[0] = 8, fast[1] = 100;  // only the handle's
+    REQUIRE(kk_create_ex(&f, L, 0.5, 0.5, 1, layout, nullptr) == KK_OK && kk_set_tile(f, 8, 100, 1) == KK_OK);
+    REQUIRE(kk_autotune(f, 4, &words, &rows, &units, nullptr) == KK_OK && words == 8 && rows == 100 && units == 1);
     for (kk_sim* s : {h, g, f}) kk_destroy(s);
   }
   return 0;
@@ -192,3 +192,43 @@ int main() {
 
 def test_autotune_times_the_tile_it_replaces(tmp_path):
     _run(tmp_path, AUTOTUNE)
+
+
+# Sweeps in pairs where that takes no more rounds of workgroups, as for every default tile; one per launch on tiles that
+# fill the device several times over, or would with twice the threads.
+PAIRS = r"""
+int main() {
+  for (unsigned L = 4; L <= 8192; L += L < 512 ? 4 : (L < 4096 ? 92 : 512))
+    for (unsigned layout : {KK_LAYOUT_INT8, KK_LAYOUT_BITPACKED}) {
+      kk_sim* h = nullptr;
+      if (layout == KK_LAYOUT_BITPACKED && L % 32) continue;
+      REQUIRE(kk_create_ex(&h, L, 0.5, 0.5, 1, layout, nullptr) == KK_OK);
+      g_launches.clear();
+      REQUIRE(kk_sweep(h, 9) == KK_OK);
+      if (g_launches.size() != (launched("halo_kernel") ? 5 : 1)) {
+        printf("%u: %zu launches\n", L, g_launches.size());
+        return 1;
+      }
+      kk_destroy(h);
+    }
+  kk_sim* h = nullptr;
+  REQUIRE(kk_create_ex(&h, 4096, 0.5, 0.5, 1, KK_LAYOUT_BITPACKED, nullptr) == KK_OK);
+  const unsigned tiles[][4] = {{16, 128, 2, 5}, {8, 256, 2, 5}, {8, 64, 1, 9}, {8, 16, 1, 9}, {2, 32, 1, 9}, {16, 40, 1, 9}};
+  for (const auto& t : tiles) {
+    REQUIRE(kk_set_tile(h, t[0], t[1], t[2]) == KK_OK);
+    g_launches.clear();
+    uint64_t launches = 0;
+    REQUIRE(kk_sweep_timed(h, 9, nullptr, &launches) == KK_OK);
+    if (launches != t[3] || launched("halo_kernel") != t[3]) {
+      printf("%u x %u: %zu launches\n", t[0], t[1], (size_t)launches);
+      return 1;
+    }
+  }
+  kk_destroy(h);
+  return 0;
+}
+"""
+
+
+def test_sweeps_in_pairs_where_they_pay(tmp_path):
+    _run(tmp_path, PAIRS)
